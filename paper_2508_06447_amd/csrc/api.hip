@@ -50,11 +50,22 @@ static int forced_count(unsigned flags, int nb) {
     return c > nb ? nb : c;
 }
 
+// Over how many workgroups the reduction of a projection is split (1 = not at all).  A function of k_in and a wide class of
+// row counts only, so that an output element is summed in the same order whatever the number of rows beside it.
+// Query/Key/Value: with 128 rows the weights (50 MB) have to come through at most 96 tiles of 64 x 128; 64 rows, all three
+// in one launch: 22 -> 17 us with 4 splits, Key alone 16 -> 9.4.  From 129 rows on more than one split gains at most 3 us
+// for as many rows as fill the chip and loses behind that (the partial sums are written and read once more per split).
+static int qkv_splits(int m, int k_in) { return m <= 128 && k_in >= 2048 ? 4 : 1; }
+// Down projection (long rows): 1 / 2 / 4 / 8 splits of 14336 take 73 / 43 / 39 / 38 us for 128 rows, 101 / 75 / 67 / 73 for
+// 300, 106 / 82 / 79 / 90 for 512, 146 / 130 / 137 / 166 for 1024; above that the unsplit tiles are ahead (1511: 195 / 225 / 208).
+static int down_splits(int m, int k_in) { return k_in < 8192 || m > 1024 ? 1 : m <= 128 ? 8 : 4; }
+
 // Workspace layout of slim_pruned_layer (every region 256-byte aligned).
 struct LayerPlan {
-    size_t h, k_all, q_win, qt, scores, table, tscore, rstd, rstd2, kc, vc, qc, o, o_all, act, total;
+    size_t h, k_all, q_win, qt, scores, table, tscore, rstd, rstd2, kc, vc, qc, o, o_all, act, partial, total;
     int nb, n_out;
     bool prune;
+    bool split_k, split_qv, split_qkv, split_down;       // which projections go through float partial sums
 };
 
 static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
@@ -85,6 +96,17 @@ static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
     p.o_all = after ? take(n_att * qd * es) : 0;         // attention output of all N rows, compacted into o
     p.o = take((size_t)p.n_out * qd * es);
     p.act = take((size_t)p.n_out * s->ffn * es);
+    size_t part = 0;                                     // floats of the largest set of partial sums
+    if (s->dtype == SLIM_BF16 && s->hidden % 64 == 0 && s->hidden < (1 << 23) && s->ffn < (1 << 23)) {   // (32-bit offsets in a tile)
+        auto room = [&](int m, size_t n, int splits) { part = std::max(part, (size_t)splits * m * n); return true; };
+        const int na = (int)n_att;
+        p.split_qkv = !p.prune && few_rows(N, (int)(qd + 2 * kv)) && room(N, qd + 2 * kv, qkv_splits(N, s->hidden));
+        p.split_k = !p.split_qkv && few_rows(N, (int)kv) && room(N, kv, qkv_splits(N, s->hidden));
+        p.split_qv = !p.split_qkv && few_rows(na, (int)(qd + kv)) && room(na, qd + kv, qkv_splits(na, s->hidden));
+        const int ds = down_splits(p.n_out, s->ffn);
+        p.split_down = ds > 1 && s->ffn % 64 == 0 && few_rows(p.n_out, s->hidden) && room(p.n_out, s->hidden, ds);
+    }
+    p.partial = take(part * sizeof(float));
     p.total = off;
     return p;
 }
@@ -558,6 +580,28 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         if (sc) return launch_linear_scaled(a, Hd, wmat, nullptr, bias, sc, m, n_feat, Hd, n_feat, out, st);
         return launch_linear(a, Hd, wmat, nullptr, nullptr, bias, m, n_feat, Hd, n_feat, dt, out, st);
     };
+    float* partial = (float*)(ws + p.partial);
+    // Up to three of the Query / Key / Value projections of the same rows through float partial sums, rotated (not the
+    // Values) at the rows' positions and, for the Keys, scored against the window query by the finishing pass.
+    auto project_split = [&](const void* a, const float* sc, int m, const int* pos_, void* q_out, void* k_out, void* v_out,
+                             const float* qt_) -> int {
+        SplitMats mats{};
+        SplitHeadsArgs out{};
+        out.score = -1;
+        auto add = [&](void* dst, const void* wmat, const void* bias, int heads, int rope) {
+            if (!dst) return;
+            const int i = mats.count++;
+            mats.w[i] = wmat; mats.n[i] = heads * d;
+            out.out[i] = dst; out.bias[i] = bias; out.heads[i] = heads; out.rope[i] = rope;
+        };
+        add(q_out, w->wq, w->bq, Hq, 1);
+        if (k_out) out.score = mats.count;
+        add(k_out, w->wk, w->bk, Hkv, 1);
+        add(v_out, w->wv, w->bv, Hkv, 0);
+        const int splits = qkv_splits(m, Hd);
+        int r = launch_split_gemm(a, Hd, mats, m, Hd, splits, partial, st);
+        return r ? r : launch_split_heads(partial, splits, m, out, sc, pos_, s->rope_theta, qt_, tscore, st);
+    };
     auto project_rope = [&](const void* a, const float* sc, const void* wmat, const void* bias, const int* pos_, int pos0,
                             int m, int heads, void* out, const float* tab, const float* qt_, float* ts) -> int {
         if (tab) return launch_linear_rope(a, Hd, wmat, bias, tab, qt_, ts, sc, m, heads, Hd, heads * d, out, st);
@@ -567,6 +611,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     // Query (+ RoPE) and Value states of m rows.  One launch for both projections where the kernel covers it.
     auto project_qv = [&](const void* a, const float* sc, const int* pos_, int m, void* q_out, void* v_out) -> int {
         int r;
+        if (p.split_qv) return project_split(a, sc, m, pos_, q_out, nullptr, v_out, nullptr);
         if (dt == SLIM_BF16 && Hd % 64 == 0 && m > 128 && !w->bq == !w->bv)
             r = launch_linear_pair(a, Hd, w->wq, w->bq, qd, qd, q_out, w->wv, w->bv, kvd, kvd, v_out, sc, m, Hd, st);
         else {
@@ -575,22 +620,28 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         }
         return r ? r : launch_rope(q_out, pos_, 0, m, Hq, d, s->rope_theta, dt, st);
     };
+    // Key states of every incoming token (and their score partials).
+    auto project_k = [&](const void* a, const float* sc, const float* tab, const float* qt_) -> int {
+        if (p.split_k) return project_split(a, sc, N, pos_in, nullptr, k_all, nullptr, qt_);
+        return project_rope(a, sc, w->wk, w->bk, pos_in, 0, N, Hkv, k_all, tab, qt_, tscore);
+    };
     auto block_scores = [&](const void* q_window, int w_eff, float* scores) -> int {
         if (fused_score) return launch_token_score_blocks(tscore, N, Hkv, s->block, s->unit, scores, st);
         return launch_score(q_window, k_all, N, w_eff, Hq, Hkv, d, s->block, s->unit, s->scoring, dt, scores, qt, st);
     };
 
+    const bool want_table = fused && (fused_score || !(p.split_k || p.split_qkv));   // the window query reads it, and the unsplit Key projection
     const void* rows_in = x_in;        // what the projections of the incoming tokens read
     const float* sc_in = nullptr;
     if (fold_attn) {
         // (the same pass over the rows leaves the cos / sin table of their positions for the Key projection)
-        SLIM_TRY(launch_row_rstd(x_in, N, Hd, s->rms_eps, dt, rstd_in, st, pos_in, d, s->rope_theta, fused ? table : nullptr));
+        SLIM_TRY(launch_row_rstd(x_in, N, Hd, s->rms_eps, dt, rstd_in, st, pos_in, d, s->rope_theta, want_table ? table : nullptr));
         sc_in = rstd_in;
     } else {
         SLIM_TRY(launch_rmsnorm(x_in, w->g_attn, N, Hd, s->rms_eps, dt, h, st));
         rows_in = h;
     }
-    if (fused && !fold_attn) SLIM_TRY(launch_rope_table(pos_in, 0, N, d, s->rope_theta, table, st));
+    if (want_table && !fold_attn) SLIM_TRY(launch_rope_table(pos_in, 0, N, d, s->rope_theta, table, st));
     const float* ktab = fused ? table : nullptr;   // cos/sin rows of the incoming tokens, for the Key projection
 
     const void* resid = x_in;          // residual stream entering the attention branch
@@ -614,7 +665,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         const unsigned char* q_last = (const unsigned char*)qc + (size_t)(N - w_eff) * qd * es;
         if (win_direct) SLIM_TRY(window_query_direct());
         else if (fused_score) SLIM_TRY(launch_window_query(q_last, w_eff, Hq, Hkv, d, dt, qt, st));
-        SLIM_TRY(project_rope(rows_in, sc_in, w->wk, w->bk, pos_in, 0, N, Hkv, k_all, ktab, fused_score ? qt : nullptr, tscore));
+        SLIM_TRY(project_k(rows_in, sc_in, ktab, fused_score ? qt : nullptr));
         SLIM_TRY(launch_attn(qc, k_all, vc, N, Hq, Hkv, d, 0.f, dt, o_all, st));
         float* scores = scores_out ? scores_out : (float*)(ws + p.scores);
         SLIM_TRY(block_scores(q_last, w_eff, scores));
@@ -633,8 +684,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
                               pos_in ? pos_in + (N - w_eff) : nullptr, N - w_eff, w_eff, Hq, q_win, nullptr, nullptr, nullptr));
         if (fused_score) SLIM_TRY(launch_window_query(q_win, w_eff, Hq, Hkv, d, dt, qt, st));
     }
-    // Key states of every incoming token.
-    SLIM_TRY(project_rope(rows_in, sc_in, w->wk, w->bk, pos_in, 0, N, Hkv, k_all, ktab, fused_score ? qt : nullptr, tscore));
+    if (!p.split_qkv) SLIM_TRY(project_k(rows_in, sc_in, ktab, fused_score ? qt : nullptr));
     const void* rows = rows_in;        // what the Q/V projections of the continuing tokens read
     const float* sc = sc_in;
     if (p.prune) {
@@ -672,8 +722,9 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         if (pos_out) SLIM_TRY(launch_positions(pos_in, pos_out, N, st));
     }
 
-    // Q, V of the rows that continue; RoPE on Q at the original positions.
-    SLIM_TRY(project_qv(rows, sc, pos, n, qc, vc));
+    // Q, V of the rows that continue; RoPE on Q at the original positions.  (Few rows, nothing dropped: K with them.)
+    if (p.split_qkv) SLIM_TRY(project_split(rows, sc, n, pos, qc, kc, vc, nullptr));
+    else SLIM_TRY(project_qv(rows, sc, pos, n, qc, vc));
     SLIM_TRY(launch_attn(qc, kc, vc, n, Hq, Hkv, d, 0.f, dt, o, st));
     }
     // y = resid + Wo o  (into x_out);  z = y + Wdown(silu(Wgate r) * Wup r), r = RMSNorm(y)  (in place)
@@ -685,7 +736,14 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         SLIM_TRY(launch_rmsnorm(x_out, w->g_ffn, n, Hd, s->rms_eps, dt, h, st));
         SLIM_TRY(launch_linear(h, Hd, w->w_gate, w->w_up, nullptr, nullptr, n, s->ffn, Hd, s->ffn, dt, act, st));
     }
-    SLIM_TRY(launch_linear(act, s->ffn, w->w_down, nullptr, x_out, nullptr, n, Hd, s->ffn, Hd, dt, x_out, st));
+    if (p.split_down) {
+        const int splits = down_splits(n, s->ffn);
+        const SplitMats mats{{w->w_down}, {Hd}, 1};
+        SLIM_TRY(launch_split_gemm(act, s->ffn, mats, n, s->ffn, splits, partial, st));
+        SLIM_TRY(launch_split_residual(partial, splits, n, Hd, x_out, x_out, st));
+    } else {
+        SLIM_TRY(launch_linear(act, s->ffn, w->w_down, nullptr, x_out, nullptr, n, Hd, s->ffn, Hd, dt, x_out, st));
+    }
 #undef SLIM_TRY
     return SLIM_OK;
 }

@@ -8,13 +8,13 @@
 // and the activation tile the "B" operand, so a lane ends up with 4 consecutive output features of
 // one token and stores them as one 8-byte vector.
 //
-// Main path (k_in a multiple of 64, more than 128 rows): 4 waves per workgroup, one per SIMD, 256x256 output tile
+// Main path (k_in a multiple of 64, many rows): 4 waves per workgroup, one per SIMD, 256x256 output tile
 // (128 features x 2 matrices x 256 tokens for SwiGLU), each wave 128 x 128 of it, so that every MFMA fragment read
 // from LDS feeds four MFMAs.  Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no
 // VGPR staging), double-buffered; MFMA fragments are read one k-step ahead of their use, across k-tiles too.  The
 // k-loop is generated assembly (gen_gemm_asm.py -> gemm_bf16_mainloops.inc): with a lone wave per SIMD the order of
-// MFMA, LDS and tile-load instructions inside the wave is the schedule.  The residual epilogue (output and down
-// projection) and few rows (<= 128, narrow tiles) use an 8-wave C++ tile with the same LDS layout and pipeline; a
+// MFMA, LDS and tile-load instructions inside the wave is the schedule.  The residual epilogue (down
+// projection) and few rows use C++ tiles with the same LDS layout and pipeline; a
 // register-staged kernel with k predicates covers ragged k_in.
 #include "slim_common.h"
 
@@ -27,8 +27,9 @@
 
 namespace slim {
 
-enum { EPI_PLAIN = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_BIAS = 3, EPI_ROPE = 4 };
+enum { EPI_PLAIN = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_BIAS = 3, EPI_ROPE = 4, EPI_PARTIAL = 5 };
 // EPI_BIAS: R is a bias vector [N].  EPI_ROPE: R is a bias vector or null, the rest comes in a EpiExtra.
+// EPI_PARTIAL: the accumulators go to a float buffer as they are (EpiExtra::partial); split_gemm_kernel only.
 
 // Extra operands: of the RoPE epilogue (heads of 128 features, one head per wave tile), of the fused RMSNorm, and
 // of a second projection of the same rows carried by the same launch.
@@ -42,6 +43,7 @@ struct EpiExtra {
     const bf16_t* r_2 = nullptr;         // its bias (EPI_BIAS)
     bf16_t* c_2 = nullptr;               // [M][ldo_2]
     int n_2 = 0, ldo_2 = 0, tiles_n1 = 0;
+    float* partial = nullptr;            // EPI_PARTIAL: [M] rows of ldo floats
 };
 
 constexpr int BK = 64;                                   // k-depth of an LDS tile (8 chunks of 16 bytes)
@@ -270,6 +272,32 @@ __device__ __forceinline__ void store_tile_rope(f32x16 (&acc)[1][4][TA], const b
     }
 }
 
+// Epilogue of the split projections: the wave's float tile, unscaled, to rows of a float buffer.  Through the
+// wave-private LDS region (rows of TW*128 bytes, 16-byte chunk c of row r at slot c ^ (r & (chunks per row - 1))), so
+// that a row of the tile leaves as TW*128 contiguous bytes.  Needs N % 4 == 0.
+template <int TW, int TA>
+__device__ __forceinline__ void store_tile_partial(f32x16 (&acc)[TW][TA], float* P, int ldp, int M, int N, int mw, int nw,
+                                                   int lane, unsigned char* region) {
+    constexpr int CPR = TW * 8, RB = TW * 128, ROWS = TA * 32, RPI = 64 / CPR;
+    const int l32 = lane & 31, hh = lane >> 5;
+    const int rrow = lane / CPR, rchunk = lane % CPR;
+    auto slot = [&](int row, int chunk) { return row * RB + ((chunk ^ (row & (CPR - 1))) << 4); };
+#pragma unroll
+    for (int j = 0; j < TA; ++j)
+#pragma unroll
+        for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int vg = 0; vg < 4; ++vg)
+                *reinterpret_cast<f32x4*>(region + slot(j * 32 + l32, i * 8 + vg * 2 + hh)) =
+                    f32x4{acc[i][j][vg * 4], acc[i][j][vg * 4 + 1], acc[i][j][vg * 4 + 2], acc[i][j][vg * 4 + 3]};
+#pragma unroll
+    for (int it = 0; it < ROWS / RPI; ++it) {
+        const int row = it * RPI + rrow, m = mw + row, n = nw + rchunk * 4;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(region + slot(row, rchunk));
+        if (m < M && n < N) *reinterpret_cast<f32x4*>(P + (size_t)m * ldp + n) = v;
+    }
+}
+
 // Workgroup -> output tile.  Workgroup ids are dealt round-robin to the 8 XCDs, so each XCD gets a
 // contiguous run of logical tiles; inside the run, bands of GM token-tiles are walked feature-tile by
 // feature-tile, so the workgroups resident on one XCD share few distinct operand tiles in its L2 (GM = 8: 32
@@ -288,41 +316,44 @@ __device__ __forceinline__ void tile_of_workgroup(int L, bool xcd_runs, int tile
     tn = rem / gm;
 }
 
-// One output tile of the few-row kernel.  8 waves arranged WGN x WGM; requires K % 64 == 0 and 16-byte aligned
-// rows.  The tile starts at token m0, feature n0; M and N bound the loads (clamped) and the stores.
+// One output tile of the few-row kernels.  WGN x WGM waves (4 or 8); requires 16-byte aligned rows; K is the row stride
+// of the weights and the k-loop runs over the first KT tiles of 64 of the rows that A and W0 / W1 point at.
+// The tile starts at token m0, feature n0; M and N bound the loads (clamped) and the stores.
 // With re.row_scale the accumulators of token row m are multiplied by row_scale[m] before the epilogue: with
 // row_scale = 1/sqrt(mean(a[m,:]^2) + eps) and a = the raw residual stream this is the projection of RMSNorm(a)
 // (unit gain; a gain vector is folded into the weights beforehand), and the normalised rows are never stored.
-template <int TW, int TA, int WGN, int WGM, int EPI>
+template <int TW, int TA, int WGN, int WGM, int EPI, int NS = 2>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
                                           const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M,
-                                          int N, int K, int m0, int n0, unsigned char* lds, const EpiExtra& re) {
-    static_assert(WGN * WGM == 8, "8 waves");
+                                          int N, int K, int KT, int m0, int n0, unsigned char* lds, const EpiExtra& re) {
+    constexpr int WV = WGN * WGM;                        // waves
+    static_assert(WV == 8 || WV == 4, "4 or 8 waves");
     static_assert(EPI != EPI_ROPE || TW == 4, "the RoPE epilogue needs one 128-wide head per wave");
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
     constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM, WROWS = BN * NW;
     constexpr int STAGE = (WROWS + BM) * BK * 2;
-    constexpr int WLD = WROWS / 64, ALD = BM / 64;       // wave-loads per k-tile per wave (8 rows each)
-    static_assert(WLD * 64 == WROWS && ALD * 64 == BM && BN % 64 == 0, "tile rows must split over 8 waves x 8 rows");
+    constexpr int LR = WV * 8;                           // tile rows that one wave-load of every wave covers
+    constexpr int WLD = WROWS / LR, ALD = BM / LR;       // wave-loads per k-tile per wave (8 rows each)
+    static_assert(WLD * LR == WROWS && ALD * LR == BM && BN % LR == 0, "tile rows must split over the waves x 8 rows");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave % WGN, wm = wave / WGN;
     const int l32 = lane & 31, hh = lane >> 5;
 
-    // Wave-load i covers rows (i*8 + wave)*8 + lane/8 of the tile; lane%8 is the LDS chunk slot, which
+    // Wave-load i covers rows (i*WV + wave)*8 + lane/8 of the tile; lane%8 is the LDS chunk slot, which
     // holds logical chunk slot ^ swz(row).  A load's address is a wave-uniform base (start of the tile's
     // rows + k offset, scalar registers) plus a loop-invariant per-lane byte offset inside the tile, so
     // the k-loop spends no vector instruction on addresses (a tile spans at most 256 rows: 32 bits do).
     unsigned woff[WLD], aoff[ALD];
 #pragma unroll
     for (int i = 0; i < WLD; ++i) {
-        const int r = (i * 8 + wave) * 8 + (lane >> 3);
+        const int r = (i * WV + wave) * 8 + (lane >> 3);
         const int mat = NW == 2 ? r / BN : 0;
         const int n = min(n0 + r - mat * BN, N - 1) - n0;
         woff[i] = (unsigned)(((size_t)n * K + ((lane & 7) ^ swz(r)) * 8) * 2);
     }
 #pragma unroll
     for (int i = 0; i < ALD; ++i) {
-        const int r = (i * 8 + wave) * 8 + (lane >> 3);
+        const int r = (i * WV + wave) * 8 + (lane >> 3);
         aoff[i] = (unsigned)(((size_t)(min(m0 + r, M - 1) - m0) * lda + ((lane & 7) ^ swz(r)) * 8) * 2);
     }
     const bf16_t* w0base = W0 + (size_t)n0 * K;
@@ -333,11 +364,11 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
         const unsigned ws = lds_wave + stage * STAGE, as = ws + WROWS * BK * 2;
 #pragma unroll
         for (int i = 0; i < WLD; ++i) {
-            const bool second = NW == 2 && (i * 8 * 8 >= BN);   // rows of wave-load i lie in one matrix (BN % 64 == 0)
-            load_global_to_lds16((second ? w1base : w0base) + k0, woff[i], ws + i * 8 * 1024);
+            const bool second = NW == 2 && (i * LR >= BN);       // rows of wave-load i lie in one matrix (BN % LR == 0)
+            load_global_to_lds16((second ? w1base : w0base) + k0, woff[i], ws + i * WV * 1024);
         }
 #pragma unroll
-        for (int i = 0; i < ALD; ++i) load_global_to_lds16(abase + k0, aoff[i], as + i * 8 * 1024);
+        for (int i = 0; i < ALD; ++i) load_global_to_lds16(abase + k0, aoff[i], as + i * WV * 1024);
     };
 
     f32x16 acc[NW][TW][TA];
@@ -350,16 +381,15 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[w][i][j][v] = 0.f;
 
-    const int KT = K / BK;
     bf16x8 af[2][TA], wf[2][NW][TW];
     // Fragment addresses: one per-lane base per (operand, stage, k-step), computed once; the MFMA tile
     // (i, j) and the matrix (gate/up) are immediate offsets of the LDS reads, so the k-loop spends no
     // vector instruction on them.  The swizzle term (row >> 1) & 7 depends only on lane % 32 because the
     // tile rows of a wave start at multiples of 32.
-    const unsigned char* wfrag[2][BK / 16];
-    const unsigned char* afrag[2][BK / 16];
+    const unsigned char* wfrag[NS][BK / 16];
+    const unsigned char* afrag[NS][BK / 16];
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
+    for (int st = 0; st < NS; ++st)
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
             wfrag[st][ks] = lds + st * STAGE + lds_off(wn * TW * 32 + l32, ks * 2 + hh);
@@ -385,16 +415,18 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
                 for (int j = 0; j < TA; ++j)
                     acc[w][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][w][i], af[buf][j], acc[w][i][j], 0, 0, 0);
     };
-    // Two LDS stages.  Fragments are read one k-step ahead of their MFMAs, also across k-tiles: the
+    // NS LDS stages.  Fragments are read one k-step ahead of their MFMAs, also across k-tiles: the
     // workgroup barrier of a k-tile sits before its last k-step, when every wave has pulled that step's
-    // fragments into registers.  Past the barrier the stage is free, so tile kt+2 is sent into it, tile
-    // kt+1 (sent one iteration earlier, waited for just before the barrier) is visible to all waves, and
-    // its first fragments are read while the last k-step's MFMAs run.  The loop is unrolled by two so the
-    // stage of every read is a compile-time constant.
-    using Stage0 = std::integral_constant<int, 0>;
-    using Stage1 = std::integral_constant<int, 1>;
-    auto k_tile = [&](int kt, auto stage_c, auto other_c) {
+    // fragments into registers.  Past the barrier the stage is free, so tile kt+NS is sent into it, tile
+    // kt+1 (sent NS-1 iterations earlier, waited for just before the barrier) is visible to all waves, and
+    // its first fragments are read while the last k-step's MFMAs run.  The loop is unrolled by NS so the
+    // stage of every read is a compile-time constant.  Loads past the last k-tile re-read it (into a stage
+    // that nobody reads), so the number of loads in flight at a wait is a constant.
+    constexpr unsigned kStageLoads = WLD + ALD;
+    constexpr unsigned kFly = (NS - 2) * kStageLoads, kPro = (NS - 1) * kStageLoads;   // in flight behind a wait
+    auto k_tile = [&](int kt, auto stage_c) {
         constexpr int stage = decltype(stage_c)::value;
+        using Next = std::integral_constant<int, (stage + 1) % NS>;
 #pragma unroll
         for (int ks = 0; ks < BK / 16 - 1; ++ks) {
             load_frags(stage_c, ks + 1, (ks + 1) & 1);
@@ -402,28 +434,41 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
             mfmas(ks & 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_s_waitcnt(0x0070);              // own reads of this stage and own part of tile kt+1 done
+        __builtin_amdgcn_s_waitcnt((kFly & 15) | 0x0070 | ((kFly >> 4) << 14));   // own reads of this stage and own part of tile kt+1 done
         workgroup_barrier();
-        if (kt + 2 < KT) issue_loads((kt + 2) * BK, stage);
-        if (kt + 1 < KT) load_frags(other_c, 0, 0);
+        issue_loads(min(kt + NS, KT - 1) * BK, stage);
+        load_frags(Next{}, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         mfmas((BK / 16 - 1) & 1);
         __builtin_amdgcn_sched_barrier(0);
     };
-    issue_loads(0, 0);
-    if (KT > 1) {
-        // only the first k-tile has to be there; the second stays in flight until the first k-tile's own wait
-        constexpr unsigned kStageLoads = WLD + ALD;
-        issue_loads(BK, 1);
-        __builtin_amdgcn_s_waitcnt((kStageLoads & 15) | 0x0070 | ((kStageLoads >> 4) << 14));
-    } else {
-        __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0) lgkmcnt(0)
-    }
+#pragma unroll
+    for (int st = 0; st < NS; ++st) issue_loads(min(st, KT - 1) * BK, st);
+    // only the first k-tile has to be there; the others stay in flight until the k-tiles' own waits
+    __builtin_amdgcn_s_waitcnt((kPro & 15) | 0x0070 | ((kPro >> 4) << 14));
     workgroup_barrier();
-    load_frags(Stage0{}, 0, 0);
-    for (int kt = 0; kt < KT; kt += 2) {
-        k_tile(kt, Stage0{}, Stage1{});
-        if (kt + 1 < KT) k_tile(kt + 1, Stage1{}, Stage0{});
+    load_frags(std::integral_constant<int, 0>{}, 0, 0);
+    for (int kt = 0;;) {
+        k_tile(kt, std::integral_constant<int, 0>{});
+        if (++kt >= KT) break;
+        k_tile(kt, std::integral_constant<int, 1 % NS>{});
+        if (++kt >= KT) break;
+        if constexpr (NS >= 3) {
+            k_tile(kt, std::integral_constant<int, 2 % NS>{});
+            if (++kt >= KT) break;
+        }
+        if constexpr (NS >= 4) {
+            k_tile(kt, std::integral_constant<int, 3 % NS>{});
+            if (++kt >= KT) break;
+        }
+        if constexpr (NS >= 5) {
+            k_tile(kt, std::integral_constant<int, 4 % NS>{});
+            if (++kt >= KT) break;
+        }
+        if constexpr (NS >= 6) {
+            k_tile(kt, std::integral_constant<int, 5 % NS>{});
+            if (++kt >= KT) break;
+        }
     }
     if (re.row_scale) {
         float inv[TA];                                   // all requested before the first is used: one wait, not TA
@@ -443,7 +488,10 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
     workgroup_barrier();
     const bool wide = (N % 8 == 0) && (ldo % 8 == 0) && (((uintptr_t)C & 15) == 0) &&
                       (EPI != EPI_RESIDUAL || ((uintptr_t)R & 15) == 0) && (EPI != EPI_BIAS || ((uintptr_t)R & 7) == 0);
-    if constexpr (EPI == EPI_ROPE) {                     // the launcher has checked what `wide` checks
+    if constexpr (EPI == EPI_PARTIAL) {
+        store_tile_partial<TW, TA>(acc[0], re.partial, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
+                                   lds + wave * (TA * 32 * TW * 128));
+    } else if constexpr (EPI == EPI_ROPE) {              // the launcher has checked what `wide` checks
         store_tile_rope<TA>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
                             lds + wave * (TA * 32 * TW * 64), re);
     } else {
@@ -537,9 +585,9 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     }
 }
 
-// Few-row kernel: every workgroup computes one tile of the same shape.
-template <int TW, int TA, int WGN, int WGM, int EPI>
-__global__ void __launch_bounds__(512) gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda,
+// Few-row kernel: every workgroup computes one tile of the same shape, from NS LDS stages.
+template <int TW, int TA, int WGN, int WGM, int EPI, int NS>
+__global__ void __launch_bounds__(64 * WGN * WGM) gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda,
                                                         const bf16_t* __restrict__ W0,
                                                         const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C,
                                                         int ldo, int M, int N, int K, int tiles_m, int tiles_n,
@@ -547,7 +595,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_kernel(const bf16_t* __restrict
     extern __shared__ __align__(16) unsigned char lds[];
     int tm, tn;
     tile_of_workgroup(blockIdx.x, true, tiles_m, tiles_n, tm, tn);
-    gemm_tile<TW, TA, WGN, WGM, EPI>(A, lda, W0, W1, R, C, ldo, M, N, K, tm * 32 * TA * WGM, tn * 32 * TW * WGN, lds, re);
+    gemm_tile<TW, TA, WGN, WGM, EPI, NS>(A, lda, W0, W1, R, C, ldo, M, N, K, K / BK, tm * 32 * TA * WGM, tn * 32 * TW * WGN, lds, re);
 }
 
 // Shapes of the two-size launch: 256-token tiles for the first big_tiles_m token-tiles, 128-token tiles
@@ -603,10 +651,46 @@ gemm_bf16_two_size_residual_kernel(const bf16_t* __restrict__ A, int lda, const 
     else tile_of_workgroup(blockIdx.x - n_big, n_big % 8 == 0, small_tiles_m, tiles_n, tm, tn, band);
     const EpiExtra none;
     if (big)
-        gemm_tile<4, 2, 2, 4, EPI_RESIDUAL>(A, lda, W0, nullptr, R, C, ldo, M, N, K, tm * S::BM_BIG, tn * S::BN, lds, none);
+        gemm_tile<4, 2, 2, 4, EPI_RESIDUAL>(A, lda, W0, nullptr, R, C, ldo, M, N, K, K / BK, tm * S::BM_BIG, tn * S::BN, lds, none);
     else
-        gemm_tile<2, 2, 4, 2, EPI_RESIDUAL>(A, lda, W0, nullptr, R, C, ldo, M, N, K,
+        gemm_tile<2, 2, 4, 2, EPI_RESIDUAL>(A, lda, W0, nullptr, R, C, ldo, M, N, K, K / BK,
                                             big_tiles_m * S::BM_BIG + tm * S::BM_SMALL, tn * S::BN, lds, none);
+}
+
+// Split projection: up to three weight matrices that read the same rows, the reduction dimension dealt to `splits`
+// workgroups, float partial sums partial[split][m][all features] that split.hip finishes.  What it is for: with few rows
+// a launch of one workgroup per output tile leaves most of the chip idle (4096 features x 512 tokens are 64 tiles of
+// 256 x 128), and the finishing pass takes the place of the RoPE kernel anyway.  Down projection (k_in 14336, 4096
+// features), with the finishing pass: 300 rows 256 -> 67 us, 512 rows 275 -> 79 us, 1024 rows 272 -> 137 us.
+struct SplitSegs {
+    const bf16_t* w[3];
+    int n[3];                            // features (multiples of 4)
+    int tile0[3], col0[3];               // first feature tile of the matrix, first column of its sums
+    int ldp;                             // floats per row of the partial buffer
+};
+
+// Workgroup -> (token tile, feature tile, split), token tiles fastest and splits slowest inside each XCD's contiguous
+// run: the tiles that read a weight panel run together on one XCD, which then fetches it from HBM once, and an XCD sees
+// few of the splits and so little of the activation matrix.
+template <int TW, int TA, int WGN, int WGM, int NS>
+__global__ void __launch_bounds__(64 * WGN * WGM, 2)
+split_gemm_kernel(const bf16_t* __restrict__ A, int lda, SplitSegs segs, float* __restrict__ partial, int M, int K, int tiles_m,
+                  int tiles_n, int splits) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int total = tiles_m * tiles_n * splits;
+    int L = blockIdx.x;
+    if (total % 8 == 0) L = (L & 7) * (total >> 3) + (L >> 3);
+    const int tm = L % tiles_m, rest = L / tiles_m, tn = rest % tiles_n, sp = rest / tiles_n;
+    const int seg = (tn >= segs.tile0[1]) + (tn >= segs.tile0[2]);
+    const bf16_t* W = seg == 0 ? segs.w[0] : seg == 1 ? segs.w[1] : segs.w[2];
+    const int N = seg == 0 ? segs.n[0] : seg == 1 ? segs.n[1] : segs.n[2];
+    const int t0 = seg == 0 ? 0 : seg == 1 ? segs.tile0[1] : segs.tile0[2];
+    const int c0 = seg == 0 ? 0 : seg == 1 ? segs.col0[1] : segs.col0[2];
+    const int KT = K / BK, lo = (int)((long long)KT * sp / splits), hi = (int)((long long)KT * (sp + 1) / splits);
+    EpiExtra re;
+    re.partial = partial + (size_t)sp * M * segs.ldp + c0;
+    gemm_tile<TW, TA, WGN, WGM, EPI_PARTIAL, NS>(A + lo * BK, lda, W + lo * BK, nullptr, nullptr, nullptr, segs.ldp, M, N, K, hi - lo,
+                                             tm * 32 * TA * WGM, (tn - t0) * 32 * TW * WGN, lds, re);
 }
 
 // Generic kernel (any k_in that is a multiple of 8): register-staged loads with k predicates.
@@ -709,15 +793,15 @@ __global__ void __launch_bounds__(256) gemm_bf16_generic_kernel(const bf16_t* __
     store_tile<TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, l32, hh);
 }
 
-template <int TW, int TA, int WGN, int WGM, int EPI, bool GENERIC>
+template <int TW, int TA, int WGN, int WGM, int EPI, bool GENERIC, int NS = 2>
 static int launch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t* W1, const bf16_t* R, bf16_t* C,
                        int ldo, int M, int N, int K, hipStream_t st, const EpiExtra& re = EpiExtra()) {
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
     constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM;
-    constexpr size_t smem = 2 * (size_t)(BN * NW + BM) * BK * 2;
+    constexpr size_t smem = NS * (size_t)(BN * NW + BM) * BK * 2;
     const void* kern;
     if constexpr (GENERIC) kern = (const void*)gemm_bf16_generic_kernel<TW, TA, WGN, WGM, EPI>;
-    else kern = (const void*)gemm_bf16_kernel<TW, TA, WGN, WGM, EPI>;
+    else kern = (const void*)gemm_bf16_kernel<TW, TA, WGN, WGM, EPI, NS>;
     static std::once_flag attr_once;                     // raising the LDS limit is per function, once
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); });
@@ -727,7 +811,7 @@ static int launch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t*
         hipLaunchKernelGGL((gemm_bf16_generic_kernel<TW, TA, WGN, WGM, EPI>), dim3(tiles_m * tiles_n), dim3(64 * WGN * WGM),
                            smem, st, A, lda, W0, W1, R, C, ldo, M, N, K, tiles_m, tiles_n);
     else
-        hipLaunchKernelGGL((gemm_bf16_kernel<TW, TA, WGN, WGM, EPI>), dim3(tiles_m * tiles_n), dim3(64 * WGN * WGM), smem,
+        hipLaunchKernelGGL((gemm_bf16_kernel<TW, TA, WGN, WGM, EPI, NS>), dim3(tiles_m * tiles_n), dim3(64 * WGN * WGM), smem,
                            st, A, lda, W0, W1, R, C, ldo, M, N, K, tiles_m, tiles_n, re);
     return check_launch();
 }
@@ -854,6 +938,76 @@ static int cu_count() {
     return n;
 }
 
+// Tile shapes of the few-row kernels: (features x tokens), waves, LDS stages.  All of them keep 80-144 KB of operand tiles
+// in flight or in use per CU, because with few rows the loop waits for memory (weights come from HBM once, and a k-tile of
+// these tiles lasts no longer than a load takes): two stages of the 128 x 128 tile (64 KB) run the k-loop at 0.70 us per
+// k-tile, four at 0.45.
+//   FEW_A  256 x 128, 8 waves, 3 stages (144 KB, one workgroup per CU): fewest operand bytes per flop
+//   FEW_B  128 x 128, 4 waves, 4 stages (128 KB)
+//   FEW_C  128 x  64, 4 waves, 3 stages  (72 KB, two per CU)
+//   FEW_D   64 x  64, 4 waves, 5 stages  (80 KB, two per CU)
+// Taken is the largest that still gives kFewWorkgroups workgroups, else FEW_D.  Measured with 4096 features and k_in 4096 (us):
+// 1024 rows A (128 workgroups) 48, B (256) 37; 1280 rows A (160) 50, B (320) 60; with 1024 features: 512 rows C 23, D 17.6;
+// 2048 rows B (128) 38, C (256) 32, D (512) 43.
+enum FewShape { FEW_A, FEW_B, FEW_C, FEW_D };
+constexpr long long kFewWorkgroups = 160;
+
+static FewShape few_shape(int M, const int* n, int count, int splits) {
+    auto workgroups = [&](int bn, int bm) {
+        long long t = 0;
+        for (int i = 0; i < count; ++i) t += (n[i] + bn - 1) / bn;
+        return t * ((M + bm - 1) / bm) * splits;
+    };
+    if (workgroups(256, 128) >= kFewWorkgroups) return FEW_A;
+    if (workgroups(128, 128) >= kFewWorkgroups) return FEW_B;
+    if (workgroups(128, 64) >= kFewWorkgroups) return FEW_C;
+    return FEW_D;
+}
+
+// Up to how many outputs the few-row tiles beat the two-size launch, whose 256-token tiles then leave CUs idle: 4096
+// features, k_in 14336, residual: 1511 rows 195 against 271 us, 2048 rows (2^23 outputs) 214 against 278, 2300 rows 355
+// against 302; k_in 4096: 1511 rows 53 against 58, 2048 rows 65 both.  Key projection (1024 features) with rotation and
+// scores: 4096 rows 53 against 58 us, 8192 rows 78 against 82.
+bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23); }
+
+template <int TW, int TA, int WGN, int WGM, int NS>
+static int launch_split_shape(const bf16_t* A, int lda, const SplitMats& mats, int M, int K, int splits, float* partial, hipStream_t st) {
+    constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM;
+    constexpr size_t stages = NS * (size_t)(BN + BM) * BK * 2, tile = (size_t)BN * BM * 4;
+    constexpr size_t smem = stages > tile ? stages : tile;
+    auto kern = split_gemm_kernel<TW, TA, WGN, WGM, NS>;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); });
+    if (attr_err != hipSuccess) return set_hip_error(attr_err);
+    SplitSegs s{};
+    int tiles_n = 0, cols = 0;
+    for (int i = 0; i < 3; ++i) {
+        s.tile0[i] = i < mats.count ? tiles_n : 1 << 30;
+        s.col0[i] = cols;
+        if (i >= mats.count) continue;
+        s.w[i] = (const bf16_t*)mats.w[i];
+        s.n[i] = mats.n[i];
+        tiles_n += (mats.n[i] + BN - 1) / BN;
+        cols += mats.n[i];
+    }
+    s.ldp = cols;
+    const int tiles_m = (M + BM - 1) / BM;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(64 * WGN * WGM), smem, st, A, lda, s, partial, M, K, tiles_m,
+                       tiles_n, splits);
+    return check_launch();
+}
+
+int launch_split_gemm(const void* a, int lda, const SplitMats& mats, int m, int k_in, int splits, float* partial, hipStream_t st) {
+    const bf16_t* A = (const bf16_t*)a;
+    switch (few_shape(m, mats.n, mats.count, splits)) {
+        case FEW_A: return launch_split_shape<2, 2, 4, 2, 3>(A, lda, mats, m, k_in, splits, partial, st);
+        case FEW_B: return launch_split_shape<2, 2, 2, 2, 4>(A, lda, mats, m, k_in, splits, partial, st);
+        case FEW_C: return launch_split_shape<2, 1, 2, 2, 3>(A, lda, mats, m, k_in, splits, partial, st);
+        default: return launch_split_shape<1, 1, 2, 2, 5>(A, lda, mats, m, k_in, splits, partial, st);
+    }
+}
+
 template <int EPI>
 static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t* W1, const bf16_t* R, bf16_t* C,
                          int ldo, int M, int N, int K, hipStream_t st, const EpiExtra& re = EpiExtra()) {
@@ -865,13 +1019,20 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
         else if (!re.row_scale && !re.w_2) return launch_bf16<2, 2, 2, 2, EPI, true>(A, lda, W0, W1, R, C, ldo, M, N, K, st);
         else return SLIM_UNSUPPORTED;
     }
-    if (M <= 128) {
-        // Few rows: the launch streams the weights once and is bound by how many workgroups pull on memory at the same
-        // time, so wide outputs use 64-feature tiles (twice the workgroups of the 128-feature ones).
-        if constexpr (EPI == EPI_SWIGLU) return launch_bf16<1, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-        else if constexpr (EPI == EPI_ROPE) return launch_bf16<4, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-        else if (N >= 2048) return launch_bf16<1, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-        else return launch_bf16<2, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+    if constexpr (EPI == EPI_SWIGLU) {
+        // Up to 256 rows the launch streams the weights: 64-feature tiles keep more of it in flight (14336 features, us: 64 rows
+        // 66 -> 49, 128 rows 65 -> 54, 200 rows 85 -> 64; at 300 rows the two-size launch is ahead, 95 against 105).
+        if (M <= 128) return launch_bf16<1, 1, 2, 4, EPI, false, 4>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+        if (M <= 256) return launch_bf16<1, 2, 2, 4, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+    } else if constexpr (EPI == EPI_ROPE) {
+        if (M <= 128) return launch_bf16<4, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+    } else if (few_rows(M, N)) {
+        switch (few_shape(M, &N, 1, 1)) {
+            case FEW_A: return launch_bf16<2, 2, 4, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+            case FEW_B: return launch_bf16<2, 2, 2, 2, EPI, false, 4>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+            case FEW_C: return launch_bf16<2, 1, 2, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+            default: return launch_bf16<1, 1, 2, 2, EPI, false, 5>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+        }
     }
     const int tiles_n = (N + TileShapes<EPI>::BN - 1) / TileShapes<EPI>::BN;
     const bool eight = EPI == EPI_RESIDUAL && !residual_in_four_waves(R, M, N, K, ldo);

@@ -148,6 +148,15 @@ int launch_gemv(const void* w0, const void* w1, const void* x, const float* scal
 int launch_gemv_qkv(const void* wq, const void* wk, const void* wv, const void* bq, const void* bk, const void* bv,
                     const void* x, float norm_eps, int n_q, int n_kv, int k_in, int position, float theta, int dtype,
                     void* q, void* k, void* v, hipStream_t st);
+// Whether the few-row projection kernels take m rows of n output features.
+bool few_rows(int m, int n);
+// Split projections: float partial sums partial[split][m][sum of n], finished by the launch_split_* below.
+struct SplitMats { const void* w[3]; int n[3]; int count; };
+int launch_split_gemm(const void* a, int lda, const SplitMats& mats, int m, int k_in, int splits, float* partial, hipStream_t st);
+int launch_split_residual(const float* partial, int splits, int m, int n, const void* residual, void* out, hipStream_t st);
+struct SplitHeadsArgs { void* out[3]; const void* bias[3]; int heads[3]; int rope[3]; int score; };
+int launch_split_heads(const float* partial, int splits, int m, const SplitHeadsArgs& a, const float* rstd, const int* pos, float theta,
+                       const float* qt, float* token_scores, hipStream_t st);
 int launch_attn(const void* q, const void* k, const void* v, int n, int Hq, int Hkv, int d, float scale,
                 int dtype, void* out, hipStream_t st);
 

@@ -233,6 +233,19 @@ def test_degenerate_small_sequences(slim, seq, block, window, keep, fold):
                 fold=fold, score_scaled=True)
 
 
+@pytest.mark.parametrize("seq,keep,bias", [
+    (65, 1.0, False), (128, 1.0, True), (129, 1.0, False),      # Query, Key and Value in one launch: 4 splits, 4, 1
+    (300, 0.4, True),           # 128 kept rows of 300: Key with 1 split, Query + Value with 4, down with 8
+    (1024, 1.0, False), (1025, 1.0, True),                      # down projection: 4 splits, none
+])
+def test_split_projections_of_few_rows(slim, seq, keep, bias):
+    """The projections that go through float partial sums, at the edges of the row counts at which the number of splits
+    changes, on a narrow model with rows long enough to be split."""
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, keep_ratio=keep, hidden=2048, n_q_heads=6, n_kv_heads=2, ffn=8256,
+                       planted=max(1, seq // 50), qkv_bias=bias)
+    check_layer(slim, wl, np.float64, label=f"few rows seq {seq} keep {keep} bias {bias}", fold=True, score_scaled=True)
+
+
 def test_reduced_qwen_shaped_layer_full_output(slim):
     """Second model family (28 query / 4 kv heads, hidden 3584, FFN 18944, Q/K/V biases, theta 1e6)."""
     wl = inputs.scaled(inputs.WORKLOADS["cfg6"], seq=1000, x_kind="planted", planted=10)

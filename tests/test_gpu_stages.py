@@ -198,6 +198,37 @@ def test_linear_all_epilogues(slim, m, n, k, dtype):
                                atol=rel * np.abs(sw).max())
 
 
+# One row past a tile's edge or short of it, last feature tile ragged, fewer k-tiles than LDS stages and one more.
+@pytest.mark.parametrize("m,n,k", [
+    (1281, 4096, 256), (1279, 4104, 64),          # 256 x 128 tiles, 3 stages
+    (769, 4096, 320), (641, 4040, 128),           # 128 x 128 tiles, 4 stages
+    (321, 4104, 256), (319, 4096, 64),            # 128 x 64 tiles, 3 stages
+    (65, 1032, 384), (63, 4096, 64),              # 64 x 64 tiles, 5 stages
+    (2048, 4096, 64), (2049, 4096, 64),           # the largest launch of the few-row tiles and the first behind it
+])
+def test_few_row_projections(slim, m, n, k):
+    """Plain, + bias and + residual (in place).  Products of bf16 numbers summed in float: the result is the exact one
+    rounded once to bf16 (2^-9), up to k float roundings of the partial sums."""
+    print(f"few rows m={m} n={n} k={k}", flush=True)
+    bf = torch.bfloat16
+    a, w, b, r = dev(rand((m, k), bf, 1)), dev(rand((n, k), bf, 2, 0.05)), dev(rand((n,), bf, 3)), dev(rand((m, n), bf, 4))
+    prod = a.double() @ w.double().T
+    size = a.double().abs() @ w.double().abs().T
+    for name, want, got in (("plain", prod, slim.slim_linear(a, w)), ("bias", prod + b.double(), slim.slim_linear_bias(a, w, b)),
+                            ("residual", prod + r.double(), slim.slim_linear(a, w, residual=r, out=r))):
+        bound = 2.0 ** -8 * want.abs() + k * 2.0 ** -24 * size + 1e-30
+        assert ((got.double() - want).abs() <= bound).all(), name
+
+
+@pytest.mark.parametrize("m,n,k", [(128, 776, 320), (129, 776, 64), (256, 840, 192), (257, 264, 128), (3, 64, 64)])
+def test_few_row_swiglu(slim, m, n, k):
+    print(f"few rows swiglu m={m} n={n} k={k}", flush=True)
+    bf = torch.bfloat16
+    a, w, w2 = rand((m, k), bf, 1), rand((n, k), bf, 2, 0.05), rand((n, k), bf, 3, 0.05)
+    want = so.silu(f64(a) @ f64(w).T) * (f64(a) @ f64(w2).T)
+    np.testing.assert_allclose(f64(slim.slim_swiglu_linear(dev(a), dev(w), dev(w2))), want, rtol=2.0 ** -8, atol=2.0 ** -8 * np.abs(want).max())
+
+
 @pytest.mark.parametrize("m,n,k,lda,ldo", [(300, 520, 192, 256, 640), (1000, 264, 128, 136, 272), (64, 512, 256, 320, 520)])
 def test_linear_with_row_strides(slim, m, n, k, lda, ldo):
     """Rows of a and of out / residual that are longer than what the call uses (lda > k_in, ldo > n_out), through the
