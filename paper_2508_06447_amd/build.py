@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libslim.so")
 PROBE_LIB = os.path.join(HERE, "libslim_probe.so")
-SOURCES = ("api.hip", "prune.hip", "norm_rope.hip", "gemm.hip", "split.hip", "attn.hip", "kvswap.hip", "decode.hip", "gemv.hip", "window.hip", "probe.hip")
+SOURCES = ("api.hip", "prune.hip", "norm_rope.hip", "gemm.hip", "split.hip", "attn.hip", "f32.hip", "kvswap.hip", "decode.hip", "gemv.hip", "window.hip", "probe.hip")
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 

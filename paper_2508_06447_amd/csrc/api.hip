@@ -572,6 +572,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     float* tscore = (float*)(ws + p.tscore);
     const bool fused = dt == SLIM_BF16 && d == 128 && Hd % 64 == 0;
     const bool fused_score = fused && p.prune && s->scoring == 0;
+    const bool f32 = dt == SLIM_F32;             // its projections normalise the rows that they read themselves
     const bool fold_attn = !w->g_attn, fold_ffn = !w->g_ffn;
     float* rstd_in = (float*)(ws + p.rstd);      // 1/rms of the incoming rows, and of the rows that continue
     float* rstd_kept = (float*)(ws + p.rstd2);
@@ -608,9 +609,26 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         int r = project(a, sc, wmat, bias, m, heads * d, out);
         return r ? r : launch_rope(out, pos_, pos0, m, heads, d, s->rope_theta, dt, st);
     };
+    // Float32: up to three projections of rows that are normalised on their way in share a launch.
+    F32Seg f32_segs[3];
+    int f32_count = 0;
+    auto f32_add = [&](const void* a, int m, const int* pos_, int pos0, const void* wmat, const void* bias, int heads, bool rope, void* out) {
+        f32_segs[f32_count++] = F32Seg{(const float*)a, Hd, m, (const float*)wmat, nullptr, (const float*)bias, nullptr, (float*)out,
+                                       heads * d, heads * d, rope ? F32_ROPE : F32_PLAIN, pos_, pos0};
+    };
+    auto f32_run = [&](const void* gain) -> int {
+        const int count = f32_count;
+        f32_count = 0;
+        return launch_f32_linear(f32_segs, count, Hd, (const float*)gain, s->rms_eps, d, s->rope_theta, st);
+    };
     // Query (+ RoPE) and Value states of m rows.  One launch for both projections where the kernel covers it.
     auto project_qv = [&](const void* a, const float* sc, const int* pos_, int m, void* q_out, void* v_out) -> int {
         int r;
+        if (f32) {
+            f32_add(a, m, pos_, 0, w->wq, w->bq, Hq, true, q_out);
+            f32_add(a, m, pos_, 0, w->wv, w->bv, Hkv, false, v_out);
+            return f32_run(w->g_attn);
+        }
         if (p.split_qv) return project_split(a, sc, m, pos_, q_out, nullptr, v_out, nullptr);
         if (dt == SLIM_BF16 && Hd % 64 == 0 && m > 128 && !w->bq == !w->bv)
             r = launch_linear_pair(a, Hd, w->wq, w->bq, qd, qd, q_out, w->wv, w->bv, kvd, kvd, v_out, sc, m, Hd, st);
@@ -622,6 +640,10 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     };
     // Key states of every incoming token (and their score partials).
     auto project_k = [&](const void* a, const float* sc, const float* tab, const float* qt_) -> int {
+        if (f32) {
+            f32_add(a, N, pos_in, 0, w->wk, w->bk, Hkv, true, k_all);
+            return f32_run(w->g_attn);
+        }
         if (p.split_k) return project_split(a, sc, N, pos_in, nullptr, k_all, nullptr, qt_);
         return project_rope(a, sc, w->wk, w->bk, pos_in, 0, N, Hkv, k_all, tab, qt_, tscore);
     };
@@ -637,7 +659,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         // (the same pass over the rows leaves the cos / sin table of their positions for the Key projection)
         SLIM_TRY(launch_row_rstd(x_in, N, Hd, s->rms_eps, dt, rstd_in, st, pos_in, d, s->rope_theta, want_table ? table : nullptr));
         sc_in = rstd_in;
-    } else {
+    } else if (!f32) {
         SLIM_TRY(launch_rmsnorm(x_in, w->g_attn, N, Hd, s->rms_eps, dt, h, st));
         rows_in = h;
     }
@@ -677,6 +699,8 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     } else {
     if (p.prune && win_direct) {
         SLIM_TRY(window_query_direct());
+    } else if (p.prune && f32) {                 // the window's Query states share the Key projection's launch
+        f32_add((const float*)x_in + (size_t)(N - w_eff) * Hd, w_eff, pos_in ? pos_in + (N - w_eff) : nullptr, N - w_eff, w->wq, w->bq, Hq, true, q_win);
     } else if (p.prune) {
         // Query states of the local window (last w_eff rows) and their head-group-summed mean.
         const unsigned char* r_win = (const unsigned char*)rows_in + (size_t)(N - w_eff) * Hd * es;
@@ -711,7 +735,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         rows = x_out;
         if (fold_attn) {
             sc = rstd_kept;
-        } else {
+        } else if (!f32) {
             SLIM_TRY(launch_rmsnorm(x_out, w->g_attn, n, Hd, s->rms_eps, dt, h, st));
             rows = h;
         }
@@ -732,6 +756,10 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     if (fold_ffn) {
         SLIM_TRY(launch_row_rstd(x_out, n, Hd, s->rms_eps, dt, rstd_kept, st));
         SLIM_TRY(launch_linear_scaled(x_out, Hd, w->w_gate, w->w_up, nullptr, rstd_kept, n, s->ffn, Hd, s->ffn, act, st));
+    } else if (f32) {
+        const F32Seg seg{(const float*)x_out, Hd, n, (const float*)w->w_gate, (const float*)w->w_up, nullptr, nullptr, (float*)act, s->ffn, s->ffn,
+                         F32_SWIGLU, nullptr, 0};
+        SLIM_TRY(launch_f32_linear(&seg, 1, Hd, (const float*)w->g_ffn, s->rms_eps, d, s->rope_theta, st));
     } else {
         SLIM_TRY(launch_rmsnorm(x_out, w->g_ffn, n, Hd, s->rms_eps, dt, h, st));
         SLIM_TRY(launch_linear(h, Hd, w->w_gate, w->w_up, nullptr, nullptr, n, s->ffn, Hd, s->ffn, dt, act, st));

@@ -126,42 +126,6 @@ attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg, co
     );
 }
 
-// fp32 path (small fp32 workloads): one wave per (query, head).  Lanes split the keys, each keeps
-// its own online-softmax state over its keys, and the 64 partial states are merged at the end.
-template <int D>
-__global__ void __launch_bounds__(64) attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kg,
-                                                      const float* __restrict__ Vg, float* __restrict__ O, int n,
-                                                      int Hq, int Hkv, float scale) {
-    const int i = blockIdx.x, h = blockIdx.y, g = h / (Hq / Hkv), lane = threadIdx.x;
-    __shared__ float qs[D];
-    for (int c = lane; c < D; c += 64) qs[c] = Q[((size_t)i * Hq + h) * D + c];
-    __syncthreads();
-    float m = -INFINITY, l = 0.f, acc[D];
-#pragma unroll
-    for (int c = 0; c < D; ++c) acc[c] = 0.f;
-    for (int j = lane; j <= i; j += 64) {
-        const float* kr = Kg + ((size_t)j * Hkv + g) * D;
-        const float* vr = Vg + ((size_t)j * Hkv + g) * D;
-        float s = 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) s += qs[c] * kr[c];
-        s *= scale;
-        const float mn = fmaxf(m, s), a = expf(m - mn), p = expf(s - mn);
-        l = l * a + p;
-#pragma unroll
-        for (int c = 0; c < D; ++c) acc[c] = acc[c] * a + p * vr[c];
-        m = mn;
-    }
-    const float mall = wave_max(m);
-    const float w = (m == -INFINITY) ? 0.f : expf(m - mall);
-    const float lall = wave_sum(l * w);
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-        const float t = wave_sum(acc[c] * w);
-        if (lane == 0) O[((size_t)i * Hq + h) * D + c] = t / lall;
-    }
-}
-
 int launch_attn(const void* q, const void* k, const void* v, int n, int Hq, int Hkv, int d, float scale,
                 int dtype, void* out, hipStream_t st) {
     if (scale == 0.f) scale = 1.0f / sqrtf((float)d);
@@ -188,17 +152,7 @@ int launch_attn(const void* q, const void* k, const void* v, int n, int Hq, int 
         }
         return check_launch();
     }
-    dim3 grid(n, Hq);
-#define SLIM_ATTN_F32(D) hipLaunchKernelGGL(attn_f32_kernel<D>, grid, dim3(64), 0, st, (const float*)q, \
-        (const float*)k, (const float*)v, (float*)out, n, Hq, Hkv, scale)
-    switch (d) {
-        case 32: SLIM_ATTN_F32(32); break;
-        case 64: SLIM_ATTN_F32(64); break;
-        case 128: SLIM_ATTN_F32(128); break;
-        default: return SLIM_UNSUPPORTED;
-    }
-#undef SLIM_ATTN_F32
-    return check_launch();
+    return launch_f32_attn((const float*)q, (const float*)k, (const float*)v, n, Hq, Hkv, d, scale, (float*)out, st);
 }
 
 }  // namespace slim

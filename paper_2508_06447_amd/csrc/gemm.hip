@@ -1040,61 +1040,6 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
                                 plan_big_tiles(M, tiles_n, cu_count(), small_tile_cost<EPI>(eight), eight), eight, st, re);
 }
 
-// fp32 path (small fp32 workloads only): 64x64 output tile, 16-deep k-tiles in LDS, 4x4 per thread.
-template <int EPI>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, int lda,
-                                                       const float* __restrict__ W0, const float* __restrict__ W1,
-                                                       const float* R, float* C, int ldo, int M, int N, int K) {
-    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
-    __shared__ float as[16][65];
-    __shared__ float ws[NW][16][65];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    float acc[NW][4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int i = tid; i < 64 * 16; i += 256) {
-            const int r = i >> 4, c = i & 15, k = k0 + c;
-            const int m = m0 + r, n = n0 + r;
-            as[c][r] = (m < M && k < K) ? A[(size_t)m * lda + k] : 0.f;
-            ws[0][c][r] = (n < N && k < K) ? W0[(size_t)n * K + k] : 0.f;
-            if (NW == 2) ws[NW - 1][c][r] = (n < N && k < K) ? W1[(size_t)n * K + k] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            float a[4], w[NW][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = as[c][ty * 4 + i];
-#pragma unroll
-            for (int q = 0; q < NW; ++q)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) w[q][j] = ws[q][c][tx * 4 + j];
-#pragma unroll
-            for (int q = 0; q < NW; ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[q][i][j] += a[i] * w[q][j];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float o = acc[0][i][j];
-            if (EPI == EPI_SWIGLU) { const float g = o; o = g / (1.0f + expf(-g)) * acc[NW - 1][i][j]; }
-            if (EPI == EPI_RESIDUAL) o += R[(size_t)m * ldo + n];
-            if (EPI == EPI_BIAS) o += R[n];
-            C[(size_t)m * ldo + n] = o;
-        }
-    }
-}
-
 // Query/Key projection with the RoPE epilogue (bf16, heads of 128, k_in a multiple of 64; checked by the caller).
 // row_scale != null: the rows of a are the raw residual stream and row_scale their 1/rms (fused RMSNorm).
 int launch_linear_rope(const void* a, int lda, const void* w, const void* bias, const float* table, const float* qt,
@@ -1156,13 +1101,9 @@ int launch_linear_pair(const void* a, int lda, const void* w_1, const void* bias
 int launch_linear(const void* a, int lda, const void* w0, const void* w1, const void* residual, const void* bias,
                   int m, int n_out, int k_in, int ldo, int dtype, void* out, hipStream_t st) {
     if (dtype == SLIM_F32) {
-        dim3 grid((n_out + 63) / 64, (m + 63) / 64);
-#define SLIM_F32_GEMM(E) hipLaunchKernelGGL(gemm_f32_kernel<E>, grid, dim3(256), 0, st, (const float*)a, lda, \
-        (const float*)w0, (const float*)w1, (const float*)(bias ? bias : residual), (float*)out, ldo, m, n_out, k_in)
-        if (w1) SLIM_F32_GEMM(EPI_SWIGLU); else if (residual) SLIM_F32_GEMM(EPI_RESIDUAL);
-        else if (bias) SLIM_F32_GEMM(EPI_BIAS); else SLIM_F32_GEMM(EPI_PLAIN);
-#undef SLIM_F32_GEMM
-        return check_launch();
+        const F32Seg seg{(const float*)a, lda, m, (const float*)w0, (const float*)w1, (const float*)bias, (const float*)residual,
+                         (float*)out, ldo, n_out, w1 ? F32_SWIGLU : F32_PLAIN, nullptr, 0};
+        return launch_f32_linear(&seg, 1, k_in, nullptr, 0.f, 0, 0.f, st);
     }
     const bf16_t *A = (const bf16_t*)a, *W0 = (const bf16_t*)w0, *W1 = (const bf16_t*)w1, *R = (const bf16_t*)residual;
     bf16_t* C = (bf16_t*)out;

@@ -157,6 +157,22 @@ int launch_split_residual(const float* partial, int splits, int m, int n, const 
 struct SplitHeadsArgs { void* out[3]; const void* bias[3]; int heads[3]; int rope[3]; int score; };
 int launch_split_heads(const float* partial, int splits, int m, const SplitHeadsArgs& a, const float* rstd, const int* pos, float theta,
                        const float* qt, float* token_scores, hipStream_t st);
+// Float32 projections of up to three matrices that share k_in (and, with gain, RMSNorm of their input rows) in one launch.
+enum F32Mode { F32_PLAIN, F32_SWIGLU, F32_ROPE };
+struct F32Seg {
+    const float* a;                      // rows [m], stride lda
+    int lda, m;
+    const float *w0, *w1;                // [n][k_in]; w1: the up matrix of F32_SWIGLU
+    const float* bias;                   // [n] or null (not with F32_SWIGLU)
+    const float* residual;               // rows of stride ldo or null (not with F32_SWIGLU); may be out
+    float* out;
+    int ldo, n;
+    F32Mode mode;
+    const int* pos;                      // F32_ROPE: positions of the rows, null = pos0, pos0 + 1, ..
+    int pos0;
+};
+int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain, float eps, int head_dim, float theta, hipStream_t st);
+int launch_f32_attn(const float* q, const float* k, const float* v, int n, int Hq, int Hkv, int d, float scale, float* out, hipStream_t st);
 int launch_attn(const void* q, const void* k, const void* v, int n, int Hq, int Hkv, int d, float scale,
                 int dtype, void* out, hipStream_t st);
 

@@ -144,6 +144,23 @@ def test_cfg1_keep_all_equals_unpruned_layer(slim):
     np.testing.assert_array_equal(res["pos"].cpu().numpy(), pos.numpy())
 
 
+@pytest.mark.parametrize("placement", ["before", "after"])
+@pytest.mark.parametrize("seq,hidden,heads,kv_heads,d,ffn,window,keep,bias", [
+    (33, 48, 2, 1, 32, 40, 5, 0.7, True),        # no dimension fills a tile
+    (200, 130, 3, 3, 64, 70, 32, 0.4, True),     # a reduction of 130: the last chunk holds two elements
+    (257, 64, 2, 1, 128, 96, 300, 0.3, False),   # window longer than the sequence
+    (100, 20, 4, 2, 32, 15, 8, 1.0, False),      # nothing dropped
+])
+def test_float32_layer_shapes(slim, seq, hidden, heads, kv_heads, d, ffn, window, keep, bias, placement):
+    """Float32 layers with gains that are not 1, against the oracle in full."""
+    wl = inputs.scaled(inputs.WORKLOADS["cfg1"], seq=seq, hidden=hidden, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=d, ffn=ffn,
+                       window=window, keep_ratio=keep, qkv_bias=bias, planted=3)
+    g = np.random.default_rng(seq)
+    gains = tuple(torch.from_numpy((1.0 + 0.2 * g.standard_normal(hidden)).astype(np.float32)) for _ in range(2))
+    r = check_layer(slim, wl, np.float64, label=f"float32 seq {seq} hidden {hidden} d {d} {placement}", placement=placement, gains=gains)
+    assert r["sc_err"] < 1e-5 and r["mx"] < F32_MAX_ABS
+
+
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("seq,block,window,keep", [(1024, 64, 64, 0.5), (1000, 64, 64, 0.3), (1536, 128, 128, 0.25)])
 def test_reduced_bf16_layer_full_output(slim, seq, block, window, keep, fold):

@@ -458,7 +458,52 @@ def test_rmsnorm_and_rope_in_one_projection(slim):
     np.testing.assert_allclose(f64(got), want, rtol=2.0 ** -8, atol=2.0 ** -8 * np.abs(want).max())
 
 
+# Tiles of 32 rows and 32 (SwiGLU: 16) features, the reduction in 16-deep chunks dealt to four waves: one short of and one
+# past each, fewer chunks than waves, reductions that are no multiple of 4, rows at any 4-byte address.
+@pytest.mark.parametrize("m,n,k,shift", [(1, 1, 1, 0), (31, 33, 15, 1), (32, 32, 16, 0), (33, 31, 17, 3), (65, 47, 63, 2), (64, 16, 65, 0),
+                                         (5, 130, 259, 1), (200, 17, 1030, 0)])
+def test_float32_projections(slim, m, n, k, shift):
+    """Float sums of k products: each within k roundings (2^-24) of the sum of the products' sizes."""
+    print(f"float32 linear m={m} n={n} k={k} shift={shift}", flush=True)
+    def at(t):                                           # the same values, `shift` floats past an aligned address
+        flat = torch.empty(t.numel() + 4, dtype=t.dtype, device="cuda")[shift:shift + t.numel()]
+        return flat.view(t.shape).copy_(t)
+    f4 = torch.float32
+    a, w, w2 = (at(rand(s, f4, i)) for i, s in enumerate(((m, k), (n, k), (n, k))))
+    r = at(rand((m, n), f4, 4))
+    prod, size = a.double() @ w.double().T, a.double().abs() @ w.double().abs().T
+    for name, want, got in (("plain", prod, slim.slim_linear(a, w)), ("residual", prod + r.double(), slim.slim_linear(a, w, residual=r, out=r))):
+        assert ((got.double() - want).abs() <= (k + 4) * 2.0 ** -24 * (size + want.abs()) + 1e-30).all(), name
+    if shift == 0:                                       # (a bias is 16-byte aligned, as before)
+        b = dev(rand((n,), f4, 5))
+        assert ((slim.slim_linear_bias(a, w, b).double() - prod - b.double()).abs() <= (k + 4) * 2.0 ** -24 * (size + b.double().abs())).all()
+    up, up_size = a.double() @ w2.double().T, a.double().abs() @ w2.double().abs().T
+    want = torch.nn.functional.silu(prod) * up           # |silu'| <= 1.1; the exponential and the division: 8 roundings of the result
+    bound = (k + 4) * 2.0 ** -24 * (1.1 * size * up.abs() + prod.abs() * up_size + 0.28 * up_size) + 2.0 ** -21 * want.abs() + 1e-30
+    assert ((slim.slim_swiglu_linear(a, w, w2).double() - want).abs() <= bound).all()
+
+
 # ------------------------------------------------------------------------------------------ attention
+@pytest.mark.parametrize("n,Hq,Hkv,d", [(1, 2, 1, 32), (15, 3, 3, 64), (16, 2, 2, 128), (17, 2, 1, 64), (63, 5, 1, 32), (65, 4, 2, 128), (129, 2, 2, 64)])
+def test_float32_attention_at_the_edges_of_its_key_tiles(slim, n, Hq, Hkv, d):
+    """Peaked logits (the running maximum moves), and a value row that is infinite or undefined stays out of the queries
+    before it."""
+    print(f"float32 attn n={n} H={Hq}/{Hkv} d={d}", flush=True)
+    q, k, v = inputs.stage_qkv(n, Hq, Hkv, d, "fp32", seed=n)
+    q = q * 4.0
+    want = so.causal_gqa_attention(f64(q), f64(k), f64(v))
+    got = f64(slim.slim_prefill_attn(dev(q), dev(k), dev(v)))
+    # a logit x is off by at most d 2^-24 sum|q k| * scale, its exponential by that share of itself, twice (sum and values)
+    size = np.abs(f64(q)).max() * np.abs(f64(k)).max() * np.sqrt(d)
+    assert np.abs(got - want).max() <= 2 * (d * 2.0 ** -24 * size + n * 2.0 ** -24) * np.abs(f64(v)).max()
+    for bad in (float("inf"), float("nan")):
+        v2 = v.clone()
+        v2[n - 1] = bad
+        got2 = f64(slim.slim_prefill_attn(dev(q), dev(k), dev(v2)))
+        np.testing.assert_allclose(got2[:n - 1], got[:n - 1], rtol=0, atol=1e-5)
+        assert not np.isfinite(got2[n - 1]).any()
+
+
 @pytest.mark.parametrize("n,Hq,Hkv,d,dtype", [
     (1, 4, 1, 128, torch.bfloat16), (37, 4, 2, 128, torch.bfloat16), (128, 8, 8, 128, torch.bfloat16),
     (200, 4, 1, 128, torch.bfloat16), (1000, 8, 2, 128, torch.bfloat16), (1280, 32, 8, 128, torch.bfloat16),
