@@ -1,12 +1,21 @@
 // Projections of ONE token (decoding phase of Fig. 2: "QKV Generation" and "FFN" for the newly decoded token):
 //   out[n] = s * (w[n, :] . x) (+ bias[n]) (+ residual[n]),   or   silu(s * w0[n, :] . x) * (s * w1[n, :] . x),
-// s = the token's 1/rms (fused RMSNorm with a folded gain: formed by every workgroup from its own LDS copy of the
-// token, or read from *scale) or 1.  HBM-bound: every weight is read once.  The token is staged in LDS as floats; a
-// wave owns 4 output features and walks their rows in 16-byte chunks, 64 chunks per step; sums by wave reduction, one
-// rounding.  Up to three weight matrices with their own bias and output share one launch (the Query, Key and Value
-// projections), and a segment can ask for RoPE at the token's position: its waves then own the features
-// {i, i+1, i+64, i+65} of a 128-wide head, so that the rotate-half partners meet in one wave.
+// s = the token's 1/rms (fused RMSNorm with a folded gain: formed by every workgroup from the token, or read from
+// *scale) or 1.  HBM-bound: every weight is read once, 16 bytes per lane, with a non-temporal hint (nothing will find it in
+// a cache again before the next token).
+//
+// A workgroup owns four weight rows (four features, or the gate and up rows of two) and its four waves deal their 1 KB
+// pieces out among themselves: a row piece meets the token's piece in registers, so no load waits for a barrier, and U
+// pieces of each row (16 to 112 registers per lane) are requested before the first is used.  With a wave per four rows, the token
+// staged in LDS and two pieces in flight, a launch of 4096 x 4096 was one round of workgroups that spent half its time on
+// latency.  Weights from HBM, us before -> now (bf16): 6144 x 4096 12.0 -> 9.2, 4096 x 4096 9.9 -> 7.1, 28672 x 4096 42.8 ->
+// 33.9 (6.9 TB/s), 4096 x 14336 27.3 -> 18.4; without the hint 9.9 / 7.4 / 37.4 / 20.3.
+//
+// Up to three matrices with their own bias and output share one launch (the Query, Key and Value projections), and a
+// segment can ask for RoPE at the token's position: its workgroups then own the features {i, i+1, i+64, i+65} of a 128-wide head,
+// so that the rotate-half partners meet in one workgroup.
 #include "slim_common.h"
+#include <math.h>
 
 namespace slim {
 
@@ -27,125 +36,133 @@ struct GemvArgs {
     const void* residual;    // segment 0 only
     int k;
     int position;            // RoPE position of the token
-    float theta;
+    double inv_freq[64];
 };
 
-template <typename T, bool SWIGLU>
-__global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
-    constexpr int V = Elem<T>::kVec, R = 4, NM = SWIGLU ? 2 : 1;
-    extern __shared__ float xs[];
-    __shared__ float part[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = a.k;
-    const T* x = (const T*)a.x;
-    float ss = 0.f;
-    for (int c = tid; c < K / V; c += 256) {
-        float f[V];
-        Elem<T>::unpack(*reinterpret_cast<const uint4*>(x + (size_t)c * V), f);
-#pragma unroll
-        for (int i = 0; i < V; ++i) { xs[c * V + i] = f[i]; ss += f[i] * f[i]; }
-    }
-    ss = wave_sum(ss);
-    if (lane == 0) part[wave] = ss;
-    __syncthreads();
-    float sc = a.scale ? *a.scale : 1.0f;
-    if (a.norm_eps >= 0.f) sc = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)K + a.norm_eps);
+constexpr int kGemvRows = 4; // weight rows per workgroup
+constexpr int kGemvGrid = 1 << 22;                       // workgroups per row of the grid (work items per dimension stay below 2^32)
 
-    // this wave's segment and rows
-    int j = blockIdx.x * 4 + wave, s = 0;
-    while (s < a.n_seg - 1 && j >= (a.seg[s].n + R - 1) / R) { j -= (a.seg[s].n + R - 1) / R; ++s; }
+// 16 bytes that no other workgroup reads.
+__device__ __forceinline__ uint4 load_once(const void* p) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
+
+template <typename T, bool SWIGLU, int U>
+__global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
+    constexpr int V = Elem<T>::kVec, R = kGemvRows, FPW = SWIGLU ? R / 2 : R;   // features per workgroup
+    __shared__ float red[4][R + 1];                      // per wave: its share of the rows' sums and of the token's sum of squares
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = a.k, nchunk = K / V;
+    long long j = blockIdx.x + (long long)blockIdx.y * kGemvGrid;
+    int s = 0;                                           // this workgroup's segment, j: its place in it
+    while (s < a.n_seg - 1 && j >= (a.seg[s].n + FPW - 1) / FPW) { j -= (a.seg[s].n + FPW - 1) / FPW; ++s; }
     const GemvSeg sg = a.seg[s];
     const int N = sg.n;
-    if (j * R >= N) return;
-    int rown[R];                                         // output feature of each of the wave's rows
-    if (sg.rope) {
-        const int head = j >> 5, i0 = (j & 31) * 2;
+    if (j * FPW >= N) return;                            // (the last row of the grid is not full)
+    const int n0 = (int)(sg.rope ? (j >> 5) * 128 + (j & 31) * 2 : j * FPW);
+    auto feature = [&](int r) { return sg.rope ? n0 + (r & 1) + (r >> 1) * 64 : n0 + r; };
+    const T* rows[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) rown[r] = head * 128 + i0 + (r & 1) + (r >> 1) * 64;
-    } else {
+    for (int r = 0; r < R; ++r)                          // features past the end repeat the last one
+        rows[r] = (SWIGLU && r >= FPW ? (const T*)a.w_up : (const T*)sg.w) + (size_t)min(feature(SWIGLU ? r % FPW : r), N - 1) * K;
+    const T* x = (const T*)a.x;
+    uint4 raw[U][R], xr[U];
+    auto load = [&](int c0) {                            // pieces past the end: the token's values are zeros there
 #pragma unroll
-        for (int r = 0; r < R; ++r) rown[r] = min(j * R + r, N - 1);   // rows past the end repeat the last one
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * 256, cc = min(c, nchunk - 1);
+            xr[u] = c < nchunk ? *reinterpret_cast<const uint4*>(x + (size_t)cc * V) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) raw[u][r] = load_once(rows[r] + (size_t)cc * V);
+        }
+    };
+    load(tid);
+    float cs = 1.f, sn = 0.f;                            // of the thread's rotation index, while the weights are on their way
+    if (sg.rope && tid < R) {
+        const double ang = (double)a.position * a.inv_freq[(n0 + (tid & 1)) & 63];
+        const double kk = rint(ang * 0.15915494309189535);
+        sincosf((float)fma(-kk, 2.4492935982947064e-16, fma(-kk, 6.283185307179586, ang)), &sn, &cs);
     }
-    const T* rows[NM][R];
+    float acc[R], ss = 0.f;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        rows[0][r] = (const T*)sg.w + (size_t)rown[r] * K;
-        if (SWIGLU) rows[NM - 1][r] = (const T*)a.w_up + (size_t)rown[r] * K;
-    }
-    float acc[NM][R];
+    for (int r = 0; r < R; ++r) acc[r] = 0.f;
+    for (int c = tid; c - lane < nchunk; c += 256 * U) { // (wave-uniform bound)
+        if (c != tid) load(c);
 #pragma unroll
-    for (int m = 0; m < NM; ++m)
+        for (int u = 0; u < U; ++u) {
+            float xf[V];
+            Elem<T>::unpack(xr[u], xf);
 #pragma unroll
-        for (int r = 0; r < R; ++r) acc[m][r] = 0.f;
-    const int nchunk = K / V;
-#pragma unroll 2
-    for (int c = lane; c < nchunk; c += 64) {
-        uint4 raw[NM][R];
-#pragma unroll
-        for (int m = 0; m < NM; ++m)
-#pragma unroll
-            for (int r = 0; r < R; ++r) raw[m][r] = *reinterpret_cast<const uint4*>(rows[m][r] + (size_t)c * V);
-        float xf[V];
-#pragma unroll
-        for (int i = 0; i < V; ++i) xf[i] = xs[c * V + i];
-#pragma unroll
-        for (int m = 0; m < NM; ++m)
+            for (int i = 0; i < V; ++i) ss += xf[i] * xf[i];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 float f[V];
-                Elem<T>::unpack(raw[m][r], f);
+                Elem<T>::unpack(raw[u][r], f);
+                if (c + u * 256 >= nchunk) continue;     // (a repeated piece may hold an infinity: 0 times it is not 0)
 #pragma unroll
-                for (int i = 0; i < V; ++i) acc[m][r] += f[i] * xf[i];
+                for (int i = 0; i < V; ++i) acc[r] += f[i] * xf[i];
             }
-    }
-#pragma unroll
-    for (int m = 0; m < NM; ++m)
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc[m][r] = wave_sum(acc[m][r]);
-    if (lane < R) {
-        auto pick = [&](const float (&v)[R], int r) { return r == 0 ? v[0] : r == 1 ? v[1] : r == 2 ? v[2] : v[3]; };
-        const int n = sg.rope ? (j >> 5) * 128 + (j & 31) * 2 + (lane & 1) + (lane >> 1) * 64 : j * R + lane;
-        if (n < N) {
-            float val = pick(acc[0], lane) * sc;
-            if (SWIGLU) {
-                const float u = pick(acc[NM - 1], lane) * sc;
-                val = val / (1.0f + __expf(-val)) * u;
-            }
-            const T* bias = (const T*)sg.bias;
-            if (bias) val += Elem<T>::ld(bias + n);
-            if (sg.rope) {
-                // partner = the row 64 features away, held by lane ^ 2; both with scale and bias applied
-                const int np = n ^ 64;                   // (n % 128) +- 64 inside the head
-                float other = pick(acc[0], lane ^ 2) * sc;
-                if (bias) other += Elem<T>::ld(bias + np);
-                const int i = n & 63;
-                const double inv_freq = pow((double)a.theta, -2.0 * (double)i / 128.0);
-                const double ang = (double)a.position * inv_freq;
-                const double kk = rint(ang * 0.15915494309189535);
-                const double red = fma(-kk, 2.4492935982947064e-16, fma(-kk, 6.283185307179586, ang));
-                float sn, cs;
-                sincosf((float)red, &sn, &cs);
-                val = (n & 64) ? val * cs + other * sn : val * cs - other * sn;
-            }
-            if (s == 0 && a.residual) val += Elem<T>::ld((const T*)a.residual + n);
-            Elem<T>::st((T*)sg.out + n, val);
         }
     }
+    // The four sums in one butterfly: after the first two exchanges a lane carries one row, row lane / 16.
+#pragma unroll
+    for (int h = R / 2, o = 32; h >= 1; h >>= 1, o >>= 1) {
+        const bool up = lane & o;
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const float keep = up ? acc[i + h] : acc[i], give = up ? acc[i] : acc[i + h];
+            acc[i] = keep + __shfl_xor(give, o, 64);
+        }
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
+    if ((lane & 15) == 0) red[wave][lane >> 4] = acc[0];
+    if (a.norm_eps >= 0.f) {
+        ss = wave_sum(ss);
+        if (lane == 0) red[wave][R] = ss;
+    }
+    __syncthreads();
+    if (tid >= FPW) return;
+    auto row_sum = [&](int r) { return red[0][r] + red[1][r] + red[2][r] + red[3][r]; };
+    const int n = feature(tid);
+    if (n >= N) return;
+    float sc = a.scale ? *a.scale : 1.0f;
+    if (a.norm_eps >= 0.f) sc = 1.0f / sqrtf(row_sum(R) / (float)K + a.norm_eps);
+    float val = row_sum(tid) * sc;
+    if (SWIGLU) val = val / (1.0f + __expf(-val)) * (row_sum(FPW + tid) * sc);
+    const T* bias = (const T*)sg.bias;
+    if (bias) val += Elem<T>::ld(bias + n);
+    if (sg.rope) {                                       // partner: the row 64 features away, with scale and bias applied
+        float other = row_sum(tid ^ 2) * sc;
+        if (bias) other += Elem<T>::ld(bias + (n ^ 64));
+        val = (n & 64) ? val * cs + other * sn : val * cs - other * sn;
+    }
+    if (s == 0 && a.residual) val += Elem<T>::ld((const T*)a.residual + n);
+    Elem<T>::st((T*)sg.out + n, val);
+}
+
+// Pieces in flight per row: all of a wave's share where that is 7 or fewer (7 beats 4 by 3 % at k_in 14336 although fewer
+// waves fit: one wait instead of two).
+template <typename T, bool S>
+static void launch_gemv_u(const GemvArgs& a, dim3 grid, hipStream_t st) {
+    const int pieces = (a.k / Elem<T>::kVec + 255) / 256;
+#define SLIM_GEMV(U) hipLaunchKernelGGL((gemv_kernel<T, S, U>), grid, dim3(256), 0, st, a)
+    if (pieces <= 2) SLIM_GEMV(2); else if (pieces > 4 && pieces <= 7) SLIM_GEMV(7); else SLIM_GEMV(4);
+#undef SLIM_GEMV
 }
 
 static int launch_gemv_args(const GemvArgs& a, int dtype, hipStream_t st) {
-    int waves = 0;
-    for (int s = 0; s < a.n_seg; ++s) waves += (a.seg[s].n + 3) / 4;
-    const dim3 grid((waves + 3) / 4);
-    const size_t smem = (size_t)a.k * sizeof(float);
-#define SLIM_GEMV(T, S) hipLaunchKernelGGL((gemv_kernel<T, S>), grid, dim3(256), smem, st, a)
-    if (dtype == SLIM_BF16) { if (a.w_up) SLIM_GEMV(bf16_t, true); else SLIM_GEMV(bf16_t, false); }
-    else                    { if (a.w_up) SLIM_GEMV(float, true);  else SLIM_GEMV(float, false); }
-#undef SLIM_GEMV
+    const int per = a.w_up ? kGemvRows / 2 : kGemvRows;
+    long long wgs = 0;
+    for (int s = 0; s < a.n_seg; ++s) wgs += ((long long)a.seg[s].n + per - 1) / per;
+    const dim3 grid((unsigned)(wgs < kGemvGrid ? wgs : kGemvGrid), (unsigned)((wgs + kGemvGrid - 1) / kGemvGrid));
+    if (dtype == SLIM_BF16) { if (a.w_up) launch_gemv_u<bf16_t, true>(a, grid, st); else launch_gemv_u<bf16_t, false>(a, grid, st); }
+    else                    { if (a.w_up) launch_gemv_u<float, true>(a, grid, st);  else launch_gemv_u<float, false>(a, grid, st); }
     return check_launch();
 }
 
-// One matrix (or gate/up pair).  k_in a multiple of 8 (bf16) or 4 (fp32), x and the weights 16-byte aligned,
-// k_in * 4 bytes of LDS (checked by the caller).  norm_eps >= 0 computes the scale from x itself.
+// One matrix (or gate/up pair).  k_in a multiple of 8 (bf16) or 4 (fp32), x and the weights 16-byte aligned
+// (checked by the caller).  norm_eps >= 0 computes the scale from x itself.
 int launch_gemv(const void* w0, const void* w1, const void* x, const float* scale, float norm_eps, const void* bias,
                 const void* residual, int n_out, int k_in, int dtype, void* out, hipStream_t st) {
     GemvArgs a{};
@@ -174,7 +191,7 @@ int launch_gemv_qkv(const void* wq, const void* wk, const void* wv, const void* 
     a.norm_eps = norm_eps;
     a.k = k_in;
     a.position = position;
-    a.theta = theta;
+    for (int i = 0; i < 64; ++i) a.inv_freq[i] = pow((double)theta, -2.0 * (double)i / 128.0);
     return launch_gemv_args(a, dtype, st);
 }
 
