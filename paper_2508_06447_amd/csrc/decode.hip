@@ -3,235 +3,269 @@
 // tokens of the blocks that currently sit in the GPU slot pool -- read through block_of_slot, wherever the KV swap
 // (Algorithm 1) has put them -- and to all response tokens.  HBM-bound: every resident key and value is read once.
 //
-// Split over the keys: one workgroup per (slot or 64-token chunk of the response, kv head) leaves a partial
-// (max, sum, weighted values) for the query heads of that kv head; a second kernel merges the partials.  Softmax
-// is order-independent, so the slot order does not matter.
+// Split over the keys: the 16-key groups of the slots and of the response are dealt to the waves of up to
+// kDecWgs / Hkv workgroups per kv head, each of which leaves a partial (max, sum, weighted values) for the query
+// heads of that kv head; a second kernel merges the partials.  Softmax is order-independent, so the slot order does
+// not matter.
 #include "slim_common.h"
+#include <algorithm>
+#include <type_traits>
 
 namespace slim {
 
 constexpr int DD = 128;          // head_dim
-constexpr int DCH = 64;          // keys per chunk
+constexpr int DGK = 16;          // keys per group
 constexpr int DGMAX = 8;         // query heads per kv head
 constexpr int DPART = DD + 2;    // floats of a partial: values, max (base-2 domain), sum
 
-// A wave owns 16 keys of a 64-key chunk and keeps its own running (max, sum, values): no workgroup barrier until
-// the four waves' states are merged at the end.  Scores: 4 lanes per key, 32 dims each (16-byte loads), reduced
-// with two shuffles.  Values: a lane owns dims 2 l, 2 l + 1 of all 16 keys (4-byte loads, a row is read by the
-// whole wave), the probabilities go through a wave-private LDS strip.
+// Value of lane H of the caller's row of 16 lanes.
+template <int H> __device__ __forceinline__ float row_lane(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + H, 0xf, 0xf, true));
+}
+// Maximum over the four lanes with the same lane % 16.
+__device__ __forceinline__ float max_over_rows(float v) {
+    const unsigned x = __builtin_bit_cast(unsigned, v);
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const float m = fmaxf(__builtin_bit_cast(float, a[0]), __builtin_bit_cast(float, a[1]));
+    const unsigned y = __builtin_bit_cast(unsigned, m);
+    const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return fmaxf(__builtin_bit_cast(float, b[0]), __builtin_bit_cast(float, b[1]));
+}
+template <int G, int H = 0, typename F> __device__ __forceinline__ void for_heads(F f) {
+    if constexpr (H < G) {
+        f(std::integral_constant<int, H>{});
+        for_heads<G, H + 1>(f);
+    }
+}
+__device__ __forceinline__ uint4 load_stream(const void* p) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
+
+// Lane (l16, q) = (lane % 16, lane / 16).
+//   S[key, head] = K . Q^T by 16-row matrix instructions: the lane supplies 16-byte pieces of key l16 and of query head l16 (heads
+//   past G repeat the last one and are ignored) and holds, for head l16, the logits of keys 4 q .. 4 q + 3: the maximum
+//   of a group takes two exchanges, the sum none until the end.
+//   O += P V by the vector ALU: the lane loads 16-byte pieces of the value rows of the same keys 4 q + e, 8 features of each, and
+//   takes P of head h from lane h of its row of 16.
+// The registers of a piece are requested anew as soon as it is used; the slot of the group after that is looked up meanwhile.
 template <typename T, int G>
 __global__ void __launch_bounds__(256) decode_attn_partial_kernel(
     const T* __restrict__ q, const unsigned char* __restrict__ pool, size_t slot_bytes, size_t layer_offset,
     const int* __restrict__ block_of_slot, int n_slots, int block, int n_prompt, const T* __restrict__ k_resp,
     const T* __restrict__ v_resp, int n_resp, int Hq, int Hkv, float scale_log2e, float* __restrict__ part) {
-    constexpr int V = Elem<T>::kVec;
-    // Query heads of this kv head: floats times scale * log2(e) (fp32 path), or the bf16 pairs as they are, for
-    // v_dot2_f32_bf16 (half the registers; the scale is then applied to the dot products).
-    __shared__ float qs[G][sizeof(T) == 2 ? DD / 2 : DD];
-    __shared__ float ps[4][16][G];                   // per wave: probabilities of its 16 keys
-    __shared__ float ws_m[4][G], ws_l[4][G];     // per wave: running max and sum
-    __shared__ float red[4][G][DD];                  // per wave: weighted values
-    const int item = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;   // G = Hq / Hkv query heads per kv head
-    const int wave = tid >> 6, lane = tid & 63;
+    constexpr int V = Elem<T>::kVec, NK = DD / (4 * V), NV = 8 / V;   // pieces of a key per lane; of a value row per lane
+    __shared__ float red[4][2][G][DD];                   // per wave and half of its lanes: weighted values
+    __shared__ float ws_m[4][G], ws_l[4][G];             // per wave: maximum and sum
+    const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, qr = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t row_stride = (size_t)Hkv * DD;
-    const int nb = (n_prompt + block - 1) / block;
+    const int nb = (n_prompt + block - 1) / block, per_slot = (block + DGK - 1) / DGK;
+    const int n_in_slots = n_slots * per_slot, n_groups = n_in_slots + (n_resp + DGK - 1) / DGK;
+    const int step = gridDim.x * 4;
 
-    const T *kp, *vp;
-    int rows;
-    if (item < n_slots) {
-        const int b = block_of_slot[item];
-        rows = (b < 0 || b >= nb) ? 0 : min(block, n_prompt - b * block);
-        kp = reinterpret_cast<const T*>(pool + (size_t)item * slot_bytes + layer_offset);
-        vp = kp + (size_t)block * row_stride;
-    } else {
-        const int j = item - n_slots;
-        rows = min(DCH, n_resp - j * DCH);
-        kp = k_resp + (size_t)j * DCH * row_stride;
-        vp = v_resp + (size_t)j * DCH * row_stride;
-    }
-    if constexpr (sizeof(T) == 2) {
-        for (int i = tid; i < G * DD / 2; i += 256)
-            qs[i / (DD / 2)][i % (DD / 2)] = __builtin_bit_cast(float, reinterpret_cast<const uint32_t*>(q + (size_t)g * G * DD)[i]);
-    } else {
-        for (int i = tid; i < G * DD; i += 256) qs[i / DD][i % DD] = Elem<T>::ld(q + (size_t)(g * G + i / DD) * DD + i % DD) * scale_log2e;
-    }
-    __syncthreads();
-
-    float m_run[G], l_run[G], oacc[G][2];
-#pragma unroll
-    for (int h = 0; h < G; ++h) { m_run[h] = -INFINITY; l_run[h] = 0.f; oacc[h][0] = oacc[h][1] = 0.f; }
-    const int kl = lane >> 2, prt = lane & 3;            // scores: key kl of the wave's 16, dims 32 prt ..
-    for (int c0 = wave * 16; c0 < rows; c0 += DCH) {     // this wave's keys c0 .. c0 + 15 (wave-uniform bounds)
-        const int cr = min(16, rows - c0);
-        float dot[G];
-#pragma unroll
-        for (int h = 0; h < G; ++h) dot[h] = 0.f;
-        // rows past the end are clamped to the last one (their logit is masked below), so no load is conditional;
-        // all loads of the chunk are requested before any arithmetic
-        uint4 raw[32 / V];
-        {
-            const T* kr = kp + (size_t)(c0 + min(kl, cr - 1)) * row_stride + (size_t)g * DD + prt * 32;
-#pragma unroll
-            for (int c = 0; c < 32 / V; ++c) raw[c] = *reinterpret_cast<const uint4*>(kr + c * V);
-        }
-        float v0[16], v1[16];
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            {   // clamped like the keys: a row past the end gets probability 0
-                const T* vr = vp + (size_t)(c0 + min(kk, cr - 1)) * row_stride + (size_t)g * DD + 2 * lane;
-                if constexpr (sizeof(T) == 2) {          // one 4-byte load for the bf16 pair
-                    const uint32_t pr = *reinterpret_cast<const uint32_t*>(vr);
-                    v0[kk] = lo_bf16(pr);
-                    v1[kk] = hi_bf16(pr);
-                } else {
-                    v0[kk] = Elem<T>::ld(vr);
-                    v1[kk] = Elem<T>::ld(vr + 1);
-                }
+    // The wave's groups are gi, gi + step, ..; those of a free slot and past the end of a short block hold no key and are passed
+    // over.  All of this is wave-uniform.
+    int gi = (int)blockIdx.x * 4 + wave, rows = 0;
+    const T *kp = nullptr, *vp = nullptr;                // first Key and Value row of the group, kv head g
+    auto find = [&]() {                                  // from gi on; false: none is left
+        for (; gi < n_groups; gi += step) {
+            if (gi < n_in_slots) {
+                const int slot = gi / per_slot, c0 = (gi - slot * per_slot) * DGK, b = block_of_slot[slot];
+                if (b < 0 || b >= nb) continue;
+                const int r = min(DGK, min(block, n_prompt - b * block) - c0);
+                if (r <= 0) continue;
+                rows = r;                                // (only of a group that is taken: the last one may be requested again)
+                kp = reinterpret_cast<const T*>(pool + (size_t)slot * slot_bytes + layer_offset) + (size_t)c0 * row_stride + (size_t)g * DD;
+                vp = kp + (size_t)block * row_stride;
+            } else {
+                const int c0 = (gi - n_in_slots) * DGK;
+                rows = min(DGK, n_resp - c0);
+                kp = k_resp + (size_t)c0 * row_stride + (size_t)g * DD;
+                vp = v_resp + (size_t)c0 * row_stride + (size_t)g * DD;
             }
+            return true;
         }
-        if constexpr (sizeof(T) == 2) {
-            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        return false;
+    };
+    uint4 kx[NK], vx[4][NV];
+    // Rows past the end repeat the last one: their P is 0.  Addresses are a wave-uniform base and a 32-bit offset of the lane.
+    const unsigned stride = (unsigned)(row_stride * sizeof(T));
+    auto load_k = [&]() {
+        const unsigned off = (unsigned)min(l16, rows - 1) * stride + qr * 16;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t kw[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
+        for (int c = 0; c < NK; ++c) kx[c] = load_stream(reinterpret_cast<const unsigned char*>(kp) + off + c * 64);
+    };
+    auto load_v = [&]() {
 #pragma unroll
-                for (int h = 0; h < G; ++h)
+        for (int e = 0; e < 4; ++e) {
+            const unsigned off = (unsigned)min(qr * 4 + e, rows - 1) * stride + l16 * 16;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        dot[h] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kw[i]),
-                                                                 __builtin_bit_cast(bf16x2, qs[h][prt * 16 + c * 4 + i]), dot[h], false);
-            }
-#pragma unroll
-            for (int h = 0; h < G; ++h) dot[h] *= scale_log2e;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 32 / V; ++c) {
-                float f[V];
-                Elem<T>::unpack(raw[c], f);
-#pragma unroll
-                for (int h = 0; h < G; ++h) {
-#pragma unroll
-                    for (int i = 0; i < V; ++i) dot[h] += f[i] * qs[h][prt * 32 + c * V + i];
-                }
-            }
+            for (int c = 0; c < NV; ++c) vx[e][c] = load_stream(reinterpret_cast<const unsigned char*>(vp) + off + c * 256);
         }
+    };
+    bool more = find();
+    if (more) { load_k(); load_v(); }
+    uint4 qx[NK];
+    {
+        const T* qp = q + (size_t)(g * G + min(l16, G - 1)) * DD + qr * V;
 #pragma unroll
-        for (int h = 0; h < G; ++h) {
-            float sc = dot[h] + __shfl_xor(dot[h], 1, 64);
-            sc += __shfl_xor(sc, 2, 64);
-            sc = kl < cr ? sc : -INFINITY;
-            float cm = sc;                               // maximum over the 16 keys (lanes 4 apart)
-#pragma unroll
-            for (int o = 4; o < 64; o <<= 1) cm = fmaxf(cm, __shfl_xor(cm, o, 64));
-            const float mn = fmaxf(m_run[h], cm);        // finite: the wave has at least one key here
-            const float al = __builtin_amdgcn_exp2f(m_run[h] - mn);
-            const float p = __builtin_amdgcn_exp2f(sc - mn);
-            float sum = p;
-#pragma unroll
-            for (int o = 4; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
-            m_run[h] = mn;
-            l_run[h] = l_run[h] * al + sum;
-            oacc[h][0] *= al;
-            oacc[h][1] *= al;
-            if (prt == 0) ps[wave][kl][h] = p;
-        }
-        __builtin_amdgcn_wave_barrier();                 // the strip is written and read by this wave only
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk)
-#pragma unroll
-            for (int h = 0; h < G; ++h)
-                {
-                    const float p = ps[wave][kk][h];
-                    oacc[h][0] += p * v0[kk];
-                    oacc[h][1] += p * v1[kk];
-                }
-        __builtin_amdgcn_wave_barrier();
+        for (int c = 0; c < NK; ++c) qx[c] = *reinterpret_cast<const uint4*>(qp + c * 4 * V);
     }
-    // ---- the four waves' states are merged, and the partial is written
+    float m_run = -INFINITY, l_run = 0.f, o[G][8];       // of head l16 (the sum: of the lane's own keys); of the lane's 8 features
 #pragma unroll
     for (int h = 0; h < G; ++h)
-        {
-            red[wave][h][2 * lane] = oacc[h][0];
-            red[wave][h][2 * lane + 1] = oacc[h][1];
-            if (lane == 0) { ws_m[wave][h] = m_run[h]; ws_l[wave][h] = l_run[h]; }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[h][i] = 0.f;
+
+    while (more) {
+        const int have = rows;
+        gi += step;
+        more = find();                                   // none left: the last group is requested once more, and not used
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NK; ++c) {
+            if constexpr (sizeof(T) == 2) {
+                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kx[c]), __builtin_bit_cast(bf16x8, qx[c]), s, 0, 0, 0);
+            } else {
+                const f32x4 a = __builtin_bit_cast(f32x4, kx[c]), b = __builtin_bit_cast(f32x4, qx[c]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], s, 0, 0, 0);
+            }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        load_k();                                        // the next group's keys fly under this one's values
+        float mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s[e] = qr * 4 + e < have ? s[e] * scale_log2e : -INFINITY;
+            mx = fmaxf(mx, s[e]);
+        }
+        const float mn = fmaxf(m_run, max_over_rows(mx)), al = __builtin_amdgcn_exp2f(m_run - mn);   // finite: the group has a key
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(s[e] - mn);
+        l_run = l_run * al + ((p[0] + p[1]) + (p[2] + p[3]));
+        m_run = mn;
+        for_heads<G>([&](auto h) {
+            const float a = row_lane<h.value>(al);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[h.value][i] *= a;
+        });
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            __builtin_amdgcn_sched_barrier(0);           // (left alone, the four values and all P of a head are unpacked at once: spills)
+            float f[8];
+#pragma unroll
+            for (int c = 0; c < NV; ++c) Elem<T>::unpack(vx[e][c], f + c * V);
+            for_heads<G>([&](auto h) {
+                const float ph = row_lane<h.value>(p[e]);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) o[h.value][i] += ph * f[i];
+            });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_v();
+    }
+    // ---- the lanes' and then the four waves' states are merged, and the partial is written
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    if (lane < G) { ws_m[wave][lane] = m_run; ws_l[wave][lane] = l_run; }
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[h][i] += __shfl_xor(o[h][i], 32, 64);
+        if (lane < 32) {
+#pragma unroll
+            for (int c = 0; c < NV; ++c)
+#pragma unroll
+                for (int i = 0; i < V; i += 4)
+                    *reinterpret_cast<f32x4*>(&red[wave][qr][h][c * 16 * V + l16 * V + i]) =
+                        f32x4{o[h][c * V + i], o[h][c * V + i + 1], o[h][c * V + i + 2], o[h][c * V + i + 3]};
+        }
+    }
     __syncthreads();
     for (int i = tid; i < G * DD; i += 256) {
         const int h = i / DD, dd = i - h * DD;
         const float M = fmaxf(fmaxf(ws_m[0][h], ws_m[1][h]), fmaxf(ws_m[2][h], ws_m[3][h]));
-        float o = 0.f, l = 0.f;
+        float acc = 0.f, l = 0.f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const float sc = ws_l[w][h] > 0.f ? __builtin_amdgcn_exp2f(ws_m[w][h] - M) : 0.f;
-            o += sc * red[w][h][dd];
+            acc += sc * (red[w][0][h][dd] + red[w][1][h][dd]);
             l += sc * ws_l[w][h];
         }
-        float* dst = part + ((size_t)item * Hq + g * G + h) * DPART;
-        dst[dd] = o;
+        float* dst = part + ((size_t)blockIdx.x * Hq + g * G + h) * DPART;
+        dst[dd] = acc;
         if (dd == 0) { dst[DD] = M; dst[DD + 1] = l; }
     }
 }
 
-// One workgroup per query head: out = sum_i 2^(m_i - M) o_i / sum_i 2^(m_i - M) l_i over the partials.  1024
-// threads = 8 groups of 128 dims; the weights of up to 1024 partials at a time are formed in parallel and kept in
-// LDS, then group j takes the partials j, j + 8, ... so that the loads of a thread do not depend on each other.
-// A partial without keys has sum 0 and zero values, and gets weight 0.
+// One workgroup per query head: out = sum_i 2^(m_i - M) o_i / sum_i 2^(m_i - M) l_i over the at most kDecParts partials.
+// 1024 threads = 8 groups of 128 features; group j takes the partials j, j + 8, ..  Everything is requested at once: the
+// launch is one trip to memory.  A partial without keys has sum 0 and zero values, and gets weight 0.
 constexpr int DMT = 1024;
+constexpr int kDecParts = 128;   // partials per query head at most
+constexpr int kDecWgs = 512;     // workgroups of the first kernel, over all kv heads
 template <typename T>
-__global__ void __launch_bounds__(DMT) decode_attn_merge_kernel(const float* __restrict__ part, int n_items, int Hq,
+__global__ void __launch_bounds__(DMT) decode_attn_merge_kernel(const float* __restrict__ part, int n_parts, int Hq,
                                                                 T* __restrict__ out) {
-    __shared__ float wts[DMT];
-    __shared__ float wred[DMT / 64];
-    __shared__ float accs[DMT / DD][DD];
+    constexpr int NG = DMT / DD, PER = kDecParts / NG;
+    __shared__ float wts[kDecParts];
+    __shared__ float wred[2][kDecParts / 64];
+    __shared__ float accs[NG][DD];
     const int h = blockIdx.x, tid = threadIdx.x, grp = tid >> 7, dd = tid & (DD - 1);
-    auto item = [&](int i) { return part + ((size_t)i * Hq + h) * DPART; };
-    float m = -INFINITY;
-    for (int i = tid; i < n_items; i += DMT) m = fmaxf(m, item(i)[DD]);
-    m = wave_max(m);
-    if ((tid & 63) == 0) wred[tid >> 6] = m;
-    __syncthreads();
-    float M = wred[0];
+    auto item = [&](int i) { return part + ((size_t)min(i, n_parts - 1) * Hq + h) * DPART; };
+    float val[PER];
 #pragma unroll
-    for (int i = 1; i < DMT / 64; ++i) M = fmaxf(M, wred[i]);
-    __syncthreads();
-    float lsum = 0.f, acc = 0.f;
-    for (int base = 0; base < n_items; base += DMT) {
-        const int i = base + tid;
-        float w = 0.f;
-        if (i < n_items) {
-            const float* p = item(i);
-            if (p[DD + 1] > 0.f) {
-                w = __builtin_amdgcn_exp2f(p[DD] - M);
-                lsum += w * p[DD + 1];
-            }
-        }
-        wts[tid] = w;
-        __syncthreads();
-        const int cnt = min(DMT, n_items - base);
-#pragma unroll 4
-        for (int j = grp; j < cnt; j += DMT / DD) acc += wts[j] * item(base + j)[dd];
-        __syncthreads();
+    for (int i = 0; i < PER; ++i) val[i] = grp + i * NG < n_parts ? item(grp + i * NG)[dd] : 0.f;
+    float m = -INFINITY, l = 0.f;
+    if (tid < kDecParts) {
+        if (tid < n_parts) { m = item(tid)[DD]; l = item(tid)[DD + 1]; }
+        const float wm = wave_max(m);
+        if ((tid & 63) == 0) wred[0][tid >> 6] = wm;
     }
-    lsum = wave_sum(lsum);
-    if ((tid & 63) == 0) wred[tid >> 6] = lsum;
+    __syncthreads();
+    float M = wred[0][0];
+#pragma unroll
+    for (int i = 1; i < kDecParts / 64; ++i) M = fmaxf(M, wred[0][i]);
+    if (tid < kDecParts) {
+        const float w = l > 0.f ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+        wts[tid] = w;
+        const float ws = wave_sum(w * l);
+        if ((tid & 63) == 0) wred[1][tid >> 6] = ws;
+    }
+    __syncthreads();
+    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) acc += wts[grp + i * NG] * val[i];
     accs[grp][dd] = acc;
     __syncthreads();
     if (grp == 0) {
-        float L = 0.f, a = 0.f;
+        float a = 0.f, l_all = 0.f;
 #pragma unroll
-        for (int i = 0; i < DMT / 64; ++i) L += wred[i];
+        for (int i = 0; i < NG; ++i) a += accs[i][dd];
 #pragma unroll
-        for (int i = 0; i < DMT / DD; ++i) a += accs[i][dd];
-        Elem<T>::st(out + (size_t)h * DD + dd, a / L);
+        for (int i = 0; i < kDecParts / 64; ++i) l_all += wred[1][i];
+        Elem<T>::st(out + (size_t)h * DD + dd, a / l_all);
     }
+}
+
+// Workgroups per kv head: enough for kDecWgs in all, every wave the same number of groups where that can be, and no more
+// partials than the caller's workspace holds (one per slot and per 64 response tokens).
+static int decode_parts(int n_slots, int block, int n_resp, int Hkv) {
+    const long long groups = (long long)n_slots * ((block + DGK - 1) / DGK) + (n_resp + DGK - 1) / DGK;
+    const long long most = std::min<long long>(std::max(16, std::min(kDecParts, kDecWgs / Hkv)), (long long)n_slots + (n_resp + 63) / 64);
+    const long long rounds = std::max<long long>(1, (groups + 4 * most - 1) / (4 * most));
+    return (int)std::max<long long>(1, std::min(most, (groups + 4 * rounds - 1) / (4 * rounds)));
 }
 
 template <typename T, int G>
 static void launch_decode_partial(const void* q, const void* pool, size_t slot_bytes, size_t layer_offset,
                                   const int* block_of_slot, int n_slots, int block, int n_prompt, const void* k_resp,
-                                  const void* v_resp, int n_resp, int Hq, int Hkv, float sl, float* part, int n_items,
+                                  const void* v_resp, int n_resp, int Hq, int Hkv, float sl, float* part, int n_parts,
                                   hipStream_t st) {
-    hipLaunchKernelGGL((decode_attn_partial_kernel<T, G>), dim3(n_items, Hkv), dim3(256), 0, st, (const T*)q,
+    hipLaunchKernelGGL((decode_attn_partial_kernel<T, G>), dim3(n_parts, Hkv), dim3(256), 0, st, (const T*)q,
                        (const unsigned char*)pool, slot_bytes, layer_offset, block_of_slot, n_slots, block, n_prompt,
                        (const T*)k_resp, (const T*)v_resp, n_resp, Hq, Hkv, sl, part);
 }
@@ -241,15 +275,15 @@ static int launch_decode_attn_t(const void* q, const void* pool, size_t slot_byt
                                 const int* block_of_slot, int n_slots, int block, int n_prompt, const void* k_resp,
                                 const void* v_resp, int n_resp, int Hq, int Hkv, float sl, void* out, float* part,
                                 hipStream_t st) {
-    const int n_items = n_slots + (n_resp + DCH - 1) / DCH;
+    const int n_parts = decode_parts(n_slots, n_slots ? block : 1, n_resp, Hkv);
 #define SLIM_DEC(GG) case GG: launch_decode_partial<T, GG>(q, pool, slot_bytes, layer_offset, block_of_slot, n_slots, block, \
-                                                            n_prompt, k_resp, v_resp, n_resp, Hq, Hkv, sl, part, n_items, st); break
+                                                            n_prompt, k_resp, v_resp, n_resp, Hq, Hkv, sl, part, n_parts, st); break
     switch (Hq / Hkv) {
         SLIM_DEC(1); SLIM_DEC(2); SLIM_DEC(3); SLIM_DEC(4); SLIM_DEC(5); SLIM_DEC(6); SLIM_DEC(7); SLIM_DEC(8);
         default: return SLIM_UNSUPPORTED;
     }
 #undef SLIM_DEC
-    hipLaunchKernelGGL(decode_attn_merge_kernel<T>, dim3(Hq), dim3(DMT), 0, st, part, n_items, Hq, (T*)out);
+    hipLaunchKernelGGL(decode_attn_merge_kernel<T>, dim3(Hq), dim3(DMT), 0, st, part, n_parts, Hq, (T*)out);
     return check_launch();
 }
 

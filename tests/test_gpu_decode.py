@@ -401,6 +401,25 @@ def test_decode_step_at_the_full_size_of_the_32k_workload(slim):
     np.testing.assert_allclose(f64(out), ref, rtol=2.0 ** -8, atol=2.0 ** -8 * np.abs(ref).max())
 
 
+# Groups of 16 keys, several per wave: short last blocks whose last groups hold no key, blocks that are no multiple of a group
+# or shorter than one, free slots between, every number of query heads per kv head.
+@pytest.mark.parametrize("n_prompt,block,n_slots,n_active,n_resp,Hq,Hkv,dtype", [
+    (400 * 64 - 27, 64, 260, 257, 33, 8, 2, torch.bfloat16), (400 * 64 - 63, 64, 257, 257, 0, 5, 1, torch.bfloat16),
+    (3000, 48, 63, 60, 65, 18, 3, torch.bfloat16), (2000, 7, 150, 140, 16, 16, 2, torch.bfloat16),
+    (1500, 17, 80, 80, 1, 12, 4, torch.bfloat16), (900, 100, 9, 9, 15, 4, 2, torch.bfloat16), (1200, 64, 19, 18, 17, 14, 2, torch.float32),
+])
+def test_decode_attention_deals_out_ragged_groups(slim, n_prompt, block, n_slots, n_active, n_resp, Hq, Hkv, dtype):
+    test_decode_attention_over_active_slots_matches_oracle(slim, n_prompt, block, n_slots, n_active, n_resp, Hq, Hkv, dtype)
+
+
+# Pieces of 256 x 16 bytes of a row: one short of and one past the end of a workgroup's step and of a wave's, and of the pieces in flight.
+@pytest.mark.parametrize("n,k,dtype", [(5, 8, torch.bfloat16), (9, 504, torch.bfloat16), (6, 2040, torch.bfloat16), (7, 2056, torch.bfloat16),
+                                       (3, 4104, torch.bfloat16), (4, 8200, torch.bfloat16), (2, 14336, torch.bfloat16), (3, 14344, torch.bfloat16),
+                                       (3, 16376, torch.bfloat16), (5, 4, torch.float32), (9, 1028, torch.float32), (2, 16376, torch.float32)])
+def test_gemv_at_the_edges_of_its_pieces(slim, n, k, dtype):
+    test_gemv_all_epilogues(slim, n, k, dtype)
+
+
 # ------------------------------------------------------------------------------ single-token projections and layer
 @pytest.mark.parametrize("n,k,dtype", [(4096, 4096, torch.bfloat16), (1024, 4096, torch.bfloat16), (70, 256, torch.bfloat16),
                                        (13, 64, torch.float32), (3584, 18944, torch.bfloat16)])
