@@ -37,10 +37,6 @@ template <int G, int H = 0, typename F> __device__ __forceinline__ void for_head
         for_heads<G, H + 1>(f);
     }
 }
-__device__ __forceinline__ uint4 load_stream(const void* p) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
-}
 
 // Lane (l16, q) = (lane % 16, lane / 16).
 //   S[key, head] = K . Q^T by 16-row matrix instructions: the lane supplies 16-byte pieces of key l16 and of query head l16 (heads
@@ -94,14 +90,14 @@ __global__ void __launch_bounds__(256) decode_attn_partial_kernel(
     auto load_k = [&]() {
         const unsigned off = (unsigned)min(l16, rows - 1) * stride + qr * 16;
 #pragma unroll
-        for (int c = 0; c < NK; ++c) kx[c] = load_stream(reinterpret_cast<const unsigned char*>(kp) + off + c * 64);
+        for (int c = 0; c < NK; ++c) kx[c] = load_stream16(reinterpret_cast<const unsigned char*>(kp) + off + c * 64);
     };
     auto load_v = [&]() {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const unsigned off = (unsigned)min(qr * 4 + e, rows - 1) * stride + l16 * 16;
 #pragma unroll
-            for (int c = 0; c < NV; ++c) vx[e][c] = load_stream(reinterpret_cast<const unsigned char*>(vp) + off + c * 256);
+            for (int c = 0; c < NV; ++c) vx[e][c] = load_stream16(reinterpret_cast<const unsigned char*>(vp) + off + c * 256);
         }
     };
     bool more = find();

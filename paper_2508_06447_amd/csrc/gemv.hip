@@ -42,12 +42,6 @@ struct GemvArgs {
 constexpr int kGemvRows = 4; // weight rows per workgroup
 constexpr int kGemvGrid = 1 << 22;                       // workgroups per row of the grid (work items per dimension stay below 2^32)
 
-// 16 bytes that no other workgroup reads.
-__device__ __forceinline__ uint4 load_once(const void* p) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
-}
-
 template <typename T, bool SWIGLU, int U>
 __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     constexpr int V = Elem<T>::kVec, R = kGemvRows, FPW = SWIGLU ? R / 2 : R;   // features per workgroup
@@ -73,7 +67,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
             const int c = c0 + u * 256, cc = min(c, nchunk - 1);
             xr[u] = c < nchunk ? *reinterpret_cast<const uint4*>(x + (size_t)cc * V) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-            for (int r = 0; r < R; ++r) raw[u][r] = load_once(rows[r] + (size_t)cc * V);
+            for (int r = 0; r < R; ++r) raw[u][r] = load_stream16(rows[r] + (size_t)cc * V);
         }
     };
     load(tid);

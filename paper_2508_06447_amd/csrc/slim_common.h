@@ -69,6 +69,12 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// 16 bytes that are read once: with a non-temporal hint.
+__device__ __forceinline__ uint4 load_stream16(const void* p) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
+
 // One 16-byte-per-lane load from global memory straight into LDS.  The LDS address of lane l is
 // (wave-uniform base) + 16*l; the base travels in M0.  The compiler does not see this as an LDS write,
 // so callers order it against LDS reads themselves: s_waitcnt vmcnt + workgroup barrier.

@@ -108,6 +108,29 @@ def test_scores_match_oracle(slim, N, block, unit, w, Hq, Hkv, d, dtype):
     np.testing.assert_allclose(f64(got), want, atol=2e-5 * max(scale, 1.0), rtol=1e-4)
 
 
+# Units of more and fewer rows than the eight of a piece, rows of more and fewer chunks than a wave's 64, odd windows and groups.
+@pytest.mark.parametrize("N,block,unit,w,Hq,Hkv,d,dtype", [
+    (333, 50, 19, 3, 6, 2, 24, torch.bfloat16), (700, 64, 9, 130, 7, 1, 520, torch.bfloat16), (65, 64, 8, 1, 9, 9, 128, torch.bfloat16),
+    (257, 40, 17, 33, 4, 2, 260, torch.float32), (100, 100, 100, 2, 5, 5, 12, torch.float32), (90, 30, 4, 5, 2, 1, 4, torch.float32),
+])
+def test_scores_at_the_edges_of_their_pieces(slim, N, block, unit, w, Hq, Hkv, d, dtype):
+    test_scores_match_oracle(slim, N, block, unit, w, Hq, Hkv, d, dtype)
+
+
+# Head counts with and without 16-byte loads, blocks and units that pass the strip of 2048 tokens by one unit, one token, altogether.
+@pytest.mark.parametrize("N,H,block,unit", [(1000, 8, 64, 8), (300, 3, 64, 7), (70, 1, 33, 33), (5000, 2, 5000, 9), (9000, 4, 4500, 2049),
+                                            (6200, 12, 4097, 2048), (2049, 5, 2049, 1)])
+def test_block_scores_from_token_scores(slim, N, H, block, unit):
+    ts = rand((N, H), torch.float32, N)
+    want = []
+    for b0 in range(0, N, block):
+        rows = f64(ts)[b0:min(b0 + block, N)].sum(1)
+        want.append(max(rows[u:u + unit].mean() for u in range(0, len(rows), unit)))
+    got = f64(slim.slim_score_blocks_from_token_scores(dev(ts), block, unit))
+    # float sums of at most unit * H values of size 4: H roundings per token, unit of the running sum
+    np.testing.assert_allclose(got, want, rtol=0, atol=(unit + H) * 2.0 ** -24 * 4 * H)
+
+
 @pytest.mark.parametrize("pooling", ["avg", "max"])
 @pytest.mark.parametrize("N,block,w,Hq,Hkv,d,dtype", [
     (4096, 64, 64, 32, 8, 128, torch.bfloat16),
