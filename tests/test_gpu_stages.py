@@ -252,6 +252,12 @@ def test_few_row_swiglu(slim, m, n, k):
     np.testing.assert_allclose(f64(slim.slim_swiglu_linear(dev(a), dev(w), dev(w2))), want, rtol=2.0 ** -8, atol=2.0 ** -8 * np.abs(want).max())
 
 
+# Row counts whose last 256-token tile is ragged and kept as one (a round of tiles saved): one row, half of it, all but a few.
+@pytest.mark.parametrize("m,n,k", [(385, 14336, 64), (400, 14336, 128), (1000, 14336, 64), (1511, 14336, 64)])
+def test_swiglu_with_a_ragged_large_tile(slim, m, n, k):
+    test_few_row_swiglu(slim, m, n, k)
+
+
 @pytest.mark.parametrize("m,n,k,lda,ldo", [(300, 520, 192, 256, 640), (1000, 264, 128, 136, 272), (64, 512, 256, 320, 520)])
 def test_linear_with_row_strides(slim, m, n, k, lda, ldo):
     """Rows of a and of out / residual that are longer than what the call uses (lda > k_in, ldo > n_out), through the
