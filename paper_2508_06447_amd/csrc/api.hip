@@ -652,7 +652,9 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         return launch_score(q_window, k_all, N, w_eff, Hq, Hkv, d, s->block, s->unit, s->scoring, dt, scores, qt, st);
     };
 
-    const bool want_table = fused && (fused_score || !(p.split_k || p.split_qkv));   // the window query reads it, and the unsplit Key projection
+    // nothing dropped: Keys in the launch of the Queries and Values (which need the same epilogue), where that saves time
+    const bool qkv = fused && Hd < (1 << 23) && !p.prune && !p.split_qkv && !p.split_qv && N > 128 && !w->bq == !w->bv && qkv_together(N, qd, kvd, kvd);
+    const bool want_table = fused && (fused_score || qkv || !(p.split_k || p.split_qkv));   // the window query reads it, and the unsplit Key projection
     const void* rows_in = x_in;        // what the projections of the incoming tokens read
     const float* sc_in = nullptr;
     if (fold_attn) {
@@ -708,7 +710,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
                               pos_in ? pos_in + (N - w_eff) : nullptr, N - w_eff, w_eff, Hq, q_win, nullptr, nullptr, nullptr));
         if (fused_score) SLIM_TRY(launch_window_query(q_win, w_eff, Hq, Hkv, d, dt, qt, st));
     }
-    if (!p.split_qkv) SLIM_TRY(project_k(rows_in, sc_in, ktab, fused_score ? qt : nullptr));
+    if (!p.split_qkv && !qkv) SLIM_TRY(project_k(rows_in, sc_in, ktab, fused_score ? qt : nullptr));
     const void* rows = rows_in;        // what the Q/V projections of the continuing tokens read
     const float* sc = sc_in;
     if (p.prune) {
@@ -748,6 +750,10 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
 
     // Q, V of the rows that continue; RoPE on Q at the original positions.  (Few rows, nothing dropped: K with them.)
     if (p.split_qkv) SLIM_TRY(project_split(rows, sc, n, pos, qc, kc, vc, nullptr));
+    else if (qkv) {
+        SLIM_TRY(launch_linear_qkv(rows, Hd, w->wq, w->bq, qd, qc, w->wk, w->bk, kvd, table, kc, w->wv, w->bv, kvd, vc, sc, n, Hd, st));
+        SLIM_TRY(launch_rope(qc, pos, 0, n, Hq, d, s->rope_theta, dt, st));
+    }
     else SLIM_TRY(project_qv(rows, sc, pos, n, qc, vc));
     SLIM_TRY(launch_attn(qc, kc, vc, n, Hq, Hkv, d, 0.f, dt, o, st));
     }

@@ -44,6 +44,11 @@ struct EpiExtra {
     const bf16_t* r_2 = nullptr;         // its bias (EPI_BIAS)
     bf16_t* c_2 = nullptr;               // [M][ldo_2]
     int n_2 = 0, ldo_2 = 0, tiles_n1 = 0;
+    // Key projection in the same launch (gemm_bf16_qkv_kernel only): feature tiles 0 .. tiles_nk - 1, with the RoPE epilogue.
+    const bf16_t* w_k = nullptr;         // [n_k][K]
+    const bf16_t* r_k = nullptr;         // its bias or null
+    bf16_t* c_k = nullptr;               // [M][n_k]
+    int n_k = 0, tiles_nk = 0;
     float* partial = nullptr;            // EPI_PARTIAL: [M] rows of ldo floats
 };
 
@@ -635,6 +640,36 @@ gemm_bf16_two_size_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* _
                                             big_tiles_m * S::BM_BIG + tm * S::BM_SMALL, tn * S::BN, lds, re);
 }
 
+// Query, Key and Value projections of the same rows in one launch: the feature tiles of the Keys (128-wide heads, rotated in the
+// epilogue, which takes longest) come first, then the other two as in the launch of a pair.  As launches of their own the Keys of
+// 2048 or 4096 rows are 32 or 64 tiles: a layer of 4096 rows that drops nothing (4096 + 1024 + 1024 features) 1550 -> 1526 us,
+// 2048 rows 858 -> 833.
+template <int EPI>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+gemm_bf16_qkv_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0, const bf16_t* R, bf16_t* C, int ldo, int M,
+                     int N, int K, int big_tiles_m, int small_tiles_m, int tiles_n, EpiExtra re) {
+    using S = TileShapes<EPI>;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int n_big = big_tiles_m * tiles_n;
+    const bool big = (int)blockIdx.x < n_big;
+    int tm, tn;
+    if (big) tile_of_workgroup(blockIdx.x, true, big_tiles_m, tiles_n, tm, tn);
+    else tile_of_workgroup(blockIdx.x - n_big, n_big % 8 == 0, small_tiles_m, tiles_n, tm, tn);
+    const int m0 = big ? tm * S::BM_BIG : big_tiles_m * S::BM_BIG + tm * S::BM_SMALL;
+    if (tn < re.tiles_nk) {
+        if (big) gemm_tile4<4, S::TA_BIG, EPI_ROPE>(A, lda, re.w_k, nullptr, re.r_k, re.c_k, re.n_k, M, re.n_k, K, m0, tn * S::BN, lds, re);
+        else gemm_tile4<4, S::TA_SMALL, EPI_ROPE>(A, lda, re.w_k, nullptr, re.r_k, re.c_k, re.n_k, M, re.n_k, K, m0, tn * S::BN, lds, re);
+        return;
+    }
+    tn -= re.tiles_nk;
+    if (tn >= re.tiles_n1) {
+        W0 = re.w_2; R = re.r_2; C = re.c_2; N = re.n_2; ldo = re.ldo_2;
+        tn -= re.tiles_n1;
+    }
+    if (big) gemm_tile4<4, S::TA_BIG, EPI>(A, lda, W0, nullptr, R, C, ldo, M, N, K, m0, tn * S::BN, lds, re);
+    else gemm_tile4<4, S::TA_SMALL, EPI>(A, lda, W0, nullptr, R, C, ldo, M, N, K, m0, tn * S::BN, lds, re);
+}
+
 // The residual epilogue reads a second tile through LDS; with a lone wave per SIMD nothing hides that pass, and the
 // launch measured slower than with the 8-wave tile (two waves per SIMD: one wave's epilogue steps overlap the
 // other's).  So output and down projection keep 8 waves: wave tiles of 64 tokens x 128 features (large) and
@@ -832,13 +867,17 @@ static int launch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t*
 //     1000 rows 224 -> 200, 1511 rows 330 -> 296; Query + Value of 2983 rows 127 -> 97), but where the model sees a tie the launch with
 //     128-token tiles is the faster one (SwiGLU 300 rows 88 against 102, down projection of 2983 rows 293 against 316).
 // The result is a pure function of its arguments; the cache only remembers it (guarded, never invalidated).
-static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool eight_waves) {
+// makespan: of the plan, in times of a 256-token tile.
+static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool eight_waves, double* makespan_out = nullptr) {
     static std::mutex mu;
-    static std::map<std::tuple<int, int, int, bool>, int> cache;
+    static std::map<std::tuple<int, int, int, bool>, std::pair<int, double>> cache;
     std::lock_guard<std::mutex> lock(mu);
     const auto key = std::make_tuple(M, tiles_n, (int)(small_cost * 1000), eight_waves);
     const auto hit = cache.find(key);
-    if (hit != cache.end()) return hit->second;
+    if (hit != cache.end()) {
+        if (makespan_out) *makespan_out = hit->second.second;
+        return hit->second.first;
+    }
     std::vector<double> speed(n_cu);
     for (int c = 0; c < n_cu; ++c) speed[c] = 1.0 + 0.08 * ((double)((c * 97) % n_cu) / (n_cu - 1) * 2.0 - 1.0);
     const int mb_floor = M / 256, mb_max = (M + 255) / 256;
@@ -867,8 +906,9 @@ static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool 
         if (mb > mb_floor) ragged = makespan * 1.03;
         else if (makespan < best) { best = makespan; best_mb = mb; }
     }
-    if (ragged < best) best_mb = mb_max;
-    cache[key] = best_mb;
+    if (ragged < best) { best = ragged; best_mb = mb_max; }
+    cache[key] = std::make_pair(best_mb, best);
+    if (makespan_out) *makespan_out = best;
     return best_mb;
 }
 
@@ -1101,6 +1141,58 @@ int launch_linear_pair(const void* a, int lda, const void* w_1, const void* bias
     return launch_two_size<EPI_PLAIN>(A, lda, W, nullptr, nullptr, (bf16_t*)out_1, ldo_1, m, n_1, k_in,
                                       plan_big_tiles(m, tiles_n, cu_count(), small_tile_cost<EPI_PLAIN>(false), false),
                                       false, st, re);
+}
+
+// Whether the Keys of m rows go into the launch of the Queries and Values (gemm_bf16_qkv_kernel).  The model says how many tile times
+// they add to it; a launch of their own takes about 1.25 rounds of their tiles and a fifth of a tile time.  Measured on a layer with nothing
+// dropped (us saved; predicted tile times saved): 16 + 4 + 4 feature tiles: 2048 rows 25; 0.36, 2983 -2; 0.00, 4096 24; 0.27, 5000 80; 0.39, 6000 10; 0.17,
+// 8192 45; 0.38, 12000 43; 0.29; 14 + 2 + 2: 2048 -4; -0.15, 3500 18; 0.30, 4096 -24; -0.10, 8192 -23; 0.07.
+bool qkv_together(int m, int n_q, int n_k, int n_v) {
+    if (m > 16384) return false;                         // many rounds either way
+    const int bn = TileShapes<EPI_PLAIN>::BN, tk = (n_k + bn - 1) / bn, tqv = (n_q + bn - 1) / bn + (n_v + bn - 1) / bn;
+    double pair = 0.0, all = 0.0;
+    plan_big_tiles(m, tqv, cu_count(), small_tile_cost<EPI_PLAIN>(false), false, &pair);
+    plan_big_tiles(m, tqv + tk, cu_count(), small_tile_cost<EPI_PLAIN>(false), false, &all);
+    return 1.25 * tk * m / 256.0 / cu_count() + 0.2 - (all - pair) > 0.12;
+}
+
+template <int EPI>
+static int launch_qkv_t(const bf16_t* A, int lda, const bf16_t* W, const bf16_t* B, bf16_t* C, int n_q, int m, int k_in, EpiExtra& re, hipStream_t st) {
+    using S = TileShapes<EPI>;
+    constexpr size_t smem = 2 * (size_t)(S::BN + S::BM_BIG) * BK * 2;
+    auto kern = gemm_bf16_qkv_kernel<EPI>;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); });
+    if (attr_err != hipSuccess) return set_hip_error(attr_err);
+    re.tiles_nk = (re.n_k + S::BN - 1) / S::BN;
+    re.tiles_n1 = (n_q + S::BN - 1) / S::BN;
+    const int tiles_n = re.tiles_nk + re.tiles_n1 + (re.n_2 + S::BN - 1) / S::BN;
+    const int big = plan_big_tiles(m, tiles_n, cu_count(), small_tile_cost<EPI>(false), false);
+    const int small = std::max(0, m - big * S::BM_BIG + S::BM_SMALL - 1) / S::BM_SMALL;
+    hipLaunchKernelGGL(kern, dim3((big + small) * tiles_n), dim3(256), smem, st, A, lda, W, B, C, n_q, m, n_q, k_in, big, small, tiles_n, re);
+    return check_launch();
+}
+
+// Query (not rotated), Key (rotated with the table) and Value projections of the same rows, each [m, n_*] contiguous.  bias_q and bias_v both or
+// neither.  bf16, n_k a multiple of 128, the others of 8, k_in % 64 == 0 and below 2^23, 16-byte aligned (checked by the caller).
+int launch_linear_qkv(const void* a, int lda, const void* w_q, const void* bias_q, int n_q, void* out_q, const void* w_k, const void* bias_k,
+                      int n_k, const float* table, void* out_k, const void* w_v, const void* bias_v, int n_v, void* out_v,
+                      const float* row_scale, int m, int k_in, hipStream_t st) {
+    EpiExtra re;
+    re.table = table;
+    re.row_scale = row_scale;
+    re.w_2 = (const bf16_t*)w_v;
+    re.r_2 = (const bf16_t*)bias_v;
+    re.c_2 = (bf16_t*)out_v;
+    re.n_2 = re.ldo_2 = n_v;
+    re.w_k = (const bf16_t*)w_k;
+    re.r_k = (const bf16_t*)bias_k;
+    re.c_k = (bf16_t*)out_k;
+    re.n_k = n_k;
+    const bf16_t *A = (const bf16_t*)a, *W = (const bf16_t*)w_q, *B = (const bf16_t*)bias_q;
+    if (bias_q) return launch_qkv_t<EPI_BIAS>(A, lda, W, B, (bf16_t*)out_q, n_q, m, k_in, re, st);
+    return launch_qkv_t<EPI_PLAIN>(A, lda, W, nullptr, (bf16_t*)out_q, n_q, m, k_in, re, st);
 }
 
 // At most one of w1 (SwiGLU), residual and bias is set.

@@ -74,14 +74,26 @@ __global__ void __launch_bounds__(256) rope_kernel(T* __restrict__ x, const int*
     const float cf0 = (float)c0, sf0 = (float)s0, cf1 = (float)c1, sf1 = (float)s1;
     const int half = d / 2;
     T* base = x + (size_t)t * H * d + 2 * p;
-    for (int h = 0; h < H; ++h) {
-        T* a = base + (size_t)h * d;
-        T* b = a + half;
-        float a0 = Elem<T>::ld(a), a1 = Elem<T>::ld(a + 1), b0 = Elem<T>::ld(b), b1 = Elem<T>::ld(b + 1);
-        Elem<T>::st(a, a0 * cf0 - b0 * sf0);
-        Elem<T>::st(a + 1, a1 * cf1 - b1 * sf1);
-        Elem<T>::st(b, b0 * cf0 + a0 * sf0);
-        Elem<T>::st(b + 1, b1 * cf1 + a1 * sf1);
+    // Four heads are read before the first is written (the compiler may not move a read of x over a write of x): 4096 rows of 32
+    // heads 18.9 -> 14.9 us.
+    for (int h0 = 0; h0 < H; h0 += 4) {
+        float a0[4], a1[4], b0[4], b1[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T* a = base + (size_t)min(h0 + u, H - 1) * d;
+            a0[u] = Elem<T>::ld(a); a1[u] = Elem<T>::ld(a + 1);
+            b0[u] = Elem<T>::ld(a + half); b1[u] = Elem<T>::ld(a + half + 1);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (h0 + u >= H) break;
+            T* a = base + (size_t)(h0 + u) * d;
+            T* b = a + half;
+            Elem<T>::st(a, a0[u] * cf0 - b0[u] * sf0);
+            Elem<T>::st(a + 1, a1[u] * cf1 - b1[u] * sf1);
+            Elem<T>::st(b, b0[u] * cf0 + a0[u] * sf0);
+            Elem<T>::st(b + 1, b1[u] * cf1 + a1[u] * sf1);
+        }
     }
 }
 

@@ -122,6 +122,10 @@ int launch_linear_scaled(const void* a, int lda, const void* w0, const void* w1,
 int launch_linear_pair(const void* a, int lda, const void* w_1, const void* bias_1, int n_1, int ldo_1, void* out_1,
                        const void* w_2, const void* bias_2, int n_2, int ldo_2, void* out_2, const float* row_scale,
                        int m, int k_in, hipStream_t st);
+bool qkv_together(int m, int n_q, int n_k, int n_v);
+int launch_linear_qkv(const void* a, int lda, const void* w_q, const void* bias_q, int n_q, void* out_q, const void* w_k, const void* bias_k,
+                      int n_k, const float* table, void* out_k, const void* w_v, const void* bias_v, int n_v, void* out_v,
+                      const float* row_scale, int m, int k_in, hipStream_t st);
 int launch_row_rstd(const void* x, int n, int hidden, float eps, int dtype, float* rstd, hipStream_t st,
                     const int* pos = nullptr, int d = 0, float theta = 0.f, float* table = nullptr);
 int launch_fold_gain(const void* w, const void* gain, int n_out, int k_in, int dtype, void* out, hipStream_t st);

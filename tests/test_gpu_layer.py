@@ -161,6 +161,15 @@ def test_float32_layer_shapes(slim, seq, hidden, heads, kv_heads, d, ffn, window
     assert r["sc_err"] < 1e-5 and r["mx"] < F32_MAX_ABS
 
 
+@pytest.mark.parametrize("bias", [False, True])
+@pytest.mark.parametrize("seq", [3500, 2047, 1700])
+def test_layer_that_drops_nothing_projects_all_three_at_once(slim, seq, bias):
+    """Rows and heads for which Query, Key and Value projections share a launch (48 query and 8 kv heads over 128 hidden features),
+    ragged last tiles, with and without biases: sampled rows against the oracle."""
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, hidden=128, n_q_heads=48, n_kv_heads=8, ffn=256, keep_ratio=1.0, planted=seq // 50, qkv_bias=bias)
+    check_layer(slim, wl, np.float64, rows_count=64, label=f"nothing dropped, seq {seq} bias {bias}", fold=True)
+
+
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("seq,block,window,keep", [(1024, 64, 64, 0.5), (1000, 64, 64, 0.3), (1536, 128, 128, 0.25)])
 def test_reduced_bf16_layer_full_output(slim, seq, block, window, keep, fold):
