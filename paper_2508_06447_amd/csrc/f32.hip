@@ -24,8 +24,8 @@ __device__ __forceinline__ f32x4 load4(const float* p, int left) {
 
 // -------------------------------------------------------------------------------------------------
 // Projections.  The float workload is small (512 rows, 128 to 688 features): what a launch costs is the chain load -> sum
-// -> store of one workgroup, not the rate of the chip, so a workgroup takes 32 rows x 32 features only and its four waves
-// a quarter of the reduction each; a wave requests four 16-deep chunks (16 KB) before it waits.  The operands go from
+// -> store of one workgroup, not the rate of the chip, so a workgroup takes 32 rows x 32 features only and its eight waves
+// an eighth of the reduction each; a wave requests two 16-deep chunks (8 KB) before it waits.  The operands go from
 // global memory into the registers that the matrix instruction reads: with so small tiles nothing would be read twice
 // from LDS.  Which 4 of a chunk's 16 reduction elements an instruction takes is free as long as both operands agree,
 // so a lane reads 16 contiguous bytes and element j of them belongs to instruction j.
@@ -35,8 +35,9 @@ __device__ __forceinline__ f32x4 load4(const float* p, int left) {
 // scaled by the gain on their way in, their sums of squares are taken from the same registers and 1/rms is applied to the
 // finished sums.  Up to three projections share a launch.
 //
-// 512 rows x 256 features, k_in 256: 40.9 -> 6.7 us (688 features in: 127 -> 10.1); the
-// whole layer of 512 tokens, 18 launches before and 10 now, 523 -> 68 us.
+// 512 rows x 256 features, k_in 256: 40.9 -> 6.2 us (688 features in: 127 -> 9.4); the
+// whole layer of 512 tokens, 18 launches before and 10 now, 523 -> 60 us (four waves and four chunks 64, eight and four 71: most
+// of a wave's share is then loads past its end).
 // -------------------------------------------------------------------------------------------------
 struct F32LinearArgs {
     F32Seg seg[3];
@@ -48,11 +49,12 @@ struct F32LinearArgs {
     double inv_freq[64];
 };
 
-// MT groups of 16 rows, G chunks of the reduction in flight per wave.
-template <int MT, int G>
-__global__ void __launch_bounds__(256) f32_linear_kernel(F32LinearArgs p) {
-    __shared__ f32x4 red[4][2 * MT][64];                 // [wave][feature group * MT + row group][lane], 16 or 32 KB
-    __shared__ float red_ss[4][16 * MT];
+// MT groups of 16 rows, NW waves that the reduction is dealt to, G chunks of it in flight per wave.
+template <int MT, int NW, int G>
+__global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
+    constexpr int EPT = 8 / NW;                          // elements of a tile group per thread behind the sum
+    __shared__ f32x4 red[NW][2 * MT][64];                // [wave][feature group * MT + row group][lane], 32 KB
+    __shared__ float red_ss[NW][16 * MT];
     const int id = blockIdx.x, s = (id >= p.tile_end[0]) + (id >= p.tile_end[1]);
     const F32Seg sg = p.seg[s];
     const int t = s ? id - p.tile_end[s - 1] : id;
@@ -80,7 +82,7 @@ __global__ void __launch_bounds__(256) f32_linear_kernel(F32LinearArgs p) {
     for (int m = 0; m < MT; ++m) pa[m] = sg.a + (size_t)min(m0 + m * 16 + l16, sg.m - 1) * sg.lda + q * 4;
     const float* pg = p.gain ? p.gain + q * 4 : nullptr;
 
-    const int n_chunks = (K + 15) / 16, lo = n_chunks * wave / 4, hi = n_chunks * (wave + 1) / 4;
+    const int n_chunks = (K + 15) / 16, lo = (int)((long long)n_chunks * wave / NW), hi = (int)((long long)n_chunks * (wave + 1) / NW);
     const int k_end = min(K, hi * 16) - q * 4;           // elements from chunk c's on: k_end - 16 c
     f32x4 acc[2][MT];
 #pragma unroll
@@ -147,37 +149,41 @@ __global__ void __launch_bounds__(256) f32_linear_kernel(F32LinearArgs p) {
         }
     }
     __syncthreads();
-    // Wave v adds the four waves' sums of the row groups v % 2, v % 2 + 2, .., elements 2 (v / 2) and the next of both feature groups.
-    const int e0 = (wave >> 1) * 2, c = q * 4 + e0;      // the thread's two places in a group of 16 features
+    // Wave v adds all waves' sums of the row groups v % 2, v % 2 + 2, .., EPT elements from EPT (v / 2) on of both feature groups.
+    const int e0 = (wave >> 1) * EPT, c = q * 4 + e0;    // the thread's places in a group of 16 features
 #pragma unroll
     for (int m = wave & 1; m < MT; m += 2) {
         const int row = m0 + m * 16 + l16;
         if (row >= sg.m) continue;
-        float v[2][2] = {};
+        float v[2][EPT] = {};
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
+        for (int x = 0; x < NW; ++x)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const f32x2 part = *reinterpret_cast<const f32x2*>(reinterpret_cast<const float*>(&red[x][i * MT + m][lane]) + e0);
-                v[i][0] += part[0];
-                v[i][1] += part[1];
+                const float* part = reinterpret_cast<const float*>(&red[x][i * MT + m][lane]) + e0;
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) v[i][e] += part[e];
             }
         if (pg) {
-            const float tot = red_ss[0][m * 16 + l16] + red_ss[1][m * 16 + l16] + red_ss[2][m * 16 + l16] + red_ss[3][m * 16 + l16];
+            float tot = 0.f;
+#pragma unroll
+            for (int x = 0; x < NW; ++x) tot += red_ss[x][m * 16 + l16];
             const float inv = 1.0f / sqrtf(tot / (float)K + p.eps);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) { v[i][0] *= inv; v[i][1] *= inv; }
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) v[i][e] *= inv;
         }
         float* out = sg.out + (size_t)row * sg.ldo;
         if (sg.mode == F32_SWIGLU) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
+            for (int e = 0; e < EPT; ++e)
                 if (f0 + c + e < sg.n) out[f0 + c + e] = v[0][e] / (1.0f + expf(-v[0][e])) * v[1][e];
             continue;
         }
         if (sg.bias) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
+            for (int e = 0; e < EPT; ++e) {
                 v[0][e] += sg.bias[min(f0 + c + e, sg.n - 1)];
                 v[1][e] += sg.bias[min(f1 + c + e, sg.n - 1)];
             }
@@ -186,7 +192,7 @@ __global__ void __launch_bounds__(256) f32_linear_kernel(F32LinearArgs p) {
             const double ps = (double)(sg.pos ? sg.pos[row] : sg.pos0 + row);
             const int r = f0 % p.head_dim + c;           // rotation index of e = 0
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
+            for (int e = 0; e < EPT; ++e) {
                 double sn, cs;
                 sincos(ps * p.inv_freq[r + e], &sn, &cs);
                 const float x1 = v[0][e], x2 = v[1][e];
@@ -197,7 +203,7 @@ __global__ void __launch_bounds__(256) f32_linear_kernel(F32LinearArgs p) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
+            for (int e = 0; e < EPT; ++e) {
                 const int f = (i ? f1 : f0) + c + e;
                 if (f < sg.n) out[f] = sg.residual ? v[i][e] + sg.residual[(size_t)row * sg.ldo + f] : v[i][e];
             }
@@ -208,7 +214,7 @@ __global__ void __launch_bounds__(256) f32_linear_kernel(F32LinearArgs p) {
 constexpr long long kF32TilesMax = 1ll << 23;
 // From how many tiles of 32 rows on tiles of 64 are taken: twice the flops per byte read, half the workgroups (us, tall
 // and not: 2048 x 2048 from 2048 features 241 / 293, 2048 x 1024 from 512, 2048 tiles, 45 / 53; 1024 tiles fill the chip with 32 rows only).
-// The reduction is cut the same way in both, so that a result does not depend on the choice.
+// Four waves there: with eight the sums of 64 rows do not fit the LDS.
 constexpr long long kF32TallTiles = 2048;
 
 int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain, float eps, int head_dim, float theta, hipStream_t st) {
@@ -249,8 +255,8 @@ int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain
     p.eps = eps;
     p.head_dim = head_dim;
     for (int i = 0; i < head_dim / 2; ++i) p.inv_freq[i] = pow((double)theta, -2.0 * (double)i / (double)head_dim);
-    auto kern = tall ? f32_linear_kernel<4, 2> : f32_linear_kernel<2, 4>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(256), 0, st, p);
+    if (tall) hipLaunchKernelGGL((f32_linear_kernel<4, 4, 2>), dim3((unsigned)tiles), dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((f32_linear_kernel<2, 8, 2>), dim3((unsigned)tiles), dim3(512), 0, st, p);
     return check_launch();
 }
 
