@@ -252,6 +252,12 @@ def test_few_row_swiglu(slim, m, n, k):
     np.testing.assert_allclose(f64(slim.slim_swiglu_linear(dev(a), dev(w), dev(w2))), want, rtol=2.0 ** -8, atol=2.0 ** -8 * np.abs(want).max())
 
 
+# Launches of eight rounds and more walk their large tiles in groups of 2 x 112: an odd number of token tiles, 128-token tiles behind them.
+@pytest.mark.parametrize("m,n,k", [(4864, 14336, 64), (5000, 14336, 64)])
+def test_swiglu_in_groups_of_tiles(slim, m, n, k):
+    test_few_row_swiglu(slim, m, n, k)
+
+
 # Row counts whose last 256-token tile is ragged and kept as one (a round of tiles saved): one row, half of it, all but a few.
 @pytest.mark.parametrize("m,n,k", [(385, 14336, 64), (400, 14336, 128), (1000, 14336, 64), (1511, 14336, 64)])
 def test_swiglu_with_a_ragged_large_tile(slim, m, n, k):
