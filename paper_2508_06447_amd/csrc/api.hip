@@ -56,16 +56,14 @@ static int forced_count(unsigned flags, int nb) {
 // in one launch: 22 -> 17 us with 4 splits, Key alone 16 -> 9.4.  From 129 rows on more than one split gains at most 3 us
 // for as many rows as fill the chip and loses behind that (the partial sums are written and read once more per split).
 static int qkv_splits(int m, int k_in) { return m <= 128 && k_in >= 2048 ? 4 : 1; }
-// Down projection (long rows): 1 / 2 / 4 / 8 splits of 14336 take 73 / 43 / 39 / 38 us for 128 rows, 101 / 75 / 67 / 73 for
-// 300, 106 / 82 / 79 / 90 for 512, 146 / 130 / 137 / 166 for 1024; above that the unsplit tiles are ahead (1511: 195 / 225 / 208).
-static int down_splits(int m, int k_in) { return k_in < 8192 || m > 1024 ? 1 : m <= 128 ? 8 : 4; }
 
 // Workspace layout of slim_pruned_layer (every region 256-byte aligned).
 struct LayerPlan {
     size_t h, k_all, q_win, qt, scores, table, tscore, rstd, rstd2, kc, vc, qc, o, o_all, act, partial, total;
     int nb, n_out;
     bool prune;
-    bool split_k, split_qv, split_qkv, split_down;       // which projections go through float partial sums
+    bool split_k, split_qv, split_qkv;                   // which projections go through float partial sums
+    ResidualCut down;                                    // and which rows of the down projection
 };
 
 static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
@@ -103,8 +101,8 @@ static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
         p.split_qkv = !p.prune && few_rows(N, (int)(qd + 2 * kv)) && room(N, qd + 2 * kv, qkv_splits(N, s->hidden));
         p.split_k = !p.split_qkv && few_rows(N, (int)kv) && room(N, kv, qkv_splits(N, s->hidden));
         p.split_qv = !p.split_qkv && few_rows(na, (int)(qd + kv)) && room(na, qd + kv, qkv_splits(na, s->hidden));
-        const int ds = down_splits(p.n_out, s->ffn);
-        p.split_down = ds > 1 && s->ffn % 64 == 0 && few_rows(p.n_out, s->hidden) && room(p.n_out, s->hidden, ds);
+        p.down = residual_cut(p.n_out, s->hidden, s->ffn);
+        if (p.down.splits > 1) room(p.n_out - p.down.whole, s->hidden, p.down.splits);
     }
     p.partial = take(part * sizeof(float));
     p.total = off;
@@ -770,13 +768,18 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         SLIM_TRY(launch_rmsnorm(x_out, w->g_ffn, n, Hd, s->rms_eps, dt, h, st));
         SLIM_TRY(launch_linear(h, Hd, w->w_gate, w->w_up, nullptr, nullptr, n, s->ffn, Hd, s->ffn, dt, act, st));
     }
-    if (p.split_down) {
-        const int splits = down_splits(n, s->ffn);
-        const SplitMats mats{{w->w_down}, {Hd}, 1};
-        SLIM_TRY(launch_split_gemm(act, s->ffn, mats, n, s->ffn, splits, partial, st));
-        SLIM_TRY(launch_split_residual(partial, splits, n, Hd, x_out, x_out, st));
-    } else {
-        SLIM_TRY(launch_linear(act, s->ffn, w->w_down, nullptr, x_out, nullptr, n, Hd, s->ffn, Hd, dt, x_out, st));
+    const int whole = p.down.splits > 1 ? p.down.whole : n, tail = n - whole;
+    if (whole) SLIM_TRY(launch_linear(act, s->ffn, w->w_down, nullptr, x_out, nullptr, whole, Hd, s->ffn, Hd, dt, x_out, st));
+    if (tail) {
+        const bf16_t* a_t = (const bf16_t*)act + (size_t)whole * s->ffn;
+        bf16_t* x_t = (bf16_t*)x_out + (size_t)whole * Hd;
+        if (p.down.large) {
+            SLIM_TRY(launch_split_gemm_large(a_t, s->ffn, w->w_down, tail, Hd, s->ffn, p.down.splits, partial, st));
+        } else {
+            const SplitMats mats{{w->w_down}, {Hd}, 1};
+            SLIM_TRY(launch_split_gemm(a_t, s->ffn, mats, tail, s->ffn, p.down.splits, partial, st));
+        }
+        SLIM_TRY(launch_split_residual(partial, p.down.splits, tail, Hd, x_t, x_t, st));
     }
 #undef SLIM_TRY
     return SLIM_OK;

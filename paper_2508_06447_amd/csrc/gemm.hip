@@ -279,29 +279,30 @@ __device__ __forceinline__ void store_tile_rope(f32x16 (&acc)[1][4][TA], const b
     }
 }
 
-// Epilogue of the split projections: the wave's float tile, unscaled, to rows of a float buffer.  Through the
+// Epilogue of the split projections: the wave's float tile, unscaled, to rows of a float buffer.  32 tokens at a time go through the
 // wave-private LDS region (rows of TW*128 bytes, 16-byte chunk c of row r at slot c ^ (r & (chunks per row - 1))), so
-// that a row of the tile leaves as TW*128 contiguous bytes.  Needs N % 4 == 0.
+// that a row of the tile leaves as TW*128 contiguous bytes; a wave's LDS operations complete in order.  Needs N % 4 == 0.
 template <int TW, int TA>
 __device__ __forceinline__ void store_tile_partial(f32x16 (&acc)[TW][TA], float* P, int ldp, int M, int N, int mw, int nw,
                                                    int lane, unsigned char* region) {
-    constexpr int CPR = TW * 8, RB = TW * 128, ROWS = TA * 32, RPI = 64 / CPR;
+    constexpr int CPR = TW * 8, RB = TW * 128, RPI = 64 / CPR;
     const int l32 = lane & 31, hh = lane >> 5;
     const int rrow = lane / CPR, rchunk = lane % CPR;
     auto slot = [&](int row, int chunk) { return row * RB + ((chunk ^ (row & (CPR - 1))) << 4); };
 #pragma unroll
-    for (int j = 0; j < TA; ++j)
+    for (int j = 0; j < TA; ++j) {
 #pragma unroll
         for (int i = 0; i < TW; ++i)
 #pragma unroll
             for (int vg = 0; vg < 4; ++vg)
-                *reinterpret_cast<f32x4*>(region + slot(j * 32 + l32, i * 8 + vg * 2 + hh)) =
+                *reinterpret_cast<f32x4*>(region + slot(l32, i * 8 + vg * 2 + hh)) =
                     f32x4{acc[i][j][vg * 4], acc[i][j][vg * 4 + 1], acc[i][j][vg * 4 + 2], acc[i][j][vg * 4 + 3]};
 #pragma unroll
-    for (int it = 0; it < ROWS / RPI; ++it) {
-        const int row = it * RPI + rrow, m = mw + row, n = nw + rchunk * 4;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(region + slot(row, rchunk));
-        if (m < M && n < N) *reinterpret_cast<f32x4*>(P + (size_t)m * ldp + n) = v;
+        for (int it = 0; it < 32 / RPI; ++it) {
+            const int row = it * RPI + rrow, m = mw + j * 32 + row, n = nw + rchunk * 4;
+            const f32x4 v = *reinterpret_cast<const f32x4*>(region + slot(row, rchunk));
+            if (m < M && n < N) *reinterpret_cast<f32x4*>(P + (size_t)m * ldp + n) = v;
+        }
     }
 }
 
@@ -497,7 +498,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
                       (EPI != EPI_RESIDUAL || ((uintptr_t)R & 15) == 0) && (EPI != EPI_BIAS || ((uintptr_t)R & 7) == 0);
     if constexpr (EPI == EPI_PARTIAL) {
         store_tile_partial<TW, TA>(acc[0], re.partial, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
-                                   lds + wave * (TA * 32 * TW * 128));
+                                   lds + wave * (32 * TW * 128));
     } else if constexpr (EPI == EPI_ROPE) {              // the launcher has checked what `wide` checks
         store_tile_rope<TA>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
                             lds + wave * (TA * 32 * TW * 64), re);
@@ -518,11 +519,12 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
 //                     row: wave-load i of a k-tile covers tile rows 32 i + r0 and lands at ldsw + i * 4096;
 //   wlim / alim       last valid row of the tile (loads of rows beyond it are clamped to it; never stored);
 //   strides in bytes, kt = K / 64, and the three tile origins.
-// The tile starts at token m0, feature n0; M and N bound the loads and the stores.  row_scale as in gemm_tile.
+// The tile starts at token m0, feature n0; M and N bound the loads and the stores.  row_scale as in gemm_tile.  KT: k-tiles to run
+// over when that is not all of K (EPI_PARTIAL).
 template <int TW, int TA, int EPI>
 __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
                                            const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M,
-                                           int N, int K, int m0, int n0, unsigned char* lds, const EpiExtra& re) {
+                                           int N, int K, int m0, int n0, unsigned char* lds, const EpiExtra& re, int KT = 0) {
     static_assert(EPI != EPI_ROPE || TW == 4, "the RoPE epilogue needs one 128-wide head per wave");
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
     constexpr int BN = 64 * TW, WROWS = BN * NW;
@@ -538,7 +540,7 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     const uint64_t abase = (uint64_t)(uintptr_t)(A + (size_t)m0 * lda);
     f32x16 acc[NW][TW][TA];
 #define SLIM_LOOP_ARGS wfrag0, afrag0, r0, chunk, N - 1 - n0, M - 1 - m0, (unsigned)K * 2, (unsigned)lda * 2,          \
-                       (unsigned)(K / BK), lds_base + wave * 1024, w0base, w1base, abase, acc
+                       (unsigned)(KT ? KT : K / BK), lds_base + wave * 1024, w0base, w1base, abase, acc
     // With a residual the k-loop itself adds the tile of R to the accumulators (it fetches the tile as MFMA fragments
     // and multiplies it by identity slices), and the tile is then stored as a plain one.  The launcher has checked that
     // the tile has all its features and that the rows of R are 16-byte aligned.
@@ -580,7 +582,10 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     workgroup_barrier();
     const bool wide = (N % 8 == 0) && (ldo % 8 == 0) && (((uintptr_t)C & 15) == 0) &&
                       (EPI != EPI_BIAS || ((uintptr_t)R & 7) == 0);
-    if constexpr (EPI == EPI_ROPE) {                     // the launcher has checked what `wide` checks
+    if constexpr (EPI == EPI_PARTIAL) {
+        store_tile_partial<TW, TA>(acc[0], re.partial, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
+                                   lds + wave * (32 * TW * 128));
+    } else if constexpr (EPI == EPI_ROPE) {              // the launcher has checked what `wide` checks
         store_tile_rope<TA>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
                             lds + wave * (TA * 32 * TW * 64), re);
     } else {
@@ -733,6 +738,23 @@ split_gemm_kernel(const bf16_t* __restrict__ A, int lda, SplitSegs segs, float* 
     re.partial = partial + (size_t)sp * M * segs.ldp + c0;
     gemm_tile<TW, TA, WGN, WGM, EPI_PARTIAL, NS>(A + lo * BK, lda, W + lo * BK, nullptr, nullptr, nullptr, segs.ldp, M, N, K, hi - lo,
                                              tm * 32 * TA * WGM, (tn - t0) * 32 * TW * WGN, lds, re);
+}
+
+// The same for one matrix in the 256 x 256 tiles and the k-loop of the main path: long reductions whose tiles alone do not fill the chip.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+split_gemm_large_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, float* __restrict__ partial, int M, int N, int K,
+                        int tiles_m, int tiles_n, int splits) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int total = tiles_m * tiles_n * splits;
+    int L = blockIdx.x;
+    if (total % 8 == 0) L = (L & 7) * (total >> 3) + (L >> 3);
+    const int sp = L / (tiles_m * tiles_n);
+    int tm, tn;
+    tile_of_workgroup(L - sp * tiles_m * tiles_n, false, tiles_m, tiles_n, tm, tn);
+    const int KT = K / BK, lo = (int)((long long)KT * sp / splits), hi = (int)((long long)KT * (sp + 1) / splits);
+    EpiExtra re;
+    re.partial = partial + (size_t)sp * M * N;
+    gemm_tile4<4, 4, EPI_PARTIAL>(A + lo * BK, lda, W + lo * BK, nullptr, nullptr, nullptr, N, M, N, K, tm * 256, tn * 256, lds, re, hi - lo);
 }
 
 // Generic kernel (any k_in that is a multiple of 8): register-staged loads with k predicates.
@@ -925,11 +947,13 @@ static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool 
 // rows of 14336 (down projection) it is 1-2 % faster while the activation matrix sits in the 256 MB memory-side cache
 // and 4-7 % slower once that matrix streams from HBM (282 MB at 9856 tokens), where the 8-wave tile, which issues a
 // k-tile's loads at once and so leaves them longest to arrive, wins.  The 8-wave tile's epilogue parks a coalesced copy
-// of the tile of R in LDS and takes any shape.
+// of the tile of R in LDS and takes any shape.  (Long rows that can be cut into rounds never stream: residual_round_rows.  What is left to the
+// 8-wave tile are features that are no multiple of 256 and widths whose rounds do not fill the chip.)
+constexpr size_t kResidualCacheBytes = (size_t)176 << 20;
 static bool residual_in_four_waves(const bf16_t* R, int M, int N, int K, int ldo) {
     const size_t activation_bytes = (size_t)M * K * sizeof(bf16_t);
     return N % 256 == 0 && ldo % 8 == 0 && ((uintptr_t)R & 15) == 0 &&
-           (K <= 8192 || activation_bytes <= ((size_t)160 << 20));
+           (K <= 8192 || activation_bytes <= kResidualCacheBytes);
 }
 
 // What a 128-token tile costs next to a 256-token one of the same launch (measured k-loop + epilogue times): the
@@ -1039,7 +1063,7 @@ bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23); }
 template <int TW, int TA, int WGN, int WGM, int NS>
 static int launch_split_shape(const bf16_t* A, int lda, const SplitMats& mats, int M, int K, int splits, float* partial, hipStream_t st) {
     constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM;
-    constexpr size_t stages = NS * (size_t)(BN + BM) * BK * 2, tile = (size_t)BN * BM * 4;
+    constexpr size_t stages = NS * (size_t)(BN + BM) * BK * 2, tile = (size_t)WGN * WGM * 32 * TW * 128;
     constexpr size_t smem = stages > tile ? stages : tile;
     auto kern = split_gemm_kernel<TW, TA, WGN, WGM, NS>;
     static std::once_flag attr_once;
@@ -1064,6 +1088,20 @@ static int launch_split_shape(const bf16_t* A, int lda, const SplitMats& mats, i
     return check_launch();
 }
 
+int launch_split_gemm_large(const void* a, int lda, const void* w, int m, int n, int k_in, int splits, float* partial, hipStream_t st) {
+    constexpr size_t smem = 2 * (size_t)512 * BK * 2;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [&] {
+        attr_err = hipFuncSetAttribute((const void*)split_gemm_large_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    });
+    if (attr_err != hipSuccess) return set_hip_error(attr_err);
+    const int tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
+    hipLaunchKernelGGL(split_gemm_large_kernel, dim3(tiles_m * tiles_n * splits), dim3(256), smem, st, (const bf16_t*)a, lda, (const bf16_t*)w,
+                       partial, m, n, k_in, tiles_m, tiles_n, splits);
+    return check_launch();
+}
+
 int launch_split_gemm(const void* a, int lda, const SplitMats& mats, int m, int k_in, int splits, float* partial, hipStream_t st) {
     const bf16_t* A = (const bf16_t*)a;
     switch (few_shape(m, mats.n, mats.count, splits)) {
@@ -1072,6 +1110,44 @@ int launch_split_gemm(const void* a, int lda, const SplitMats& mats, int m, int 
         case FEW_C: return launch_split_shape<2, 1, 2, 2, 3>(A, lda, mats, m, k_in, splits, partial, st);
         default: return launch_split_shape<1, 1, 2, 2, 5>(A, lda, mats, m, k_in, splits, partial, st);
     }
+}
+
+// Rows per launch of a residual projection with long rows (down projection): one round of 256 x 256 tiles, if its rows of A stay in the
+// memory-side cache and it fills the chip.  As one launch the tiles of all rows drift apart, the rows come from HBM once per
+// group of feature tiles, and the last round is as long as a full one.  4096 features from 14336, one launch -> rounds (us): 5000 rows 647 ->
+// 540, 7000 857 -> 699, 9856 1014 -> 954, 16384 1651 -> 1536, 26240 2543 -> 2468; 3584 from 18944 (rounds of 4608 rows, 167 MB): 9216
+// 1209 -> 988, 12288 1601 -> 1427, 20000 2304 -> 2236.  With rows of 4096 the same cut is 4 % slower at 9856 rows, so it is not made there.
+static int residual_round_rows(const void* R, int N, int K, int ldo) {
+    if (K <= 8192 || N % 256 != 0 || ldo % 8 != 0 || ((uintptr_t)R & 15)) return 0;
+    const int tiles_n = N / 256, tm = cu_count() / tiles_n;
+    return tm * tiles_n * 100 >= 92 * cu_count() && (size_t)tm * 256 * K * sizeof(bf16_t) <= kResidualCacheBytes ? tm * 256 : 0;
+}
+
+// How launch_linear's residual projection of m rows is cut when its caller has room for float partial sums: `whole` rows in full rounds,
+// the others split over `splits` workgroups per tile (1: not at all, launch_linear takes all rows; !large: split_gemm_kernel's tiles).
+// 4096 features from 14336, with the finishing pass, large tiles against the unsplit few-row ones (us): 768 rows, 5 splits 92 / 132, 1024 rows, 4 113 /
+// 137, 1280 rows, 3 138 / 193, 1511 rows, 2 174 / 190, 1664 rows, 2 180 / 200; 3584 from 18944: 1024 rows, 4 128 / 174, 1500 rows, 3 191 / 244.
+// Up to 512 rows the few-row tiles: 1 / 2 / 4 / 8 splits of 14336 take 73 / 43 / 39 / 38 us for 128 rows, 101 / 75 / 67 / 73 for 300, 106 / 82 /
+// 79 / 90 for 512.  Large tiles: one round of workgroups; or 3 splits that make two full ones (2500 rows 274 / 278, 3072 rows of 18944 363 / 434).  No gain is left at 113
+// tiles and more (2 splits: 1904 rows 199 / 202, 2300 rows of 18944 286 / 276).
+ResidualCut residual_cut(int m, int n, int k_in) {
+    ResidualCut c{0, 1, false};
+    if (k_in < 8192 || k_in % BK != 0 || k_in >= (1 << 23) || n % 4 != 0) return c;
+    if (m <= 1024 && few_rows(m, n)) c.splits = m <= 128 ? 8 : 4;
+    if (m <= 512) return c;
+    const int round = residual_round_rows(nullptr, n, k_in, n);
+    const int whole = round && m > round ? m / round * round : 0, tail = m - whole;
+    if (tail <= 128) return c;
+    const long long tiles = (long long)((tail + 255) / 256) * ((n + 255) / 256);
+    const int cu = cu_count();
+    int s = 1;
+    if (tiles * 16 <= 7ll * cu) s = (int)std::min<long long>(8, cu / tiles);
+    else if (3 * tiles <= 2ll * cu && 3 * tiles * 100 >= 184ll * cu) s = 3;
+    if (s < 2 || 2 * tiles * s < cu) return c;           // (narrow outputs leave the large tiles' launch half empty)
+    c.whole = whole;
+    c.splits = s;
+    c.large = true;
+    return c;
 }
 
 template <int EPI>
@@ -1084,6 +1160,13 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
         if constexpr (EPI == EPI_ROPE) return SLIM_UNSUPPORTED;
         else if (!re.row_scale && !re.w_2) return launch_bf16<2, 2, 2, 2, EPI, true>(A, lda, W0, W1, R, C, ldo, M, N, K, st);
         else return SLIM_UNSUPPORTED;
+    }
+    if constexpr (EPI == EPI_RESIDUAL) {
+        const int round = residual_round_rows(R, N, K, ldo);
+        for (; round && M > round; M -= round, A += (size_t)round * lda, R += (size_t)round * ldo, C += (size_t)round * ldo) {
+            const int rc = launch_two_size<EPI>(A, lda, W0, W1, R, C, ldo, round, N, K, round / 256, false, st, re);
+            if (rc) return rc;
+        }
     }
     if constexpr (EPI == EPI_SWIGLU) {
         // Up to 256 rows the launch streams the weights: 64-feature tiles keep more of it in flight (14336 features, us: 64 rows

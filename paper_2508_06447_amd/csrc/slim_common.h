@@ -163,6 +163,9 @@ bool few_rows(int m, int n);
 // Split projections: float partial sums partial[split][m][sum of n], finished by the launch_split_* below.
 struct SplitMats { const void* w[3]; int n[3]; int count; };
 int launch_split_gemm(const void* a, int lda, const SplitMats& mats, int m, int k_in, int splits, float* partial, hipStream_t st);
+struct ResidualCut { int whole, splits; bool large; };
+ResidualCut residual_cut(int m, int n, int k_in);
+int launch_split_gemm_large(const void* a, int lda, const void* w, int m, int n, int k_in, int splits, float* partial, hipStream_t st);
 int launch_split_residual(const float* partial, int splits, int m, int n, const void* residual, void* out, hipStream_t st);
 struct SplitHeadsArgs { void* out[3]; const void* bias[3]; int heads[3]; int rope[3]; int score; };
 int launch_split_heads(const float* partial, int splits, int m, const SplitHeadsArgs& a, const float* rstd, const int* pos, float theta,

@@ -161,6 +161,25 @@ def test_float32_layer_shapes(slim, seq, hidden, heads, kv_heads, d, ffn, window
     assert r["sc_err"] < 1e-5 and r["mx"] < F32_MAX_ABS
 
 
+@pytest.mark.parametrize("seq,hidden,ffn", [
+    (513, 4096, 8192), (769, 4096, 8256),                # 5 and 4 splits of one round, one row past a tile
+    (1279, 3584, 8256),                                  # 3 splits of 129 k-tiles
+    (2500, 4096, 8192),                                  # 3 splits that make two rounds
+    (4097, 4096, 8256), (4230, 4096, 8256), (5000, 4096, 8256),   # one round of whole rows and a tail: one row, 134 rows, 904 rows
+])
+def test_down_projection_cut_by_rows_and_reduction(slim, seq, hidden, ffn):
+    """Layers (nothing dropped, one query head per kv head) whose down projection runs in rounds of whole tiles and a split tail: the GPU's
+    z against an FFN in float64 on the GPU's own y, rows on both sides of every cut."""
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, hidden=hidden, n_q_heads=1, n_kv_heads=1, ffn=ffn, keep_ratio=1.0, planted=4)
+    x, w, pos = inputs.hidden_states(wl), inputs.layer_weights(wl), inputs.positions(wl)
+    z = run_gpu(slim, wl, x, w, pos, wl.n_blocks, fold=True)["x"]
+    y = run_gpu(slim, wl, x, dict(w, w_down=torch.zeros_like(w["w_down"])), pos, wl.n_blocks, fold=True)["x"]
+    cut = [0, 255, 256, 511, 512, 767, 768, 1023, 1024, 4095, 4096, 4097, seq - 129, seq - 2, seq - 1]
+    rows = torch.tensor(sorted({r for r in cut if 0 <= r < seq}), device="cuda")
+    want = so.ffn_residual(oracle_shape(wl), oracle_weights(w, np.float64), f64(y[rows]))
+    assert_residual_close(z[rows], want, [want], f"down projection seq {seq} hidden {hidden} ffn {ffn}")
+
+
 @pytest.mark.parametrize("bias", [False, True])
 @pytest.mark.parametrize("seq", [3500, 2047, 1700])
 def test_layer_that_drops_nothing_projects_all_three_at_once(slim, seq, bias):
