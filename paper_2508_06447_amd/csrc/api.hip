@@ -742,8 +742,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         resid = x_out;
         pos = pos_out;
     } else {
-        if (kept_blocks_out) SLIM_TRY(launch_select(nullptr, p.nb, p.nb, 0, kept_blocks_out, st));
-        if (pos_out) SLIM_TRY(launch_positions(pos_in, pos_out, N, st));
+        SLIM_TRY(launch_keep_all(kept_blocks_out, p.nb, pos_in, pos_out, N, st));
     }
 
     // Q, V of the rows that continue; RoPE on Q at the original positions.  (Few rows, nothing dropped: K with them.)

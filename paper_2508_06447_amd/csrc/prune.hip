@@ -1,6 +1,7 @@
 // Block-wise prompt token pruning (Section 4.2): block scores (Eq. 1-2), block selection,
 // hidden-state compaction.  All three are HBM-/latency-bound; none uses matrix cores.
 #include "slim_common.h"
+#include <algorithm>
 
 namespace slim {
 
@@ -659,6 +660,20 @@ __global__ void positions_kernel(const int* __restrict__ pos_in, int* __restrict
 
 int launch_positions(const int* pos_in, int* pos_out, int n, hipStream_t st) {
     hipLaunchKernelGGL(positions_kernel, dim3((n + 255) / 256), dim3(256), 0, st, pos_in, pos_out, n);
+    return check_launch();
+}
+
+// A layer that drops nothing: kept = 0 .. nb - 1 and the positions as they came in, either may be null.  One launch: two of them were
+// 5 of the 293 us of a 512-token layer.
+__global__ void keep_all_kernel(int* __restrict__ kept, int nb, const int* __restrict__ pos_in, int* __restrict__ pos_out, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (kept && i < nb) kept[i] = i;
+    if (pos_out && i < n) pos_out[i] = pos_in ? pos_in[i] : i;
+}
+
+int launch_keep_all(int* kept, int nb, const int* pos_in, int* pos_out, int n, hipStream_t st) {
+    if (!kept && !pos_out) return SLIM_OK;
+    hipLaunchKernelGGL(keep_all_kernel, dim3((std::max(n, nb) + 255) / 256), dim3(256), 0, st, kept, nb, pos_in, pos_out, n);
     return check_launch();
 }
 

@@ -145,6 +145,7 @@ int launch_kv_swap(const int* candidate, int n_candidates, int n_blocks, double 
                    int* block_of_slot, int* in_memory, int n_slots, void* gpu_pool, void* host_pool,
                    size_t block_bytes, int* info, int* workspace, hipStream_t st);
 int launch_positions(const int* pos_in, int* pos_out, int n, hipStream_t st);
+int launch_keep_all(int* kept, int nb, const int* pos_in, int* pos_out, int n, hipStream_t st);
 int launch_select(const float* scores, int nb, int n_keep, unsigned flags, int* kept, hipStream_t st);
 int launch_compact(const void* src, const int* pos_in, const int* kept, int n_keep, int block, int N,
                    int row_elems, int dtype, void* dst, int* pos_out, hipStream_t st);
