@@ -392,8 +392,7 @@ int slim_decode_attn(const void* q, const void* gpu_pool, size_t slot_bytes, siz
  *   slim_gemv: the single-token projection, out[n] = s * (w[n, :] . x) + bias[n] + residual[n] (NULL = absent), or
  *              with w_up: silu(s * w . x) * (s * w_up . x);  s = *scale (device float, e.g. the token's 1/rms from
  *              slim_row_rstd for a folded gain) or 1 when scale is NULL.  Every weight is read once.  out may alias
- *              residual.  k_in % 8 == 0 (bf16) / % 4 (fp32), k_in <= 16376 (the token is staged in 64 KiB of LDS as floats,
- *              beside 16 bytes of partial sums; UNSUPPORTED beyond), 16-byte aligned w, w_up, x.
+ *              residual.  k_in % 8 == 0 (bf16) / % 4 (fp32), k_in <= 16376 (UNSUPPORTED beyond), 16-byte aligned w, w_up, x.
  *   slim_decode_layer:
  *     x_new [hidden], position = the token's position (for RoPE), x_out [hidden] (may not alias x_new)
  *     gpu_pool / slot_bytes / layer_offset / block_of_slot / n_slots / n_prompt_tokens: as slim_decode_attn
