@@ -283,6 +283,8 @@ typedef struct slim_layer_weights {   /* device pointers, [out_features, in_feat
 /* Tokens left after keeping n_keep of the blocks of an n_tokens sequence (last block among them). */
 int slim_kept_tokens(int n_tokens, int block, int n_keep);
 
+/* Never falls as n_tokens grows with all blocks kept, as n_keep grows, or as whole blocks are added at a fixed n_keep:
+ * a workspace for the longest sequence serves the shorter ones. */
 size_t slim_pruned_layer_workspace_bytes(const slim_layer_shape* s, int n_tokens, int n_keep);
 
 /* One layer.  With n_keep >= nb it is a Preserve layer (no scoring, nothing dropped).  Otherwise:

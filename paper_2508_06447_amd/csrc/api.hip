@@ -55,11 +55,12 @@ static int forced_count(unsigned flags, int nb) {
 // Query/Key/Value: with 128 rows the weights (50 MB) have to come through at most 96 tiles of 64 x 128; 64 rows, all three
 // in one launch: 22 -> 17 us with 4 splits, Key alone 16 -> 9.4.  From 129 rows on more than one split gains at most 3 us
 // for as many rows as fill the chip and loses behind that (the partial sums are written and read once more per split).
-static int qkv_splits(int m, int k_in) { return m <= 128 && k_in >= 2048 ? 4 : 1; }
+constexpr int kSplitRows = 128;
+static int qkv_splits(int m, int k_in) { return m <= kSplitRows && k_in >= 2048 ? 4 : 1; }
 
 // Workspace layout of slim_pruned_layer (every region 256-byte aligned).
 struct LayerPlan {
-    size_t h, k_all, q_win, qt, scores, table, tscore, rstd, rstd2, kc, vc, qc, o, o_all, act, partial, total;
+    size_t h, k_all, q_win, qt, scores, table, tscore, rstd, rstd2, kc, vc, qc, o, o_all, act, qkv_partial, total;
     int nb, n_out;
     bool prune;
     bool split_k, split_qv, split_qkv;                   // which projections go through float partial sums
@@ -91,21 +92,32 @@ static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
     p.kc = (p.prune && !after) ? take((size_t)p.n_out * kv * es) : p.k_all;   // compacted keys
     p.vc = take(n_att * kv * es);
     p.qc = take(n_att * qd * es);
+    // Partial sums lie over regions that hold nothing while they live: those of the Query / Key / Value projections from here on
+    // (o_all, o and act come later), those of the down projection in front of act (all that is there has been used by then).
+    // Both are given room for the most that any fewer rows take, so that the workspace of a sequence serves every shorter one
+    // although only some row counts are split; of the rows that continue, as many as whole blocks would have.
+    p.qkv_partial = off;
+    size_t qkv_part = 0, down_part = 0;                  // floats
+    if (s->dtype == SLIM_BF16 && s->hidden % 64 == 0 && s->hidden < (1 << 23) && s->ffn < (1 << 23)) {   // (32-bit offsets in a tile)
+        const int na = (int)n_att, n_most = p.prune ? n_keep * s->block : N, na_most = after ? N : n_most;
+        p.split_qkv = !p.prune && few_rows(N, (int)(qd + 2 * kv));
+        p.split_k = !p.split_qkv && few_rows(N, (int)kv);
+        p.split_qv = !p.split_qkv && few_rows(na, (int)(qd + kv));
+        p.down = residual_cut(p.n_out, s->hidden, s->ffn);
+        auto room = [&](int m, size_t n) {               // of the few-row projections of up to m rows of n features
+            const int most = few_rows_most(m, (int)n);
+            qkv_part = std::max(qkv_part, n * std::max(most, std::min(most, kSplitRows) * qkv_splits(1, s->hidden)));
+        };
+        if (!p.prune) room(N, qd + 2 * kv);
+        room(N, kv);
+        room(na_most, qd + kv);
+        down_part = residual_cut_partial_floats(n_most, s->hidden, s->ffn);
+    }
     p.o_all = after ? take(n_att * qd * es) : 0;         // attention output of all N rows, compacted into o
     p.o = take((size_t)p.n_out * qd * es);
+    off = std::max(off, align_up(down_part * sizeof(float), 256));
     p.act = take((size_t)p.n_out * s->ffn * es);
-    size_t part = 0;                                     // floats of the largest set of partial sums
-    if (s->dtype == SLIM_BF16 && s->hidden % 64 == 0 && s->hidden < (1 << 23) && s->ffn < (1 << 23)) {   // (32-bit offsets in a tile)
-        auto room = [&](int m, size_t n, int splits) { part = std::max(part, (size_t)splits * m * n); return true; };
-        const int na = (int)n_att;
-        p.split_qkv = !p.prune && few_rows(N, (int)(qd + 2 * kv)) && room(N, qd + 2 * kv, qkv_splits(N, s->hidden));
-        p.split_k = !p.split_qkv && few_rows(N, (int)kv) && room(N, kv, qkv_splits(N, s->hidden));
-        p.split_qv = !p.split_qkv && few_rows(na, (int)(qd + kv)) && room(na, qd + kv, qkv_splits(na, s->hidden));
-        p.down = residual_cut(p.n_out, s->hidden, s->ffn);
-        if (p.down.splits > 1) room(p.n_out - p.down.whole, s->hidden, p.down.splits);
-    }
-    p.partial = take(part * sizeof(float));
-    p.total = off;
+    p.total = std::max(off, p.qkv_partial + align_up(qkv_part * sizeof(float), 256));
     return p;
 }
 
@@ -579,7 +591,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         if (sc) return launch_linear_scaled(a, Hd, wmat, nullptr, bias, sc, m, n_feat, Hd, n_feat, out, st);
         return launch_linear(a, Hd, wmat, nullptr, nullptr, bias, m, n_feat, Hd, n_feat, dt, out, st);
     };
-    float* partial = (float*)(ws + p.partial);
+    float *qkv_partial = (float*)(ws + p.qkv_partial), *down_partial = (float*)ws;
     // Up to three of the Query / Key / Value projections of the same rows through float partial sums, rotated (not the
     // Values) at the rows' positions and, for the Keys, scored against the window query by the finishing pass.
     auto project_split = [&](const void* a, const float* sc, int m, const int* pos_, void* q_out, void* k_out, void* v_out,
@@ -598,8 +610,8 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         add(k_out, w->wk, w->bk, Hkv, 1);
         add(v_out, w->wv, w->bv, Hkv, 0);
         const int splits = qkv_splits(m, Hd);
-        int r = launch_split_gemm(a, Hd, mats, m, Hd, splits, partial, st);
-        return r ? r : launch_split_heads(partial, splits, m, out, sc, pos_, s->rope_theta, qt_, tscore, st);
+        int r = launch_split_gemm(a, Hd, mats, m, Hd, splits, qkv_partial, st);
+        return r ? r : launch_split_heads(qkv_partial, splits, m, out, sc, pos_, s->rope_theta, qt_, tscore, st);
     };
     auto project_rope = [&](const void* a, const float* sc, const void* wmat, const void* bias, const int* pos_, int pos0,
                             int m, int heads, void* out, const float* tab, const float* qt_, float* ts) -> int {
@@ -773,12 +785,12 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         const bf16_t* a_t = (const bf16_t*)act + (size_t)whole * s->ffn;
         bf16_t* x_t = (bf16_t*)x_out + (size_t)whole * Hd;
         if (p.down.large) {
-            SLIM_TRY(launch_split_gemm_large(a_t, s->ffn, w->w_down, tail, Hd, s->ffn, p.down.splits, partial, st));
+            SLIM_TRY(launch_split_gemm_large(a_t, s->ffn, w->w_down, tail, Hd, s->ffn, p.down.splits, down_partial, st));
         } else {
             const SplitMats mats{{w->w_down}, {Hd}, 1};
-            SLIM_TRY(launch_split_gemm(a_t, s->ffn, mats, tail, s->ffn, p.down.splits, partial, st));
+            SLIM_TRY(launch_split_gemm(a_t, s->ffn, mats, tail, s->ffn, p.down.splits, down_partial, st));
         }
-        SLIM_TRY(launch_split_residual(partial, p.down.splits, tail, Hd, x_t, x_t, st));
+        SLIM_TRY(launch_split_residual(down_partial, p.down.splits, tail, Hd, x_t, x_t, st));
     }
 #undef SLIM_TRY
     return SLIM_OK;

@@ -1060,6 +1060,9 @@ static FewShape few_shape(int M, const int* n, int count, int splits) {
 // scores: 4096 rows 53 against 58 us, 8192 rows 78 against 82.
 bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23); }
 
+// The most rows up to m that few_rows takes.
+int few_rows_most(int m, int n) { return (int)std::min<long long>(m, (1ll << 23) / n); }
+
 template <int TW, int TA, int WGN, int WGM, int NS>
 static int launch_split_shape(const bf16_t* A, int lda, const SplitMats& mats, int M, int K, int splits, float* partial, hipStream_t st) {
     constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM;
@@ -1148,6 +1151,25 @@ ResidualCut residual_cut(int m, int n, int k_in) {
     c.splits = s;
     c.large = true;
     return c;
+}
+
+// The most floats that residual_cut has its caller keep for any row count up to m.  The splits change only behind 128 rows, the last
+// few_rows takes, and from one count of 256-row tiles to the next; behind the second round, or tiles for three splits, nothing is new.
+size_t residual_cut_partial_floats(int m, int n, int k_in) {
+    size_t most = 0;
+    auto look = [&](int rows) {
+        rows = std::min(rows, m);
+        const ResidualCut c = residual_cut(rows, n, k_in);
+        if (c.splits > 1) most = std::max(most, (size_t)c.splits * (rows - c.whole) * n);
+    };
+    const int round = residual_round_rows(nullptr, n, k_in, n), last = round ? 2 * round : 256 * (2 * cu_count() / (3 * ((n + 255) / 256)));
+    look(128);
+    look(few_rows_most(1024, n));
+    for (int rows = 256; rows <= std::max(last, 1024); rows += 256) {
+        look(rows);
+        if (rows >= m) break;
+    }
+    return most;
 }
 
 template <int EPI>

@@ -161,11 +161,13 @@ int launch_gemv_qkv(const void* wq, const void* wk, const void* wv, const void* 
                     void* q, void* k, void* v, hipStream_t st);
 // Whether the few-row projection kernels take m rows of n output features.
 bool few_rows(int m, int n);
+int few_rows_most(int m, int n);
 // Split projections: float partial sums partial[split][m][sum of n], finished by the launch_split_* below.
 struct SplitMats { const void* w[3]; int n[3]; int count; };
 int launch_split_gemm(const void* a, int lda, const SplitMats& mats, int m, int k_in, int splits, float* partial, hipStream_t st);
 struct ResidualCut { int whole, splits; bool large; };
 ResidualCut residual_cut(int m, int n, int k_in);
+size_t residual_cut_partial_floats(int m, int n, int k_in);
 int launch_split_gemm_large(const void* a, int lda, const void* w, int m, int n, int k_in, int splits, float* partial, hipStream_t st);
 int launch_split_residual(const float* partial, int splits, int m, int n, const void* residual, void* out, hipStream_t st);
 struct SplitHeadsArgs { void* out[3]; const void* bias[3]; int heads[3]; int rope[3]; int score; };

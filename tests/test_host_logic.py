@@ -54,6 +54,40 @@ def test_layer_workspace_grows_with_tokens_and_is_aligned(lib):
     assert 0 < a < b and a % 256 == 0 and b % 256 == 0
 
 
+SHAPES = {"llama": (4096, 32, 8, 14336, inputs.WORKLOADS["cfg3"].window), "qwen": (3584, 28, 4, 18944, inputs.WORKLOADS["cfg6"].window)}
+
+
+@pytest.mark.parametrize("placement", [0, 1])
+@pytest.mark.parametrize("family", SHAPES)
+def test_a_workspace_serves_every_shorter_sequence(lib, family, placement):
+    """Only some row counts have projections that go through partial sums; the size reported never falls with the length all the same,
+    so a program may allocate once for its longest prompt.  (10752 tokens of the LLaMA shape split the down projection of their last 2560
+    rows, 10753 do not.)"""
+    hidden, hq, hkv, ffn, window = SHAPES[family]
+    shape = slim.make_shape(hidden, hq, hkv, 128, ffn, 64, 8, window, torch.bfloat16)
+    shape.placement = placement
+    size = lambda n, keep: slim.pruned_layer_workspace_bytes(shape, n, keep)
+    keep_all = [size(n, slim.n_blocks(n, 64)) for n in range(1, 11000)]
+    assert all(a <= b for a, b in zip(keep_all, keep_all[1:]))
+    longer = [size(n, slim.n_blocks(n, 64)) for n in range(10752, 40000, 64)]
+    assert all(a <= b for a, b in zip(longer, longer[1:]))
+    for tail in (64, 1, 37):                             # a ragged last block leaves fewer rows at the same number of kept blocks
+        for keep in (2, 8, 16, 17, 26, 40, 64, 84, 85, 150):
+            by_length = [size(nb * 64 + tail, keep) for nb in range(keep, 400, 5)]
+            assert all(a <= b for a, b in zip(by_length, by_length[1:])), (tail, keep)
+        by_keep = [size(400 * 64 + tail, keep) for keep in range(2, 400)]
+        assert all(a <= b for a, b in zip(by_keep, by_keep[1:])), tail
+
+
+def test_a_model_workspace_serves_every_shorter_sequence(lib):
+    shape = slim.make_shape(4096, 32, 8, 128, 14336, 64, 8, 64, torch.bfloat16)
+    sizes = []
+    for n in range(64, 16385, 64):
+        keeps = slim.schedule_keep_counts(n, 64, 16, {4: 0.5, 8: 0.25, 12: 0.125})
+        sizes.append(lib.slim_prefill_model_workspace_bytes(C.byref(shape), 16, (C.c_int * 16)(*keeps), n))
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 def test_generators_are_seeded_and_per_matrix():
     wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=64, hidden=64, ffn=128, n_q_heads=2, n_kv_heads=1, head_dim=32)
     a, b = inputs.layer_weights(wl, 3), inputs.layer_weights(wl, 3)
