@@ -539,6 +539,27 @@ def test_float32_attention_at_the_edges_of_its_key_tiles(slim, n, Hq, Hkv, d):
         assert not np.isfinite(got2[n - 1]).any()
 
 
+@pytest.mark.parametrize("n,d", [(512, 32), (4100, 64), (16384, 32), (16384, 64), (16384, 128)])
+def test_float32_attention_keeps_its_precision_over_long_sequences(slim, n, d):
+    """Relative rms error of the last queries.  A rounding is 2^-24 / sqrt(3) of what is rounded (rms); a running sum of L terms of random sign
+    adds up to sqrt(L / 2) of them, measured by its end.  Per wave (8 of them, 4 for heads of 128) one such sum over its 16-key tiles, inside a tile
+    16 products, a logit of size 1 from two sums of d / 2 products, 16 for exponentials, the merge and the division; 1.3 for the sample."""
+    print(f"float32 attn precision n={n} d={d}", flush=True)
+    q, k, v = inputs.stage_qkv(n, 4, 2, d, "fp32", seed=n + d)
+    got = f64(slim.slim_prefill_attn(dev(q), dev(k), dev(v)))[n - 64:]
+    want = np.empty_like(got)
+    for h in range(4):
+        s = f64(q)[n - 64:, h] @ f64(k)[:, h // 2].T / np.sqrt(d)
+        s[np.arange(n)[None] > np.arange(n - 64, n)[:, None]] = -np.inf
+        p = np.exp(s - s.max(1, keepdims=True))
+        want[:, h] = p @ f64(v)[:, h // 2] / p.sum(1, keepdims=True)
+    tiles = n / 16 / (4 if d == 128 else 8)
+    err, logit = np.linalg.norm(got - want) / np.linalg.norm(want), np.sqrt((f64(q) ** 2).mean() * (f64(k) ** 2).mean())
+    bound = 1.3 * 2.0 ** -24 / np.sqrt(3) * np.sqrt(tiles / 2 + 16 / 2 + logit ** 2 * d / 4 + 16)
+    print(f"   rel rms {err:.3e}, bound {bound:.3e}", flush=True)
+    assert err <= bound
+
+
 @pytest.mark.parametrize("n,Hq,Hkv,d,dtype", [
     (1, 4, 1, 128, torch.bfloat16), (37, 4, 2, 128, torch.bfloat16), (128, 8, 8, 128, torch.bfloat16),
     (200, 4, 1, 128, torch.bfloat16), (1000, 8, 2, 128, torch.bfloat16), (1280, 32, 8, 128, torch.bfloat16),
