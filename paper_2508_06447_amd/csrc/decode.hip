@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(256) decode_attn_partial_kernel(
         const int have = rows;
         gi += step;
         more = find();                                   // none left: the last group is requested once more, and not used
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+        f32x4 s = {0.f, 0.f, 0.f, 0.f}, sp[NK];    // (float32: eight sums of 16 products, half the error of one of 128)
 #pragma unroll
         for (int c = 0; c < NK; ++c) {
             if constexpr (sizeof(T) == 2) {
@@ -126,9 +126,10 @@ __global__ void __launch_bounds__(256) decode_attn_partial_kernel(
             } else {
                 const f32x4 a = __builtin_bit_cast(f32x4, kx[c]), b = __builtin_bit_cast(f32x4, qx[c]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], s, 0, 0, 0);
+                for (int j = 0; j < 4; ++j) sp[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], j ? sp[c] : s, 0, 0, 0);
             }
         }
+        if constexpr (sizeof(T) == 4) s = ((sp[0] + sp[1]) + (sp[2] + sp[3])) + ((sp[4] + sp[5]) + (sp[6] + sp[7]));
         __builtin_amdgcn_sched_barrier(0);
         load_k();                                        // the next group's keys fly under this one's values
         float mx = -INFINITY;

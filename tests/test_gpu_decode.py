@@ -298,6 +298,30 @@ def test_decode_attention_over_active_slots_matches_oracle(slim, n_prompt, block
     assert torch.isfinite(got.float()).all()              # nothing outside the active rows was read (it is NaN)
 
 
+@pytest.mark.parametrize("n_slots,n_resp,G", [(1, 1, 8), (8, 7, 4), (128, 16, 4), (512, 301, 1)])
+def test_float32_decode_attention_keeps_its_precision(slim, n_slots, n_resp, G):
+    """Relative rms error over many tokens.  A rounding is 2^-24 / sqrt(3) of what is rounded (rms); a running sum of L terms of random sign adds
+    up to sqrt(L / 2) of them, measured by its end.  A logit of size 1: sums of 16 products and their sum; the values: four keys of every group
+    that a wave takes, then the partials of the 8 groups of the merge; 16 for exponentials, divisions and the sums of lanes and waves; 1.3 for the sample."""
+    Hkv, d, block = 8, 128, 64
+    print(f"float32 decode precision slots={n_slots} resp={n_resp} G={G}", flush=True)
+    num = den = logit2 = 0.0
+    for seed in range(6):
+        pool, q = rand((n_slots, 2, block, Hkv, d), torch.float32, 10 * seed + 1), rand((G * Hkv, d), torch.float32, 10 * seed + 2)
+        kr, vr = rand((n_resp, Hkv, d), torch.float32, 10 * seed + 3), rand((n_resp, Hkv, d), torch.float32, 10 * seed + 4)
+        held = torch.from_numpy(np.random.default_rng(seed).permutation(n_slots).astype(np.int32))
+        got = f64(slim.slim_decode_attn(q.cuda(), pool.cuda(), held.cuda(), block, n_slots * block, Hkv, kr.cuda(), vr.cuda()))
+        k, v = (np.concatenate([f64(pool[:, i]).reshape(-1, Hkv, d), f64(r)]) for i, r in ((0, kr), (1, vr)))
+        want = so.decode_attention(f64(q), k, v)
+        num, den = num + ((got - want) ** 2).sum(), den + (want ** 2).sum()
+        logit2 += (f64(q) ** 2).mean() * (k ** 2).mean() / 6
+    groups = n_slots * 4 + (n_resp + 15) // 16
+    rounds = -(-groups // 256)                           # 64 workgroups of 4 waves per kv head at most
+    err, bound = np.sqrt(num / den), 1.3 * 2.0 ** -24 / np.sqrt(3) * np.sqrt(logit2 * (16 + 3) / 2 + 4 * rounds / 2 + min(64, groups) / 8 / 2 + 16)
+    print(f"   rel rms {err:.3e}, bound {bound:.3e}", flush=True)
+    assert err <= bound
+
+
 def test_a_decode_step_scores_selects_swaps_and_attends(slim):
     """One decode step of a layer through the C ABI: scores from stored unit keys and the window of recent Query
     states, top-k candidate set, overlap-aware swap of the K/V payloads, attention of the new token over what is
