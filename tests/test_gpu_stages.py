@@ -117,6 +117,21 @@ def test_scores_at_the_edges_of_their_pieces(slim, N, block, unit, w, Hq, Hkv, d
     test_scores_match_oracle(slim, N, block, unit, w, Hq, Hkv, d, dtype)
 
 
+@pytest.mark.parametrize("unit,d", [(8, 128), (9, 128), (64, 128), (100, 64)])
+def test_scores_sum_a_unit_before_the_products(slim, unit, d):
+    """Relative rms error of bf16 scores whose units have many rows.  The rows' sum is all but exact in float32 and each lane then adds
+    2 x 8 products of it (1024 features): a running sum of 16 terms of random sign adds up to 16 / 2 roundings of 2^-24 / sqrt(3) (rms), measured by
+    its end; 6 / 2 for the sum over the lanes, 3 for the window query, its division and the unit's; 1.3 for the sample."""
+    N, w, Hkv = 640 * unit, 4, 1024 // d
+    q, k = rand((w, 4 * Hkv, d), torch.bfloat16, unit), rand((N, Hkv, d), torch.bfloat16, unit + 1)
+    got = f64(slim.slim_score_blocks(dev(q), dev(k), unit, unit))
+    qt = f64(q).reshape(w, Hkv, 4, d).sum((0, 2)) / (w * 4 * Hkv)
+    want = (f64(k).reshape(-1, unit, Hkv, d).mean(1) * qt).sum((1, 2))
+    err, bound = np.linalg.norm(got - want) / np.linalg.norm(want), 1.3 * 2.0 ** -24 / np.sqrt(3) * np.sqrt(16 / 2 + 6 / 2 + 3)
+    print(f"   unit {unit}: rel rms {err:.3e}, bound {bound:.3e}", flush=True)
+    assert err <= bound
+
+
 # Head counts with and without 16-byte loads, blocks and units that pass the strip of 2048 tokens by one unit, one token, altogether.
 @pytest.mark.parametrize("N,H,block,unit", [(1000, 8, 64, 8), (300, 3, 64, 7), (70, 1, 33, 33), (5000, 2, 5000, 9), (9000, 4, 4500, 2049),
                                             (6200, 12, 4097, 2048), (2049, 5, 2049, 1)])
