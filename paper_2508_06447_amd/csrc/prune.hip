@@ -82,10 +82,10 @@ __global__ void __launch_bounds__(kWqChunks * kWqSlices) window_query_vec_kernel
     part2[grp][el] = s;
     __syncthreads();
     if (grp == 0 && blockIdx.x * EL + el < Hkv * d) {
-        float tot = 0.f;
+        float tot[4] = {0.f, 0.f, 0.f, 0.f};             // (one sum of 16 or 32 takes twice their error)
 #pragma unroll
-        for (int i = 0; i < NG; ++i) tot += part2[i][el];
-        qt[blockIdx.x * EL + el] = tot / ((float)w * (float)Hq);
+        for (int i = 0; i < NG; ++i) tot[i & 3] += part2[i][el];
+        qt[blockIdx.x * EL + el] = ((tot[0] + tot[1]) + (tot[2] + tot[3])) / ((float)w * (float)Hq);
     }
 }
 

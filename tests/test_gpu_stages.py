@@ -132,6 +132,20 @@ def test_scores_sum_a_unit_before_the_products(slim, unit, d):
     assert err <= bound
 
 
+def test_float32_window_query_keeps_its_precision(slim):
+    """Relative rms error of the mean over 32 tokens and 4 heads per kv head: sums of 4 and of 8 terms of random sign, 2 more to put four of those
+    together, the division; a running sum of L terms adds up to L / 2 roundings of 2^-24 / sqrt(3) (rms), measured by its end."""
+    num = den = 0.0
+    for seed in range(20):
+        q = rand((32, 32, 128), torch.float32, seed)
+        want = f64(q).reshape(32, 8, 4, 128).sum((0, 2)).ravel() / (32 * 32)
+        num += ((f64(slim.slim_window_query(dev(q), 8)) - want) ** 2).sum()
+        den += (want ** 2).sum()
+    err, bound = np.sqrt(num / den), 1.1 * 2.0 ** -24 / np.sqrt(3) * np.sqrt((4 + 8 + 2) / 2 + 1)
+    print(f"   rel rms {err:.3e}, bound {bound:.3e}", flush=True)
+    assert err <= bound
+
+
 # Head counts with and without 16-byte loads, blocks and units that pass the strip of 2048 tokens by one unit, one token, altogether.
 @pytest.mark.parametrize("N,H,block,unit", [(1000, 8, 64, 8), (300, 3, 64, 7), (70, 1, 33, 33), (5000, 2, 5000, 9), (9000, 4, 4500, 2049),
                                             (6200, 12, 4097, 2048), (2049, 5, 2049, 1)])
