@@ -210,8 +210,9 @@ __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
     }
 }
 
-// Work items of a launch stay below 2^32: what is larger goes one segment, and then so many rows, at a time.
+// Work items of a launch stay below 2^32: what is larger goes one segment, and then so many features and so many rows, at a time.
 constexpr long long kF32TilesMax = 1ll << 23;
+constexpr int kF32FeaturesMax = 1 << 27;                 // (2^23 tiles of 16; whole heads)
 // From how many tiles of 32 rows on tiles of 64 are taken: twice the flops per byte read, half the workgroups (us, tall
 // and not: 2048 x 2048 from 2048 features 241 / 293, 2048 x 1024 from 512, 2048 tiles, 45 / 53; 1024 tiles fill the chip with 32 rows only).
 // Four waves there: with eight the sums of 64 rows do not fit the LDS.
@@ -220,7 +221,7 @@ constexpr long long kF32TallTiles = 2048;
 int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain, float eps, int head_dim, float theta, hipStream_t st) {
     F32LinearArgs p{};
     auto tiles_n = [](const F32Seg& g) { return g.mode == F32_SWIGLU ? (g.n + 15ll) / 16 : (g.n + 31ll) / 32; };
-    long long small = 0, tiles = 0, widest = 1;
+    long long small = 0, tiles = 0;
     for (int s = 0; s < count; ++s) small += (segs[s].m + 31ll) / 32 * tiles_n(segs[s]);
     const bool tall = small >= kF32TallTiles;
     const int rows = tall ? 64 : 32;
@@ -228,24 +229,33 @@ int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain
         if (s < count) {
             p.seg[s] = segs[s];
             p.tiles_m[s] = (segs[s].m + rows - 1) / rows;
-            widest = std::max(widest, tiles_n(segs[s]));
             tiles += p.tiles_m[s] * tiles_n(segs[s]);
         }
         p.tile_end[s] = (int)(tiles < (1ll << 31) ? tiles : (1ll << 31) - 1);
     }
     if (tiles > kF32TilesMax) {
         for (int s = 0; s < count; ++s) {
-            const int step = (int)(widest < kF32TilesMax ? kF32TilesMax / widest : 1) * rows;
-            for (int m = 0; m < segs[s].m;) {
-                F32Seg part = segs[s];
-                part.m = step < segs[s].m - m ? step : segs[s].m - m;
-                part.a += (size_t)m * part.lda;
-                part.out += (size_t)m * part.ldo;
-                if (part.residual) part.residual += (size_t)m * part.ldo;
-                if (part.pos) part.pos += m; else part.pos0 += m;
-                const int rc = launch_f32_linear(&part, 1, k_in, gain, eps, head_dim, theta, st);
-                if (rc) return rc;
-                m += part.m;
+            for (int n = 0; n < segs[s].n;) {
+                F32Seg cols = segs[s];
+                cols.n = std::min(kF32FeaturesMax, segs[s].n - n);
+                cols.w0 += (size_t)n * k_in;
+                if (cols.w1) cols.w1 += (size_t)n * k_in;
+                if (cols.bias) cols.bias += n;
+                if (cols.residual) cols.residual += n;
+                cols.out += n;
+                n += cols.n;
+                const int step = (int)(kF32TilesMax / tiles_n(cols)) * rows;
+                for (int m = 0; m < cols.m;) {
+                    F32Seg part = cols;
+                    part.m = std::min(step, cols.m - m);
+                    part.a += (size_t)m * part.lda;
+                    part.out += (size_t)m * part.ldo;
+                    if (part.residual) part.residual += (size_t)m * part.ldo;
+                    if (part.pos) part.pos += m; else part.pos0 += m;
+                    const int rc = launch_f32_linear(&part, 1, k_in, gain, eps, head_dim, theta, st);
+                    if (rc) return rc;
+                    m += part.m;
+                }
             }
         }
         return SLIM_OK;

@@ -547,6 +547,21 @@ def test_float32_projections(slim, m, n, k, shift):
     assert ((slim.slim_swiglu_linear(a, w, w2).double() - want).abs() <= bound).all()
 
 
+@pytest.mark.parametrize("n,swiglu", [(2 ** 28 + 40, False), (2 ** 27 + 24, True)])
+def test_float32_projection_to_more_features_than_a_launch_has_tiles(slim, n, swiglu):
+    """One input feature: an output is a single product, so the plain projection is exact."""
+    print(f"float32 linear n={n} swiglu={swiglu}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    a = torch.tensor([[1.5], [-0.75]], device="cuda")
+    w = torch.empty(n, 1, device="cuda").normal_(generator=g)
+    if not swiglu:
+        assert torch.equal(slim.slim_linear(a, w), a * w.T)
+        return
+    w2 = torch.empty(n, 1, device="cuda").normal_(generator=g)
+    want = torch.nn.functional.silu(a * w.T) * (a * w2.T)
+    assert ((slim.slim_swiglu_linear(a, w, w2) - want).abs() <= 2.0 ** -20 * want.abs() + 1e-30).all()   # (each side: 8 roundings of the result)
+
+
 # ------------------------------------------------------------------------------------------ attention
 @pytest.mark.parametrize("n,Hq,Hkv,d", [(1, 2, 1, 32), (15, 3, 3, 64), (16, 2, 2, 128), (17, 2, 1, 64), (63, 5, 1, 32), (65, 4, 2, 128), (129, 2, 2, 64)])
 def test_float32_attention_at_the_edges_of_its_key_tiles(slim, n, Hq, Hkv, d):
