@@ -708,6 +708,7 @@ int launch_select(const float* scores, int nb, int n_keep, unsigned flags, int* 
 // -------------------------------------------------------------------------------------------------
 constexpr int kCopyThreads = 256;
 constexpr int kCopyVecs = 1;
+constexpr size_t kCopyChunks = 1 << 23;                  // workgroups per kept block in one plane of the grid (work items per dimension stay below 2^32)
 
 template <typename V>
 __global__ void __launch_bounds__(kCopyThreads) compact_kernel(const V* __restrict__ src, V* __restrict__ dst,
@@ -722,7 +723,7 @@ __global__ void __launch_bounds__(kCopyThreads) compact_kernel(const V* __restri
     const size_t seg = (size_t)rows * row_vecs;
     const V* s = src + (size_t)kb * block * row_vecs;
     V* d = dst + (size_t)i * block * row_vecs;
-    const size_t base = (size_t)blockIdx.x * (kCopyThreads * kCopyVecs) + threadIdx.x;
+    const size_t base = (blockIdx.x + blockIdx.z * kCopyChunks) * (kCopyThreads * kCopyVecs) + threadIdx.x;
     V tmp[kCopyVecs];
 #pragma unroll
     for (int u = 0; u < kCopyVecs; ++u) {
@@ -734,7 +735,7 @@ __global__ void __launch_bounds__(kCopyThreads) compact_kernel(const V* __restri
         size_t o = base + (size_t)u * kCopyThreads;
         if (o < seg) __builtin_nontemporal_store(tmp[u], d + o);
     }
-    if (blockIdx.x == 0 && pos_out) {
+    if (blockIdx.x == 0 && blockIdx.z == 0 && pos_out) {
         for (int r = threadIdx.x; r < rows; r += kCopyThreads) {
             int t = kb * block + r;
             pos_out[(size_t)i * block + r] = pos_in ? pos_in[t] : t;
@@ -748,20 +749,16 @@ int launch_compact(const void* src, const int* pos_in, const int* kept, int n_ke
                    int row_elems, int dtype, void* dst, int* pos_out, hipStream_t st) {
     const size_t row_bytes = (size_t)row_elems * elem_size(dtype);
     const int nb = (N + block - 1) / block;
-    const size_t per = (size_t)kCopyThreads * kCopyVecs;
-    if (row_bytes % 16 == 0 && aligned16(src) && aligned16(dst)) {
-        size_t rv = row_bytes / 16, chunks = ((size_t)block * rv + per - 1) / per;
-        hipLaunchKernelGGL(compact_kernel<u32x4>, dim3((unsigned)chunks, n_keep), dim3(kCopyThreads), 0, st,
-                           (const u32x4*)src, (u32x4*)dst, kept, block, N, nb, rv, pos_in, pos_out);
-    } else if (row_bytes % 4 == 0) {
-        size_t rv = row_bytes / 4, chunks = ((size_t)block * rv + per - 1) / per;
-        hipLaunchKernelGGL(compact_kernel<uint32_t>, dim3((unsigned)chunks, n_keep), dim3(kCopyThreads), 0, st,
-                           (const uint32_t*)src, (uint32_t*)dst, kept, block, N, nb, rv, pos_in, pos_out);
-    } else {
-        size_t rv = row_bytes / 2, chunks = ((size_t)block * rv + per - 1) / per;
-        hipLaunchKernelGGL(compact_kernel<uint16_t>, dim3((unsigned)chunks, n_keep), dim3(kCopyThreads), 0, st,
-                           (const uint16_t*)src, (uint16_t*)dst, kept, block, N, nb, rv, pos_in, pos_out);
-    }
+    const size_t per = (size_t)kCopyThreads * kCopyVecs, rows = std::min(block, N);   // (a block may be longer than all there is)
+#define SLIM_COMPACT(V) do { \
+        const size_t rv = row_bytes / sizeof(V), chunks = (rows * rv + per - 1) / per; \
+        const dim3 grid((unsigned)std::min(kCopyChunks, chunks), n_keep, (unsigned)((chunks + kCopyChunks - 1) / kCopyChunks)); \
+        hipLaunchKernelGGL(compact_kernel<V>, grid, dim3(kCopyThreads), 0, st, \
+                           (const V*)src, (V*)dst, kept, block, N, nb, rv, pos_in, pos_out); } while (0)
+    if (row_bytes % 16 == 0 && aligned16(src) && aligned16(dst)) SLIM_COMPACT(u32x4);
+    else if (row_bytes % 4 == 0) SLIM_COMPACT(uint32_t);
+    else SLIM_COMPACT(uint16_t);
+#undef SLIM_COMPACT
     return check_launch();
 }
 

@@ -67,6 +67,16 @@ def test_compact_3d_keys(slim):
     assert torch.equal(dst.cpu(), k[T])
 
 
+@pytest.mark.parametrize("N,block,row", [(1000, 2 ** 24, 4096), (2 ** 22 + 1, 2 ** 23, 1025)])
+def test_compaction_of_one_long_block(slim, N, block, row):
+    """A block longer than the sequence, and one of more pieces (2 bytes each: 8.6 GB) than a launch has work items."""
+    print(f"compaction N={N} block={block} row={row}", flush=True)
+    src = torch.empty(N, row, dtype=torch.bfloat16, device="cuda")
+    src.view(torch.int16).random_(generator=torch.Generator(device="cuda").manual_seed(N))
+    dst, pos = slim.slim_compact_tokens(src, torch.zeros(1, dtype=torch.int32, device="cuda"), block)
+    assert torch.equal(dst.view(torch.int16), src.view(torch.int16)) and torch.equal(pos, torch.arange(N, dtype=torch.int32, device="cuda"))
+
+
 # ------------------------------------------------------------------------------------------ selection
 @pytest.mark.parametrize("nb", [2, 3, 7, 32, 128, 512, 1024, 1025, 5000])
 def test_select_bit_exact_including_ties(slim, nb):
