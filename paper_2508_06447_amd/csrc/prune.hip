@@ -703,11 +703,14 @@ int launch_select(const float* scores, int nb, int n_keep, unsigned flags, int* 
 
 // -------------------------------------------------------------------------------------------------
 // Compaction: a kept block is one contiguous run of block*row bytes in src and in dst, so the gather
-// is a segmented copy.  grid = (chunks per block, kept blocks); each thread moves kCopyVecs 16-byte vectors, past the caches.
-// One vector each: 81 MB of rows 26.7 us (6.0 TB/s), two 27.5, four 28.6, eight 41.5; without the non-temporal store 28.8 to 43.
+// is a segmented copy.  grid = (chunks per block, kept blocks); each thread moves copy_vecs<V>() vectors, past the caches.
+// One 16-byte vector each: 81 MB of rows 26.7 us (6.0 TB/s), two 27.5, four 28.6, eight 41.5; without the non-temporal store 28.8 to 43.
+// Of the narrow vectors of other rows four each, for more bytes in flight: 22 MB of rows of 1026 (4-byte vectors) or 1025 (2-byte)
+// bf16 15.5 and 25.6 us with one, 10.6 and 17.7 with four.
 // -------------------------------------------------------------------------------------------------
 constexpr int kCopyThreads = 256;
-constexpr int kCopyVecs = 1;
+constexpr int kCopyVecs = 1;                             // 16-byte ones
+template <typename V> constexpr int copy_vecs() { return sizeof(V) == 16 ? kCopyVecs : 4; }
 constexpr size_t kCopyChunks = 1 << 23;                  // workgroups per kept block in one plane of the grid (work items per dimension stay below 2^32)
 
 template <typename V>
@@ -716,6 +719,7 @@ __global__ void __launch_bounds__(kCopyThreads) compact_kernel(const V* __restri
                                                                int nb, size_t row_vecs,
                                                                const int* __restrict__ pos_in,
                                                                int* __restrict__ pos_out) {
+    constexpr int VECS = copy_vecs<V>();
     const int i = blockIdx.y;
     const int kb = kept[i];
     if ((unsigned)kb >= (unsigned)nb) return;
@@ -723,15 +727,15 @@ __global__ void __launch_bounds__(kCopyThreads) compact_kernel(const V* __restri
     const size_t seg = (size_t)rows * row_vecs;
     const V* s = src + (size_t)kb * block * row_vecs;
     V* d = dst + (size_t)i * block * row_vecs;
-    const size_t base = (blockIdx.x + blockIdx.z * kCopyChunks) * (kCopyThreads * kCopyVecs) + threadIdx.x;
-    V tmp[kCopyVecs];
+    const size_t base = (blockIdx.x + blockIdx.z * kCopyChunks) * (kCopyThreads * VECS) + threadIdx.x;
+    V tmp[VECS];
 #pragma unroll
-    for (int u = 0; u < kCopyVecs; ++u) {
+    for (int u = 0; u < VECS; ++u) {
         size_t o = base + (size_t)u * kCopyThreads;
         if (o < seg) tmp[u] = __builtin_nontemporal_load(s + o);
     }
 #pragma unroll
-    for (int u = 0; u < kCopyVecs; ++u) {
+    for (int u = 0; u < VECS; ++u) {
         size_t o = base + (size_t)u * kCopyThreads;
         if (o < seg) __builtin_nontemporal_store(tmp[u], d + o);
     }
@@ -749,9 +753,9 @@ int launch_compact(const void* src, const int* pos_in, const int* kept, int n_ke
                    int row_elems, int dtype, void* dst, int* pos_out, hipStream_t st) {
     const size_t row_bytes = (size_t)row_elems * elem_size(dtype);
     const int nb = (N + block - 1) / block;
-    const size_t per = (size_t)kCopyThreads * kCopyVecs, rows = std::min(block, N);   // (a block may be longer than all there is)
+    const size_t rows = std::min(block, N);   // (a block may be longer than all there is)
 #define SLIM_COMPACT(V) do { \
-        const size_t rv = row_bytes / sizeof(V), chunks = (rows * rv + per - 1) / per; \
+        const size_t rv = row_bytes / sizeof(V), per = kCopyThreads * copy_vecs<V>(), chunks = (rows * rv + per - 1) / per; \
         const dim3 grid((unsigned)std::min(kCopyChunks, chunks), n_keep, (unsigned)((chunks + kCopyChunks - 1) / kCopyChunks)); \
         hipLaunchKernelGGL(compact_kernel<V>, grid, dim3(kCopyThreads), 0, st, \
                            (const V*)src, (V*)dst, kept, block, N, nb, rv, pos_in, pos_out); } while (0)
