@@ -107,7 +107,9 @@ static void launch_window_query_t(const void* q_win, int w, int Hq, int Hkv, int
 // selection and compaction of 32768 tokens.
 // A unit's rows are summed whole before the products with the window query (LONG: over several pieces of eight), so that a product takes one
 // rounding: with the products of every piece added up the error of units of 64 bf16 rows was 2.3e-7 (relative rms), so it is 0.9e-7.
-template <typename T, bool LONG>
+// R: rows of a piece.  Units of one, two and up to four rows have pieces of as many; read as eight they load a row several times (67 MB of
+// bf16 keys, blocks of 64, units of 1 / 2 / 4: 29.7 / 19.6 / 16.8 us in pieces of eight, 22.4 / 15.8 / 14.7 so).
+template <typename T, int R, bool LONG>
 __global__ void __launch_bounds__(1024) block_score_kernel(const T* __restrict__ k, const float* __restrict__ qt,
                                                             int N, int E /*Hkv*d*/, int block, int unit,
                                                             float* __restrict__ scores) {
@@ -115,12 +117,11 @@ __global__ void __launch_bounds__(1024) block_score_kernel(const T* __restrict__
     extern __shared__ float smem[];                      // qt copy [E] + per-wave maxima [16]
     float* qs = smem;
     float* wmax = smem + E;
-    constexpr int R = 8;
     const int j = blockIdx.x, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b0 = j * block, b1 = min(b0 + block, N);
     const int nchunk = E / V;
-    // the wave's next piece: rows t .. t + 7 of the unit u0 .. u1, chunks c0 + lane
+    // the wave's next piece: rows t .. t + R - 1 of the unit u0 .. u1, chunks c0 + lane
     int u0 = b0 + wave * unit, u1 = min(u0 + unit, b1), t = u0, c0 = 0;
     uint4 raw[R];
     auto load = [&]() {                                  // rows and chunks past the end repeat the last one and are left out below
@@ -246,8 +247,12 @@ template <typename T>
 static void launch_block_score(const T* k, const float* qt, int N, int E, int block, int unit, float* scores, hipStream_t st) {
     const int nb = (N + block - 1) / block, waves = std::min(16, (block + unit - 1) / unit);
     const size_t smem = (size_t)(E + 16) * sizeof(float);
-#define SLIM_SCORE(L) hipLaunchKernelGGL((block_score_kernel<T, L>), dim3(nb), dim3(64 * waves), smem, st, k, qt, N, E, block, unit, scores)
-    if (unit > 8) SLIM_SCORE(true); else SLIM_SCORE(false);
+#define SLIM_SCORE(R, L) hipLaunchKernelGGL((block_score_kernel<T, R, L>), dim3(nb), dim3(64 * waves), smem, st, k, qt, N, E, block, unit, scores)
+    if (unit > 8) SLIM_SCORE(8, true);
+    else if (unit > 4) SLIM_SCORE(8, false);
+    else if (unit > 2) SLIM_SCORE(4, false);
+    else if (unit > 1) SLIM_SCORE(2, false);
+    else SLIM_SCORE(1, false);
 #undef SLIM_SCORE
 }
 

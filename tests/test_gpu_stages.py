@@ -122,6 +122,8 @@ def test_scores_match_oracle(slim, N, block, unit, w, Hq, Hkv, d, dtype):
 @pytest.mark.parametrize("N,block,unit,w,Hq,Hkv,d,dtype", [
     (333, 50, 19, 3, 6, 2, 24, torch.bfloat16), (700, 64, 9, 130, 7, 1, 520, torch.bfloat16), (65, 64, 8, 1, 9, 9, 128, torch.bfloat16),
     (257, 40, 17, 33, 4, 2, 260, torch.float32), (100, 100, 100, 2, 5, 5, 12, torch.float32), (90, 30, 4, 5, 2, 1, 4, torch.float32),
+    (131, 16, 1, 4, 4, 2, 128, torch.bfloat16), (133, 11, 2, 4, 4, 2, 260, torch.float32), (200, 23, 3, 4, 8, 8, 128, torch.bfloat16),
+    (67, 64, 4, 4, 8, 8, 72, torch.bfloat16), (150, 33, 5, 4, 4, 4, 64, torch.bfloat16),
 ])
 def test_scores_at_the_edges_of_their_pieces(slim, N, block, unit, w, Hq, Hkv, d, dtype):
     test_scores_match_oracle(slim, N, block, unit, w, Hq, Hkv, d, dtype)
