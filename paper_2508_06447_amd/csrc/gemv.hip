@@ -5,8 +5,8 @@
 // a cache again before the next token).
 //
 // A workgroup owns four weight rows (four features, or the gate and up rows of two) and its four waves deal their 1 KB
-// pieces out among themselves: a row piece meets the token's piece in registers, so no load waits for a barrier, and U
-// pieces of each row (16 to 112 registers per lane) are requested before the first is used.  With a wave per four rows, the token
+// pieces out among themselves (short rows: each wave owns four): a row piece meets the token's piece in registers, so no load waits for a
+// barrier, and U pieces of each row (32 to 112 registers per lane, 8 to 28 for the token's) are requested before the first is used.  With a wave per four rows, the token
 // staged in LDS and two pieces in flight, a launch of 4096 x 4096 was one round of workgroups that spent half its time on
 // latency.  Weights from HBM, us before -> now (bf16): 6144 x 4096 12.0 -> 9.2, 4096 x 4096 9.9 -> 7.1, 28672 x 4096 42.8 ->
 // 33.9 (6.9 TB/s), 4096 x 14336 27.3 -> 18.4; without the hint 9.9 / 7.4 / 37.4 / 20.3.
@@ -42,13 +42,16 @@ struct GemvArgs {
 constexpr int kGemvRows = 4; // weight rows per workgroup
 constexpr int kGemvGrid = 1 << 22;                       // workgroups per row of the grid (work items per dimension stay below 2^32)
 
-template <typename T, bool SWIGLU, int U>
+// KW: waves that share the rows (4, or 1: each of the four waves has four rows of its own).
+template <typename T, bool SWIGLU, int U, int KW>
 __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
-    constexpr int V = Elem<T>::kVec, R = kGemvRows, FPW = SWIGLU ? R / 2 : R;   // features per workgroup
+    constexpr int V = Elem<T>::kVec, R = kGemvRows, FPW = SWIGLU ? R / 2 : R;   // features of four rows
     __shared__ float red[4][R + 1];                      // per wave: its share of the rows' sums and of the token's sum of squares
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = a.k, nchunk = K / V;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tid = KW == 1 ? lane : threadIdx.x;
+    const int K = a.k, nchunk = K / V;
     long long j = blockIdx.x + (long long)blockIdx.y * kGemvGrid;
-    int s = 0;                                           // this workgroup's segment, j: its place in it
+    if (KW == 1) j = j * 4 + wave;
+    int s = 0;                                           // the segment of these four rows, j: their place in it
     while (s < a.n_seg - 1 && j >= (a.seg[s].n + FPW - 1) / FPW) { j -= (a.seg[s].n + FPW - 1) / FPW; ++s; }
     const GemvSeg sg = a.seg[s];
     const int N = sg.n;
@@ -64,7 +67,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     auto load = [&](int c0) {                            // pieces past the end: the token's values are zeros there
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int c = c0 + u * 256, cc = min(c, nchunk - 1);
+            const int c = c0 + u * 64 * KW, cc = min(c, nchunk - 1);
             xr[u] = c < nchunk ? *reinterpret_cast<const uint4*>(x + (size_t)cc * V) : make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int r = 0; r < R; ++r) raw[u][r] = load_stream16(rows[r] + (size_t)cc * V);
@@ -80,7 +83,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     float acc[R], ss = 0.f;
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0.f;
-    for (int c = tid; c - lane < nchunk; c += 256 * U) { // (wave-uniform bound)
+    for (int c = tid; c - lane < nchunk; c += 64 * KW * U) { // (wave-uniform bound)
         if (c != tid) load(c);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -92,7 +95,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
             for (int r = 0; r < R; ++r) {
                 float f[V];
                 Elem<T>::unpack(raw[u][r], f);
-                if (c + u * 256 >= nchunk) continue;     // (a repeated piece may hold an infinity: 0 times it is not 0)
+                if (c + u * 64 * KW >= nchunk) continue;     // (a repeated piece may hold an infinity: 0 times it is not 0)
 #pragma unroll
                 for (int i = 0; i < V; ++i) acc[r] += f[i] * xf[i];
             }
@@ -110,18 +113,25 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     }
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
-    if ((lane & 15) == 0) red[wave][lane >> 4] = acc[0];
-    if (a.norm_eps >= 0.f) {
-        ss = wave_sum(ss);
-        if (lane == 0) red[wave][R] = ss;
+    if (KW == 1) {
+        if (a.norm_eps >= 0.f) ss = wave_sum(ss);
+    } else {
+        if ((lane & 15) == 0) red[wave][lane >> 4] = acc[0];
+        if (a.norm_eps >= 0.f) {
+            ss = wave_sum(ss);
+            if (lane == 0) red[wave][R] = ss;
+        }
+        __syncthreads();
     }
-    __syncthreads();
+    float sums[R + 1];
+#pragma unroll
+    for (int r = 0; r <= R; ++r) sums[r] = KW > 1 ? red[0][r] + red[1][r] + red[2][r] + red[3][r] : r < R ? __shfl(acc[0], (r & 3) * 16, 64) : ss;
     if (tid >= FPW) return;
-    auto row_sum = [&](int r) { return red[0][r] + red[1][r] + red[2][r] + red[3][r]; };
+    auto row_sum = [&](int r) { return r == 0 ? sums[0] : r == 1 ? sums[1] : r == 2 ? sums[2] : sums[3]; };
     const int n = feature(tid);
     if (n >= N) return;
     float sc = a.scale ? *a.scale : 1.0f;
-    if (a.norm_eps >= 0.f) sc = 1.0f / sqrtf(row_sum(R) / (float)K + a.norm_eps);
+    if (a.norm_eps >= 0.f) sc = 1.0f / sqrtf(sums[R] / (float)K + a.norm_eps);
     float val = row_sum(tid) * sc;
     if (SWIGLU) val = val / (1.0f + __expf(-val)) * (row_sum(FPW + tid) * sc);
     const T* bias = (const T*)sg.bias;
@@ -135,13 +145,20 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     Elem<T>::st((T*)sg.out + n, val);
 }
 
-// Pieces in flight per row: all of a wave's share where that is 7 or fewer (7 beats 4 by 3 % at k_in 14336 although fewer
+// Rows of up to 192 pieces of 16 bytes are a wave's own: dealt to four waves they leave some without any (128256 rows of bf16, us dealt / own: k_in 256
+// 38.5 / 15.6, 512 42.8 / 20.0, 1024 50.6 / 37.7, 1280 56.0 / 46.5).  Pieces in flight per row: all of a wave's share where that is 7 or fewer (7 beats 4 by 3 % at k_in 14336 although fewer
 // waves fit: one wait instead of two).
+constexpr int kGemvOwnPieces = 192;
+
 template <typename T, bool S>
 static void launch_gemv_u(const GemvArgs& a, dim3 grid, hipStream_t st) {
     const int pieces = (a.k / Elem<T>::kVec + 255) / 256;
-#define SLIM_GEMV(U) hipLaunchKernelGGL((gemv_kernel<T, S, U>), grid, dim3(256), 0, st, a)
-    if (pieces <= 2) SLIM_GEMV(2); else if (pieces > 4 && pieces <= 7) SLIM_GEMV(7); else SLIM_GEMV(4);
+#define SLIM_GEMV(U, KW) hipLaunchKernelGGL((gemv_kernel<T, S, U, KW>), grid, dim3(256), 0, st, a)
+    if (a.k / Elem<T>::kVec <= 128) SLIM_GEMV(2, 1);
+    else if (a.k / Elem<T>::kVec <= kGemvOwnPieces) SLIM_GEMV(3, 1);
+    else if (pieces <= 2) SLIM_GEMV(2, 4);
+    else if (pieces > 4 && pieces <= 7) SLIM_GEMV(7, 4);
+    else SLIM_GEMV(4, 4);
 #undef SLIM_GEMV
 }
 
@@ -149,6 +166,7 @@ static int launch_gemv_args(const GemvArgs& a, int dtype, hipStream_t st) {
     const int per = a.w_up ? kGemvRows / 2 : kGemvRows;
     long long wgs = 0;
     for (int s = 0; s < a.n_seg; ++s) wgs += ((long long)a.seg[s].n + per - 1) / per;
+    if (a.k / (dtype == SLIM_BF16 ? Elem<bf16_t>::kVec : Elem<float>::kVec) <= kGemvOwnPieces) wgs = (wgs + 3) / 4;
     const dim3 grid((unsigned)(wgs < kGemvGrid ? wgs : kGemvGrid), (unsigned)((wgs + kGemvGrid - 1) / kGemvGrid));
     if (dtype == SLIM_BF16) { if (a.w_up) launch_gemv_u<bf16_t, true>(a, grid, st); else launch_gemv_u<bf16_t, false>(a, grid, st); }
     else                    { if (a.w_up) launch_gemv_u<float, true>(a, grid, st);  else launch_gemv_u<float, false>(a, grid, st); }

@@ -436,10 +436,13 @@ def test_decode_attention_deals_out_ragged_groups(slim, n_prompt, block, n_slots
     test_decode_attention_over_active_slots_matches_oracle(slim, n_prompt, block, n_slots, n_active, n_resp, Hq, Hkv, dtype)
 
 
-# Pieces of 256 x 16 bytes of a row: one short of and one past the end of a workgroup's step and of a wave's, and of the pieces in flight.
+# Pieces of 256 x 16 bytes of a row: one short of and one past the end of a workgroup's step and of a wave's, and of the pieces in flight; rows of
+# up to 192 pieces of 16 bytes, which a wave has to itself, and the first that are shared.
 @pytest.mark.parametrize("n,k,dtype", [(5, 8, torch.bfloat16), (9, 504, torch.bfloat16), (6, 2040, torch.bfloat16), (7, 2056, torch.bfloat16),
                                        (3, 4104, torch.bfloat16), (4, 8200, torch.bfloat16), (2, 14336, torch.bfloat16), (3, 14344, torch.bfloat16),
-                                       (3, 16376, torch.bfloat16), (5, 4, torch.float32), (9, 1028, torch.float32), (2, 16376, torch.float32)])
+                                       (3, 16376, torch.bfloat16), (5, 4, torch.float32), (9, 1028, torch.float32), (2, 16376, torch.float32),
+                                       (17, 512, torch.bfloat16), (19, 520, torch.bfloat16), (16, 1024, torch.bfloat16), (21, 1032, torch.bfloat16),
+                                       (18, 1536, torch.bfloat16), (15, 1544, torch.bfloat16), (35, 768, torch.float32), (23, 516, torch.float32)])
 def test_gemv_at_the_edges_of_its_pieces(slim, n, k, dtype):
     test_gemv_all_epilogues(slim, n, k, dtype)
 
