@@ -1036,7 +1036,8 @@ static int launch_two_size(const bf16_t* A, int lda, const bf16_t* W0, const bf1
 //   FEW_B  128 x 128, 4 waves, 4 stages (128 KB)
 //   FEW_C  128 x  64, 4 waves, 3 stages  (72 KB, two per CU)
 //   FEW_D   64 x  64, 4 waves, 5 stages  (80 KB, two per CU)
-// Taken is the largest that still gives kFewWorkgroups workgroups, else FEW_D.  Measured with 4096 features and k_in 4096 (us):
+// Taken is the largest that still gives kFewWorkgroups workgroups, else FEW_D; FEW_A also where FEW_B would begin a second round
+// (residual, 3584 features, k_in 3584, 1290 rows: A (154) 46, B (308) 65; 2048 from 2048, 2049 rows: A (136) 28, B (272) 40).  Measured with 4096 features and k_in 4096 (us):
 // 1024 rows A (128 workgroups) 48, B (256) 37; 1280 rows A (160) 50, B (320) 60; with 1024 features: 512 rows C 23, D 17.6;
 // 2048 rows B (128) 38, C (256) 32, D (512) 43.
 enum FewShape { FEW_A, FEW_B, FEW_C, FEW_D };
@@ -1048,7 +1049,7 @@ static FewShape few_shape(int M, const int* n, int count, int splits) {
         for (int i = 0; i < count; ++i) t += (n[i] + bn - 1) / bn;
         return t * ((M + bm - 1) / bm) * splits;
     };
-    if (workgroups(256, 128) >= kFewWorkgroups) return FEW_A;
+    if (workgroups(256, 128) >= kFewWorkgroups || workgroups(128, 128) > cu_count()) return FEW_A;
     if (workgroups(128, 128) >= kFewWorkgroups) return FEW_B;
     if (workgroups(128, 64) >= kFewWorkgroups) return FEW_C;
     return FEW_D;

@@ -265,6 +265,7 @@ def test_linear_all_epilogues(slim, m, n, k, dtype):
 # One row past a tile's edge or short of it, last feature tile ragged, fewer k-tiles than LDS stages and one more.
 @pytest.mark.parametrize("m,n,k", [
     (1281, 4096, 256), (1279, 4104, 64),          # 256 x 128 tiles, 3 stages
+    (1153, 3584, 128), (2049, 2048, 64),          # the same, in place of more 128 x 128 tiles than CUs
     (769, 4096, 320), (641, 4040, 128),           # 128 x 128 tiles, 4 stages
     (321, 4104, 256), (319, 4096, 64),            # 128 x 64 tiles, 3 stages
     (65, 1032, 384), (63, 4096, 64),              # 64 x 64 tiles, 5 stages
