@@ -1059,10 +1059,14 @@ static FewShape few_shape(int M, const int* n, int count, int splits) {
 // features, k_in 14336, residual: 1511 rows 195 against 271 us, 2048 rows (2^23 outputs) 214 against 278, 2300 rows 355
 // against 302; k_in 4096: 1511 rows 53 against 58, 2048 rows 65 both.  Key projection (1024 features) with rotation and
 // scores: 4096 rows 53 against 58 us, 8192 rows 78 against 82.
-bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23); }
+// And only where their 256 x 128 tiles are no more than a round: k_in 4096, 5120 features, 1600 rows (260 tiles) 106 against 80, 1040 features, 7000 rows
+// (275) 101 against 79; 520 from 1024, 11000 rows (258) 30 against 24.
+bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23) && (m + 127ll) / 128 * ((n + 255ll) / 256) <= cu_count(); }
 
 // The most rows up to m that few_rows takes.
-int few_rows_most(int m, int n) { return (int)std::min<long long>(m, (1ll << 23) / n); }
+int few_rows_most(int m, int n) {
+    return (int)std::min<long long>({m, (1ll << 23) / n, cu_count() / ((n + 255ll) / 256) * 128});
+}
 
 template <int TW, int TA, int WGN, int WGM, int NS>
 static int launch_split_shape(const bf16_t* A, int lda, const SplitMats& mats, int M, int K, int splits, float* partial, hipStream_t st) {

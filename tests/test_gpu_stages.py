@@ -270,6 +270,7 @@ def test_linear_all_epilogues(slim, m, n, k, dtype):
     (321, 4104, 256), (319, 4096, 64),            # 128 x 64 tiles, 3 stages
     (65, 1032, 384), (63, 4096, 64),              # 64 x 64 tiles, 5 stages
     (2048, 4096, 64), (2049, 4096, 64),           # the largest launch of the few-row tiles and the first behind it
+    (32768, 104, 64), (32769, 104, 64),           # the same for narrow outputs: a round of 256 x 128 tiles and one more
 ])
 def test_few_row_projections(slim, m, n, k):
     """Plain, + bias and + residual (in place).  Products of bf16 numbers summed in float: the result is the exact one
