@@ -1197,9 +1197,14 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
     }
     if constexpr (EPI == EPI_SWIGLU) {
         // Up to 256 rows the launch streams the weights: 64-feature tiles keep more of it in flight (14336 features, us: 64 rows
-        // 66 -> 49, 128 rows 65 -> 54, 200 rows 85 -> 64; at 300 rows the two-size launch is ahead, 95 against 105).
+        // 66 -> 49, 128 rows 65 -> 54, 200 rows 85 -> 64; at 300 rows the two-size launch is ahead, 95 against 105).  A second round of
+        // them, one to a CU, costs more than it saves: with two stages two fit a CU, and the two-size launch takes more than 128 rows (18944 features: 64
+        // rows 61 -> 57, 200 rows 96 -> 82, 256 rows 102 -> 84).  From three rounds on it does not (36864 features, 200 rows 215 against 184).
+        const int tiles = (N + 63) / 64;
+        const bool second_round = tiles > cu_count() && tiles <= 2 * cu_count();
+        if (M <= 128 && second_round) return launch_bf16<1, 1, 2, 4, EPI, false, 2>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
         if (M <= 128) return launch_bf16<1, 1, 2, 4, EPI, false, 4>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-        if (M <= 256) return launch_bf16<1, 2, 2, 4, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+        if (M <= 256 && !second_round) return launch_bf16<1, 2, 2, 4, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
     } else if constexpr (EPI == EPI_ROPE) {
         if (M <= 128) return launch_bf16<4, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
     } else if (few_rows(M, N)) {

@@ -286,7 +286,8 @@ def test_few_row_projections(slim, m, n, k):
         assert ((got.double() - want).abs() <= bound).all(), name
 
 
-@pytest.mark.parametrize("m,n,k", [(128, 776, 320), (129, 776, 64), (256, 840, 192), (257, 264, 128), (3, 64, 64)])
+@pytest.mark.parametrize("m,n,k", [(128, 776, 320), (129, 776, 64), (256, 840, 192), (257, 264, 128), (3, 64, 64),
+                                   (70, 16384, 64), (128, 16392, 192), (200, 16392, 64), (100, 32776, 64), (130, 32776, 64)])      # one, two and three rounds
 def test_few_row_swiglu(slim, m, n, k):
     print(f"few rows swiglu m={m} n={n} k={k}", flush=True)
     bf = torch.bfloat16
