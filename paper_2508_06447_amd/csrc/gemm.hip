@@ -977,14 +977,16 @@ static int cu_count() {
 
 // Token tiles per group of a launch's large tiles: as many as make one round of workgroups, so that all XCDs work on the same few
 // activation panels and each on its own weight panels (with one run of tiles per XCD over the whole launch they work on eight distant
-// row bands).  Only where the group fills the chip to 85 % and divides evenly over the XCDs; 0: one group.
-// From 8 rounds on: SwiGLU projection, 14336 features (112 tiles, groups of 2 x 112): 6000 rows 1075 -> 1044 us, 9856 1804 -> 1720, 20000 3690 ->
-// 3431, 26240 4733 -> 4488; Query + Value (20 tiles, 12 x 20): 26240 rows 936 -> 847.  With fewer rounds it is 3 % faster alone (4096 rows 711 ->
-// 689) and 0.3 to 0.5 % slower in a layer, whose rows are still in the caches.  18944 features (148 tiles) have no such group: with 2 x 148
+// row bands).  0: one group.
+// Only where the group fills the chip to 85 %, divides evenly over the XCDs and leaves some CUs: groups of exactly a round lose (us without / with:
+// 8192 features from 1024, 27136 rows 402 / 439; SwiGLU, 8192 from 2048, 16384 rows 885 / 922; 4096 from 4096, 40960 rows 1059 / 1093).
+// From 8 rounds of large tiles on: SwiGLU projection, 14336 features (112 tiles, groups of 2 x 112): 6000 rows 1075 -> 1044 us, 9856 1804 -> 1720, 20000 3690 ->
+// 3431, 26240 4733 -> 4488; Query + Value (20 tiles, 12 x 20; 26240 rows are fewer rounds): 32768 rows 1142 -> 1069, 40960 1410 -> 1312.  With fewer
+// rounds it is 3 % faster alone (SwiGLU, 4096 rows 711 -> 689) and 0.3 to 0.5 % slower in a layer, whose rows are still in the caches.  18944 features (148 tiles) have no such group: with 2 x 148
 // between 8 % faster and 4 % slower.  Residual and RoPE launches measure the same either way.
 static int rounds_of(int big_tiles_m, int tiles_n) {
     const int rm = cu_count() / tiles_n;
-    return rm >= 2 && (long long)big_tiles_m * tiles_n >= 8ll * cu_count() && rm * tiles_n * 100 >= cu_count() * 85 && rm * tiles_n % 8 == 0 ? rm : 0;
+    return rm >= 2 && (long long)big_tiles_m * tiles_n >= 8ll * cu_count() && rm * tiles_n * 100 >= cu_count() * 85 && rm * tiles_n < cu_count() && rm * tiles_n % 8 == 0 ? rm : 0;
 }
 
 template <int EPI>

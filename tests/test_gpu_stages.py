@@ -302,6 +302,19 @@ def test_swiglu_in_groups_of_tiles(slim, m, n, k):
     test_few_row_swiglu(slim, m, n, k)
 
 
+# The same for two matrices in one launch, in groups of 12 x (16 + 4).
+@pytest.mark.parametrize("m,bias", [(30000, False), (32900, True)])
+def test_linear_pair_in_groups_of_tiles(slim, m, bias):
+    print(f"pair in groups m={m} bias={bias}", flush=True)
+    bf, k = torch.bfloat16, 64
+    a = dev(rand((m, k), bf, 1))
+    w, b = ([dev(rand(s, bf, 2 + i)) for i, s in enumerate(shapes)] for shapes in (((4096, k), (1024, k)), ((4096,), (1024,))))
+    got = slim.slim_linear_pair(a, w[0], w[1], *(b if bias else (None, None)))
+    for g, wi, bi in zip(got, w, b):
+        want, size = a.double() @ wi.double().T + (bi.double() if bias else 0.0), a.double().abs() @ wi.double().abs().T
+        assert ((g.double() - want).abs() <= 2.0 ** -8 * want.abs() + k * 2.0 ** -24 * size + 1e-30).all()
+
+
 # Row counts whose last 256-token tile is ragged and kept as one (a round of tiles saved): one row, half of it, all but a few.
 @pytest.mark.parametrize("m,n,k", [(385, 14336, 64), (400, 14336, 128), (1000, 14336, 64), (1511, 14336, 64)])
 def test_swiglu_with_a_ragged_large_tile(slim, m, n, k):
