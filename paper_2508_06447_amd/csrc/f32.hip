@@ -22,6 +22,21 @@ __device__ __forceinline__ f32x4 load4(const float* p, int left) {
     return v;
 }
 
+// p[0..N-1] = v, of which only `left` are there.
+template <int N> __device__ __forceinline__ void store_some(float* p, const float (&v)[N], int left) {
+    typedef float any __attribute__((ext_vector_type(N == 1 ? 2 : N), aligned(4)));
+    if (N > 1 && left >= N) {
+        any x;
+#pragma unroll
+        for (int e = 0; e < N; ++e) x[e] = v[e];
+        *reinterpret_cast<any*>(p) = x;
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+            if (e < left) p[e] = v[e];
+    }
+}
+
 // -------------------------------------------------------------------------------------------------
 // Projections.  The float workload is small (512 rows, 128 to 688 features): what a launch costs is the chain load -> sum
 // -> store of one workgroup, not the rate of the chip, so a workgroup takes 32 rows x 32 features only and its eight waves
@@ -177,8 +192,8 @@ __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
         float* out = sg.out + (size_t)row * sg.ldo;
         if (sg.mode == F32_SWIGLU) {
 #pragma unroll
-            for (int e = 0; e < EPT; ++e)
-                if (f0 + c + e < sg.n) out[f0 + c + e] = v[0][e] / (1.0f + expf(-v[0][e])) * v[1][e];
+            for (int e = 0; e < EPT; ++e) v[0][e] = v[0][e] / (1.0f + expf(-v[0][e])) * v[1][e];
+            store_some<EPT>(out + f0 + c, v[0], sg.n - f0 - c);
             continue;
         }
         if (sg.bias) {
@@ -201,29 +216,38 @@ __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
             }
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i) {
+            const int f = (i ? f1 : f0) + c;
+            if (sg.residual) {
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const int f = (i ? f1 : f0) + c + e;
-                if (f < sg.n) out[f] = sg.residual ? v[i][e] + sg.residual[(size_t)row * sg.ldo + f] : v[i][e];
+                for (int e = 0; e < EPT; ++e)
+                    if (f + e < sg.n) v[i][e] += sg.residual[(size_t)row * sg.ldo + f + e];
             }
+            store_some<EPT>(out + f, v[i], sg.n - f);
+        }
     }
 }
 
 // Work items of a launch stay below 2^32: what is larger goes one segment, and then so many features and so many rows, at a time.
 constexpr long long kF32TilesMax = 1ll << 23;
 constexpr int kF32FeaturesMax = 1 << 27;                 // (2^23 tiles of 16; whole heads)
-// From how many tiles of 32 rows on tiles of 64 are taken: twice the flops per byte read, half the workgroups (us, tall
+// From how many tiles of 32 rows on tiles of 64 are taken (of more than 32 rows): twice the flops per byte read, half the workgroups (us, tall
 // and not: 2048 x 2048 from 2048 features 241 / 293, 2048 x 1024 from 512, 2048 tiles, 45 / 53; 1024 tiles fill the chip with 32 rows only).
 // Four waves there: with eight the sums of 64 rows do not fit the LDS.
+// Reductions of up to 64 (tall: 32) go to four (two) waves of one chunk each; more have none (us, before and so: 100000 x 16 from 16 16.6 / 5.9, 8192 x 512 from
+// 64 23 / 13, 2000 x 1024 from 64 17.8 / 8.5; 16 x 100000 from 64, which were tall, 30 / 9.9).
 constexpr long long kF32TallTiles = 2048;
 
 int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain, float eps, int head_dim, float theta, hipStream_t st) {
     F32LinearArgs p{};
     auto tiles_n = [](const F32Seg& g) { return g.mode == F32_SWIGLU ? (g.n + 15ll) / 16 : (g.n + 31ll) / 32; };
     long long small = 0, tiles = 0;
-    for (int s = 0; s < count; ++s) small += (segs[s].m + 31ll) / 32 * tiles_n(segs[s]);
-    const bool tall = small >= kF32TallTiles;
+    int m_most = 0;
+    for (int s = 0; s < count; ++s) {
+        small += (segs[s].m + 31ll) / 32 * tiles_n(segs[s]);
+        m_most = std::max(m_most, segs[s].m);
+    }
+    const bool tall = small >= kF32TallTiles && m_most > 32;
     const int rows = tall ? 64 : 32;
     for (int s = 0; s < 3; ++s) {
         if (s < count) {
@@ -265,7 +289,10 @@ int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain
     p.eps = eps;
     p.head_dim = head_dim;
     for (int i = 0; i < head_dim / 2; ++i) p.inv_freq[i] = pow((double)theta, -2.0 * (double)i / (double)head_dim);
-    if (tall) hipLaunchKernelGGL((f32_linear_kernel<4, 4, 2>), dim3((unsigned)tiles), dim3(256), 0, st, p);
+    if (tall && k_in <= 32) hipLaunchKernelGGL((f32_linear_kernel<4, 2, 1>), dim3((unsigned)tiles), dim3(128), 0, st, p);
+    else if (tall && k_in <= 64) hipLaunchKernelGGL((f32_linear_kernel<4, 4, 1>), dim3((unsigned)tiles), dim3(256), 0, st, p);
+    else if (tall) hipLaunchKernelGGL((f32_linear_kernel<4, 4, 2>), dim3((unsigned)tiles), dim3(256), 0, st, p);
+    else if (k_in <= 64) hipLaunchKernelGGL((f32_linear_kernel<2, 4, 1>), dim3((unsigned)tiles), dim3(256), 0, st, p);
     else hipLaunchKernelGGL((f32_linear_kernel<2, 8, 2>), dim3((unsigned)tiles), dim3(512), 0, st, p);
     return check_launch();
 }

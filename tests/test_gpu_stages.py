@@ -550,10 +550,12 @@ def test_rmsnorm_and_rope_in_one_projection(slim):
     np.testing.assert_allclose(f64(got), want, rtol=2.0 ** -8, atol=2.0 ** -8 * np.abs(want).max())
 
 
-# Tiles of 32 rows and 32 (SwiGLU: 16) features, the reduction in 16-deep chunks dealt to four waves: one short of and one
-# past each, fewer chunks than waves, reductions that are no multiple of 4, rows at any 4-byte address.
+# Tiles of 32 rows and 32 (SwiGLU: 16) features, the reduction in 16-deep chunks dealt to eight waves (up to 64: four): one short of and one
+# past each, fewer chunks than waves, reductions that are no multiple of 4, rows at any 4-byte address; from 2048 tiles on tiles of 64 rows and four waves
+# (up to 32: two).
 @pytest.mark.parametrize("m,n,k,shift", [(1, 1, 1, 0), (31, 33, 15, 1), (32, 32, 16, 0), (33, 31, 17, 3), (65, 47, 63, 2), (64, 16, 65, 0),
-                                         (5, 130, 259, 1), (200, 17, 1030, 0)])
+                                         (5, 130, 259, 1), (200, 17, 1030, 0), (2049, 1025, 67, 1), (1025, 1030, 130, 0), (1057, 1999, 64, 3),
+                                         (2100, 1000, 33, 2), (4097, 530, 32, 0), (2065, 1003, 13, 1), (31, 65600, 64, 0)])
 def test_float32_projections(slim, m, n, k, shift):
     """Float sums of k products: each within k roundings (2^-24) of the sum of the products' sizes."""
     print(f"float32 linear m={m} n={n} k={k} shift={shift}", flush=True)
