@@ -150,6 +150,8 @@ def test_cfg1_keep_all_equals_unpruned_layer(slim):
     (200, 130, 3, 3, 64, 70, 32, 0.4, True),     # a reduction of 130: the last chunk holds two elements
     (257, 64, 2, 1, 128, 96, 300, 0.3, False),   # window longer than the sequence
     (100, 20, 4, 2, 32, 15, 8, 1.0, False),      # nothing dropped
+    (2100, 130, 16, 4, 64, 600, 32, 1.0, True),  # Query + Value and gate/up in tiles of 64 rows
+    (2100, 48, 32, 32, 64, 40, 32, 0.6, False),  # Keys and the window's Queries in tiles of 64 rows
 ])
 def test_float32_layer_shapes(slim, seq, hidden, heads, kv_heads, d, ffn, window, keep, bias, placement):
     """Float32 layers with gains that are not 1, against the oracle in full."""
@@ -281,7 +283,9 @@ def test_degenerate_small_sequences(slim, seq, block, window, keep, fold):
 @pytest.mark.parametrize("seq,keep,bias", [
     (65, 1.0, False), (128, 1.0, True), (129, 1.0, False),      # Query, Key and Value in one launch: 4 splits, 4, 1
     (300, 0.4, True),           # 128 kept rows of 300: Key with 1 split, Query + Value with 4, down with 8
-    (1024, 1.0, False), (1025, 1.0, True),                      # down projection: 4 splits, none
+    (512, 1.0, True), (513, 1.0, False),                        # down projection: 4 splits of few-row tiles, 8 of large ones
+    (1024, 1.0, False), (1025, 1.0, True),                      # 8 and 6 splits of large tiles
+    (3584, 1.0, False), (3585, 1.0, True),                      # 2 splits of large tiles, none
 ])
 def test_split_projections_of_few_rows(slim, seq, keep, bias):
     """The projections that go through float partial sums, at the edges of the row counts at which the number of splits
