@@ -17,14 +17,13 @@
 // projection) and few rows use C++ tiles with the same LDS layout and pipeline; a
 // register-staged kernel with k predicates covers ragged k_in.
 #include "slim_common.h"
+#include "tile_plan.h"
 
 #include <algorithm>
 #include <map>
 #include <mutex>
-#include <queue>
 #include <tuple>
 #include <type_traits>
-#include <vector>
 
 namespace slim {
 
@@ -880,64 +879,17 @@ static int launch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t*
     return check_launch();
 }
 
-// How many 256-token tiles to run before the 128-token tiles.  Workgroups are handed to free CUs in id
-// order, which is list scheduling; it is simulated for each candidate and the shortest makespan wins.
-// The model, fitted to sweeps of the split on the layer's shapes:
-//   a 128-token tile costs small_cost of a 256-token one (small_tile_cost);
-//   CU speeds are spread over +-8 % (tiles do not run equally fast on all CUs, which is what makes a
-//   fine-grained tail pay even when the large tiles fill whole rounds);
-//   for the 8-wave tiles only (the sweeps of the 4-wave tiles show neither effect):
-//     +1 % / +3 % when the per-XCD run of large tiles is not a multiple of 8 / of 4 tiles (the run then
-//     straddles columns of the band walk and shares fewer operand panels in that XCD's L2);
-//     +5 % for fewer than 4 token-tiles of small tiles (too few rows to share a weight panel between the
-//     workgroups that run together);
-//   a ragged last tile of 256 is taken only for a gain of 3 % or more: it saves a round (SwiGLU, 14336 features: 400 rows 138 -> 102 us,
-//     1000 rows 224 -> 200, 1511 rows 330 -> 296; Query + Value of 2983 rows 127 -> 97), but where the model sees a tie the launch with
-//     128-token tiles is the faster one (SwiGLU 300 rows 88 against 102, down projection of 2983 rows 293 against 316).
-// The result is a pure function of its arguments; the cache only remembers it (guarded, never invalidated).
-// makespan: of the plan, in times of a 256-token tile.
+// plan_tiles, remembered: the result is a pure function of its arguments (guarded, never invalidated).
+// makespan_out: of the plan, in times of a 256-token tile.
 static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool eight_waves, double* makespan_out = nullptr) {
     static std::mutex mu;
     static std::map<std::tuple<int, int, int, bool>, std::pair<int, double>> cache;
     std::lock_guard<std::mutex> lock(mu);
     const auto key = std::make_tuple(M, tiles_n, (int)(small_cost * 1000), eight_waves);
-    const auto hit = cache.find(key);
-    if (hit != cache.end()) {
-        if (makespan_out) *makespan_out = hit->second.second;
-        return hit->second.first;
-    }
-    std::vector<double> speed(n_cu);
-    for (int c = 0; c < n_cu; ++c) speed[c] = 1.0 + 0.08 * ((double)((c * 97) % n_cu) / (n_cu - 1) * 2.0 - 1.0);
-    const int mb_floor = M / 256, mb_max = (M + 255) / 256;
-    int best_mb = mb_floor;
-    double best = 1e300, ragged = 1e300;
-    typedef std::pair<double, int> Slot;                 // (time the CU becomes free, CU)
-    for (int mb = mb_max; mb >= 0 && mb >= mb_max - 24; --mb) {
-        const int small_tiles_m = std::max(0, M - mb * 256 + 127) / 128;
-        const long nb = (long)mb * tiles_n, ns = (long)small_tiles_m * tiles_n;
-        std::priority_queue<Slot, std::vector<Slot>, std::greater<Slot>> free_at;
-        for (int c = 0; c < n_cu; ++c) free_at.push(Slot(0.0, c));
-        double makespan = 0.0;
-        for (long i = 0; i < nb + ns; ++i) {
-            Slot s = free_at.top();
-            free_at.pop();
-            s.first += speed[s.second] * (i < nb ? 1.0 : small_cost);
-            if (s.first > makespan) makespan = s.first;
-            free_at.push(s);
-        }
-        if (eight_waves && nb > 0 && nb % 8 == 0) {
-            const long run = nb / 8;
-            if (run % 8 != 0) makespan *= 1.01;
-            if (run % 4 != 0) makespan *= 1.03;
-        }
-        if (eight_waves && small_tiles_m > 0 && small_tiles_m < 4 && mb > 0) makespan *= 1.05;
-        if (mb > mb_floor) ragged = makespan * 1.03;
-        else if (makespan < best) { best = makespan; best_mb = mb; }
-    }
-    if (ragged < best) { best = ragged; best_mb = mb_max; }
-    cache[key] = std::make_pair(best_mb, best);
-    if (makespan_out) *makespan_out = best;
-    return best_mb;
+    auto hit = cache.find(key);
+    if (hit == cache.end()) hit = cache.emplace(key, plan_tiles(M, tiles_n, n_cu, small_cost, eight_waves)).first;
+    if (makespan_out) *makespan_out = hit->second.second;
+    return hit->second.first;
 }
 
 // Which tile the residual epilogue runs in.  The 4-wave tile takes the residual tile in as MFMA fragments (16-byte loads
