@@ -123,15 +123,20 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
         }
         __syncthreads();
     }
-    float sums[R + 1];
+    float own[R];                                        // KW 1: the rows' sums, in every lane
+    if (KW == 1) {
 #pragma unroll
-    for (int r = 0; r <= R; ++r) sums[r] = KW > 1 ? red[0][r] + red[1][r] + red[2][r] + red[3][r] : r < R ? __shfl(acc[0], (r & 3) * 16, 64) : ss;
+        for (int r = 0; r < R; ++r) own[r] = __shfl(acc[0], r * 16, 64);
+    }
     if (tid >= FPW) return;
-    auto row_sum = [&](int r) { return r == 0 ? sums[0] : r == 1 ? sums[1] : r == 2 ? sums[2] : sums[3]; };
+    auto row_sum = [&](int r) {
+        if (KW == 1) return r == 0 ? own[0] : r == 1 ? own[1] : r == 2 ? own[2] : own[3];
+        return red[0][r] + red[1][r] + red[2][r] + red[3][r];
+    };
     const int n = feature(tid);
     if (n >= N) return;
     float sc = a.scale ? *a.scale : 1.0f;
-    if (a.norm_eps >= 0.f) sc = 1.0f / sqrtf(sums[R] / (float)K + a.norm_eps);
+    if (a.norm_eps >= 0.f) sc = 1.0f / sqrtf((KW == 1 ? ss : row_sum(R)) / (float)K + a.norm_eps);
     float val = row_sum(tid) * sc;
     if (SWIGLU) val = val / (1.0f + __expf(-val)) * (row_sum(FPW + tid) * sc);
     const T* bias = (const T*)sg.bias;
