@@ -13,9 +13,9 @@
 // from LDS feeds four MFMAs.  Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no
 // VGPR staging), double-buffered; MFMA fragments are read one k-step ahead of their use, across k-tiles too.  The
 // k-loop is generated assembly (gen_gemm_asm.py -> gemm_bf16_mainloops.inc): with a lone wave per SIMD the order of
-// MFMA, LDS and tile-load instructions inside the wave is the schedule.  The residual epilogue (down
-// projection) and few rows use C++ tiles with the same LDS layout and pipeline; a
-// register-staged kernel with k predicates covers ragged k_in.
+// MFMA, LDS and tile-load instructions inside the wave is the schedule.  The residual of the output and down projections comes in
+// as MFMA fragments inside that loop.  Few rows, and residuals that the loop does not take (residual_in_four_waves), use C++ tiles with the
+// same LDS layout and pipeline; a register-staged kernel with k predicates covers ragged k_in.
 #include "slim_common.h"
 #include "tile_plan.h"
 
@@ -29,7 +29,7 @@ namespace slim {
 
 enum { EPI_PLAIN = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_BIAS = 3, EPI_ROPE = 4, EPI_PARTIAL = 5 };
 // EPI_BIAS: R is a bias vector [N].  EPI_ROPE: R is a bias vector or null, the rest comes in a EpiExtra.
-// EPI_PARTIAL: the accumulators go to a float buffer as they are (EpiExtra::partial); split_gemm_kernel only.
+// EPI_PARTIAL: the accumulators go to a float buffer as they are (EpiExtra::partial); split_gemm_kernel and split_gemm_large_kernel only.
 
 // Extra operands: of the RoPE epilogue (heads of 128 features, one head per wave tile), of the fused RMSNorm, and
 // of a second projection of the same rows carried by the same launch.
@@ -335,6 +335,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
                                           int N, int K, int KT, int m0, int n0, unsigned char* lds, const EpiExtra& re) {
     constexpr int WV = WGN * WGM;                        // waves
     static_assert(WV == 8 || WV == 4, "4 or 8 waves");
+    static_assert(NS >= 2 && NS <= 5, "the k-loop is written out for up to 5 stages");
     static_assert(EPI != EPI_ROPE || TW == 4, "the RoPE epilogue needs one 128-wide head per wave");
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
     constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM, WROWS = BN * NW;
@@ -470,10 +471,6 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
         }
         if constexpr (NS >= 5) {
             k_tile(kt, std::integral_constant<int, 4 % NS>{});
-            if (++kt >= KT) break;
-        }
-        if constexpr (NS >= 6) {
-            k_tile(kt, std::integral_constant<int, 5 % NS>{});
             if (++kt >= KT) break;
         }
     }
@@ -680,10 +677,9 @@ gemm_bf16_qkv_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __rest
     else gemm_tile4<4, S::TA_SMALL, EPI>(A, lda, W0, nullptr, R, C, ldo, M, N, K, m0, tn * S::BN, lds, re);
 }
 
-// The residual epilogue reads a second tile through LDS; with a lone wave per SIMD nothing hides that pass, and the
-// launch measured slower than with the 8-wave tile (two waves per SIMD: one wave's epilogue steps overlap the
-// other's).  So output and down projection keep 8 waves: wave tiles of 64 tokens x 128 features (large) and
-// 64 x 64 (small), the same workgroup tiles as above.
+// Residual projections that the 4-wave loop does not take (residual_in_four_waves).  Their epilogue reads a second tile through LDS; with
+// a lone wave per SIMD nothing hides that pass, with two one wave's epilogue steps overlap the other's.  So 8 waves: wave tiles of 64
+// tokens x 128 features (large) and 64 x 64 (small), the same workgroup tiles as above.
 __global__ void __launch_bounds__(512)
 gemm_bf16_two_size_residual_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0, const bf16_t* R,
                                    bf16_t* C, int ldo, int M, int N, int K, int big_tiles_m, int small_tiles_m,
