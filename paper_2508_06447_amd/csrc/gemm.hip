@@ -1088,6 +1088,14 @@ static int residual_round_rows(const void* R, int N, int K, int ldo) {
 // Up to 512 rows the few-row tiles: 1 / 2 / 4 / 8 splits of 14336 take 73 / 43 / 39 / 38 us for 128 rows, 101 / 75 / 67 / 73 for 300, 106 / 82 /
 // 79 / 90 for 512.  Large tiles: one round of workgroups; or 3 splits that make two full ones (2500 rows 274 / 278, 3072 rows of 18944 363 / 434).  No gain is left at 113
 // tiles and more (2 splits: 1904 rows 199 / 202, 2300 rows of 18944 286 / 276).
+static int large_splits(long long tiles_m, int n) {      // for so many 256-row tiles; 1: none
+    const long long tiles = tiles_m * ((n + 255) / 256), cu = cu_count();
+    long long s = 1;
+    if (tiles * 16 <= 7 * cu) s = std::min<long long>(8, cu / tiles);
+    else if (3 * tiles <= 2 * cu && 3 * tiles * 100 >= 184 * cu) s = 3;
+    return 2 * tiles * s < cu ? 1 : (int)s;              // (narrow outputs leave the large tiles' launch half empty)
+}
+
 ResidualCut residual_cut(int m, int n, int k_in) {
     ResidualCut c{0, 1, false};
     if (k_in < 8192 || k_in % BK != 0 || k_in >= (1 << 23) || n % 4 != 0) return c;
@@ -1096,35 +1104,33 @@ ResidualCut residual_cut(int m, int n, int k_in) {
     const int round = residual_round_rows(nullptr, n, k_in, n);
     const int whole = round && m > round ? m / round * round : 0, tail = m - whole;
     if (tail <= 128) return c;
-    const long long tiles = (long long)((tail + 255) / 256) * ((n + 255) / 256);
-    const int cu = cu_count();
-    int s = 1;
-    if (tiles * 16 <= 7ll * cu) s = (int)std::min<long long>(8, cu / tiles);
-    else if (3 * tiles <= 2ll * cu && 3 * tiles * 100 >= 184ll * cu) s = 3;
-    if (s < 2 || 2 * tiles * s < cu) return c;           // (narrow outputs leave the large tiles' launch half empty)
+    const int s = large_splits((tail + 255) / 256, n);
+    if (s < 2) return c;
     c.whole = whole;
     c.splits = s;
     c.large = true;
     return c;
 }
 
-// The most floats that residual_cut has its caller keep for any row count up to m.  The splits change only behind 128 rows, the last
-// few_rows takes, and from one count of 256-row tiles to the next; behind the second round, or tiles for three splits, nothing is new.
+// The most floats that residual_cut has its caller keep for any row count up to m.  Splits change only behind 128 rows, behind the last that
+// few_rows takes, and from one count of 256-row tiles to the next; behind whole rounds the tails of one come back, from 129 rows on.
 size_t residual_cut_partial_floats(int m, int n, int k_in) {
-    size_t most = 0;
-    auto look = [&](int rows) {
+    size_t most = 0;                                     // rows times splits
+    for (int rows : {128, 512, 768, few_rows_most(1024, n)}) {
         rows = std::min(rows, m);
         const ResidualCut c = residual_cut(rows, n, k_in);
-        if (c.splits > 1) most = std::max(most, (size_t)c.splits * (rows - c.whole) * n);
-    };
-    const int round = residual_round_rows(nullptr, n, k_in, n), last = round ? 2 * round : 256 * (2 * cu_count() / (3 * ((n + 255) / 256)));
-    look(128);
-    look(few_rows_most(1024, n));
-    for (int rows = 256; rows <= std::max(last, 1024); rows += 256) {
-        look(rows);
-        if (rows >= m) break;
+        if (c.splits > 1 && !c.large) most = std::max(most, (size_t)c.splits * rows);
     }
-    return most;
+    if (m <= 512 || residual_cut(128, n, k_in).splits < 2) return most * n;
+    const int round = residual_round_rows(nullptr, n, k_in, n), tiles_n = (n + 255) / 256;
+    const int last = round ? round / 256 : 2 * cu_count() / (3 * tiles_n);   // (more tiles have no splits)
+    for (int t = 1; t <= last && 256 * (t - 1) < m; ++t) {
+        const int first = std::min(256 * t, m), later = round ? std::min(256 * t, m - round) : 0;
+        const int rows = std::max(first > 512 ? first : 0, later > std::max(128, 256 * (t - 1)) ? later : 0);
+        const int s = rows ? large_splits(t, n) : 1;
+        if (s > 1) most = std::max(most, (size_t)s * rows);
+    }
+    return most * n;
 }
 
 template <int EPI>
