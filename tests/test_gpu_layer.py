@@ -295,6 +295,30 @@ def test_split_projections_of_few_rows(slim, seq, keep, bias):
     check_layer(slim, wl, np.float64, label=f"few rows seq {seq} keep {keep} bias {bias}", fold=True, score_scaled=True)
 
 
+@pytest.mark.parametrize("hidden,seq,keep,placement", [
+    (2048, 1, 1.0, 0), (2048, 65, 1.0, 0), (2048, 128, 1.0, 0), (2048, 512, 1.0, 0), (2048, 513, 1.0, 0), (2048, 3584, 1.0, 0),
+    (2048, 300, 0.4, 0), (2048, 1500, 0.5, 0), (2048, 1500, 0.5, 1), (4096, 2560, 1.0, 0), (4096, 5376, 1.0, 0), (4096, 4000, 0.6, 1),
+])
+def test_partial_sums_share_the_workspace_with_nothing_alive(slim, hidden, seq, keep, placement):
+    """A workspace of exactly the size asked for: results do not depend on what it holds, and nothing is written behind it."""
+    print(f"workspace hidden {hidden} seq {seq} keep {keep} placement {placement}", flush=True)
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, keep_ratio=keep, hidden=hidden, n_q_heads=6, n_kv_heads=2, ffn=8256, planted=max(1, seq // 50))
+    x, w = inputs.hidden_states(wl).cuda(), {k: v.cuda() for k, v in inputs.layer_weights(wl).items() if not k.startswith("g_")}
+    shape = slim.make_shape(wl.hidden, wl.n_q_heads, wl.n_kv_heads, wl.head_dim, wl.ffn, wl.block, wl.unit, wl.window, x.dtype, wl.rope_theta, wl.rms_eps,
+                            3, 0, placement)
+    size = slim.pruned_layer_workspace_bytes(shape, seq, wl.n_keep)
+    buf = torch.empty(size + 4096, dtype=torch.uint8, device="cuda")
+    seen = []
+    for fill in (0, 255, 0x7f):                           # zeros, NaN, 3.4e38
+        buf.fill_(fill)
+        res = slim.slim_pruned_layer(shape, w, x, None, wl.n_keep, workspace=buf[:size])
+        assert (buf[size:] == fill).all()
+        seen.append({k: v.clone() for k, v in res.items() if v is not None})
+    for other in seen[1:]:
+        assert all(torch.equal(seen[0][k], other[k]) for k in seen[0])
+    assert torch.isfinite(seen[0]["x"].float()).all()
+
+
 def test_reduced_qwen_shaped_layer_full_output(slim):
     """Second model family (28 query / 4 kv heads, hidden 3584, FFN 18944, Q/K/V biases, theta 1e6)."""
     wl = inputs.scaled(inputs.WORKLOADS["cfg6"], seq=1000, x_kind="planted", planted=10)
