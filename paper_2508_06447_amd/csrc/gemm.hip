@@ -4,14 +4,16 @@
 // SwiGLU (two weight matrices, silu(gate) * up), and RoPE (+ bias, + per-token score partials) for the
 // Query/Key projections of 128-wide heads.
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16, fp32 accumulation.  The weight tile is the MFMA "A" operand
+// bf16 path: MFMA with fp32 accumulation, v_mfma_f32_16x16x32_bf16 in the main path (it runs against the power limit, and this
+// instruction takes less of it: see the generator) and 32x32x16 in the few-row and ragged kernels.  The weight tile is the MFMA "A" operand
 // and the activation tile the "B" operand, so a lane ends up with 4 consecutive output features of
 // one token and stores them as one 8-byte vector.
 //
 // Main path (k_in a multiple of 64, many rows): 4 waves per workgroup, one per SIMD, 256x256 output tile
 // (128 features x 2 matrices x 256 tokens for SwiGLU), each wave 128 x 128 of it, so that every MFMA fragment read
-// from LDS feeds four MFMAs.  Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no
-// VGPR staging), double-buffered; MFMA fragments are read one k-step ahead of their use, across k-tiles too.  The
+// from LDS feeds eight MFMAs.  Measured (us, 32x32x16 -> 16x16x32 loop): SwiGLU 9856 x 14336 from 4096 1705 -> 1540 (1.36 -> 1.50
+// PFLOP/s), its down projection 903 -> 839, 8192^3 775 -> 708 (1.56 PFLOP/s), Keys of 32768 rows with rotation and scores 235 -> 216.
+// Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no VGPR staging), double-buffered; MFMA fragments are read one k-step ahead of their use, across k-tiles too.  The
 // k-loop is generated assembly (gen_gemm_asm.py -> gemm_bf16_mainloops.inc): with a lone wave per SIMD the order of
 // MFMA, LDS and tile-load instructions inside the wave is the schedule.  The residual of the output and down projections comes in
 // as MFMA fragments inside that loop.  Few rows, and residuals that the loop does not take (residual_in_four_waves), use C++ tiles with the
@@ -64,31 +66,36 @@ __device__ __forceinline__ int lds_off(int r, int c) { return (r * 8 + (c ^ swz(
 #include "gemm_bf16_mainloops.inc"
 #pragma clang diagnostic pop
 
-// Epilogue shared by both bf16 kernels.  acc[w][i][j][v] is out[token m][feature n] with
-//   m = mw + j*32 + l32,   n = nw + i*32 + 8*(v/4) + 4*hh + (v%4)      (mw, nw: the wave's origin)
-template <int TW, int TA, int EPI>
-__device__ __forceinline__ void store_tile(f32x16 (&acc)[EPI == EPI_SWIGLU ? 2 : 1][TW][TA], const bf16_t* R,
-                                           bf16_t* C, int ldo, int M, int N, int mw, int nw, int l32, int hh) {
-    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
+// Accumulators of a wave tile of 32 TW features x 32 TA tokens, as MFMA tiles of T x T (T = 16 in the generated k-loops, 32 in the others):
+// acc[w][i][j][4 * vg + e] is out[token m][feature n] with
+//   m = mw + j*T + (lane % T),   n = nw + i*T + 8*vg + 4*(lane / T) + e      (mw, nw: the wave's origin)
+template <int T> struct MfmaTile;
+template <> struct MfmaTile<16> { typedef f32x4 Acc; static constexpr int kGroups = 1; };
+template <> struct MfmaTile<32> { typedef f32x16 Acc; static constexpr int kGroups = 4; };
+
+template <int T, int TW, int TA, int EPI>
+__device__ __forceinline__ void store_tile(typename MfmaTile<T>::Acc (&acc)[EPI == EPI_SWIGLU ? 2 : 1][TW * 32 / T][TA * 32 / T], const bf16_t* R,
+                                           bf16_t* C, int ldo, int M, int N, int mw, int nw, int lane, const float (&inv)[TA * 32 / T]) {
+    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1, NI = TW * 32 / T, NJ = TA * 32 / T, VG = MfmaTile<T>::kGroups;
     const bool vec_ok = (N % 4 == 0) && (ldo % 4 == 0);
 #pragma unroll
-    for (int j = 0; j < TA; ++j) {
-        const int m = mw + j * 32 + l32;
+    for (int j = 0; j < NJ; ++j) {
+        const int m = mw + j * T + (lane & (T - 1));
         if (m >= M) continue;
 #pragma unroll
-        for (int i = 0; i < TW; ++i) {
+        for (int i = 0; i < NI; ++i) {
 #pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                const int n = nw + i * 32 + 8 * vg + 4 * hh;
+            for (int vg = 0; vg < VG; ++vg) {
+                const int n = nw + i * T + 8 * vg + 4 * (lane / T);
                 if (n >= N) continue;
                 float o[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     if (EPI == EPI_SWIGLU) {
-                        const float g = acc[0][i][j][vg * 4 + e], u = acc[NW - 1][i][j][vg * 4 + e];
+                        const float g = acc[0][i][j][vg * 4 + e] * inv[j], u = acc[NW - 1][i][j][vg * 4 + e] * inv[j];
                         o[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;   // v_rcp_f32: 1 ulp, the result is rounded to bf16
                     } else {
-                        o[e] = acc[0][i][j][vg * 4 + e];
+                        o[e] = acc[0][i][j][vg * 4 + e] * inv[j];
                     }
                 }
                 bf16_t* dst = C + (size_t)m * ldo + n;
@@ -124,13 +131,13 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[EPI == EPI_SWIGLU ? 2 :
 //   rows are read back 16 bytes per lane and stored.
 // Region layout: row = token (TA*32 rows of TW*64 bytes), 16-byte chunk c of row r at slot
 // c ^ (r & (chunks per row - 1)).  Needs N % 8 == 0, ldo % 8 == 0 and 16-byte aligned out / residual.
-template <int TW, int TA, int EPI>
-__device__ __forceinline__ void store_tile_via_lds(f32x16 (&acc)[EPI == EPI_SWIGLU ? 2 : 1][TW][TA], const bf16_t* R,
-                                                   bf16_t* C, int ldo, int M, int N, int mw, int nw, int lane,
-                                                   unsigned char* region) {
-    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
+template <int T, int TW, int TA, int EPI>
+__device__ __forceinline__ void store_tile_via_lds(typename MfmaTile<T>::Acc (&acc)[EPI == EPI_SWIGLU ? 2 : 1][TW * 32 / T][TA * 32 / T],
+                                                   const bf16_t* R, bf16_t* C, int ldo, int M, int N, int mw, int nw, int lane,
+                                                   unsigned char* region, const float (&inv)[TA * 32 / T]) {
+    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1, NI = TW * 32 / T, NJ = TA * 32 / T, VG = MfmaTile<T>::kGroups;
     constexpr int CPR = TW * 4, RB = TW * 64, ROWS = TA * 32, RPI = 64 / CPR;
-    const int l32 = lane & 31, hh = lane >> 5;
+    const int lt = lane & (T - 1), lq = lane / T;         // token of a tile, and which 4 of 8 (16) features
     const int rrow = lane / CPR, rchunk = lane % CPR;     // coalesced phases: lane -> (row in group, chunk)
     auto slot = [&](int row, int chunk) { return row * RB + ((chunk ^ (row & (CPR - 1))) << 4); };
     if (EPI == EPI_RESIDUAL) {
@@ -142,32 +149,32 @@ __device__ __forceinline__ void store_tile_via_lds(f32x16 (&acc)[EPI == EPI_SWIG
             *reinterpret_cast<uint4*>(region + slot(row, rchunk)) = v;
         }
     }
-    uint2 bias4[EPI == EPI_BIAS ? TW * 4 : 1];            // the lane's bias values, requested together
+    uint2 bias4[EPI == EPI_BIAS ? NI * VG : 1];           // the lane's bias values, requested together
     if (EPI == EPI_BIAS) {
 #pragma unroll
-        for (int i = 0; i < TW; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                const int n = nw + i * 32 + 8 * vg + 4 * hh;
-                bias4[i * 4 + vg] = n < N ? *reinterpret_cast<const uint2*>(R + n) : make_uint2(0, 0);
+            for (int vg = 0; vg < VG; ++vg) {
+                const int n = nw + i * T + 8 * vg + 4 * lq;
+                bias4[i * VG + vg] = n < N ? *reinterpret_cast<const uint2*>(R + n) : make_uint2(0, 0);
             }
     }
 #pragma unroll
-    for (int j = 0; j < TA; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int i = 0; i < TW; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                const int row = j * 32 + l32;
-                uint2* cell = reinterpret_cast<uint2*>(region + slot(row, i * 4 + vg) + hh * 8);
+            for (int vg = 0; vg < VG; ++vg) {
+                const int row = j * T + lt;
+                uint2* cell = reinterpret_cast<uint2*>(region + slot(row, i * (T / 8) + vg + (lq >> 1)) + (lq & 1) * 8);
                 float o[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     if (EPI == EPI_SWIGLU) {
-                        const float g = acc[0][i][j][vg * 4 + e], u = acc[NW - 1][i][j][vg * 4 + e];
+                        const float g = acc[0][i][j][vg * 4 + e] * inv[j], u = acc[NW - 1][i][j][vg * 4 + e] * inv[j];
                         o[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;   // v_rcp_f32: 1 ulp, the result is rounded to bf16
                     } else {
-                        o[e] = acc[0][i][j][vg * 4 + e];
+                        o[e] = acc[0][i][j][vg * 4 + e] * inv[j];
                     }
                 }
                 if (EPI == EPI_RESIDUAL) {
@@ -175,7 +182,7 @@ __device__ __forceinline__ void store_tile_via_lds(f32x16 (&acc)[EPI == EPI_SWIG
                     o[0] += lo_bf16(r.x); o[1] += hi_bf16(r.x); o[2] += lo_bf16(r.y); o[3] += hi_bf16(r.y);
                 }
                 if (EPI == EPI_BIAS) {                    // 4 consecutive features of the bias vector (N % 8 == 0 here)
-                    const uint2 r = bias4[EPI == EPI_BIAS ? i * 4 + vg : 0];
+                    const uint2 r = bias4[EPI == EPI_BIAS ? i * VG + vg : 0];
                     o[0] += lo_bf16(r.x); o[1] += hi_bf16(r.x); o[2] += lo_bf16(r.y); o[3] += hi_bf16(r.y);
                 }
                 *cell = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
@@ -189,85 +196,89 @@ __device__ __forceinline__ void store_tile_via_lds(f32x16 (&acc)[EPI == EPI_SWIG
 }
 
 // RoPE epilogue.  The wave tile is 128 features wide and starts at a multiple of 128, so it is one head and the
-// rotate-half partner of feature f < 64 (sub-tile i = 0, 1) is the same accumulator element of sub-tile i + 2 in
+// rotate-half partner of feature f < 64 is the same accumulator element half of the sub-tiles further on in
 // the same lane: the rotation needs no exchange.  out[f] = x[f] cos - x[f+64] sin, out[f+64] = x[f+64] cos +
 // x[f] sin with the angle of (token, f) from the table; x includes the bias.  One rounding to bf16.  With a
-// window query, the rounded values are dotted with it (64 of the head's features per lane, the other half in
-// lane ^ 32) and the per-(token, head) partial goes to token_scores.
-template <int TA>
-__device__ __forceinline__ void store_tile_rope(f32x16 (&acc)[1][4][TA], const bf16_t* bias, bf16_t* C, int ldo, int M,
+// window query, the rounded values are dotted with it (2 T of the head's features per lane, the others in the lanes
+// T apart) and the per-(token, head) partial goes to token_scores.
+template <int T, int TA>
+__device__ __forceinline__ void store_tile_rope(typename MfmaTile<T>::Acc (&acc)[1][128 / T][TA * 32 / T], const bf16_t* bias, bf16_t* C, int ldo, int M,
                                                 int N, int mw, int nw, int lane, unsigned char* region,
-                                                const EpiExtra& re) {
+                                                const EpiExtra& re, const float (&inv)[TA * 32 / T]) {
     constexpr int TW = 4, CPR = TW * 4, RB = TW * 64, ROWS = TA * 32, RPI = 64 / CPR;
+    constexpr int NJ = TA * 32 / T, VG = MfmaTile<T>::kGroups;
     if (nw >= N) return;                                 // wave-uniform: no head here (N is a multiple of 128)
-    const int l32 = lane & 31, hh = lane >> 5;
+    const int lt = lane & (T - 1), lq = lane / T;
     const int rrow = lane / CPR, rchunk = lane % CPR;
     auto slot = [&](int row, int chunk) { return row * RB + ((chunk ^ (row & (CPR - 1))) << 4); };
     const bool score = re.qt != nullptr;
-    float dot[TA];
+    float dot[NJ];
 #pragma unroll
-    for (int j = 0; j < TA; ++j) dot[j] = 0.f;
+    for (int j = 0; j < NJ; ++j) dot[j] = 0.f;
     // Per half of the head's rotation indices (i), every table, bias and window-query value the lane needs is requested
-    // first and used afterwards: 8 * TA + 16 loads in flight, one wait.  (Left to the compiler, the loads went out two
+    // first and used afterwards: 8 * TA + 16 (T = 16: half of the second) loads in flight, one wait.  (Left to the compiler, the loads went out two
     // at a time, each pair waited for: forty memory round trips per tile.)
-    const float* trow0[TA];
+    const float* trow0[NJ];
 #pragma unroll
-    for (int j = 0; j < TA; ++j) trow0[j] = re.table + (size_t)min(mw + j * 32 + l32, M - 1) * 128 + 4 * hh;
+    for (int j = 0; j < NJ; ++j) trow0[j] = re.table + (size_t)min(mw + j * T + lt, M - 1) * 128 + 4 * lq;
+    constexpr int NS = 32 / T * VG;                      // pieces of 8 (16) rotation indices in half of the 64
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        float4 c4[4][TA], s4[4][TA], q1[4], q2[4];
-        uint2 r1[4], r2[4];
+    for (int h = 0; h < 2; ++h) {
+        float4 c4[NS][NJ], s4[NS][NJ], q1[NS], q2[NS];
+        uint2 r1[NS], r2[NS];
 #pragma unroll
-        for (int vg = 0; vg < 4; ++vg) {
-            const int f = i * 32 + 8 * vg + 4 * hh;      // rotation index of element e = 0
+        for (int p = 0; p < NS; ++p) {
+            const int f = h * 32 + p * (32 / NS);        // rotation index of element e = 0 in lane group 0
 #pragma unroll
-            for (int j = 0; j < TA; ++j) {
-                c4[vg][j] = *reinterpret_cast<const float4*>(trow0[j] + i * 32 + 8 * vg);
-                s4[vg][j] = *reinterpret_cast<const float4*>(trow0[j] + i * 32 + 8 * vg + 64);
+            for (int j = 0; j < NJ; ++j) {
+                c4[p][j] = *reinterpret_cast<const float4*>(trow0[j] + f);
+                s4[p][j] = *reinterpret_cast<const float4*>(trow0[j] + f + 64);
             }
-            r1[vg] = r2[vg] = make_uint2(0, 0);
+            r1[p] = r2[p] = make_uint2(0, 0);
             if (bias) {
-                r1[vg] = *reinterpret_cast<const uint2*>(bias + nw + f);
-                r2[vg] = *reinterpret_cast<const uint2*>(bias + nw + 64 + f);
+                r1[p] = *reinterpret_cast<const uint2*>(bias + nw + f + 4 * lq);
+                r2[p] = *reinterpret_cast<const uint2*>(bias + nw + 64 + f + 4 * lq);
             }
-            q1[vg] = q2[vg] = make_float4(0.f, 0.f, 0.f, 0.f);
+            q1[p] = q2[p] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (score) {
-                q1[vg] = *reinterpret_cast<const float4*>(re.qt + nw + f);
-                q2[vg] = *reinterpret_cast<const float4*>(re.qt + nw + 64 + f);
+                q1[p] = *reinterpret_cast<const float4*>(re.qt + nw + f + 4 * lq);
+                q2[p] = *reinterpret_cast<const float4*>(re.qt + nw + 64 + f + 4 * lq);
             }
         }
 #pragma unroll
-        for (int vg = 0; vg < 4; ++vg) {
-            const float b1[4] = {lo_bf16(r1[vg].x), hi_bf16(r1[vg].x), lo_bf16(r1[vg].y), hi_bf16(r1[vg].y)};
-            const float b2[4] = {lo_bf16(r2[vg].x), hi_bf16(r2[vg].x), lo_bf16(r2[vg].y), hi_bf16(r2[vg].y)};
+        for (int p = 0; p < NS; ++p) {
+            const float b1[4] = {lo_bf16(r1[p].x), hi_bf16(r1[p].x), lo_bf16(r1[p].y), hi_bf16(r1[p].y)};
+            const float b2[4] = {lo_bf16(r2[p].x), hi_bf16(r2[p].x), lo_bf16(r2[p].y), hi_bf16(r2[p].y)};
+            const int i = h * (32 / T) + p / VG, vg = p % VG, chunk = i * (T / 8) + vg + (lq >> 1);
 #pragma unroll
-            for (int j = 0; j < TA; ++j) {
-                const int row = j * 32 + l32;
-                const float c[4] = {c4[vg][j].x, c4[vg][j].y, c4[vg][j].z, c4[vg][j].w};
-                const float sn[4] = {s4[vg][j].x, s4[vg][j].y, s4[vg][j].z, s4[vg][j].w};
+            for (int j = 0; j < NJ; ++j) {
+                const int row = j * T + lt;
+                const float c[4] = {c4[p][j].x, c4[p][j].y, c4[p][j].z, c4[p][j].w};
+                const float sn[4] = {s4[p][j].x, s4[p][j].y, s4[p][j].z, s4[p][j].w};
                 float o1[4], o2[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float x1 = acc[0][i][j][vg * 4 + e] + b1[e], x2 = acc[0][i + 2][j][vg * 4 + e] + b2[e];
+                    const float x1 = acc[0][i][j][vg * 4 + e] * inv[j] + b1[e], x2 = acc[0][i + 64 / T][j][vg * 4 + e] * inv[j] + b2[e];
                     o1[e] = x1 * c[e] - x2 * sn[e];
                     o2[e] = x2 * c[e] + x1 * sn[e];
                 }
                 const uint2 p1 = make_uint2(pack_bf16x2(o1[0], o1[1]), pack_bf16x2(o1[2], o1[3]));
                 const uint2 p2 = make_uint2(pack_bf16x2(o2[0], o2[1]), pack_bf16x2(o2[2], o2[3]));
-                *reinterpret_cast<uint2*>(region + slot(row, i * 4 + vg) + hh * 8) = p1;
-                *reinterpret_cast<uint2*>(region + slot(row, (i + 2) * 4 + vg) + hh * 8) = p2;
+                *reinterpret_cast<uint2*>(region + slot(row, chunk) + (lq & 1) * 8) = p1;
+                *reinterpret_cast<uint2*>(region + slot(row, chunk + 8) + (lq & 1) * 8) = p2;
                 if (score)
-                    dot[j] += lo_bf16(p1.x) * q1[vg].x + hi_bf16(p1.x) * q1[vg].y + lo_bf16(p1.y) * q1[vg].z + hi_bf16(p1.y) * q1[vg].w +
-                              lo_bf16(p2.x) * q2[vg].x + hi_bf16(p2.x) * q2[vg].y + lo_bf16(p2.y) * q2[vg].z + hi_bf16(p2.y) * q2[vg].w;
+                    dot[j] += lo_bf16(p1.x) * q1[p].x + hi_bf16(p1.x) * q1[p].y + lo_bf16(p1.y) * q1[p].z + hi_bf16(p1.y) * q1[p].w +
+                              lo_bf16(p2.x) * q2[p].x + hi_bf16(p2.x) * q2[p].y + lo_bf16(p2.y) * q2[p].z + hi_bf16(p2.y) * q2[p].w;
             }
         }
     }
     if (score) {
 #pragma unroll
-        for (int j = 0; j < TA; ++j) {
-            const float tot = dot[j] + __shfl_xor(dot[j], 32, 64);
-            const int m = mw + j * 32 + l32;
-            if (hh == 0 && m < M) re.token_scores[(size_t)m * (N >> 7) + (nw >> 7)] = tot;
+        for (int j = 0; j < NJ; ++j) {
+            float tot = dot[j] + __shfl_xor(dot[j], 32, 64);
+            if (T == 16) tot += __shfl_xor(tot, 16, 64);
+            const int m = mw + j * T + lt;
+            if (lq == 0 && m < M) re.token_scores[(size_t)m * (N >> 7) + (nw >> 7)] = tot;
         }
     }
 #pragma unroll
@@ -281,21 +292,25 @@ __device__ __forceinline__ void store_tile_rope(f32x16 (&acc)[1][4][TA], const b
 // Epilogue of the split projections: the wave's float tile, unscaled, to rows of a float buffer.  32 tokens at a time go through the
 // wave-private LDS region (rows of TW*128 bytes, 16-byte chunk c of row r at slot c ^ (r & (chunks per row - 1))), so
 // that a row of the tile leaves as TW*128 contiguous bytes; a wave's LDS operations complete in order.  Needs N % 4 == 0.
-template <int TW, int TA>
-__device__ __forceinline__ void store_tile_partial(f32x16 (&acc)[TW][TA], float* P, int ldp, int M, int N, int mw, int nw,
+template <int T, int TW, int TA>
+__device__ __forceinline__ void store_tile_partial(typename MfmaTile<T>::Acc (&acc)[TW * 32 / T][TA * 32 / T], float* P, int ldp, int M, int N, int mw, int nw,
                                                    int lane, unsigned char* region) {
-    constexpr int CPR = TW * 8, RB = TW * 128, RPI = 64 / CPR;
-    const int l32 = lane & 31, hh = lane >> 5;
+    constexpr int CPR = TW * 8, RB = TW * 128, RPI = 64 / CPR, VG = MfmaTile<T>::kGroups;
+    const int lt = lane & (T - 1), lq = lane / T;
     const int rrow = lane / CPR, rchunk = lane % CPR;
     auto slot = [&](int row, int chunk) { return row * RB + ((chunk ^ (row & (CPR - 1))) << 4); };
 #pragma unroll
     for (int j = 0; j < TA; ++j) {
 #pragma unroll
-        for (int i = 0; i < TW; ++i)
+        for (int t = 0; t < 32 / T; ++t)
 #pragma unroll
-            for (int vg = 0; vg < 4; ++vg)
-                *reinterpret_cast<f32x4*>(region + slot(l32, i * 8 + vg * 2 + hh)) =
-                    f32x4{acc[i][j][vg * 4], acc[i][j][vg * 4 + 1], acc[i][j][vg * 4 + 2], acc[i][j][vg * 4 + 3]};
+            for (int i = 0; i < TW * 32 / T; ++i)
+#pragma unroll
+                for (int vg = 0; vg < VG; ++vg) {
+                    const auto& c = acc[i][j * (32 / T) + t];
+                    *reinterpret_cast<f32x4*>(region + slot(t * T + lt, i * (T / 4) + vg * 2 + lq)) =
+                        f32x4{c[vg * 4], c[vg * 4 + 1], c[vg * 4 + 2], c[vg * 4 + 3]};
+                }
 #pragma unroll
         for (int it = 0; it < 32 / RPI; ++it) {
             const int row = it * RPI + rrow, m = mw + j * 32 + row, n = nw + rchunk * 4;
@@ -474,36 +489,26 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
             if (++kt >= KT) break;
         }
     }
-    if (re.row_scale) {
-        float inv[TA];                                   // all requested before the first is used: one wait, not TA
+    float inv[TA];                                       // (all requested before the first is used)
 #pragma unroll
-        for (int j = 0; j < TA; ++j) inv[j] = re.row_scale[min(m0 + (wm * TA + j) * 32 + l32, M - 1)];
-#pragma unroll
-        for (int j = 0; j < TA; ++j)
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int i = 0; i < TW; ++i)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[w][i][j][v] *= inv[j];
-    }
+    for (int j = 0; j < TA; ++j) inv[j] = re.row_scale ? re.row_scale[min(m0 + (wm * TA + j) * 32 + l32, M - 1)] : 1.f;
     // The epilogue reuses the stage buffers: every wave must be past its last fragment reads.
     __builtin_amdgcn_s_waitcnt(0x0070);
     workgroup_barrier();
     const bool wide = (N % 8 == 0) && (ldo % 8 == 0) && (((uintptr_t)C & 15) == 0) &&
                       (EPI != EPI_RESIDUAL || ((uintptr_t)R & 15) == 0) && (EPI != EPI_BIAS || ((uintptr_t)R & 7) == 0);
     if constexpr (EPI == EPI_PARTIAL) {
-        store_tile_partial<TW, TA>(acc[0], re.partial, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
+        store_tile_partial<32, TW, TA>(acc[0], re.partial, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
                                    lds + wave * (32 * TW * 128));
     } else if constexpr (EPI == EPI_ROPE) {              // the launcher has checked what `wide` checks
-        store_tile_rope<TA>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
-                            lds + wave * (TA * 32 * TW * 64), re);
+        store_tile_rope<32, TA>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
+                            lds + wave * (TA * 32 * TW * 64), re, inv);
     } else {
         if (wide)
-            store_tile_via_lds<TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
-                                            lds + wave * (TA * 32 * TW * 64));
+            store_tile_via_lds<32, TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane,
+                                            lds + wave * (TA * 32 * TW * 64), inv);
         else
-            store_tile<TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, l32, hh);
+            store_tile<32, TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane, inv);
     }
 }
 
@@ -526,15 +531,15 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     constexpr int BN = 64 * TW, WROWS = BN * NW;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
-    const int l32 = lane & 31, hh = lane >> 5;
+    const int lt = lane & 15, lq = lane >> 4;            // MFMA tiles of 16 x 16, fragments of 16 rows x 32 of k
     const unsigned lds_base = (unsigned)(uintptr_t)lds;
-    const unsigned wfrag0 = lds_base + lds_off(wn * TW * 32 + l32, hh);
-    const unsigned afrag0 = lds_base + WROWS * BK * 2 + lds_off(wm * TA * 32 + l32, hh);
+    const unsigned wfrag0 = lds_base + lds_off(wn * TW * 32 + lt, lq);
+    const unsigned afrag0 = lds_base + WROWS * BK * 2 + lds_off(wm * TA * 32 + lt, lq);
     const unsigned r0 = wave * 8 + (lane >> 3), chunk = ((lane & 7) ^ swz(r0)) * 16;
     const uint64_t w0base = (uint64_t)(uintptr_t)(W0 + (size_t)n0 * K);
     const uint64_t w1base = NW == 2 ? (uint64_t)(uintptr_t)(W1 + (size_t)n0 * K) : w0base;
     const uint64_t abase = (uint64_t)(uintptr_t)(A + (size_t)m0 * lda);
-    f32x16 acc[NW][TW][TA];
+    f32x4 acc[NW][2 * TW][2 * TA];
 #define SLIM_LOOP_ARGS wfrag0, afrag0, r0, chunk, N - 1 - n0, M - 1 - m0, (unsigned)K * 2, (unsigned)lda * 2,          \
                        (unsigned)(KT ? KT : K / BK), lds_base + wave * 1024, w0base, w1base, abase, acc
     // With a residual the k-loop itself adds the tile of R to the accumulators (it fetches the tile as MFMA fragments
@@ -542,8 +547,8 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     // the tile has all its features and that the rows of R are 16-byte aligned.
     constexpr int EPI_OUT = EPI == EPI_RESIDUAL ? (int)EPI_PLAIN : EPI;
     if constexpr (EPI == EPI_RESIDUAL) {
-        const unsigned rrow0 = wm * TA * 32 + l32;                              // the lane's token row of the tile (j = 0)
-        const unsigned rcol0 = (unsigned)(n0 + wn * TW * 32 + 8 * hh) * 2;      // byte column of its 8 features
+        const unsigned rrow0 = wm * TA * 32 + lt;                               // the lane's token row of the tile (j = 0)
+        const unsigned rcol0 = (unsigned)(n0 + wn * TW * 32 + 8 * lq) * 2;      // byte column of its 8 features
         const bf16_t* rbase = R + (size_t)m0 * ldo;
         if constexpr (TA == 4) gemm_mainloop_4_4_1_resid(SLIM_LOOP_ARGS, rrow0, rcol0, (unsigned)ldo * 2, rbase);
         else gemm_mainloop_4_2_1_resid(SLIM_LOOP_ARGS, rrow0, rcol0, (unsigned)ldo * 2, rbase);
@@ -557,39 +562,30 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     // few to spare, and be spilled to scratch memory.
     int tid_e = tid;
     asm volatile("" : "+v"(tid_e));
-    const int lane_e = tid_e & 63, l32_e = lane_e & 31, hh_e = lane_e >> 5;
+    const int lane_e = tid_e & 63;
     static_assert((TW == 4 && NW == 1 && (TA == 4 || TA == 2)) || (TW == 2 && NW == 2 && (TA == 4 || TA == 2)),
                   "no generated k-loop for this wave tile");
-    if (re.row_scale) {
-        float inv[TA];                                   // all requested before the first is used: one wait, not TA
+    float inv[2 * TA];                                   // (all requested before the first is used)
 #pragma unroll
-        for (int j = 0; j < TA; ++j) inv[j] = re.row_scale[min(m0 + (wm * TA + j) * 32 + l32_e, M - 1)];
-#pragma unroll
-        for (int j = 0; j < TA; ++j)
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int i = 0; i < TW; ++i)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[w][i][j][v] *= inv[j];
-    }
+    for (int j = 0; j < 2 * TA; ++j)
+        inv[j] = re.row_scale ? re.row_scale[min(m0 + wm * TA * 32 + j * 16 + (lane_e & 15), M - 1)] : 1.f;
     // The epilogue reuses the stage buffers: every wave must be past its last fragment reads and tile loads.
     __builtin_amdgcn_s_waitcnt(0x0070);
     workgroup_barrier();
     const bool wide = (N % 8 == 0) && (ldo % 8 == 0) && (((uintptr_t)C & 15) == 0) &&
                       (EPI != EPI_BIAS || ((uintptr_t)R & 7) == 0);
     if constexpr (EPI == EPI_PARTIAL) {
-        store_tile_partial<TW, TA>(acc[0], re.partial, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
+        store_tile_partial<16, TW, TA>(acc[0], re.partial, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
                                    lds + wave * (32 * TW * 128));
     } else if constexpr (EPI == EPI_ROPE) {              // the launcher has checked what `wide` checks
-        store_tile_rope<TA>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
-                            lds + wave * (TA * 32 * TW * 64), re);
+        store_tile_rope<16, TA>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
+                            lds + wave * (TA * 32 * TW * 64), re, inv);
     } else {
         if (wide)
-            store_tile_via_lds<TW, TA, EPI_OUT>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
-                                            lds + wave * (TA * 32 * TW * 64));
+            store_tile_via_lds<16, TW, TA, EPI_OUT>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e,
+                                            lds + wave * (TA * 32 * TW * 64), inv);
         else
-            store_tile<TW, TA, EPI_OUT>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, l32_e, hh_e);
+            store_tile<16, TW, TA, EPI_OUT>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane_e, inv);
     }
 }
 
@@ -849,7 +845,10 @@ __global__ void __launch_bounds__(256) gemm_bf16_generic_kernel(const bf16_t* __
         __syncthreads();
     }
 
-    store_tile<TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, l32, hh);
+    float inv[TA];
+#pragma unroll
+    for (int j = 0; j < TA; ++j) inv[j] = 1.f;
+    store_tile<32, TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane, inv);
 }
 
 template <int TW, int TA, int WGN, int WGM, int EPI, bool GENERIC, int NS = 2>
@@ -900,7 +899,7 @@ static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool 
 constexpr size_t kResidualCacheBytes = (size_t)176 << 20;
 static bool residual_in_four_waves(const bf16_t* R, int M, int N, int K, int ldo) {
     const size_t activation_bytes = (size_t)M * K * sizeof(bf16_t);
-    return N % 256 == 0 && ldo % 8 == 0 && ((uintptr_t)R & 15) == 0 &&
+    return N % 256 == 0 && ldo % 8 == 0 && ((uintptr_t)R & 15) == 0 && K >= 2 * BK &&   // (two k-tiles: see the generated loop)
            (K <= 8192 || activation_bytes <= kResidualCacheBytes);
 }
 

@@ -5,19 +5,23 @@ includes the file; its C++ part computes the operands and runs the epilogues on 
 return.  Run `python gen_gemm_asm.py` after changing this file (an argument names another output directory); the .inc is
 committed and tests/test_generated_sources.py checks that it is current.
 
-Shape of a workgroup: 4 waves, one per SIMD, arranged 2 (features) x 2 (tokens); a wave owns TW x TA MFMA tiles of
-32 x 32 (for SwiGLU: of each of the NW = 2 weight matrices), 128 x 128 outputs in the large tiles, so that each
-fragment read from LDS feeds four MFMAs.  The 16 accumulators fill the accumulation registers (they are the asm
-statement's outputs); fragments are double-buffered in v0..; a lone wave per SIMD means the order of matrix, LDS and
-tile-load instructions in the wave is the schedule, so it is written out here.
+Shape of a workgroup: 4 waves, one per SIMD, arranged 2 (features) x 2 (tokens); a wave owns 32 TW x 32 TA outputs (for
+SwiGLU: of each of the NW = 2 weight matrices), 128 x 128 in the large tiles, as 16 x 16 MFMA tiles, so that each fragment read
+from LDS feeds eight MFMAs.  The 64 accumulators fill the accumulation registers (they are the asm statement's outputs);
+fragments are double-buffered in v0..; a lone wave per SIMD means the order of matrix, LDS and tile-load instructions in
+the wave is the schedule, so it is written out here.
+
+Why v_mfma_f32_16x16x32_bf16: the loop runs against the power limit, and per flop the 16 x 16 x 32 instruction reads and writes half the
+accumulator bytes of the 32 x 32 x 16 one.  Normal operands from registers, all CUs, nothing else in the loop: 32 x 32 x 16
+1840 TFLOP/s, 16 x 16 x 32 2080; consecutive MFMAs that change both operands 2 to 3 % less.  So they come in pairs that share the weight
+fragment, and the token fragments are walked back and forth.
 
 k-loop: k-tiles of 64, two LDS stages (tile rows of 128 bytes, 16-byte chunks XOR-swizzled as in gemm.hip), operand
-tiles global -> LDS directly.  Per k-tile: four k-steps of TW*TA*NW MFMAs; the fragments of step s+1 are read beside
-the MFMAs of step s, also across k-tiles.  The one barrier of a k-tile sits before its last k-step, when every wave
-holds that step's fragments and its own part of the next tile has landed; from there on the stage is refilled with
-the tile two ahead.  Those tile loads are issued over three k-steps (a third beside the last k-step, the rest beside
-the first two k-steps of the next tile): issued in one burst right after the barrier they back the wave's
-instruction issue up behind the memory pipeline and cost a quarter of the MFMA rate.
+tiles global -> LDS directly.  Per k-tile: two k-steps of 4*TW*TA*NW MFMAs; the fragments of a step are read beside
+the MFMAs of the step before, also across k-tiles.  The one barrier of a k-tile sits between its k-steps, when every wave
+holds the second step's fragments and its own part of the next tile has landed; from there on the stage is refilled with
+the tile two ahead.  Those tile loads are issued over three quarters of the way to the next barrier: issued in one burst right after the
+barrier they back the wave's instruction issue up behind the memory pipeline and cost a quarter of the MFMA rate.
 """
 import os
 import sys
@@ -25,8 +29,9 @@ import sys
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from gen_attn_asm import Ins, vr, sr, V, S, valu, salu, nop, label, branch, raw, fix_hazards, weight   # noqa: E402
 
-SPREAD = 3
-N_ACC_IN_VGPRS = 4
+LOADS_IN_STEP_1 = 2                                            # thirds of a tile's loads beside the k-step behind the barrier
+CARRY_TO, READS_TO = 0.5, 0.95                                 # parts of a k-step over which the other loads, and the fragment reads, go
+N_ACC_IN_VGPRS = 16                                            # accumulators of 4 registers
 S_KPW, S_KPW2, S_KPA, S_CNT, S_LST, S_TMP = 40, 42, 44, 46, 47, 48
 FIRST_S, LAST_S = 40, 48
 
@@ -34,18 +39,19 @@ FIRST_S, LAST_S = 40, 48
 class Shape:
     def __init__(self, TW, TA, NW, resid=False):
         self.TW, self.TA, self.NW = TW, TA, NW
-        # resid: out = a . w^T + R.  The loop's prologue requests the wave's part of the residual tile as MFMA B
-        # fragments (lane (token, half) takes features 8*half .. 8*half+7 of each group of 16 output features: 16-byte
-        # loads), and behind the first k-tile, when they have arrived, adds them to the accumulators with two MFMAs per
-        # accumulator whose A operand is a slice of the identity (row f of the 32-row tile has its one at k = f - 16p
-        # for the group p): acc += I . R, exact, no vector ALU work, and the epilogue is the plain one.
+        # resid: out = a . w^T + R.  The wave's part of the residual tile is loaded as MFMA B fragments (lane (token, q)
+        # takes features 8q .. 8q+7 of each group of 32 output features: 16-byte loads) and added to the
+        # accumulators with two MFMAs per fragment whose A operand is a slice of the identity (row f of the 16-row tile p of the group
+        # has its one at k = f + 16p): acc += I . R, exact, no vector ALU work, and the epilogue is the plain one.  The fragments come
+        # 64 tokens at a time: requested in the prologue and added behind the first k-tile, then, for 128 tokens, requested there and
+        # added behind the second.
         self.resid = resid
-        self.NWF, self.NAF = NW * TW, TA                       # fragments per k-step
+        self.NWF, self.NAF = 2 * NW * TW, 2 * TA               # fragments per k-step
         n = 4 * (self.NWF + self.NAF)
         self.FRAG = [0, n]                                     # two fragment buffers: W frags then A frags
         self.WADR = 2 * n                                      # [stage][ks] LDS addresses of the W fragments
-        self.AADR = self.WADR + 8
-        self.WOFS = self.AADR + 8                              # lane offsets of the tile loads: <= 8 W, <= 8 A
+        self.AADR = self.WADR + 4
+        self.WOFS = self.AADR + 4                              # lane offsets of the tile loads: <= 8 W, <= 8 A
         self.AOFS = self.WOFS + 8
         self.TMPV = self.AOFS + 8
         self.BN = 32 * TW * 2                                  # features per matrix in a workgroup tile
@@ -55,48 +61,55 @@ class Shape:
         self.NLW = self.WROWS // 32                            # wave-loads per wave and k-tile: weights, then activations
         self.NLD = (self.WROWS + self.AROWS) // 32
         assert self.STAGE <= 65536 and self.NLW <= 8 and self.NLD - self.NLW <= 8
-        self.ROFS = self.TMPV + 1                              # byte offsets of the lane's TA residual rows
-        self.IDENT = (self.ROFS + TA + 2) & ~1                 # two identity slices, 4 registers each (ROFS + TA stays spare)
-        self.RES = self.IDENT + 8                              # residual fragments, 4 registers per (j, i, p)
-        self.LAST_V = self.RES + 4 * TA * TW * 2 - 1 if resid else self.TMPV
-        assert self.LAST_V < 256
+        self.ROFS = self.TMPV + 1                              # byte offsets of the lane's residual rows
+        self.IDENT = (self.ROFS + self.NAF + 2) & ~1           # two identity slices, 4 registers each (ROFS + NAF stays spare)
+        self.RES = self.IDENT + 8                              # residual fragments of four 16-token tiles, 4 registers each
+        self.LAST_V = self.RES + 16 * TW - 1 if resid else self.TMPV
+        assert self.LAST_V < 244
         self.name = f"{TW}_{TA}_{NW}" + ("_resid" if resid else "")
 
     def acc(self, w, i, j):
-        return f"%[c{(w * self.TW + i) * self.TA + j}]"
+        return f"%[c{(w * 2 * self.TW + i) * self.NAF + j}]"
 
-    def mfma(self, buf, w, i, j, zero):
-        wf = self.FRAG[buf] + 4 * (w * self.TW + i)
-        af = self.FRAG[buf] + 4 * (self.NWF + j)
-        c = self.acc(w, i, j)
-        return Ins(f"v_mfma_f32_32x32x16_bf16 {c}, {V(wf, 4)}, {V(af, 4)}, {'0' if zero else c}", "mfma",
-                   r=vr(wf, 4) + vr(af, 4) + ([] if zero else [c]), w=[c])
+    def mfma_pair(self, buf, w, i, j0, j1, zero):
+        wf = self.FRAG[buf] + 4 * (w * 2 * self.TW + i)
+        text, r, wr = [], vr(wf, 4), []
+        for j in (j0, j1):
+            af, c = self.FRAG[buf] + 4 * (self.NWF + j), self.acc(w, i, j)
+            text.append(f"v_mfma_f32_16x16x32_bf16 {c}, {V(wf, 4)}, {V(af, 4)}, {'0' if zero else c}")
+            r, wr = r + vr(af, 4) + ([] if zero else [c]), wr + [c]
+        return Ins("\\n".join(text), "mfma", r=r, w=wr)
 
-    def res_frag(self, j, i, p):
-        return self.RES + 4 * ((j * self.TW + i) * 2 + p)
+    def res_frag(self, j, g):
+        return self.RES + 4 * ((j & 3) * self.TW + g)
 
-    def residual_mfmas(self):
+    def residual_loads(self, batch):
+        return [Ins(f"global_load_dwordx4 {V(self.res_frag(j, g), 4)}, {V(self.ROFS + j)}, %[rbase] offset:{g * 64}", "vmem",
+                    r=vr(self.ROFS + j), w=vr(self.res_frag(j, g), 4))
+                for j in range(4 * batch, 4 * batch + 4) for g in range(self.TW)]
+
+    def residual_mfmas(self, batch):
         out = []
-        for p in range(2):                                     # the two MFMAs of an accumulator 16 apart
-            for j in range(self.TA):
-                for i in range(self.TW):
-                    c, a, b = self.acc(0, i, j), self.IDENT + 4 * p, self.res_frag(j, i, p)
-                    out.append(Ins(f"v_mfma_f32_32x32x16_bf16 {c}, {V(a, 4)}, {V(b, 4)}, {c}", "mfma",
+        for p in range(2):                                     # a group's two accumulators
+            for g in range(self.TW):
+                for j in range(4 * batch, 4 * batch + 4):
+                    c, a, b = self.acc(0, 2 * g + p, j), self.IDENT + 4 * p, self.res_frag(j, g)
+                    out.append(Ins(f"v_mfma_f32_16x16x32_bf16 {c}, {V(a, 4)}, {V(b, 4)}, {c}", "mfma",
                                    r=vr(a, 4) + vr(b, 4) + [c], w=[c]))
         return out
 
     def frag_reads(self, buf, stage, ks):
         out = []
         for w in range(self.NW):
-            for i in range(self.TW):
-                d = self.FRAG[buf] + 4 * (w * self.TW + i)
-                off = (w * self.BN + i * 32) * 128
-                out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(self.WADR + stage * 4 + ks)} offset:{off}", "lds",
-                               r=vr(self.WADR + stage * 4 + ks), w=vr(d, 4)))
-        for j in range(self.TA):
+            for i in range(2 * self.TW):
+                d = self.FRAG[buf] + 4 * (w * 2 * self.TW + i)
+                off = (w * self.BN + i * 16) * 128
+                out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(self.WADR + stage * 2 + ks)} offset:{off}", "lds",
+                               r=vr(self.WADR + stage * 2 + ks), w=vr(d, 4)))
+        for j in range(self.NAF):
             d = self.FRAG[buf] + 4 * (self.NWF + j)
-            out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(self.AADR + stage * 4 + ks)} offset:{j * 32 * 128}", "lds",
-                           r=vr(self.AADR + stage * 4 + ks), w=vr(d, 4)))
+            out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(self.AADR + stage * 2 + ks)} offset:{j * 16 * 128}", "lds",
+                           r=vr(self.AADR + stage * 2 + ks), w=vr(d, 4)))
         return out
 
     def tile_loads(self, stage):
@@ -119,40 +132,39 @@ class Shape:
         return out
 
     @staticmethod
-    def deal(mf, fills):
-        out, k = [], 0
-        for i, m in enumerate(mf):
-            out.append(m)
-            want = (i + 1) * len(fills) // len(mf)
-            out += fills[k:want]
-            k = want
-        return out
+    def deal(mf, *streams):
+        """The instructions of each stream (fills, from, to) spread evenly behind the MFMA pairs of that part (0 to 1) of the step."""
+        behind = [[] for _ in mf]
+        for fills, lo, hi in streams:
+            for k, f in enumerate(fills):
+                behind[int((lo + (hi - lo) * k / len(fills)) * len(mf))].append(f)
+        return [x for m, fs in zip(mf, behind) for x in [m] + fs]
 
     def k_tile(self, stage, first):
         """One k-tile from `stage`; the fragments of its k-step 0 are in buffer 0 (already requested)."""
-        seq = []
-        order = [(w, i, j) for w in range(self.NW) for i in range(self.TW) for j in range(self.TA)]
-        share = lambda loads, k: loads[k * len(loads) // SPREAD:(k + 1) * len(loads) // SPREAD]
-        for ks in range(4):
-            buf = ks & 1
-            seq.append(raw("s_waitcnt lgkmcnt(0)", "wait"))
-            mf = [self.mfma(buf, w, i, j, first and ks == 0) for (w, i, j) in order]
-            if ks < 3:
-                carry = share(self.tile_loads(stage ^ 1), ks + 1) if (not first and ks + 1 < SPREAD) else []
-                seq += self.deal(mf, self.frag_reads(buf ^ 1, stage, ks + 1) + carry)
-            else:
-                seq += [raw("s_waitcnt vmcnt(0)", "wait"), raw("s_barrier", "barrier")]
-                seq += self.deal(mf, self.frag_reads(buf ^ 1, stage ^ 1, 0) + share(self.tile_loads(stage), 0))
+        rows = [(w, i) for w in range(self.NW) for i in range(2 * self.TW)]
+        order = []
+        for n, (w, i) in enumerate(rows):                      # token fragments back and forth
+            js = list(range(self.NAF))[::-1 if n & 1 else 1]
+            order += [(w, i, js[k], js[k + 1]) for k in range(0, self.NAF, 2)]
+        pairs = lambda buf, zero: [self.mfma_pair(buf, *o, zero) for o in order]
+        early = lambda loads: LOADS_IN_STEP_1 * len(loads) // 3
+        seq = [raw("s_waitcnt lgkmcnt(0)", "wait")]
+        carry = [] if first else self.tile_loads(stage ^ 1)
+        seq += self.deal(pairs(0, first), (self.frag_reads(1, stage, 1), 0, READS_TO), (carry[early(carry):], 0, CARRY_TO))
+        seq += [raw("s_waitcnt vmcnt(0) lgkmcnt(0)", "wait"), raw("s_barrier", "barrier")]
+        loads = self.tile_loads(stage)
+        seq += self.deal(pairs(1, False), (self.frag_reads(0, stage ^ 1, 0), 0, READS_TO), (loads[:early(loads)], 0, 1))
         return seq
 
     def body(self):
         pro = []
         e = pro.append
         for st in range(2):
-            for ks in range(4):
+            for ks in range(2):
                 for adr, src in ((self.WADR, "wfrag0"), (self.AADR, "afrag0")):
-                    r = adr + st * 4 + ks
-                    e(valu(f"v_xor_b32 {V(r)}, {ks << 5}, %[{src}]", w=vr(r)))
+                    r = adr + st * 2 + ks
+                    e(valu(f"v_xor_b32 {V(r)}, {ks << 6}, %[{src}]", w=vr(r)))
                     if st:
                         e(valu(f"v_add_u32 {V(r)}, {self.STAGE}, {V(r)}", r=vr(r), w=vr(r)))
         # tile-load lane offsets: row 32 i + r0 of its matrix, clamped to the last valid row
@@ -173,26 +185,21 @@ class Shape:
         pro += self.tile_loads(0) + self.tile_loads(1)
         n_res = 0
         if self.resid:
-            for j in range(self.TA):                           # row = min(rrow0 + 32 j, alim) of the workgroup tile
-                e(valu(f"v_add_u32 {V(self.TMPV)}, {32 * j}, %[rrow0]", w=vr(self.TMPV)))
+            for j in range(self.NAF):                          # row = min(rrow0 + 16 j, alim) of the workgroup tile
+                e(valu(f"v_add_u32 {V(self.TMPV)}, {16 * j}, %[rrow0]", w=vr(self.TMPV)))
                 e(valu(f"v_min_i32 {V(self.TMPV)}, %[alim], {V(self.TMPV)}", r=vr(self.TMPV), w=vr(self.TMPV)))
                 e(valu(f"v_mad_u32_u24 {V(self.ROFS + j)}, {V(self.TMPV)}, %[rstride], %[rcol0]", r=vr(self.TMPV), w=vr(self.ROFS + j)))
-            for j in range(self.TA):
-                for i in range(self.TW):
-                    for p in range(2):
-                        d = self.res_frag(j, i, p)
-                        e(Ins(f"global_load_dwordx4 {V(d, 4)}, {V(self.ROFS + j)}, %[rbase] offset:{i * 64 + p * 32}", "vmem",
-                              r=vr(self.ROFS + j), w=vr(d, 4)))
-                        n_res += 1
-            # identity slices: t = f - 8*half - 16p with f = rrow0 & 31 and half = bit 4 of rcol0; the lane's one is
+            pro += self.residual_loads(0)
+            n_res = 4 * self.TW
+            # identity slices: t = f + 16p - 8q with f = rrow0 & 15 and q = bits 4 and 5 of rcol0; the lane's one is
             # bf16 element t of its 8 (if 0 <= t < 8): dword t >> 1, upper half if t is odd
-            t, val, idx = self.TMPV, self.ROFS + self.TA, self.TMPV      # ROFS + TA is a spare register below IDENT
+            t, val, idx = self.TMPV, self.ROFS + self.NAF, self.TMPV     # ROFS + NAF is a spare register below IDENT
             for p in range(2):
-                e(valu(f"v_and_b32 {V(t)}, 31, %[rrow0]", w=vr(t)))
-                e(valu(f"v_bfe_u32 {V(val)}, %[rcol0], 4, 1", w=vr(val)))
+                e(valu(f"v_and_b32 {V(t)}, 15, %[rrow0]", w=vr(t)))
+                e(valu(f"v_bfe_u32 {V(val)}, %[rcol0], 4, 2", w=vr(val)))
                 e(valu(f"v_lshlrev_b32 {V(val)}, 3, {V(val)}", r=vr(val), w=vr(val)))
                 e(valu(f"v_sub_u32 {V(t)}, {V(t)}, {V(val)}", r=vr(t) + vr(val), w=vr(t)))
-                e(valu(f"v_subrev_u32 {V(t)}, {16 * p}, {V(t)}", r=vr(t), w=vr(t)))
+                e(valu(f"v_add_u32 {V(t)}, {16 * p}, {V(t)}", r=vr(t), w=vr(t)))
                 sh = self.IDENT + 7                            # free until the last select of p = 1 writes it
                 e(valu(f"v_and_b32 {V(sh)}, 1, {V(t)}", r=vr(t), w=vr(sh)))
                 e(valu(f"v_lshlrev_b32 {V(sh)}, 4, {V(sh)}", r=vr(sh), w=vr(sh)))
@@ -208,30 +215,34 @@ class Shape:
         e(raw("s_barrier", "barrier"))
         pro += self.frag_reads(0, 0, 0)
         body0f, body0, body1 = self.k_tile(0, True), self.k_tile(0, False), self.k_tile(1, False)
-        if self.resid:
-            body0f = body0f + self.residual_mfmas()            # behind the first k-tile's wait for every load
         dec = lambda: [salu(f"s_sub_u32 {S(S_CNT)}, {S(S_CNT)}, 1", r=sr(S_CNT), w=sr(S_CNT) + ["scc"]),
                        salu(f"s_cmp_eq_u32 {S(S_CNT)}, 0", r=sr(S_CNT), w=["scc"]), branch("s_cbranch_scc1 GDONE_%=")]
-        seq = fix_hazards(pro + body0f) + dec() + [label("GLOOP_%=")]
-        loop = body1 + dec() + body0 + dec() + [branch("s_branch GLOOP_%=")]
-        seq += fix_hazards(loop, history=body0 + body1)
+        seq = pro + body0f
+        if self.resid:                                         # behind the first k-tile's wait for every load
+            seq += self.residual_mfmas(0)
+        if self.resid and self.TA == 4:                        # the launcher has at least two k-tiles
+            seq += self.residual_loads(1) + dec()[:1] + body1 + self.residual_mfmas(1)
+        seq = fix_hazards(seq) + dec() + [label("GLOOP_%=")]
+        first, second = (body0, body1) if self.resid and self.TA == 4 else (body1, body0)
+        loop = first + dec() + second + dec() + [branch("s_branch GLOOP_%=")]
+        seq += fix_hazards(loop, history=second + first + second)
         # drain the trailing loads; the accumulators are read by the compiler's code next: pad past the MFMA latency
         seq += [label("GDONE_%="), raw("s_waitcnt vmcnt(0) lgkmcnt(0)", "wait"), nop(8), nop(8)]
-        n_mfma = sum(1 for x in body0 if x.kind == "mfma")
+        n_mfma = 2 * sum(1 for x in body0 if x.kind == "mfma")
         n_oth = sum(weight(x) for x in body0 if x.kind not in ("mfma", "label"))
         print(f"wave tile {self.name}: k-tile of {n_mfma} MFMAs and {n_oth} other instructions, vgprs to v{self.LAST_V}", file=sys.stderr)
         return seq
 
     def function(self):
-        n = self.NW * self.TW * self.TA
+        n = self.NW * 2 * self.TW * self.NAF
         seq = self.body()
-        out = [f"// wave tile of {self.TW} x {self.TA} MFMA tiles, {self.NW} weight matri{'x' if self.NW == 1 else 'ces'}"
+        out = [f"// wave tile of {2 * self.TW} x {2 * self.TA} MFMA tiles, {self.NW} weight matri{'x' if self.NW == 1 else 'ces'}"
                + ("; adds the residual tile to the accumulators" if self.resid else ""),
                f"__device__ __forceinline__ void gemm_mainloop_{self.name}(unsigned wfrag0, unsigned afrag0, unsigned r0, unsigned chunk,",
                "        int wlim, int alim, unsigned wstride, unsigned astride, unsigned kt, unsigned ldsw, uint64_t w0base,",
-               f"        uint64_t w1base, uint64_t abase, f32x16 (&acc)[{self.NW}][{self.TW}][{self.TA}]"
+               f"        uint64_t w1base, uint64_t abase, f32x4 (&acc)[{self.NW}][{2 * self.TW}][{self.NAF}]"
                + (", unsigned rrow0, unsigned rcol0, unsigned rstride, const void* rbase" if self.resid else "") + ") {",
-               "    f32x16 " + ", ".join(f"c{k}" for k in range(n)) + ";",
+               "    f32x4 " + ", ".join(f"c{k}" for k in range(n)) + ";",
                "    const unsigned w0base_lo = (unsigned)w0base, w0base_hi = (unsigned)(w0base >> 32);",
                "    const unsigned w1base_lo = (unsigned)w1base, w1base_hi = (unsigned)(w1base >> 32);",
                "    const unsigned abase_lo = (unsigned)abase, abase_hi = (unsigned)(abase >> 32);",
@@ -255,8 +266,8 @@ class Shape:
             out.append("    (void)w1base_lo; (void)w1base_hi;")
         k = 0
         for w in range(self.NW):
-            for i in range(self.TW):
-                for j in range(self.TA):
+            for i in range(2 * self.TW):
+                for j in range(self.NAF):
                     out.append(f"    acc[{w}][{i}][{j}] = c{k};")
                     k += 1
         out.append("}")
