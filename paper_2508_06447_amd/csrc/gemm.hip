@@ -13,7 +13,8 @@
 // (128 features x 2 matrices x 256 tokens for SwiGLU), each wave 128 x 128 of it, so that every MFMA fragment read
 // from LDS feeds eight MFMAs.  Measured (us, 32x32x16 -> 16x16x32 loop): SwiGLU 9856 x 14336 from 4096 1705 -> 1540 (1.36 -> 1.50
 // PFLOP/s), its down projection 903 -> 839, 8192^3 775 -> 708 (1.56 PFLOP/s), Keys of 32768 rows with rotation and scores 235 -> 216.
-// Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no VGPR staging), double-buffered; MFMA fragments are read one k-step ahead of their use, across k-tiles too.  The
+// Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no VGPR staging), into rings of three weight and two
+// activation tiles; MFMA fragments are read one k-step ahead of their use, across k-tiles too.  The
 // k-loop is generated assembly (gen_gemm_asm.py -> gemm_bf16_mainloops.inc): with a lone wave per SIMD the order of
 // MFMA, LDS and tile-load instructions inside the wave is the schedule.  The residual of the output and down projections comes in
 // as MFMA fragments inside that loop.  Few rows, and residuals that the loop does not take (residual_in_four_waves), use C++ tiles with the
@@ -65,6 +66,8 @@ __device__ __forceinline__ int lds_off(int r, int c) { return (r * 8 + (c ^ swz(
 #pragma clang diagnostic ignored "-Winline-asm"
 #include "gemm_bf16_mainloops.inc"
 #pragma clang diagnostic pop
+constexpr int kRingW = 3;                                // weight tiles that the generated loops keep in LDS; activation tiles behind them
+constexpr size_t kRingBytes = (size_t)(kRingW * 256 + 2 * 256) * BK * 2;   // (two of 256 rows, or three of 128)
 
 // Accumulators of a wave tile of 32 TW features x 32 TA tokens, as MFMA tiles of T x T (T = 16 in the generated k-loops, 32 in the others):
 // acc[w][i][j][4 * vg + e] is out[token m][feature n] with
@@ -534,7 +537,7 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     const int lt = lane & 15, lq = lane >> 4;            // MFMA tiles of 16 x 16, fragments of 16 rows x 32 of k
     const unsigned lds_base = (unsigned)(uintptr_t)lds;
     const unsigned wfrag0 = lds_base + lds_off(wn * TW * 32 + lt, lq);
-    const unsigned afrag0 = lds_base + WROWS * BK * 2 + lds_off(wm * TA * 32 + lt, lq);
+    const unsigned afrag0 = lds_base + kRingW * WROWS * BK * 2 + lds_off(wm * TA * 32 + lt, lq);
     const unsigned r0 = wave * 8 + (lane >> 3), chunk = ((lane & 7) ^ swz(r0)) * 16;
     const uint64_t w0base = (uint64_t)(uintptr_t)(W0 + (size_t)n0 * K);
     const uint64_t w1base = NW == 2 ? (uint64_t)(uintptr_t)(W1 + (size_t)n0 * K) : w0base;
@@ -941,8 +944,7 @@ static int launch_two_size(const bf16_t* A, int lda, const bf16_t* W0, const bf1
                            int ldo, int M, int N, int K, int big_tiles_m, bool eight_waves, hipStream_t st,
                            const EpiExtra& re = EpiExtra()) {
     using S = TileShapes<EPI>;
-    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
-    constexpr size_t smem = 2 * (size_t)(S::BN * NW + S::BM_BIG) * BK * 2;
+    constexpr size_t smem8 = 2 * (size_t)(S::BN + S::BM_BIG) * BK * 2;
     static std::once_flag attr_once, attr8_once;
     static hipError_t attr_err = hipSuccess, attr8_err = hipSuccess;
     if ((size_t)K >= (1u << 23) || (size_t)lda >= (1u << 23) || (size_t)ldo >= (1u << 23))
@@ -953,7 +955,7 @@ static int launch_two_size(const bf16_t* A, int lda, const bf16_t* W0, const bf1
     if (EPI == EPI_RESIDUAL && eight_waves) {
         auto kern = gemm_bf16_two_size_residual_kernel;
         std::call_once(attr8_once, [&] {
-            attr8_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            attr8_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem8);
         });
         if (attr8_err != hipSuccess) return set_hip_error(attr8_err);
         // Long activation rows that stream from HBM (the matrix does not fit the memory-side cache): bands of 2
@@ -961,17 +963,17 @@ static int launch_two_size(const bf16_t* A, int lda, const bf16_t* W0, const bf1
         // activation panel is fetched once instead of once per group of 4 feature tiles (down projection of 9856
         // tokens -1.8 %, of 32768 tokens -2.6 %; with rows of 4096 the same walk is 6 % slower, so it is not used there).
         const int band = ((size_t)M * K * sizeof(bf16_t) > ((size_t)160 << 20) && K > 8192) ? 2 : 8;
-        hipLaunchKernelGGL(kern, grid, dim3(512), smem, st, A, lda, W0, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m, tiles_n,
+        hipLaunchKernelGGL(kern, grid, dim3(512), smem8, st, A, lda, W0, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m, tiles_n,
                            band);
     } else {
         auto kern = gemm_bf16_two_size_kernel<EPI>;
         std::call_once(attr_once, [&] {
-            attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingBytes);
         });
         if (attr_err != hipSuccess) return set_hip_error(attr_err);
         EpiExtra walk = re;
         if (EPI == EPI_SWIGLU || EPI == EPI_PLAIN || EPI == EPI_BIAS) walk.round_m = rounds_of(big_tiles_m, tiles_n);
-        hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, A, lda, W0, W1, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m,
+        hipLaunchKernelGGL(kern, grid, dim3(256), kRingBytes, st, A, lda, W0, W1, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m,
                            tiles_n, walk);
     }
     return check_launch();
@@ -1046,15 +1048,14 @@ static int launch_split_shape(const bf16_t* A, int lda, const SplitMats& mats, i
 }
 
 int launch_split_gemm_large(const void* a, int lda, const void* w, int m, int n, int k_in, int splits, float* partial, hipStream_t st) {
-    constexpr size_t smem = 2 * (size_t)512 * BK * 2;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] {
-        attr_err = hipFuncSetAttribute((const void*)split_gemm_large_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        attr_err = hipFuncSetAttribute((const void*)split_gemm_large_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingBytes);
     });
     if (attr_err != hipSuccess) return set_hip_error(attr_err);
     const int tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
-    hipLaunchKernelGGL(split_gemm_large_kernel, dim3(tiles_m * tiles_n * splits), dim3(256), smem, st, (const bf16_t*)a, lda, (const bf16_t*)w,
+    hipLaunchKernelGGL(split_gemm_large_kernel, dim3(tiles_m * tiles_n * splits), dim3(256), kRingBytes, st, (const bf16_t*)a, lda, (const bf16_t*)w,
                        partial, m, n, k_in, tiles_m, tiles_n, splits);
     return check_launch();
 }
@@ -1249,18 +1250,17 @@ bool qkv_together(int m, int n_q, int n_k, int n_v) {
 template <int EPI>
 static int launch_qkv_t(const bf16_t* A, int lda, const bf16_t* W, const bf16_t* B, bf16_t* C, int n_q, int m, int k_in, EpiExtra& re, hipStream_t st) {
     using S = TileShapes<EPI>;
-    constexpr size_t smem = 2 * (size_t)(S::BN + S::BM_BIG) * BK * 2;
     auto kern = gemm_bf16_qkv_kernel<EPI>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
-    std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); });
+    std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingBytes); });
     if (attr_err != hipSuccess) return set_hip_error(attr_err);
     re.tiles_nk = (re.n_k + S::BN - 1) / S::BN;
     re.tiles_n1 = (n_q + S::BN - 1) / S::BN;
     const int tiles_n = re.tiles_nk + re.tiles_n1 + (re.n_2 + S::BN - 1) / S::BN;
     const int big = plan_big_tiles(m, tiles_n, cu_count(), small_tile_cost<EPI>(false), false);
     const int small = std::max(0, m - big * S::BM_BIG + S::BM_SMALL - 1) / S::BM_SMALL;
-    hipLaunchKernelGGL(kern, dim3((big + small) * tiles_n), dim3(256), smem, st, A, lda, W, B, C, n_q, m, n_q, k_in, big, small, tiles_n, re);
+    hipLaunchKernelGGL(kern, dim3((big + small) * tiles_n), dim3(256), kRingBytes, st, A, lda, W, B, C, n_q, m, n_q, k_in, big, small, tiles_n, re);
     return check_launch();
 }
 

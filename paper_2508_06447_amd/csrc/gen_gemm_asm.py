@@ -16,12 +16,18 @@ accumulator bytes of the 32 x 32 x 16 one.  Normal operands from registers, all 
 1840 TFLOP/s, 16 x 16 x 32 2080; consecutive MFMAs that change both operands 2 to 3 % less.  So they come in pairs that share the weight
 fragment, and the token fragments are walked back and forth.
 
-k-loop: k-tiles of 64, two LDS stages (tile rows of 128 bytes, 16-byte chunks XOR-swizzled as in gemm.hip), operand
-tiles global -> LDS directly.  Per k-tile: two k-steps of 4*TW*TA*NW MFMAs; the fragments of a step are read beside
-the MFMAs of the step before, also across k-tiles.  The one barrier of a k-tile sits between its k-steps, when every wave
-holds the second step's fragments and its own part of the next tile has landed; from there on the stage is refilled with
-the tile two ahead.  Those tile loads are issued over three quarters of the way to the next barrier: issued in one burst right after the
-barrier they back the wave's instruction issue up behind the memory pipeline and cost a quarter of the MFMA rate.
+k-loop: k-tiles of 64 (tile rows of 128 bytes, 16-byte chunks XOR-swizzled as in gemm.hip), operand tiles global -> LDS directly, into
+rings: three weight tiles and two activation tiles (all 160 KB of a CU; three activation tiles where they have 128 rows).  Per k-tile: two
+k-steps of 4*TW*TA*NW MFMAs; the fragments of a step are read beside the MFMAs of the step before, also across k-tiles.  The one barrier of
+a k-tile sits between its k-steps, when every wave holds the second step's fragments and its own part of the next tile has landed; from
+there on the slots just read are refilled.  What bounds the loop below the power limit is how long those tile loads have to arrive: issued in one
+burst right behind the barrier they back the wave's instruction issue up behind the memory pipeline, spread out the last of them come late.
+With two slots for each operand (loads over three quarters of the way to the barrier that waits for them) zero operands, which
+do not reach the power limit, ran at 1440 (8192 x 4096 from 14336) and 1710 TFLOP/s (8192^3); with the third weight slot 1870 and 2080.  So
+the activation tile goes first, and the weight tile behind it has until the barrier after the next.  Normal operands, two -> three slots (us):
+down projection 4096 x 4096 from 14336 353 -> 319, 9856 rows 864 -> 823, 12288 x 3584 from 18944 1314 -> 1205; SwiGLU 4096 x 14336 from 4096 663
+-> 643; 8192^3 731 -> 707.  (Launches of less than a round with short rows lose: Query + Value of 2000 rows 73.5 -> 75.)  The slots are
+immediate offsets and the loop six k-tiles long; one k-tile with the slots in registers takes four vector instructions per k-tile and is 1 % slower.
 """
 import os
 import sys
@@ -29,11 +35,13 @@ import sys
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from gen_attn_asm import Ins, vr, sr, V, S, valu, salu, nop, label, branch, raw, fix_hazards, weight   # noqa: E402
 
-LOADS_IN_STEP_1 = 2                                            # thirds of a tile's loads beside the k-step behind the barrier
-CARRY_TO, READS_TO = 0.5, 0.95                                 # parts of a k-step over which the other loads, and the fragment reads, go
+RING_W = 3                                                     # weight tiles in LDS
+A_TO, W_TO = 0.75, 1.9                                         # k-steps behind the barrier over which the activation, then the weight loads go
+FIRST_TO = 0.9                                                 # part of the first k-step over which the loads of the third tiles go
+READS_TO = 0.95                                                # part of a k-step over which the fragment reads go
 N_ACC_IN_VGPRS = 16                                            # accumulators of 4 registers
-S_KPW, S_KPW2, S_KPA, S_CNT, S_LST, S_TMP = 40, 42, 44, 46, 47, 48
-FIRST_S, LAST_S = 40, 48
+S_KPW, S_KPW2, S_KPA, S_CNT, S_LSTW, S_LSTA, S_TMP = 40, 42, 44, 46, 47, 48, 49
+FIRST_S, LAST_S = 40, 49
 
 
 class Shape:
@@ -49,18 +57,20 @@ class Shape:
         self.NWF, self.NAF = 2 * NW * TW, 2 * TA               # fragments per k-step
         n = 4 * (self.NWF + self.NAF)
         self.FRAG = [0, n]                                     # two fragment buffers: W frags then A frags
-        self.WADR = 2 * n                                      # [stage][ks] LDS addresses of the W fragments
-        self.AADR = self.WADR + 4
-        self.WOFS = self.AADR + 4                              # lane offsets of the tile loads: <= 8 W, <= 8 A
+        self.WADR = 2 * n                                      # [ks][slot >> 1] LDS addresses of the W fragments
+        self.AADR = self.WADR + 4                              # [ks] of the A fragments
+        self.WOFS = self.AADR + 2                              # lane offsets of the tile loads: <= 8 W, <= 8 A
         self.AOFS = self.WOFS + 8
         self.TMPV = self.AOFS + 8
         self.BN = 32 * TW * 2                                  # features per matrix in a workgroup tile
         self.WROWS = self.BN * NW
         self.AROWS = 32 * TA * 2
-        self.STAGE = (self.WROWS + self.AROWS) * 128
+        self.RING_A = 2 if TA == 4 else 3
+        self.period = RING_W * self.RING_A if self.RING_A != RING_W else RING_W        # k-tiles until the slots repeat
         self.NLW = self.WROWS // 32                            # wave-loads per wave and k-tile: weights, then activations
         self.NLD = (self.WROWS + self.AROWS) // 32
-        assert self.STAGE <= 65536 and self.NLW <= 8 and self.NLD - self.NLW <= 8
+        self.NLA = self.NLD - self.NLW
+        assert self.WROWS == 256 and self.RING_A * self.AROWS <= 512 and self.NLW <= 8 and self.NLA <= 8
         self.ROFS = self.TMPV + 1                              # byte offsets of the lane's residual rows
         self.IDENT = (self.ROFS + self.NAF + 2) & ~1           # two identity slices, 4 registers each (ROFS + NAF stays spare)
         self.RES = self.IDENT + 8                              # residual fragments of four 16-token tiles, 4 registers each
@@ -98,75 +108,95 @@ class Shape:
                                    r=vr(a, 4) + vr(b, 4) + [c], w=[c]))
         return out
 
-    def frag_reads(self, buf, stage, ks):
+    def frag_reads(self, buf, t, ks):
+        """Fragments of k-step ks of k-tile t."""
+        ws, as_ = t % RING_W, t % self.RING_A
+        wadr = self.WADR + 2 * ks + (ws >> 1)
         out = []
         for w in range(self.NW):
             for i in range(2 * self.TW):
                 d = self.FRAG[buf] + 4 * (w * 2 * self.TW + i)
-                off = (w * self.BN + i * 16) * 128
-                out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(self.WADR + stage * 2 + ks)} offset:{off}", "lds",
-                               r=vr(self.WADR + stage * 2 + ks), w=vr(d, 4)))
+                off = ((ws & 1) * self.WROWS + w * self.BN + i * 16) * 128
+                out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(wadr)} offset:{off}", "lds", r=vr(wadr), w=vr(d, 4)))
         for j in range(self.NAF):
             d = self.FRAG[buf] + 4 * (self.NWF + j)
-            out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(self.AADR + stage * 2 + ks)} offset:{j * 16 * 128}", "lds",
-                           r=vr(self.AADR + stage * 2 + ks), w=vr(d, 4)))
+            off = (as_ * self.AROWS + j * 16) * 128
+            out.append(Ins(f"ds_read_b128 {V(d, 4)}, {V(self.AADR + ks)} offset:{off}", "lds", r=vr(self.AADR + ks), w=vr(d, 4)))
         return out
 
-    def tile_loads(self, stage):
-        """The wave's wave-loads of the k-tile at the pending pointers into `stage`; then the pointers move on
-        (they stay on the last k-tile once it is reached: later loads re-read it into a stage nobody reads)."""
+    def loads(self, t, weights):
+        """The wave's wave-loads of the weight or activation tile t, at the pending pointers; then the pointers move on (they stay on the
+        last k-tile once it is reached: later loads re-read it into a slot nobody reads).  Lists of instructions that stay together."""
         out = []
-        for i in range(self.NLD):
-            if i < self.NLW:
-                ofs, ptr = self.WOFS + i, (S_KPW2 if (self.NW == 2 and i * 32 >= self.BN) else S_KPW)
-            else:
-                ofs, ptr = self.AOFS + i - self.NLW, S_KPA
-            out.append(salu(f"s_add_u32 m0, %[ldsw], {stage * self.STAGE + i * 4096}", w=["m0", "scc"]))
-            out.append(Ins(f"global_load_lds_dwordx4 {V(ofs)}, {S(ptr, 2)}", "vmem", r=vr(ofs) + ["m0"] + sr(ptr, 2)))
-        out += [salu(f"s_sub_u32 {S(S_LST)}, {S(S_LST)}, 1", r=sr(S_LST), w=sr(S_LST) + ["scc"]),
-                salu(f"s_cmp_gt_i32 {S(S_LST)}, 0", r=sr(S_LST), w=["scc"]),
-                salu(f"s_cselect_b32 {S(S_TMP)}, 128, 0", r=["scc"], w=sr(S_TMP))]
-        for p in (S_KPW, S_KPW2, S_KPA) if self.NW == 2 else (S_KPW, S_KPA):
-            out += [salu(f"s_add_u32 {S(p)}, {S(p)}, {S(S_TMP)}", r=sr(p) + sr(S_TMP), w=sr(p) + ["scc"]),
-                    salu(f"s_addc_u32 {S(p + 1)}, {S(p + 1)}, 0", r=sr(p + 1) + ["scc"], w=sr(p + 1) + ["scc"])]
+        if weights:
+            base, n, ofs, lst, ptrs = t % RING_W * self.WROWS * 128, self.NLW, self.WOFS, S_LSTW, [S_KPW, S_KPW2][:self.NW]
+        else:
+            base, n, ofs, lst, ptrs = (RING_W * self.WROWS + t % self.RING_A * self.AROWS) * 128, self.NLA, self.AOFS, S_LSTA, [S_KPA]
+        for i in range(n):
+            p = ptrs[i * 32 // self.BN] if weights else ptrs[0]
+            out.append([salu(f"s_add_u32 m0, %[ldsw], {base + i * 4096}", w=["m0", "scc"]),
+                        Ins(f"global_load_lds_dwordx4 {V(ofs + i)}, {S(p, 2)}", "vmem", r=vr(ofs + i) + ["m0"] + sr(p, 2))])
+        out.append([salu(f"s_sub_u32 {S(lst)}, {S(lst)}, 1", r=sr(lst), w=sr(lst) + ["scc"]),
+                    salu(f"s_cmp_gt_i32 {S(lst)}, 0", r=sr(lst), w=["scc"]),
+                    salu(f"s_cselect_b32 {S(S_TMP)}, 128, 0", r=["scc"], w=sr(S_TMP))])
+        for p in ptrs:
+            out.append([salu(f"s_add_u32 {S(p)}, {S(p)}, {S(S_TMP)}", r=sr(p) + sr(S_TMP), w=sr(p) + ["scc"]),
+                        salu(f"s_addc_u32 {S(p + 1)}, {S(p + 1)}, 0", r=sr(p + 1) + ["scc"], w=sr(p + 1) + ["scc"])])
+        return out
+
+    def refill(self, t):
+        """What goes out behind the barrier of k-tile t, as (k-steps behind it, instructions)."""
+        return self.timed((self.loads(t + self.RING_A, False), 0, A_TO), (self.loads(t + RING_W, True), A_TO, W_TO))
+
+    def timed(self, *parts):
+        """(loads, from, to): as (k-steps, instructions)."""
+        pair = 1.0 / (self.NW * 2 * self.TW * self.TA)         # m0 is written an MFMA pair ahead of its load, which saves a wait state
+        out, last = [], 0
+        for xs, lo, hi in parts:
+            for k, x in enumerate(xs):
+                at = max(last, lo + (hi - lo) * k / len(xs))   # (and never before the load ahead of it)
+                last = at + pair if x[-1].kind == "vmem" else at
+                out += [(at, x[:1]), (last, x[1:])] if x[-1].kind == "vmem" else [(at, x)]
         return out
 
     @staticmethod
-    def deal(mf, *streams):
-        """The instructions of each stream (fills, from, to) spread evenly behind the MFMA pairs of that part (0 to 1) of the step."""
+    def deal(mf, reads, fills):
+        """The fragment reads spread evenly, and the fills (part of the step, instructions), behind the MFMA pairs of a step."""
         behind = [[] for _ in mf]
-        for fills, lo, hi in streams:
-            for k, f in enumerate(fills):
-                behind[int((lo + (hi - lo) * k / len(fills)) * len(mf))].append(f)
-        return [x for m, fs in zip(mf, behind) for x in [m] + fs]
+        for k, x in enumerate(reads):
+            behind[int(READS_TO * k / len(reads) * len(mf))].append(x)
+        for at, xs in fills:
+            behind[min(int(at * len(mf) + 1e-9), len(mf) - 1)] += xs
+        return [x for m, xs in zip(mf, behind) for x in [m] + xs]
 
-    def k_tile(self, stage, first):
-        """One k-tile from `stage`; the fragments of its k-step 0 are in buffer 0 (already requested)."""
+    def k_tile(self, t, first, in_flight=None):
+        """k-tile t; the fragments of its k-step 0 are in buffer 0 (already requested).  in_flight: loads that may be on their way at its barrier."""
         rows = [(w, i) for w in range(self.NW) for i in range(2 * self.TW)]
         order = []
         for n, (w, i) in enumerate(rows):                      # token fragments back and forth
             js = list(range(self.NAF))[::-1 if n & 1 else 1]
             order += [(w, i, js[k], js[k + 1]) for k in range(0, self.NAF, 2)]
         pairs = lambda buf, zero: [self.mfma_pair(buf, *o, zero) for o in order]
-        early = lambda loads: LOADS_IN_STEP_1 * len(loads) // 3
+        if first:                                              # the last tiles of the rings that the prologue has left out
+            carry = self.timed(((self.loads(2, False) if self.RING_A == 3 else []) + self.loads(2, True), 0, FIRST_TO))
+        else:
+            carry = [(at - 1, x) for at, x in self.refill(t + self.period - 1) if at >= 1]
+        if in_flight is None:
+            in_flight = self.NLW + (self.NLA if self.RING_A == 3 else 0)
         seq = [raw("s_waitcnt lgkmcnt(0)", "wait")]
-        carry = [] if first else self.tile_loads(stage ^ 1)
-        seq += self.deal(pairs(0, first), (self.frag_reads(1, stage, 1), 0, READS_TO), (carry[early(carry):], 0, CARRY_TO))
-        seq += [raw("s_waitcnt vmcnt(0) lgkmcnt(0)", "wait"), raw("s_barrier", "barrier")]
-        loads = self.tile_loads(stage)
-        seq += self.deal(pairs(1, False), (self.frag_reads(0, stage ^ 1, 0), 0, READS_TO), (loads[:early(loads)], 0, 1))
+        seq += self.deal(pairs(0, first), self.frag_reads(1, t, 1), carry)
+        seq += [raw(f"s_waitcnt vmcnt({in_flight}) lgkmcnt(0)", "wait"), raw("s_barrier", "barrier")]
+        seq += self.deal(pairs(1, False), self.frag_reads(0, t + 1, 0), [(at, x) for at, x in self.refill(t) if at < 1])
         return seq
 
     def body(self):
         pro = []
         e = pro.append
-        for st in range(2):
-            for ks in range(2):
-                for adr, src in ((self.WADR, "wfrag0"), (self.AADR, "afrag0")):
-                    r = adr + st * 2 + ks
-                    e(valu(f"v_xor_b32 {V(r)}, {ks << 6}, %[{src}]", w=vr(r)))
-                    if st:
-                        e(valu(f"v_add_u32 {V(r)}, {self.STAGE}, {V(r)}", r=vr(r), w=vr(r)))
+        for ks in range(2):
+            for r, src, add in ((self.WADR + 2 * ks, "wfrag0", 0), (self.WADR + 2 * ks + 1, "wfrag0", 2 * self.WROWS * 128), (self.AADR + ks, "afrag0", 0)):
+                e(valu(f"v_xor_b32 {V(r)}, {ks << 6}, %[{src}]", w=vr(r)))
+                if add:
+                    e(valu(f"v_add_u32 {V(r)}, {add}, {V(r)}", r=vr(r), w=vr(r)))
         # tile-load lane offsets: row 32 i + r0 of its matrix, clamped to the last valid row
         for i in range(self.NLD):
             is_w = i < self.NLW
@@ -181,8 +211,10 @@ class Shape:
             e(salu(f"s_mov_b32 {S(p)}, %[{name}_lo]", w=sr(p)))
             e(salu(f"s_mov_b32 {S(p + 1)}, %[{name}_hi]", w=sr(p + 1)))
         e(salu(f"s_mov_b32 {S(S_CNT)}, %[kt]", w=sr(S_CNT)))
-        e(salu(f"s_mov_b32 {S(S_LST)}, %[kt]", w=sr(S_LST)))
-        pro += self.tile_loads(0) + self.tile_loads(1)
+        e(salu(f"s_mov_b32 {S(S_LSTW)}, %[kt]", w=sr(S_LSTW)))
+        e(salu(f"s_mov_b32 {S(S_LSTA)}, %[kt]", w=sr(S_LSTA)))
+        for t in range(2):
+            pro += sum(self.loads(t, True) + self.loads(t, False), [])
         n_res = 0
         if self.resid:
             for j in range(self.NAF):                          # row = min(rrow0 + 16 j, alim) of the workgroup tile
@@ -209,27 +241,27 @@ class Shape:
                 for dw in range(4):
                     e(valu(f"v_cmp_eq_u32 vcc, {dw}, {V(idx)}", r=vr(idx), w=["vcc"], kind="vcmp"))
                     e(valu(f"v_cndmask_b32 {V(self.IDENT + 4 * p + dw)}, 0, {V(val)}, vcc", r=vr(val) + ["vcc"], w=vr(self.IDENT + 4 * p + dw)))
-        # only the first k-tile has to be there: the second one (and the residual fragments) may stay in flight
-        # until the first k-tile's own wait before its barrier
+        # only the first k-tile has to be there: the second one (and the residual fragments) may stay in flight until the first one's own wait
         e(raw(f"s_waitcnt vmcnt({self.NLD + n_res})", "wait"))
         e(raw("s_barrier", "barrier"))
         pro += self.frag_reads(0, 0, 0)
-        body0f, body0, body1 = self.k_tile(0, True), self.k_tile(0, False), self.k_tile(1, False)
         dec = lambda: [salu(f"s_sub_u32 {S(S_CNT)}, {S(S_CNT)}, 1", r=sr(S_CNT), w=sr(S_CNT) + ["scc"]),
                        salu(f"s_cmp_eq_u32 {S(S_CNT)}, 0", r=sr(S_CNT), w=["scc"]), branch("s_cbranch_scc1 GDONE_%=")]
-        seq = pro + body0f
-        if self.resid:                                         # behind the first k-tile's wait for every load
+        seq, peeled = pro + self.k_tile(0, True), 1
+        if self.resid:                                         # behind the first k-tile's wait, which covers their loads
             seq += self.residual_mfmas(0)
         if self.resid and self.TA == 4:                        # the launcher has at least two k-tiles
-            seq += self.residual_loads(1) + dec()[:1] + body1 + self.residual_mfmas(1)
+            late = sum(1 for at, x in self.refill(0) if at >= 1 and x[0].kind == "vmem")
+            seq += self.residual_loads(1) + dec()[:1] + self.k_tile(1, False, late) + self.residual_mfmas(1)
+            peeled = 2
         seq = fix_hazards(seq) + dec() + [label("GLOOP_%=")]
-        first, second = (body0, body1) if self.resid and self.TA == 4 else (body1, body0)
-        loop = first + dec() + second + dec() + [branch("s_branch GLOOP_%=")]
-        seq += fix_hazards(loop, history=second + first + second)
+        body = [self.k_tile(t, False) for t in range(peeled, peeled + self.period)]
+        loop = sum((b + dec() for b in body), []) + [branch("s_branch GLOOP_%=")]
+        seq += fix_hazards(loop, history=body[-2] + body[-1])
         # drain the trailing loads; the accumulators are read by the compiler's code next: pad past the MFMA latency
         seq += [label("GDONE_%="), raw("s_waitcnt vmcnt(0) lgkmcnt(0)", "wait"), nop(8), nop(8)]
-        n_mfma = 2 * sum(1 for x in body0 if x.kind == "mfma")
-        n_oth = sum(weight(x) for x in body0 if x.kind not in ("mfma", "label"))
+        n_mfma = 2 * sum(1 for x in body[0] if x.kind == "mfma")
+        n_oth = sum(weight(x) for x in body[0] if x.kind not in ("mfma", "label"))
         print(f"wave tile {self.name}: k-tile of {n_mfma} MFMAs and {n_oth} other instructions, vgprs to v{self.LAST_V}", file=sys.stderr)
         return seq
 
