@@ -89,6 +89,61 @@ __global__ void __launch_bounds__(kWqChunks * kWqSlices) window_query_vec_kernel
     }
 }
 
+// A small window is reduced by every workgroup of the scoring launch itself, which saves the launch in front of it: qs[e] as above, C chunks side by
+// side and up to kWinSlices slices of the (token, head of the group) pairs per chunk.  `part` holds (slices) * E floats.  Ends with a barrier.
+// Up to kWinBytes of Query states, which come from the L2 once per workgroup; 32 / 8 heads of 128 (us, own launch -> inside): scores of 32768
+// tokens' keys, 4 tokens (32 KB) 14.3 -> 12.0, 8 (64 KB) 14.4 -> 13.9, of 131072 tokens' 42.0 -> 39.7 and 41.9 -> 41.1.  From unit keys, where a launch is
+// hardly longer than that, only while all workgroups run at once (kUnitWinWaves): 512 blocks, 4 tokens 8.3 -> 6.4, 8 tokens 8.3 -> 7.4; but
+// 1024 blocks, 4 tokens 8.2 -> 9.9.
+constexpr int kWinSlices = 4;
+constexpr size_t kWinBytes = 64 << 10;
+constexpr int kUnitWinWaves = 4096;                      // 16 per CU
+__host__ __device__ inline int window_slices(int threads, int chunks) {
+    return threads >= kWinSlices * chunks ? kWinSlices : threads >= 2 * chunks ? 2 : 1;
+}
+template <typename T>
+__device__ __forceinline__ void window_query_in_lds(const T* __restrict__ q_win, int w, int Hq, int Hkv, int d, float* qs, float* part) {
+    constexpr int V = Elem<T>::kVec;
+    const int E = Hkv * d, C = E / V, S = window_slices(blockDim.x, C), G = Hq / Hkv, pairs = w * G;
+    for (int i = threadIdx.x; i < C * S; i += blockDim.x) {
+        const int slice = i / C, e = (i - slice * C) * V, g = e / d;
+        const T* base = q_win + (size_t)g * G * d + (e - g * d);
+        float acc[2][V];                                 // two sums of half the pairs each
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[0][v] = acc[1][v] = 0.f;
+        for (int p0 = slice; p0 < pairs; p0 += 4 * S) {
+            uint4 raw[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int p = min(p0 + u * S, pairs - 1), t = p / G;
+                raw[u] = *reinterpret_cast<const uint4*>(base + ((size_t)t * Hq + (p - t * G)) * d);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float f[V];
+                Elem<T>::unpack(raw[u], f);
+                if (p0 + u * S < pairs) {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) acc[u & 1][v] += f[v];
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) part[(size_t)slice * E + e + v] = acc[0][v] + acc[1][v];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += blockDim.x) {
+        float s = part[e];
+        for (int i = 1; i < S; ++i) s += part[(size_t)i * E + e];
+        qs[e] = s / ((float)w * (float)Hq);
+    }
+    __syncthreads();
+}
+// Whether the scoring launch reduces the window itself.
+template <typename T> static bool window_in_score(const void* q_win, int w, int Hq, int Hkv, int d) {
+    return d % Elem<T>::kVec == 0 && aligned16(q_win) && (size_t)w * Hq * d * sizeof(T) <= kWinBytes && Hkv * d <= 1024;
+}
+
 template <typename T>
 static void launch_window_query_t(const void* q_win, int w, int Hq, int Hkv, int d, float* qt, hipStream_t st) {
     const int E = Hkv * d, V = Elem<T>::kVec;
@@ -109,12 +164,13 @@ static void launch_window_query_t(const void* q_win, int w, int Hq, int Hkv, int
 // rounding: with the products of every piece added up the error of units of 64 bf16 rows was 2.3e-7 (relative rms), so it is 0.9e-7.
 // R: rows of a piece.  Units of one, two and up to four rows have pieces of as many; read as eight they load a row several times (67 MB of
 // bf16 keys, blocks of 64, units of 1 / 2 / 4: 29.7 / 19.6 / 16.8 us in pieces of eight, 22.4 / 15.8 / 14.7 so).
+// w > 0: qt is not there yet and the workgroup takes it from the window's w Query rows.
 template <typename T, int R, bool LONG>
 __global__ void __launch_bounds__(1024) block_score_kernel(const T* __restrict__ k, const float* __restrict__ qt,
                                                             int N, int E /*Hkv*d*/, int block, int unit,
-                                                            float* __restrict__ scores) {
+                                                            float* __restrict__ scores, const T* __restrict__ q_win, int w, int Hq, int d) {
     constexpr int V = Elem<T>::kVec;
-    extern __shared__ float smem[];                      // qt copy [E] + per-wave maxima [16]
+    extern __shared__ float smem[];                      // qt copy [E] + per-wave maxima [16] + slices of the window
     float* qs = smem;
     float* wmax = smem + E;
     const int j = blockIdx.x, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
@@ -130,8 +186,12 @@ __global__ void __launch_bounds__(1024) block_score_kernel(const T* __restrict__
         for (int r = 0; r < R; ++r) raw[r] = *reinterpret_cast<const uint4*>(p + (size_t)min(t + r, u1 - 1) * E);
     };
     if (u0 < b1) load();
-    for (int e = threadIdx.x; e < E; e += blockDim.x) qs[e] = qt[e];
-    __syncthreads();
+    if (w > 0) {
+        window_query_in_lds<T>(q_win, w, Hq, E / d, d, qs, smem + E + 16);
+    } else {
+        for (int e = threadIdx.x; e < E; e += blockDim.x) qs[e] = qt[e];
+        __syncthreads();
+    }
     float best = -INFINITY, acc = 0.f, ksum[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) ksum[i] = 0.f;
@@ -244,10 +304,15 @@ __global__ void __launch_bounds__(512) block_pool_score_kernel(const T* __restri
 
 // pooling: 0 = TokenUnits (Eq. 1-2), 1 = average pooling, 2 = max pooling
 template <typename T>
-static void launch_block_score(const T* k, const float* qt, int N, int E, int block, int unit, float* scores, hipStream_t st) {
-    const int nb = (N + block - 1) / block, waves = std::min(16, (block + unit - 1) / unit);
-    const size_t smem = (size_t)(E + 16) * sizeof(float);
-#define SLIM_SCORE(R, L) hipLaunchKernelGGL((block_score_kernel<T, R, L>), dim3(nb), dim3(64 * waves), smem, st, k, qt, N, E, block, unit, scores)
+static void launch_block_score(const T* k, const void* q_win, int w, int Hq, int Hkv, int d, float* qt, int N, int block, int unit,
+                               float* scores, hipStream_t st) {
+    const int nb = (N + block - 1) / block, waves = std::min(16, (block + unit - 1) / unit), E = Hkv * d;
+    const bool own = window_in_score<T>(q_win, w, Hq, Hkv, d);
+    const int slices = own ? window_slices(64 * waves, E / Elem<T>::kVec) : 0;
+    const size_t smem = ((size_t)E * (1 + slices) + 16) * sizeof(float);
+    if (!own) launch_window_query_t<T>(q_win, w, Hq, Hkv, d, qt, st);
+#define SLIM_SCORE(R, L) hipLaunchKernelGGL((block_score_kernel<T, R, L>), dim3(nb), dim3(64 * waves), smem, st, k, qt, N, E, block, unit, scores, \
+                                            (const T*)q_win, own ? w : 0, Hq, d)
     if (unit > 8) SLIM_SCORE(8, true);
     else if (unit > 4) SLIM_SCORE(8, false);
     else if (unit > 2) SLIM_SCORE(4, false);
@@ -256,32 +321,23 @@ static void launch_block_score(const T* k, const float* qt, int N, int E, int bl
 #undef SLIM_SCORE
 }
 
+template <typename T>
+static void launch_score_t(const void* q_win, const void* k, int N, int w, int Hq, int Hkv, int d, int block, int unit, int pooling, float* scores,
+                           float* qtilde, hipStream_t st) {
+    if (pooling == 0) return launch_block_score((const T*)k, q_win, w, Hq, Hkv, d, qtilde, N, block, unit, scores, st);
+    const int E = Hkv * d, nb = (N + block - 1) / block;
+    const size_t smem = (size_t)(E + 512 * Elem<T>::kVec + 8) * sizeof(float);
+    launch_window_query_t<T>(q_win, w, Hq, Hkv, d, qtilde, st);
+    if (pooling == 1)
+        hipLaunchKernelGGL((block_pool_score_kernel<T, false>), dim3(nb), dim3(512), smem, st, (const T*)k, qtilde, N, E, block, scores);
+    else
+        hipLaunchKernelGGL((block_pool_score_kernel<T, true>), dim3(nb), dim3(512), smem, st, (const T*)k, qtilde, N, E, block, scores);
+}
+
 int launch_score(const void* q_win, const void* k, int N, int w, int Hq, int Hkv, int d, int block, int unit,
                  int pooling, int dtype, float* scores, float* qtilde, hipStream_t st) {
-    const int E = Hkv * d, nb = (N + block - 1) / block;
-    if (dtype == SLIM_BF16) {
-        launch_window_query_t<bf16_t>(q_win, w, Hq, Hkv, d, qtilde, st);
-        const size_t smem_p = (size_t)(E + 512 * Elem<bf16_t>::kVec + 8) * sizeof(float);
-        if (pooling == 1)
-            hipLaunchKernelGGL((block_pool_score_kernel<bf16_t, false>), dim3(nb), dim3(512), smem_p, st, (const bf16_t*)k,
-                               qtilde, N, E, block, scores);
-        else if (pooling == 2)
-            hipLaunchKernelGGL((block_pool_score_kernel<bf16_t, true>), dim3(nb), dim3(512), smem_p, st, (const bf16_t*)k,
-                               qtilde, N, E, block, scores);
-        else
-            launch_block_score((const bf16_t*)k, qtilde, N, E, block, unit, scores, st);
-    } else {
-        launch_window_query_t<float>(q_win, w, Hq, Hkv, d, qtilde, st);
-        const size_t smem_p = (size_t)(E + 512 * Elem<float>::kVec + 8) * sizeof(float);
-        if (pooling == 1)
-            hipLaunchKernelGGL((block_pool_score_kernel<float, false>), dim3(nb), dim3(512), smem_p, st, (const float*)k,
-                               qtilde, N, E, block, scores);
-        else if (pooling == 2)
-            hipLaunchKernelGGL((block_pool_score_kernel<float, true>), dim3(nb), dim3(512), smem_p, st, (const float*)k,
-                               qtilde, N, E, block, scores);
-        else
-            launch_block_score((const float*)k, qtilde, N, E, block, unit, scores, st);
-    }
+    if (dtype == SLIM_BF16) launch_score_t<bf16_t>(q_win, k, N, w, Hq, Hkv, d, block, unit, pooling, scores, qtilde, st);
+    else launch_score_t<float>(q_win, k, N, w, Hq, Hkv, d, block, unit, pooling, scores, qtilde, st);
     return check_launch();
 }
 
@@ -322,27 +378,47 @@ __global__ void __launch_bounds__(256) unit_keys_kernel(const T* __restrict__ k,
     }
 }
 
-// One workgroup per block, one wave per stored unit key: dot with qt, max over the units the block has.
+// One workgroup per block, one wave per stored unit key: dot with qt, max over the units the block has.  OWN: the window query as in
+// block_score_kernel, with the first kUnitAhead pieces of a wave's first unit key requested before it (only there: the registers cost a workgroup per
+// CU, 67 MB of unit keys 15.3 -> 18.7 us).
+constexpr int kUnitAhead = 4;
+template <typename T, bool OWN>
 __global__ void __launch_bounds__(1024) unit_score_kernel(const float* __restrict__ k_rep,
                                                            const float* __restrict__ qt, int N, int E, int block,
-                                                           int unit, int M, float* __restrict__ scores) {
-    extern __shared__ float smem[];                      // qt copy [E] + per-wave maxima [16]
+                                                           int unit, int M, float* __restrict__ scores, const T* __restrict__ q_win, int w, int Hq,
+                                                           int d) {
+    extern __shared__ float smem[];                      // qt copy [E] + per-wave maxima [16] + slices of the window
     float* qs = smem;
     float* wmax = smem + E;
     const int j = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (int e = threadIdx.x; e < E; e += blockDim.x) qs[e] = qt[e];
-    __syncthreads();
     const int rows = min(block, N - j * block);
     const int m_have = (rows + unit - 1) / unit;         // units this block really has
+    float4 ahead[OWN ? kUnitAhead : 1];
+    if constexpr (OWN) {
+        const float* kr = k_rep + ((size_t)j * M + min(wave, m_have - 1)) * E;
+#pragma unroll
+        for (int u = 0; u < kUnitAhead; ++u) ahead[u] = *reinterpret_cast<const float4*>(kr + 4 * min(lane + 64 * u, E / 4 - 1));
+        window_query_in_lds<T>(q_win, w, Hq, E / d, d, qs, smem + E + 16);
+    } else {
+        for (int e = threadIdx.x; e < E; e += blockDim.x) qs[e] = qt[e];
+        __syncthreads();
+    }
     float best = -INFINITY;
     for (int m = wave; m < m_have; m += nw) {
         const float* kr = k_rep + ((size_t)j * M + m) * E;
         float acc = 0.f;
-#pragma unroll 4
-        for (int c = lane; c < E / 4; c += 64) {
-            const float4 a = *reinterpret_cast<const float4*>(kr + 4 * c);
-            acc += a.x * qs[4 * c] + a.y * qs[4 * c + 1] + a.z * qs[4 * c + 2] + a.w * qs[4 * c + 3];
+        auto add = [&](int c, const float4& a) { acc += a.x * qs[4 * c] + a.y * qs[4 * c + 1] + a.z * qs[4 * c + 2] + a.w * qs[4 * c + 3]; };
+        int c0 = lane;
+        if constexpr (OWN) {
+            if (m == wave) {
+#pragma unroll
+                for (int u = 0; u < kUnitAhead; ++u)
+                    if (lane + 64 * u < E / 4) add(lane + 64 * u, ahead[u]);
+                c0 += 64 * kUnitAhead;
+            }
         }
+#pragma unroll 4
+        for (int c = c0; c < E / 4; c += 64) add(c, *reinterpret_cast<const float4*>(kr + 4 * c));
         best = fmaxf(best, wave_sum(acc));
     }
     if (lane == 0) wmax[wave] = best;
@@ -436,16 +512,22 @@ int launch_unit_keys(const void* k, int N, int E, int block, int unit, int dtype
     return check_launch();
 }
 
+template <typename T>
+static void launch_unit_score_t(const void* q_win, const float* k_rep, int N, int w, int Hq, int Hkv, int d, int block, int unit, float* scores,
+                                float* qtilde, hipStream_t st) {
+    const int E = Hkv * d, nb = (N + block - 1) / block, M = (block + unit - 1) / unit, waves = std::min(16, M);
+    const bool own = window_in_score<T>(q_win, w, Hq, Hkv, d) && (long long)nb * waves <= kUnitWinWaves;
+    const int slices = own ? window_slices(64 * waves, E / Elem<T>::kVec) : 0;
+    const size_t smem = ((size_t)E * (1 + slices) + 16) * sizeof(float);
+    if (!own) launch_window_query_t<T>(q_win, w, Hq, Hkv, d, qtilde, st);
+    auto kern = own ? unit_score_kernel<T, true> : unit_score_kernel<T, false>;
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(64 * waves), smem, st, k_rep, qtilde, N, E, block, unit, M, scores, (const T*)q_win, w, Hq, d);
+}
+
 int launch_score_from_unit_keys(const void* q_win, const float* k_rep, int N, int w, int Hq, int Hkv, int d,
                                 int block, int unit, int dtype, float* scores, float* qtilde, hipStream_t st) {
-    const int E = Hkv * d, nb = (N + block - 1) / block, M = (block + unit - 1) / unit;
-    const int waves = M > 16 ? 16 : M;
-    if (dtype == SLIM_BF16)
-        launch_window_query_t<bf16_t>(q_win, w, Hq, Hkv, d, qtilde, st);
-    else
-        launch_window_query_t<float>(q_win, w, Hq, Hkv, d, qtilde, st);
-    hipLaunchKernelGGL(unit_score_kernel, dim3(nb), dim3(64 * waves), (size_t)(E + 16) * sizeof(float), st, k_rep, qtilde,
-                       N, E, block, unit, M, scores);
+    if (dtype == SLIM_BF16) launch_unit_score_t<bf16_t>(q_win, k_rep, N, w, Hq, Hkv, d, block, unit, scores, qtilde, st);
+    else launch_unit_score_t<float>(q_win, k_rep, N, w, Hq, Hkv, d, block, unit, scores, qtilde, st);
     return check_launch();
 }
 
@@ -560,17 +642,29 @@ __global__ void __launch_bounds__(kSelThreads) select_blocks_kernel(const float*
     }
 }
 
-// The same selection for up to 256 * KPT blocks: four waves instead of sixteen, the keys read once and kept in registers (thread t
-// holds KPT consecutive ones), a histogram per digit so that a pass takes two barriers, one prefix sum, and a second one over equal scores
-// only when not all of them are taken.  512 blocks 5.7 -> 4.5 us, in a layer 7.5 -> 6.5: what is left is the launch and the scores' way from the L2.
 constexpr int kSelSmall = 256;
+// Inclusive prefix sum over the wave's lanes, in the vector ALU (a shuffle goes through LDS: six of them in a row took longer than the rest of
+// a digit).
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);            // row_shr:1, 2, 4, 8 inside 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);            // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);            // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// The same selection for up to 256 * KPT blocks: four waves instead of sixteen, the keys read once and kept in registers (thread t
+// holds KPT consecutive ones), a histogram per digit so that a pass takes two barriers, no further digits once all candidates with the last one are
+// taken, one prefix sum, and a second one over equal scores only when not all of them are taken.  512 blocks 5.7 us at first, 4.7 with that,
+// 4.1 with the prefix sums in the vector ALU and the early end (2048 blocks 7.7 -> 5.8): what is left is the launch and the scores' way from the L2.
 template <int KPT>
 __global__ void __launch_bounds__(kSelSmall) select_few_blocks_kernel(const float* __restrict__ scores, int nb, int n_keep,
                                                                       unsigned flags, int* __restrict__ kept) {
     __shared__ int hist[4][256];
     __shared__ int wsum[2][kSelSmall / 64];
     __shared__ uint32_t s_prefix[4];
-    __shared__ int s_remaining[4], s_all;
+    __shared__ int s_remaining[4], s_all[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j0 = tid * KPT;
     const bool f_first = flags & SLIM_FORCE_FIRST, f_last = flags & SLIM_FORCE_LAST;
     auto forced = [&](int j) { return (f_first && j == 0) || (f_last && j == nb - 1); };
@@ -589,6 +683,7 @@ __global__ void __launch_bounds__(kSelSmall) select_few_blocks_kernel(const floa
     __syncthreads();
     uint32_t prefix = 0;
     int remaining = take;
+    bool all = false;                                    // every candidate from `prefix` up is taken: no further digit matters
     if (take > 0) {
 #pragma unroll
         for (int pass = 0; pass < 4; ++pass) {
@@ -604,19 +699,14 @@ __global__ void __launch_bounds__(kSelSmall) select_few_blocks_kernel(const floa
                 int c[4], tot = 0;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) { c[k] = hist[pass][255 - (4 * lane + k)]; tot += c[k]; }
-                int inc = tot;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int t = __shfl_up(inc, o, 64);
-                    if (lane >= o) inc += t;
-                }
+                const int inc = wave_inclusive_scan(tot);
                 int above = inc - tot;                   // candidates with a larger digit than this lane's first
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     if (above < remaining && remaining <= above + c[k]) {      // true for exactly one (lane, k)
                         s_prefix[pass] = prefix | ((uint32_t)(255 - (4 * lane + k)) << shift);
                         s_remaining[pass] = remaining - above;
-                        if (pass == 3) s_all = remaining - above == c[k];
+                        s_all[pass] = remaining - above == c[k];
                     }
                     above += c[k];
                 }
@@ -624,16 +714,13 @@ __global__ void __launch_bounds__(kSelSmall) select_few_blocks_kernel(const floa
             __syncthreads();
             prefix = s_prefix[pass];
             remaining = s_remaining[pass];
+            all = s_all[pass];
+            if (all) break;
         }
     }
     // Exclusive prefix sum of one number per thread; `buf` is used once per buffer.
     auto scan = [&](int v, int buf) {
-        int inc = v;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += t;
-        }
+        const int inc = wave_inclusive_scan(v);
         if (lane == 63) wsum[buf][wave] = inc;
         __syncthreads();
         int base = 0;
@@ -644,10 +731,10 @@ __global__ void __launch_bounds__(kSelSmall) select_few_blocks_kernel(const floa
     unsigned keep = fz, eq = 0;
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
-        if ((open >> i & 1) && key[i] > prefix) keep |= 1u << i;
-        if ((open >> i & 1) && key[i] == prefix) eq |= 1u << i;
+        if ((open >> i & 1) && (key[i] > prefix || (all && key[i] == prefix))) keep |= 1u << i;
+        if ((open >> i & 1) && key[i] == prefix && !all) eq |= 1u << i;
     }
-    if (take > 0 && !s_all) {                            // equal scores in ascending index order, `remaining` of them
+    if (take > 0 && !all) {                            // equal scores in ascending index order, `remaining` of them
         int rank = scan(__popc(eq), 0);
 #pragma unroll
         for (int i = 0; i < KPT; ++i)
