@@ -50,8 +50,8 @@ template <int N> __device__ __forceinline__ void store_some(float* p, const floa
 // scaled by the gain on their way in, their sums of squares are taken from the same registers and 1/rms is applied to the
 // finished sums.  Up to three projections share a launch.
 //
-// 512 rows x 256 features, k_in 256: 40.9 -> 6.2 us (688 features in: 127 -> 9.4); the
-// whole layer of 512 tokens, 18 launches before and 10 now, 523 -> 60 us (four waves and four chunks 64, eight and four 71: most
+// 512 rows x 256 features, k_in 256: 40.9 -> 6.2 us (688 features in: 127 -> 9.4), with tiles of 16 rows 5.3 (6.1); the
+// whole layer of 512 tokens, 18 launches before and 9 now, 523 -> 50 us (four waves and four chunks 64, eight and four 71: most
 // of a wave's share is then loads past its end).
 // -------------------------------------------------------------------------------------------------
 struct F32LinearArgs {
@@ -64,16 +64,23 @@ struct F32LinearArgs {
     double inv_freq[64];
 };
 
-// MT groups of 16 rows, NW waves that the reduction is dealt to, G chunks of it in flight per wave.
-template <int MT, int NW, int G>
+// MT groups of 16 rows, NW waves that the reduction is dealt to, G chunks of it in flight per wave.  ONCE: they are all that a wave has.
+template <int MT, int NW, int G, bool ONCE = false>
 __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
-    constexpr int EPT = 8 / NW;                          // elements of a tile group per thread behind the sum
+    constexpr int MG = MT > 1 ? 2 : 1;                   // row groups that the waves take side by side behind the sum
+    constexpr int EPT = 4 * MG >= NW ? 4 * MG / NW : 1;  // and elements of a tile group per thread
     __shared__ f32x4 red[NW][2 * MT][64];                // [wave][feature group * MT + row group][lane], 32 KB
     __shared__ float red_ss[NW][16 * MT];
     const int id = blockIdx.x, s = (id >= p.tile_end[0]) + (id >= p.tile_end[1]);
-    const F32Seg sg = p.seg[s];
-    const int t = s ? id - p.tile_end[s - 1] : id;
-    const int tm = t % p.tiles_m[s], tn = t / p.tiles_m[s];
+    // In the smallest launches all three segments are requested with the tile ids: an index would make theirs a second trip to the arguments.
+    auto pick = [&](auto x0, auto x1, auto x2) { return s == 0 ? x0 : s == 1 ? x1 : x2; };
+#define SLIM_SEG(f) (MT == 1 ? pick(p.seg[0].f, p.seg[1].f, p.seg[2].f) : p.seg[s].f)
+    const F32Seg sg{SLIM_SEG(a), SLIM_SEG(lda), SLIM_SEG(m), SLIM_SEG(w0), SLIM_SEG(w1), SLIM_SEG(bias), SLIM_SEG(residual), SLIM_SEG(out),
+                    SLIM_SEG(ldo), SLIM_SEG(n), SLIM_SEG(mode), SLIM_SEG(pos), SLIM_SEG(pos0)};
+#undef SLIM_SEG
+    const int t = MT == 1 ? id - pick(0, p.tile_end[0], p.tile_end[1]) : s ? id - p.tile_end[s - 1] : id;
+    const int tiles_m = MT == 1 ? pick(p.tiles_m[0], p.tiles_m[1], p.tiles_m[2]) : p.tiles_m[s];
+    const int tm = t % tiles_m, tn = t / tiles_m;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, q = lane >> 4;
     const int m0 = tm * 16 * MT, K = p.k;
 
@@ -117,18 +124,7 @@ __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
             if (pg) g[u] = load4(pg + k, left);
         }
     };
-    if (lo < hi) load(lo);
-    for (int c = lo; c < hi; c += G) {
-        f32x4 cw[G][2], ca[G][MT], cg[G];
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) cw[u][i] = w[u][i];
-#pragma unroll
-            for (int m = 0; m < MT; ++m) ca[u][m] = a[u][m];
-            cg[u] = g[u];
-        }
-        if (c + G < hi) load(c + G);     // the next group flies under this one's matrix instructions
+    auto multiply = [&](f32x4 (&cw)[G][2], f32x4 (&ca)[G][MT], f32x4 (&cg)[G]) {
         if (pg) {
 #pragma unroll
             for (int u = 0; u < G; ++u)
@@ -149,6 +145,24 @@ __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
 #pragma unroll
                     for (int m = 0; m < MT; ++m)
                         acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(cw[u][i][j], ca[u][m][j], acc[i][m], 0, 0, 0);
+    };
+    if (lo < hi) load(lo);
+    if (ONCE) {
+        if (lo < hi) multiply(w, a, g);
+    } else {
+        for (int c = lo; c < hi; c += G) {
+            f32x4 cw[G][2], ca[G][MT], cg[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) cw[u][i] = w[u][i];
+#pragma unroll
+                for (int m = 0; m < MT; ++m) ca[u][m] = a[u][m];
+                cg[u] = g[u];
+            }
+            if (c + G < hi) load(c + G); // the next group flies under this one's matrix instructions
+            multiply(cw, ca, cg);
+        }
     }
     // Accumulator element e of lane (l16, q) in tile (i, m): feature f_i + q * 4 + e, row m0 + m * 16 + l16.
 #pragma unroll
@@ -164,10 +178,11 @@ __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
         }
     }
     __syncthreads();
-    // Wave v adds all waves' sums of the row groups v % 2, v % 2 + 2, .., EPT elements from EPT (v / 2) on of both feature groups.
-    const int e0 = (wave >> 1) * EPT, c = q * 4 + e0;    // the thread's places in a group of 16 features
+    // Wave v adds all waves' sums of the row groups v % MG, v % MG + MG, .., EPT elements from EPT (v / MG) on of both feature groups.
+    const int e0 = wave / MG * EPT, c = q * 4 + e0;      // the thread's places in a group of 16 features
+    if (e0 >= 4) return;
 #pragma unroll
-    for (int m = wave & 1; m < MT; m += 2) {
+    for (int m = wave % MG; m < MT; m += MG) {
         const int row = m0 + m * 16 + l16;
         if (row >= sg.m) continue;
         float v[2][EPT] = {};
@@ -237,6 +252,9 @@ constexpr int kF32FeaturesMax = 1 << 27;                 // (2^23 tiles of 16; w
 // Reductions of up to 64 (tall: 32) go to four (two) waves of one chunk each; more have none (us, before and so: 100000 x 16 from 16 16.6 / 5.9, 8192 x 512 from
 // 64 23 / 13, 2000 x 1024 from 64 17.8 / 8.5; 16 x 100000 from 64, which were tall, 30 / 9.9).
 constexpr long long kF32TallTiles = 2048;
+// Up to how many tiles of 32 rows tiles of 16 are taken: a CU's four matrix pipes take 13 ns for a 16-deep chunk of 32 x 32, and half of the chip's CUs have no
+// tile (us: 256 x 256 from 256 5.6 -> 5.0, from 688 8.6 -> 6.0; 100 x 1000 from 1000 11.0 -> 8.0; the layer of 512 tokens 56.6 -> 49.5).
+constexpr long long kF32LowTiles = 128;
 
 int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain, float eps, int head_dim, float theta, hipStream_t st) {
     F32LinearArgs p{};
@@ -247,8 +265,8 @@ int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain
         small += (segs[s].m + 31ll) / 32 * tiles_n(segs[s]);
         m_most = std::max(m_most, segs[s].m);
     }
-    const bool tall = small >= kF32TallTiles && m_most > 32;
-    const int rows = tall ? 64 : 32;
+    const bool tall = small >= kF32TallTiles && m_most > 32, low = small <= kF32LowTiles && m_most > 16 && k_in > 64;
+    const int rows = tall ? 64 : low ? 16 : 32;
     for (int s = 0; s < 3; ++s) {
         if (s < count) {
             p.seg[s] = segs[s];
@@ -293,6 +311,8 @@ int launch_f32_linear(const F32Seg* segs, int count, int k_in, const float* gain
     else if (tall && k_in <= 64) hipLaunchKernelGGL((f32_linear_kernel<4, 4, 1>), dim3((unsigned)tiles), dim3(256), 0, st, p);
     else if (tall) hipLaunchKernelGGL((f32_linear_kernel<4, 4, 2>), dim3((unsigned)tiles), dim3(256), 0, st, p);
     else if (k_in <= 64) hipLaunchKernelGGL((f32_linear_kernel<2, 4, 1>), dim3((unsigned)tiles), dim3(256), 0, st, p);
+    else if (low && k_in <= 256) hipLaunchKernelGGL((f32_linear_kernel<1, 8, 2, true>), dim3((unsigned)tiles), dim3(512), 0, st, p);
+    else if (low) hipLaunchKernelGGL((f32_linear_kernel<1, 8, 2>), dim3((unsigned)tiles), dim3(512), 0, st, p);
     else hipLaunchKernelGGL((f32_linear_kernel<2, 8, 2>), dim3((unsigned)tiles), dim3(512), 0, st, p);
     return check_launch();
 }
