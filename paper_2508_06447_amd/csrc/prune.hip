@@ -1,6 +1,7 @@
 // Block-wise prompt token pruning (Section 4.2): block scores (Eq. 1-2), block selection,
 // hidden-state compaction.  All three are HBM-/latency-bound; none uses matrix cores.
 #include "slim_common.h"
+#include "window_plan.h"
 #include <algorithm>
 
 namespace slim {
@@ -90,29 +91,21 @@ __global__ void __launch_bounds__(kWqChunks * kWqSlices) window_query_vec_kernel
 }
 
 // A small window is reduced by every workgroup of the scoring launch itself, which saves the launch in front of it: qs[e] as above, C chunks side by
-// side and up to kWinSlices slices of the (token, head of the group) pairs per chunk.  `part` holds (slices) * E floats.  Ends with a barrier.
-// Up to kWinBytes of Query states, which come from the L2 once per workgroup; 32 / 8 heads of 128 (us, own launch -> inside): scores of 32768
-// tokens' keys, 4 tokens (32 KB) 14.3 -> 12.0, 8 (64 KB) 14.4 -> 13.9, of 131072 tokens' 42.0 -> 39.7 and 41.9 -> 41.1.  From unit keys, where a launch is
-// hardly longer than that, only while all workgroups run at once (kUnitWinWaves): 512 blocks, 4 tokens 8.3 -> 6.4, 8 tokens 8.3 -> 7.4; but
-// 1024 blocks, 4 tokens 8.2 -> 9.9.
-constexpr int kWinSlices = 4;
-constexpr size_t kWinBytes = 64 << 10;
-constexpr int kUnitWinWaves = 4096;                      // 16 per CU
-__host__ __device__ inline int window_slices(int threads, int chunks) {
-    return threads >= kWinSlices * chunks ? kWinSlices : threads >= 2 * chunks ? 2 : 1;
-}
+// side and S slices (a power of two) of the (token, head of the group) pairs per chunk, C * S threads; a thread adds four pairs at a time, and everything is
+// added pairwise, so that no sum is longer than that of the separate launch.  `part` holds S * E floats.  Ends with a barrier.
 template <typename T>
-__device__ __forceinline__ void window_query_in_lds(const T* __restrict__ q_win, int w, int Hq, int Hkv, int d, float* qs, float* part) {
+__device__ __forceinline__ void window_query_in_lds(const T* __restrict__ q_win, int w, int Hq, int Hkv, int d, int S, float* qs, float* part) {
     constexpr int V = Elem<T>::kVec;
-    const int E = Hkv * d, C = E / V, S = window_slices(blockDim.x, C), G = Hq / Hkv, pairs = w * G;
-    for (int i = threadIdx.x; i < C * S; i += blockDim.x) {
-        const int slice = i / C, e = (i - slice * C) * V, g = e / d;
+    const int E = Hkv * d, C = E / V, G = Hq / Hkv, pairs = w * G;
+    if ((int)threadIdx.x < C * S) {
+        const int slice = threadIdx.x / C, e = (threadIdx.x - slice * C) * V, g = e / d;
         const T* base = q_win + (size_t)g * G * d + (e - g * d);
-        float acc[2][V];                                 // two sums of half the pairs each
+        float acc[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[0][v] = acc[1][v] = 0.f;
+        for (int v = 0; v < V; ++v) acc[v] = 0.f;
         for (int p0 = slice; p0 < pairs; p0 += 4 * S) {
             uint4 raw[4];
+            float f[4][V];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int p = min(p0 + u * S, pairs - 1), t = p / G;
@@ -120,28 +113,36 @@ __device__ __forceinline__ void window_query_in_lds(const T* __restrict__ q_win,
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                float f[V];
-                Elem<T>::unpack(raw[u], f);
-                if (p0 + u * S < pairs) {
+                Elem<T>::unpack(raw[u], f[u]);
+                if (p0 + u * S >= pairs) {
 #pragma unroll
-                    for (int v = 0; v < V; ++v) acc[u & 1][v] += f[v];
+                    for (int v = 0; v < V; ++v) f[u][v] = 0.f;
                 }
             }
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] += (f[0][v] + f[1][v]) + (f[2][v] + f[3][v]);
         }
 #pragma unroll
-        for (int v = 0; v < V; ++v) part[(size_t)slice * E + e + v] = acc[0][v] + acc[1][v];
+        for (int v = 0; v < V; ++v) part[(size_t)slice * E + e + v] = acc[v];
     }
     __syncthreads();
+    for (; S > 4; S >>= 2) {                             // slices i, i + S/4, i + S/2, i + 3S/4 (an odd power of two: 8 -> 2)
+        const int n = (S >> 2) * E;
+        for (int i = threadIdx.x; i < n; i += blockDim.x) part[i] = (part[i] + part[i + n]) + (part[i + 2 * n] + part[i + 3 * n]);
+        __syncthreads();
+    }
     for (int e = threadIdx.x; e < E; e += blockDim.x) {
         float s = part[e];
-        for (int i = 1; i < S; ++i) s += part[(size_t)i * E + e];
+        if (S > 1) s += part[E + e];
+        if (S > 2) s += part[2 * E + e] + part[3 * E + e];
         qs[e] = s / ((float)w * (float)Hq);
     }
     __syncthreads();
 }
-// Whether the scoring launch reduces the window itself.
-template <typename T> static bool window_in_score(const void* q_win, int w, int Hq, int Hkv, int d) {
-    return d % Elem<T>::kVec == 0 && aligned16(q_win) && (size_t)w * Hq * d * sizeof(T) <= kWinBytes && Hkv * d <= 1024;
+// Whether the scoring launch reduces the window itself (16-byte chunks of one head, aligned), and with how many slices and threads.
+template <typename T> static WindowPlan window_in_score(const void* q_win, int w, int Hq, int Hkv, int d, int nb, int waves, size_t key_bytes) {
+    if (d % Elem<T>::kVec != 0 || !aligned16(q_win)) return {0, 64 * waves};
+    return window_plan(Hkv * d, Elem<T>::kVec, w, Hq / Hkv, nb, waves, (long long)key_bytes);
 }
 
 template <typename T>
@@ -164,11 +165,11 @@ static void launch_window_query_t(const void* q_win, int w, int Hq, int Hkv, int
 // rounding: with the products of every piece added up the error of units of 64 bf16 rows was 2.3e-7 (relative rms), so it is 0.9e-7.
 // R: rows of a piece.  Units of one, two and up to four rows have pieces of as many; read as eight they load a row several times (67 MB of
 // bf16 keys, blocks of 64, units of 1 / 2 / 4: 29.7 / 19.6 / 16.8 us in pieces of eight, 22.4 / 15.8 / 14.7 so).
-// w > 0: qt is not there yet and the workgroup takes it from the window's w Query rows.
+// slices > 0: qt is not there yet and the workgroup takes it from the window's w Query rows, in so many.
 template <typename T, int R, bool LONG>
 __global__ void __launch_bounds__(1024) block_score_kernel(const T* __restrict__ k, const float* __restrict__ qt,
                                                             int N, int E /*Hkv*d*/, int block, int unit,
-                                                            float* __restrict__ scores, const T* __restrict__ q_win, int w, int Hq, int d) {
+                                                            float* __restrict__ scores, const T* __restrict__ q_win, int w, int Hq, int d, int slices) {
     constexpr int V = Elem<T>::kVec;
     extern __shared__ float smem[];                      // qt copy [E] + per-wave maxima [16] + slices of the window
     float* qs = smem;
@@ -186,8 +187,8 @@ __global__ void __launch_bounds__(1024) block_score_kernel(const T* __restrict__
         for (int r = 0; r < R; ++r) raw[r] = *reinterpret_cast<const uint4*>(p + (size_t)min(t + r, u1 - 1) * E);
     };
     if (u0 < b1) load();
-    if (w > 0) {
-        window_query_in_lds<T>(q_win, w, Hq, E / d, d, qs, smem + E + 16);
+    if (slices > 0) {
+        window_query_in_lds<T>(q_win, w, Hq, E / d, d, slices, qs, smem + E + 16);
     } else {
         for (int e = threadIdx.x; e < E; e += blockDim.x) qs[e] = qt[e];
         __syncthreads();
@@ -307,12 +308,11 @@ template <typename T>
 static void launch_block_score(const T* k, const void* q_win, int w, int Hq, int Hkv, int d, float* qt, int N, int block, int unit,
                                float* scores, hipStream_t st) {
     const int nb = (N + block - 1) / block, waves = std::min(16, (block + unit - 1) / unit), E = Hkv * d;
-    const bool own = window_in_score<T>(q_win, w, Hq, Hkv, d);
-    const int slices = own ? window_slices(64 * waves, E / Elem<T>::kVec) : 0;
-    const size_t smem = ((size_t)E * (1 + slices) + 16) * sizeof(float);
-    if (!own) launch_window_query_t<T>(q_win, w, Hq, Hkv, d, qt, st);
-#define SLIM_SCORE(R, L) hipLaunchKernelGGL((block_score_kernel<T, R, L>), dim3(nb), dim3(64 * waves), smem, st, k, qt, N, E, block, unit, scores, \
-                                            (const T*)q_win, own ? w : 0, Hq, d)
+    const WindowPlan plan = window_in_score<T>(q_win, w, Hq, Hkv, d, nb, waves, (size_t)block * E * sizeof(T));
+    const size_t smem = ((size_t)E * (1 + plan.slices) + 16) * sizeof(float);
+    if (!plan.slices) launch_window_query_t<T>(q_win, w, Hq, Hkv, d, qt, st);
+#define SLIM_SCORE(R, L) hipLaunchKernelGGL((block_score_kernel<T, R, L>), dim3(nb), dim3(plan.threads), smem, st, k, qt, N, E, block, unit, scores, \
+                                            (const T*)q_win, w, Hq, d, plan.slices)
     if (unit > 8) SLIM_SCORE(8, true);
     else if (unit > 4) SLIM_SCORE(8, false);
     else if (unit > 2) SLIM_SCORE(4, false);
@@ -386,7 +386,7 @@ template <typename T, bool OWN>
 __global__ void __launch_bounds__(1024) unit_score_kernel(const float* __restrict__ k_rep,
                                                            const float* __restrict__ qt, int N, int E, int block,
                                                            int unit, int M, float* __restrict__ scores, const T* __restrict__ q_win, int w, int Hq,
-                                                           int d) {
+                                                           int d, int slices) {
     extern __shared__ float smem[];                      // qt copy [E] + per-wave maxima [16] + slices of the window
     float* qs = smem;
     float* wmax = smem + E;
@@ -398,7 +398,7 @@ __global__ void __launch_bounds__(1024) unit_score_kernel(const float* __restric
         const float* kr = k_rep + ((size_t)j * M + min(wave, m_have - 1)) * E;
 #pragma unroll
         for (int u = 0; u < kUnitAhead; ++u) ahead[u] = *reinterpret_cast<const float4*>(kr + 4 * min(lane + 64 * u, E / 4 - 1));
-        window_query_in_lds<T>(q_win, w, Hq, E / d, d, qs, smem + E + 16);
+        window_query_in_lds<T>(q_win, w, Hq, E / d, d, slices, qs, smem + E + 16);
     } else {
         for (int e = threadIdx.x; e < E; e += blockDim.x) qs[e] = qt[e];
         __syncthreads();
@@ -516,12 +516,12 @@ template <typename T>
 static void launch_unit_score_t(const void* q_win, const float* k_rep, int N, int w, int Hq, int Hkv, int d, int block, int unit, float* scores,
                                 float* qtilde, hipStream_t st) {
     const int E = Hkv * d, nb = (N + block - 1) / block, M = (block + unit - 1) / unit, waves = std::min(16, M);
-    const bool own = window_in_score<T>(q_win, w, Hq, Hkv, d) && (long long)nb * waves <= kUnitWinWaves;
-    const int slices = own ? window_slices(64 * waves, E / Elem<T>::kVec) : 0;
-    const size_t smem = ((size_t)E * (1 + slices) + 16) * sizeof(float);
-    if (!own) launch_window_query_t<T>(q_win, w, Hq, Hkv, d, qtilde, st);
-    auto kern = own ? unit_score_kernel<T, true> : unit_score_kernel<T, false>;
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(64 * waves), smem, st, k_rep, qtilde, N, E, block, unit, M, scores, (const T*)q_win, w, Hq, d);
+    const WindowPlan plan = window_in_score<T>(q_win, w, Hq, Hkv, d, nb, waves, 0);
+    const size_t smem = ((size_t)E * (1 + plan.slices) + 16) * sizeof(float);
+    if (!plan.slices) launch_window_query_t<T>(q_win, w, Hq, Hkv, d, qtilde, st);
+    auto kern = plan.slices ? unit_score_kernel<T, true> : unit_score_kernel<T, false>;
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(plan.threads), smem, st, k_rep, qtilde, N, E, block, unit, M, scores, (const T*)q_win, w, Hq, d,
+                       plan.slices);
 }
 
 int launch_score_from_unit_keys(const void* q_win, const float* k_rep, int N, int w, int Hq, int Hkv, int d,
