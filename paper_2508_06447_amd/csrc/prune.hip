@@ -391,16 +391,18 @@ __global__ void __launch_bounds__(1024) unit_score_kernel(const float* __restric
     float* qs = smem;
     float* wmax = smem + E;
     const int j = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int rows = min(block, N - j * block);
-    const int m_have = (rows + unit - 1) / unit;         // units this block really has
+    auto units = [&]() { return (min(block, N - j * block) + unit - 1) / unit; };      // units this block really has
+    int m_have;
     float4 ahead[OWN ? kUnitAhead : 1];
     if constexpr (OWN) {
+        m_have = units();
         const float* kr = k_rep + ((size_t)j * M + min(wave, m_have - 1)) * E;
 #pragma unroll
         for (int u = 0; u < kUnitAhead; ++u) ahead[u] = *reinterpret_cast<const float4*>(kr + 4 * min(lane + 64 * u, E / 4 - 1));
         window_query_in_lds<T>(q_win, w, Hq, E / d, d, slices, qs, smem + E + 16);
     } else {
         for (int e = threadIdx.x; e < E; e += blockDim.x) qs[e] = qt[e];
+        m_have = units();                                // (a division: behind the request for qt, not in front of it)
         __syncthreads();
     }
     float best = -INFINITY;
