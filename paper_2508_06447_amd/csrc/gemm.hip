@@ -902,7 +902,7 @@ static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool 
 constexpr size_t kResidualCacheBytes = (size_t)176 << 20;
 static bool residual_in_four_waves(const bf16_t* R, int M, int N, int K, int ldo) {
     const size_t activation_bytes = (size_t)M * K * sizeof(bf16_t);
-    return N % 256 == 0 && ldo % 8 == 0 && ((uintptr_t)R & 15) == 0 && K >= 2 * BK &&   // (two k-tiles: see the generated loop)
+    return N % 256 == 0 && ldo % 8 == 0 && ((uintptr_t)R & 15) == 0 &&
            (K <= 8192 || activation_bytes <= kResidualCacheBytes);
 }
 

@@ -90,20 +90,20 @@ class Shape:
             r, wr = r + vr(af, 4) + ([] if zero else [c]), wr + [c]
         return Ins("\\n".join(text), "mfma", r=r, w=wr)
 
-    def res_frag(self, j, g):
-        return self.RES + 4 * ((j & 3) * self.TW + g)
+    def res_frag(self, j, g, base):
+        return base + 4 * ((j & 3) * self.TW + g)
 
-    def residual_loads(self, batch):
-        return [Ins(f"global_load_dwordx4 {V(self.res_frag(j, g), 4)}, {V(self.ROFS + j)}, %[rbase] offset:{g * 64}", "vmem",
-                    r=vr(self.ROFS + j), w=vr(self.res_frag(j, g), 4))
+    def residual_loads(self, batch, base):
+        return [Ins(f"global_load_dwordx4 {V(self.res_frag(j, g, base), 4)}, {V(self.ROFS + j)}, %[rbase] offset:{g * 64}", "vmem",
+                    r=vr(self.ROFS + j), w=vr(self.res_frag(j, g, base), 4))
                 for j in range(4 * batch, 4 * batch + 4) for g in range(self.TW)]
 
-    def residual_mfmas(self, batch):
+    def residual_mfmas(self, batch, base):
         out = []
         for p in range(2):                                     # a group's two accumulators
             for g in range(self.TW):
                 for j in range(4 * batch, 4 * batch + 4):
-                    c, a, b = self.acc(0, 2 * g + p, j), self.IDENT + 4 * p, self.res_frag(j, g)
+                    c, a, b = self.acc(0, 2 * g + p, j), self.IDENT + 4 * p, self.res_frag(j, g, base)
                     out.append(Ins(f"v_mfma_f32_16x16x32_bf16 {c}, {V(a, 4)}, {V(b, 4)}, {c}", "mfma",
                                    r=vr(a, 4) + vr(b, 4) + [c], w=[c]))
         return out
@@ -169,14 +169,17 @@ class Shape:
             behind[min(int(at * len(mf) + 1e-9), len(mf) - 1)] += xs
         return [x for m, xs in zip(mf, behind) for x in [m] + xs]
 
-    def k_tile(self, t, first, in_flight=None):
-        """k-tile t; the fragments of its k-step 0 are in buffer 0 (already requested).  in_flight: loads that may be on their way at its barrier."""
+    def pairs(self, buf, zero):
+        """The MFMAs of a k-step from fragment buffer buf."""
         rows = [(w, i) for w in range(self.NW) for i in range(2 * self.TW)]
         order = []
         for n, (w, i) in enumerate(rows):                      # token fragments back and forth
             js = list(range(self.NAF))[::-1 if n & 1 else 1]
             order += [(w, i, js[k], js[k + 1]) for k in range(0, self.NAF, 2)]
-        pairs = lambda buf, zero: [self.mfma_pair(buf, *o, zero) for o in order]
+        return [self.mfma_pair(buf, *o, zero) for o in order]
+
+    def k_tile(self, t, first, in_flight=None):
+        """k-tile t; the fragments of its k-step 0 are in buffer 0 (already requested).  in_flight: loads that may be on their way at its barrier."""
         if first:                                              # the last tiles of the rings that the prologue has left out
             carry = self.timed(((self.loads(2, False) if self.RING_A == 3 else []) + self.loads(2, True), 0, FIRST_TO))
         else:
@@ -184,9 +187,57 @@ class Shape:
         if in_flight is None:
             in_flight = self.NLW + (self.NLA if self.RING_A == 3 else 0)
         seq = [raw("s_waitcnt lgkmcnt(0)", "wait")]
-        seq += self.deal(pairs(0, first), self.frag_reads(1, t, 1), carry)
+        seq += self.deal(self.pairs(0, first), self.frag_reads(1, t, 1), carry)
         seq += [raw(f"s_waitcnt vmcnt({in_flight}) lgkmcnt(0)", "wait"), raw("s_barrier", "barrier")]
-        seq += self.deal(pairs(1, False), self.frag_reads(0, t + 1, 0), [(at, x) for at, x in self.refill(t) if at < 1])
+        seq += self.deal(self.pairs(1, False), self.frag_reads(0, t + 1, 0), [(at, x) for at, x in self.refill(t) if at < 1])
+        return seq
+
+    def residual_setup(self):
+        """Byte offsets of the lane's residual rows: row = min(rrow0 + 16 j, alim) of the workgroup tile."""
+        out = []
+        for j in range(self.NAF):
+            out += [valu(f"v_add_u32 {V(self.TMPV)}, {16 * j}, %[rrow0]", w=vr(self.TMPV)),
+                    valu(f"v_min_i32 {V(self.TMPV)}, %[alim], {V(self.TMPV)}", r=vr(self.TMPV), w=vr(self.TMPV)),
+                    valu(f"v_mad_u32_u24 {V(self.ROFS + j)}, {V(self.TMPV)}, %[rstride], %[rcol0]", r=vr(self.TMPV), w=vr(self.ROFS + j))]
+        return out
+
+    def identity(self):
+        """Identity slices: t = f + 16p - 8q with f = rrow0 & 15 and q = bits 4 and 5 of rcol0; the lane's one is
+        bf16 element t of its 8 (if 0 <= t < 8): dword t >> 1, upper half if t is odd."""
+        out = []
+        e = out.append
+        t, val, idx = self.TMPV, self.ROFS + self.NAF, self.TMPV         # ROFS + NAF is a spare register below IDENT
+        for p in range(2):
+            e(valu(f"v_and_b32 {V(t)}, 15, %[rrow0]", w=vr(t)))
+            e(valu(f"v_bfe_u32 {V(val)}, %[rcol0], 4, 2", w=vr(val)))
+            e(valu(f"v_lshlrev_b32 {V(val)}, 3, {V(val)}", r=vr(val), w=vr(val)))
+            e(valu(f"v_sub_u32 {V(t)}, {V(t)}, {V(val)}", r=vr(t) + vr(val), w=vr(t)))
+            e(valu(f"v_add_u32 {V(t)}, {16 * p}, {V(t)}", r=vr(t), w=vr(t)))
+            sh = self.IDENT + 7                            # free until the last select of p = 1 writes it
+            e(valu(f"v_and_b32 {V(sh)}, 1, {V(t)}", r=vr(t), w=vr(sh)))
+            e(valu(f"v_lshlrev_b32 {V(sh)}, 4, {V(sh)}", r=vr(sh), w=vr(sh)))
+            e(valu(f"v_mov_b32 {V(val)}, 0x3f80", w=vr(val)))                  # bf16 1.0
+            e(valu(f"v_lshlrev_b32 {V(val)}, {V(sh)}, {V(val)}", r=vr(sh) + vr(val), w=vr(val)))
+            e(valu(f"v_ashrrev_i32 {V(idx)}, 1, {V(t)}", r=vr(t), w=vr(idx)))
+            for dw in range(4):
+                e(valu(f"v_cmp_eq_u32 vcc, {dw}, {V(idx)}", r=vr(idx), w=["vcc"], kind="vcmp"))
+                e(valu(f"v_cndmask_b32 {V(self.IDENT + 4 * p + dw)}, 0, {V(val)}, vcc", r=vr(val) + ["vcc"], w=vr(self.IDENT + 4 * p + dw)))
+        return out
+
+    def only_k_tile(self):
+        """The whole product where it has one k-tile, whose loads have been issued: no rings, nothing else fetched.  With 128 tokens to a wave the second
+        batch of residual fragments has the place of the second fragment buffer, so that all of them are on their way at once."""
+        seq, both = [], self.resid and self.TA == 4
+        if self.resid:
+            seq += self.residual_setup() + self.residual_loads(0, self.RES) + (self.residual_loads(1, self.FRAG[1]) if both else []) + self.identity()
+        seq += [raw(f"s_waitcnt vmcnt({sum(x.kind == 'vmem' for x in seq)})", "wait"), raw("s_barrier", "barrier")]
+        seq += self.frag_reads(0, 0, 0) + [raw("s_waitcnt lgkmcnt(0)", "wait")]
+        if both:                                               # (the first step's last MFMAs have read their operands before the next fragments arrive)
+            seq += self.pairs(0, True) + [nop(8)] + self.frag_reads(0, 0, 1) + [raw("s_waitcnt lgkmcnt(0)", "wait")] + self.pairs(0, False)
+        else:
+            seq += self.deal(self.pairs(0, True), self.frag_reads(1, 0, 1), []) + [raw("s_waitcnt lgkmcnt(0)", "wait")] + self.pairs(1, False)
+        if self.resid:
+            seq += [raw("s_waitcnt vmcnt(0)", "wait")] + self.residual_mfmas(0, self.RES) + (self.residual_mfmas(1, self.FRAG[1]) if both else [])
         return seq
 
     def body(self):
@@ -213,34 +264,15 @@ class Shape:
         e(salu(f"s_mov_b32 {S(S_CNT)}, %[kt]", w=sr(S_CNT)))
         e(salu(f"s_mov_b32 {S(S_LSTW)}, %[kt]", w=sr(S_LSTW)))
         e(salu(f"s_mov_b32 {S(S_LSTA)}, %[kt]", w=sr(S_LSTA)))
-        for t in range(2):
-            pro += sum(self.loads(t, True) + self.loads(t, False), [])
+        pro += sum(self.loads(0, True) + self.loads(0, False), [])
+        # a product of one k-tile leaves here: with the rings' other tiles on their way, which it does not read, it took 2 to 4 % longer
+        pro += [salu("s_cmp_eq_u32 %[kt], 1", w=["scc"]), branch("s_cbranch_scc1 GSHORT_%=")]
+        entry = list(pro)
+        pro += sum(self.loads(1, True) + self.loads(1, False), [])
         n_res = 0
         if self.resid:
-            for j in range(self.NAF):                          # row = min(rrow0 + 16 j, alim) of the workgroup tile
-                e(valu(f"v_add_u32 {V(self.TMPV)}, {16 * j}, %[rrow0]", w=vr(self.TMPV)))
-                e(valu(f"v_min_i32 {V(self.TMPV)}, %[alim], {V(self.TMPV)}", r=vr(self.TMPV), w=vr(self.TMPV)))
-                e(valu(f"v_mad_u32_u24 {V(self.ROFS + j)}, {V(self.TMPV)}, %[rstride], %[rcol0]", r=vr(self.TMPV), w=vr(self.ROFS + j)))
-            pro += self.residual_loads(0)
+            pro += self.residual_setup() + self.residual_loads(0, self.RES) + self.identity()
             n_res = 4 * self.TW
-            # identity slices: t = f + 16p - 8q with f = rrow0 & 15 and q = bits 4 and 5 of rcol0; the lane's one is
-            # bf16 element t of its 8 (if 0 <= t < 8): dword t >> 1, upper half if t is odd
-            t, val, idx = self.TMPV, self.ROFS + self.NAF, self.TMPV     # ROFS + NAF is a spare register below IDENT
-            for p in range(2):
-                e(valu(f"v_and_b32 {V(t)}, 15, %[rrow0]", w=vr(t)))
-                e(valu(f"v_bfe_u32 {V(val)}, %[rcol0], 4, 2", w=vr(val)))
-                e(valu(f"v_lshlrev_b32 {V(val)}, 3, {V(val)}", r=vr(val), w=vr(val)))
-                e(valu(f"v_sub_u32 {V(t)}, {V(t)}, {V(val)}", r=vr(t) + vr(val), w=vr(t)))
-                e(valu(f"v_add_u32 {V(t)}, {16 * p}, {V(t)}", r=vr(t), w=vr(t)))
-                sh = self.IDENT + 7                            # free until the last select of p = 1 writes it
-                e(valu(f"v_and_b32 {V(sh)}, 1, {V(t)}", r=vr(t), w=vr(sh)))
-                e(valu(f"v_lshlrev_b32 {V(sh)}, 4, {V(sh)}", r=vr(sh), w=vr(sh)))
-                e(valu(f"v_mov_b32 {V(val)}, 0x3f80", w=vr(val)))                  # bf16 1.0
-                e(valu(f"v_lshlrev_b32 {V(val)}, {V(sh)}, {V(val)}", r=vr(sh) + vr(val), w=vr(val)))
-                e(valu(f"v_ashrrev_i32 {V(idx)}, 1, {V(t)}", r=vr(t), w=vr(idx)))
-                for dw in range(4):
-                    e(valu(f"v_cmp_eq_u32 vcc, {dw}, {V(idx)}", r=vr(idx), w=["vcc"], kind="vcmp"))
-                    e(valu(f"v_cndmask_b32 {V(self.IDENT + 4 * p + dw)}, 0, {V(val)}, vcc", r=vr(val) + ["vcc"], w=vr(self.IDENT + 4 * p + dw)))
         # only the first k-tile has to be there: the second one (and the residual fragments) may stay in flight until the first one's own wait
         e(raw(f"s_waitcnt vmcnt({self.NLD + n_res})", "wait"))
         e(raw("s_barrier", "barrier"))
@@ -249,15 +281,16 @@ class Shape:
                        salu(f"s_cmp_eq_u32 {S(S_CNT)}, 0", r=sr(S_CNT), w=["scc"]), branch("s_cbranch_scc1 GDONE_%=")]
         seq, peeled = pro + self.k_tile(0, True), 1
         if self.resid:                                         # behind the first k-tile's wait, which covers their loads
-            seq += self.residual_mfmas(0)
-        if self.resid and self.TA == 4:                        # the launcher has at least two k-tiles
+            seq += self.residual_mfmas(0, self.RES)
+        if self.resid and self.TA == 4:                        # (at least two k-tiles here)
             late = sum(1 for at, x in self.refill(0) if at >= 1 and x[0].kind == "vmem")
-            seq += self.residual_loads(1) + dec()[:1] + self.k_tile(1, False, late) + self.residual_mfmas(1)
+            seq += self.residual_loads(1, self.RES) + dec()[:1] + self.k_tile(1, False, late) + self.residual_mfmas(1, self.RES)
             peeled = 2
         seq = fix_hazards(seq) + dec() + [label("GLOOP_%=")]
         body = [self.k_tile(t, False) for t in range(peeled, peeled + self.period)]
         loop = sum((b + dec() for b in body), []) + [branch("s_branch GLOOP_%=")]
         seq += fix_hazards(loop, history=body[-2] + body[-1])
+        seq += [label("GSHORT_%=")] + fix_hazards(self.only_k_tile(), history=entry)
         # drain the trailing loads; the accumulators are read by the compiler's code next: pad past the MFMA latency
         seq += [label("GDONE_%="), raw("s_waitcnt vmcnt(0) lgkmcnt(0)", "wait"), nop(8), nop(8)]
         n_mfma = 2 * sum(1 for x in body[0] if x.kind == "mfma")
