@@ -495,6 +495,21 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
     float inv[TA];                                       // (all requested before the first is used)
 #pragma unroll
     for (int j = 0; j < TA; ++j) inv[j] = re.row_scale ? re.row_scale[min(m0 + (wm * TA + j) * 32 + l32, M - 1)] : 1.f;
+    // SwiGLU's two products per output only where there is a scale: they are not hidden here (129 x 4096 from 64 4.72 us, always multiplied 4.89).
+    if (EPI == EPI_SWIGLU) {
+        if (re.row_scale) {
+#pragma unroll
+            for (int j = 0; j < TA; ++j)
+#pragma unroll
+                for (int w = 0; w < NW; ++w)
+#pragma unroll
+                    for (int i = 0; i < TW; ++i)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[w][i][j][v] *= inv[j];
+        }
+#pragma unroll
+        for (int j = 0; j < TA; ++j) inv[j] = 1.f;
+    }
     // The epilogue reuses the stage buffers: every wave must be past its last fragment reads.
     __builtin_amdgcn_s_waitcnt(0x0070);
     workgroup_barrier();
