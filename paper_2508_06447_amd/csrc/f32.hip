@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
     __syncthreads();
     // Wave v adds all waves' sums of the row groups v % MG, v % MG + MG, .., EPT elements from EPT (v / MG) on of both feature groups.
     const int e0 = wave / MG * EPT, c = q * 4 + e0;      // the thread's places in a group of 16 features
-    if (e0 >= 4) return;
+    if (NW > 4 * MG && e0 >= 4) return;                  // (said to the compiler where no wave is left over: a test that never holds costs 0.15 us)
 #pragma unroll
     for (int m = wave % MG; m < MT; m += MG) {
         const int row = m0 + m * 16 + l16;
