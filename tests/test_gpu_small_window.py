@@ -72,8 +72,8 @@ def test_float32_window_query_of_a_scoring_launch(slim, w, Hq, Hkv, d):
 
 @pytest.mark.parametrize("nb", [5, 256, 1000, 1024, 1025, 4096])
 @pytest.mark.parametrize("kind", ["first digit", "second digit", "last digit", "equal"])
-def test_selection_ends_at_any_digit(slim, nb, kind):
-    """The digit at which every candidate from the threshold up is taken: the sign and exponent, further ones, the last, or never (ties)."""
+def test_selection_of_scores_that_differ_in_one_digit(slim, nb, kind):
+    """Scores that differ in the sign and exponent, in a further digit, in the last, or not at all, at kept counts that end the search anywhere."""
     g = np.random.default_rng(nb)
     bits = {"first digit": np.where(np.arange(nb) % 3 == 0, 0x42000000, 0x3f800000), "second digit": 0x3f800000 + (g.permutation(nb) % 64 << 16),
             "last digit": 0x3f800000 + g.permutation(nb), "equal": np.full(nb, 0x3f800000)}[kind]
@@ -81,3 +81,41 @@ def test_selection_ends_at_any_digit(slim, nb, kind):
     for n_keep in sorted({2, max(2, (nb + 2) // 3), nb // 2 + 1, nb - 1}):
         kept = slim.slim_select_topk_blocks(torch.from_numpy(scores.copy()).cuda(), n_keep)
         np.testing.assert_array_equal(kept.cpu().numpy(), so.select_blocks(scores, n_keep))
+
+
+def last_digit_of_the_search(keys, take):
+    """Radix selection, eight bits at a time from the top: the digit at whose threshold every remaining candidate is taken; None: ties are left."""
+    for p in range(4):
+        digit = keys >> np.uint32(24 - 8 * p) & np.uint32(255)
+        count = np.bincount(digit, minlength=256)[::-1].cumsum()[::-1]       # candidates with this digit or a larger one
+        threshold = int(np.nonzero(count >= take)[0].max())
+        if count[threshold] == take:
+            return p
+        take -= count[threshold + 1] if threshold < 255 else 0
+        keys = keys[digit == threshold]
+    return None
+
+
+@pytest.mark.parametrize("flags", [0, 1, 2, 3])
+@pytest.mark.parametrize("digit", [0, 1, 2, 3])
+@pytest.mark.parametrize("nb", [5, 64, 65, 256, 257, 1000, 1024, 1025, 4096])
+def test_selection_ends_at_a_digit(slim, nb, digit, flags):
+    """A third of the blocks are above the others by the given digit, with anything in the digits below it: as many kept blocks end the search there; one fewer
+    and one more do not."""
+    g = np.random.default_rng(4 * nb + digit)
+    forced = sorted({0} if flags & slim.FORCE_FIRST else set()) + ([nb - 1] if flags & slim.FORCE_LAST else [])
+    free = np.setdiff1d(np.arange(nb), forced)
+    high = g.choice(free, len(free) // 3 + 1, replace=False)
+    shift = 24 - 8 * digit
+    keys = np.full(nb, 0xbf8a9b00 if digit else 0, np.uint32) >> np.uint32(shift + 8) << np.uint32(shift + 8) if digit else np.zeros(nb, np.uint32)
+    low_digit, high_digit = (0xbe, 0xc1) if digit == 0 else (0x21, 0x95)                # (a finite float in any case)
+    keys |= np.uint32(low_digit << shift)
+    keys[high] += np.uint32(high_digit - low_digit << shift)
+    keys |= (g.integers(0, 1 << shift, nb) if shift else np.zeros(nb)).astype(np.uint32)
+    scores = (keys & np.uint32(0x7fffffff)).view(np.float32)                             # keys of positive scores: their bits with the sign bit set
+    assert np.isfinite(scores).all()
+    ends = {take: last_digit_of_the_search(keys[free], take) for take in (len(high) - 1, len(high), len(high) + 1) if 0 < take < len(free)}
+    assert ends[len(high)] == digit and all(e != digit or digit == 3 for t, e in ends.items() if t != len(high)), ends
+    for take in ends:
+        kept = slim.slim_select_topk_blocks(torch.from_numpy(scores.copy()).cuda(), take + len(forced), flags)
+        np.testing.assert_array_equal(kept.cpu().numpy(), so.select_blocks(scores, take + len(forced), bool(flags & slim.FORCE_FIRST), bool(flags & slim.FORCE_LAST)))
