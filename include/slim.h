@@ -61,7 +61,8 @@ const char* slim_last_hip_error(void);
  *   k      [N, Hkv, d]      Key states of all prompt tokens (post-RoPE), dtype
  *   scores [nb]             out, float
  *   workspace               >= slim_score_blocks_workspace_bytes(Hkv, d) bytes, 256-byte aligned;
- *                           holds the head-group-summed window query between the two kernels.
+ *                           scratch for the head-group-summed window query; what it holds afterwards is
+ *                           unspecified (a small window never reaches it).
  * Errors: INVALID_ARG (null, sizes < 1, Hq % Hkv, unit > block), UNSUPPORTED ((Hkv*d) % 8 != 0 for
  * bf16 or % 4 for f32, or Hkv*d > 8192), WORKSPACE_TOO_SMALL.
  */
@@ -73,14 +74,14 @@ int slim_score_blocks(const void* q_win, const void* k, int n_tokens, int window
 /* ------------------------------------------------------------------------------------------------
  * slim_score_blocks for callers that cannot allocate device memory or pass a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and
- * results (bit for bit) as slim_score_blocks, minus the workspace: the head-group-summed window query
- * goes through a 32 KiB array that lives in the library's device image (one copy per GPU, held until the
+ * results (bit for bit) as slim_score_blocks, minus the workspace: its place is taken
+ * by a 32 KiB array that lives in the library's device image (one copy per GPU, held until the
  * process ends).  The call allocates and frees nothing.  The first call on a device looks up that
  * device's copy of the array (one runtime query, no allocation; make that first call outside a capture).
  * Limit: Hkv * head_dim <= 8192 (UNSUPPORTED beyond, as for slim_score_blocks).  Every call on one GPU
  * shares that GPU's array: calls that overlap on one GPU (different streams, or different threads)
- * race on it, so serialise them; the array keeps the last call's window query and every call overwrites
- * all of it that it reads.  Other errors as slim_score_blocks.
+ * race on it, so serialise them; every call writes what it reads of the array, and what the array holds
+ * afterwards is unspecified.  Other errors as slim_score_blocks.
  */
 int slim_score_blocks_static(const void* q_win, const void* k, int n_tokens, int window, int n_q_heads,
                              int n_kv_heads, int head_dim, int block, int unit, int dtype, float* scores,

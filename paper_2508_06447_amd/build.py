@@ -13,7 +13,8 @@ LIB = os.path.join(HERE, "libslim.so")
 PROBE_LIB = os.path.join(HERE, "libslim_probe.so")
 SOURCES = ("api.hip", "prune.hip", "norm_rope.hip", "gemm.hip", "split.hip", "attn.hip", "f32.hip", "kvswap.hip", "decode.hip", "gemv.hip", "window.hip", "probe.hip")
 # Kernel arguments in registers when a wave starts (up to 16 dwords): without it a kernel's first instructions wait for their way from host memory.
-# Per launch 0.1 to 0.25 us: five launches of scoring, selection and compaction 55.8 -> 54.5 us, ten of the small float32 layer 60.2 -> 59.3.
+# Per launch 0.1 to 0.25 us: the five launches of scoring, selection and compaction 54.0 -> 52.8 us, the small float32 layer's nine 49.6 -> 49.1, a decoded token's
+# layer 88.9 -> 88.6.
 FLAGS = ["-O3", "-mllvm", "-amdgpu-kernarg-preload-count=16", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 

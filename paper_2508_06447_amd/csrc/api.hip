@@ -183,7 +183,7 @@ int slim_score_blocks_static(const void* q_win, const void* k, int n_tokens, int
     float* qt = nullptr;
     const int rc = scratch_of_current_device(&qt);
     if (rc != SLIM_OK) return rc;
-    // Both kernels write every element of the scratch they read (qt[0 .. E)), so nothing needs clearing.
+    // A call reads of the scratch only what it has written (qt[0 .. E), or nothing where the scoring launch reduces the window), so nothing needs clearing.
     return launch_score(q_win, k, n_tokens, window, n_q_heads, n_kv_heads, head_dim, block, unit, 0, dtype, scores, qt,
                         (hipStream_t)stream);
 }

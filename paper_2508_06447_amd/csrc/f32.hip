@@ -69,7 +69,7 @@ template <int MT, int NW, int G, bool ONCE = false>
 __global__ void __launch_bounds__(64 * NW) f32_linear_kernel(F32LinearArgs p) {
     constexpr int MG = MT > 1 ? 2 : 1;                   // row groups that the waves take side by side behind the sum
     constexpr int EPT = 4 * MG >= NW ? 4 * MG / NW : 1;  // and elements of a tile group per thread
-    __shared__ f32x4 red[NW][2 * MT][64];                // [wave][feature group * MT + row group][lane], 32 KB
+    __shared__ f32x4 red[NW][2 * MT][64];                // [wave][feature group * MT + row group][lane], 32 KB (MT = 1: 16)
     __shared__ float red_ss[NW][16 * MT];
     const int id = blockIdx.x, s = (id >= p.tile_end[0]) + (id >= p.tile_end[1]);
     // In the smallest launches all three segments are requested with the tile ids: an index would make theirs a second trip to the arguments.
