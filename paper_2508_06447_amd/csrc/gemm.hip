@@ -907,13 +907,11 @@ static int plan_big_tiles(int M, int tiles_n, int n_cu, double small_cost, bool 
 
 // Which tile the residual epilogue runs in.  The 4-wave tile takes the residual tile in as MFMA fragments (16-byte loads
 // at the lane's own rows and features), which needs every tile to have all of its features and 16-byte aligned rows of
-// R.  Measured against the 8-wave tile on one machine, 4096 features out: with rows of 4096 (output projection) it is
-// the faster one at every token count from 2048 to 32768 (-1.5 % to -6 %; -4 % inside the layer at 9856 tokens); with
-// rows of 14336 (down projection) it is 1-2 % faster while the activation matrix sits in the 256 MB memory-side cache
-// and 4-7 % slower once that matrix streams from HBM (282 MB at 9856 tokens), where the 8-wave tile, which issues a
-// k-tile's loads at once and so leaves them longest to arrive, wins.  The 8-wave tile's epilogue parks a coalesced copy
-// of the tile of R in LDS and takes any shape.  (Long rows that can be cut into rounds never stream: residual_round_rows.  What is left to the
-// 8-wave tile are features that are no multiple of 256 and widths whose rounds do not fill the chip.)
+// R.  The 8-wave tile's epilogue parks a coalesced copy of the tile of R in LDS and takes any shape; it issues a k-tile's loads at once.
+// One launch of either, all rows (us, 4 waves / 8 waves): 4096 features from 4096, 4096 rows 96 / 116, 9856 232 / 290, 32768 783 / 955; from 14336, 4096 rows
+// 307 / 380, 9856 786 / 1005, 32768 2647 / 3176; 6656 from 14336, 6000 rows 837 / 1004, 16384 rows 2187 / 2586.
+// The bound on long activation rows was drawn with the 4-wave loops before these, which lost 4-7 % once the rows streamed from HBM; these do not lose, and
+// of the shapes that the 4-wave tile could take, widths whose rounds do not fill the chip (6656; residual_round_rows) still go to the 8-wave tile.
 constexpr size_t kResidualCacheBytes = (size_t)176 << 20;
 static bool residual_in_four_waves(const bf16_t* R, int M, int N, int K, int ldo) {
     const size_t activation_bytes = (size_t)M * K * sizeof(bf16_t);
@@ -921,9 +919,9 @@ static bool residual_in_four_waves(const bf16_t* R, int M, int N, int K, int ldo
            (K <= 8192 || activation_bytes <= kResidualCacheBytes);
 }
 
-// What a 128-token tile costs next to a 256-token one of the same launch (measured k-loop + epilogue times): the
-// 4-wave small tiles run 8 MFMAs per k-step against 6 fragment reads and 3 tile loads (SwiGLU: 8 against 6 and 3,
-// with the longer epilogue per output), the 8-wave ones keep the ratio of the large tile.
+// What a 128-token tile costs next to a 256-token one of the same launch.  Launches of exactly a round (us, 256-token tiles / 128-token tiles, half the rows): 4096
+// features from 1024 31.2 / 19.9, from 4096 94 / 52, from 14336 300 / 165, with residual 34.3 / 21.1, 96 / 54, 304 / 167 (8 waves 40 / 24, 117 / 66, 379 / 206); SwiGLU,
+// 8192 from 1024 29.7 / 18.1, from 4096 91 / 51.  Rows that come from HBM cost small tiles more: 8192 rows of 14336 605 in large ones, 749 in small.
 template <int EPI> constexpr double small_tile_cost(bool eight_waves) {
     return eight_waves ? 0.5 : (EPI == EPI_SWIGLU ? 0.7 : 0.6);
 }
@@ -944,11 +942,10 @@ static int cu_count() {
 // activation panels and each on its own weight panels (with one run of tiles per XCD over the whole launch they work on eight distant
 // row bands).  0: one group.
 // Only where the group fills the chip to 85 %, divides evenly over the XCDs and leaves some CUs: groups of exactly a round lose (us without / with:
-// 8192 features from 1024, 27136 rows 402 / 439; SwiGLU, 8192 from 2048, 16384 rows 885 / 922; 4096 from 4096, 40960 rows 1059 / 1093).
-// From 8 rounds of large tiles on: SwiGLU projection, 14336 features (112 tiles, groups of 2 x 112): 6000 rows 1075 -> 1044 us, 9856 1804 -> 1720, 20000 3690 ->
-// 3431, 26240 4733 -> 4488; Query + Value (20 tiles, 12 x 20; 26240 rows are fewer rounds): 32768 rows 1142 -> 1069, 40960 1410 -> 1312.  With fewer
-// rounds it is 3 % faster alone (SwiGLU, 4096 rows 711 -> 689) and 0.3 to 0.5 % slower in a layer, whose rows are still in the caches.  18944 features (148 tiles) have no such group: with 2 x 148
-// between 8 % faster and 4 % slower.  Residual and RoPE launches measure the same either way.
+// 8192 features from 1024, 27136 rows 364 / 393; with a second matrix of 256 features 380 / 483).
+// From 8 rounds of large tiles on: SwiGLU projection, 14336 features (112 tiles, groups of 2 x 112): 9856 rows 1524 -> 1506, 20000 3122 -> 3098, 26240 4036 ->
+// 4029 (6000 rows 934 / 937); Query + Value (20 tiles, 12 x 20; 26240 rows are fewer rounds, 786 / 753): 32768 rows 969 -> 928, 40960 1210 -> 1157.
+// 18944 features (148 tiles) have no such group, and the nearest, 2 x 148, changes nothing.  Residual and RoPE launches measure the same either way.
 static int rounds_of(int big_tiles_m, int tiles_n) {
     const int rm = cu_count() / tiles_n;
     return rm >= 2 && (long long)big_tiles_m * tiles_n >= 8ll * cu_count() && rm * tiles_n * 100 >= cu_count() * 85 && rm * tiles_n < cu_count() && rm * tiles_n % 8 == 0 ? rm : 0;
@@ -1021,12 +1018,12 @@ static FewShape few_shape(int M, const int* n, int count, int splits) {
     return FEW_D;
 }
 
-// Up to how many outputs the few-row tiles beat the two-size launch, whose 256-token tiles then leave CUs idle: 4096
-// features, k_in 14336, residual: 1511 rows 195 against 271 us, 2048 rows (2^23 outputs) 214 against 278, 2300 rows 355
-// against 302; k_in 4096: 1511 rows 53 against 58, 2048 rows 65 both.  Key projection (1024 features) with rotation and
-// scores: 4096 rows 53 against 58 us, 8192 rows 78 against 82.
-// And only where their 256 x 128 tiles are no more than a round: k_in 4096, 5120 features, 1600 rows (260 tiles) 106 against 80, 1040 features, 7000 rows
-// (275) 101 against 79; 520 from 1024, 11000 rows (258) 30 against 24.
+// Up to how many outputs the few-row tiles are taken.  The line was drawn against the two-size launch with 32 x 32 x 16 loops; against the present ones (us, few-row /
+// two-size): 4096 features from 4096, 768 rows 32 / 37, 1024 37 / 42, 1280 48 / 39, 1511 52 / 43, 2048 62 / 52; from 14336 with residual 1024 rows 122 / 134, 1280 159 /
+// 128, 1511 170 / 138, 2048 206 / 169; 3584 from 3584, 1024 rows 34 / 37, 1511 46 / 38; 1024 features, 3000 rows 32 / 38, 4096 37 / 41, 6000 51 / 42, 8192 62 / 76.
+// So from 128 tiles of 256 x 128 up to a round of them the two-size launch is now the faster one, except where it begins a second round.
+// And only where their 256 x 128 tiles are no more than a round: k_in 4096, 5120 features, 1600 rows (260 tiles) 111 against 83, 4096 features, 2300 rows (288)
+// 103 against 76.
 bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23) && (m + 127ll) / 128 * ((n + 255ll) / 256) <= cu_count(); }
 
 // The most rows up to m that few_rows takes.
@@ -1087,9 +1084,9 @@ int launch_split_gemm(const void* a, int lda, const SplitMats& mats, int m, int 
 
 // Rows per launch of a residual projection with long rows (down projection): one round of 256 x 256 tiles, if its rows of A stay in the
 // memory-side cache and it fills the chip.  As one launch the tiles of all rows drift apart, the rows come from HBM once per
-// group of feature tiles, and the last round is as long as a full one.  4096 features from 14336, one launch -> rounds (us): 5000 rows 647 ->
-// 540, 7000 857 -> 699, 9856 1014 -> 954, 16384 1651 -> 1536, 26240 2543 -> 2468; 3584 from 18944 (rounds of 4608 rows, 167 MB): 9216
-// 1209 -> 988, 12288 1601 -> 1427, 20000 2304 -> 2236.  With rows of 4096 the same cut is 4 % slower at 9856 rows, so it is not made there.
+// group of feature tiles, and the last round is as long as a full one.  4-wave tiles, one launch / rounds (us): 4096 features from 14336, 6000 rows 476 / 507, 8192 612 /
+// 610, 9856 786 / 797, 16384 1394 / 1229, 32768 2647 / 2455; 3584 from 18944 (rounds of 4608 rows, 167 MB), 6000 rows 618 / 636, 9216 831 / 817, 12288 1188 / 1181.
+// With rows of 4096 the same cut is 4 % slower at 9856 rows, so it is not made there.
 static int residual_round_rows(const void* R, int N, int K, int ldo) {
     if (K <= 8192 || N % 256 != 0 || ldo % 8 != 0 || ((uintptr_t)R & 15)) return 0;
     const int tiles_n = N / 256, tm = cu_count() / tiles_n;
@@ -1102,7 +1099,8 @@ static int residual_round_rows(const void* R, int N, int K, int ldo) {
 // 137, 1280 rows, 3 138 / 193, 1511 rows, 2 174 / 190, 1664 rows, 2 180 / 200; 3584 from 18944: 1024 rows, 4 128 / 174, 1500 rows, 3 191 / 244.
 // Up to 512 rows the few-row tiles: 1 / 2 / 4 / 8 splits of 14336 take 73 / 43 / 39 / 38 us for 128 rows, 101 / 75 / 67 / 73 for 300, 106 / 82 /
 // 79 / 90 for 512.  Large tiles: one round of workgroups; or 3 splits that make two full ones (2500 rows 274 / 278, 3072 rows of 18944 363 / 434).  No gain is left at 113
-// tiles and more (2 splits: 1904 rows 199 / 202, 2300 rows of 18944 286 / 276).
+// tiles and more (2 splits: 1904 rows 199 / 202, 2300 rows of 18944 286 / 276).  Those figures are the 32 x 32 x 16 loops'; with the present ones, whole layers without
+// and with 2 splits: 1904 rows 774 / 745, 2048 rows 798 / 765, 2300 rows of 18944 961 / 909 (and 1511 rows 685 / 641, 1664 rows 697 / 654, which are split).
 static int large_splits(long long tiles_m, int n) {      // for so many 256-row tiles; 1: none
     const long long tiles = tiles_m * ((n + 255) / 256), cu = cu_count();
     long long s = 1;
@@ -1167,10 +1165,10 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
         }
     }
     if constexpr (EPI == EPI_SWIGLU) {
-        // Up to 256 rows the launch streams the weights: 64-feature tiles keep more of it in flight (14336 features, us: 64 rows
-        // 66 -> 49, 128 rows 65 -> 54, 200 rows 85 -> 64; at 300 rows the two-size launch is ahead, 95 against 105).  A second round of
-        // them, one to a CU, costs more than it saves: with two stages two fit a CU, and the two-size launch takes more than 128 rows (18944 features: 64
-        // rows 61 -> 57, 200 rows 96 -> 82, 256 rows 102 -> 84).  From three rounds on it does not (36864 features, 200 rows 215 against 184).
+        // Up to 256 rows the launch streams the weights: 64-feature tiles keep more of it in flight.  A second round of
+        // them, one to a CU, costs more than it saves: with two stages two fit a CU, and the two-size launch takes more than 128 rows.  From three rounds on it
+        // does not.  us, 64-feature tiles / two-size launch, weights again and again from the memory-side cache: 14336 features, 64 rows 36 / 39, 128 rows 37 / 42,
+        // 200 rows 58 / 47, 300 rows 100 / 81; 18944 features, 200 rows 94 / 68; 36864 features (from HBM), 64 rows 136 / 159, 200 rows 180 / 191.
         const int tiles = (N + 63) / 64;
         const bool second_round = tiles > cu_count() && tiles <= 2 * cu_count();
         if (M <= 128 && second_round) return launch_bf16<1, 1, 2, 4, EPI, false, 2>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);

@@ -26,7 +26,8 @@ With two slots for each operand (loads over three quarters of the way to the bar
 do not reach the power limit, ran at 1440 (8192 x 4096 from 14336) and 1710 TFLOP/s (8192^3); with the third weight slot 1870 and 2080.  So
 the activation tile goes first, and the weight tile behind it has until the barrier after the next.  Normal operands, two -> three slots (us):
 down projection 4096 x 4096 from 14336 353 -> 319, 9856 rows 864 -> 823, 12288 x 3584 from 18944 1314 -> 1205; SwiGLU 4096 x 14336 from 4096 663
--> 643; 8192^3 731 -> 707.  (Launches of less than a round with short rows lose: Query + Value of 2000 rows 73.5 -> 75.)  The slots are
+-> 643; 8192^3 731 -> 707.  (Launches of less than a round with short rows lose 2 %: Query + Value of 2000 rows 73.5 -> 75, 85 -> 80 with what the 16 x 16 x 32
+instruction gives.)  Products of one k-tile leave the rings alone.  The slots are
 immediate offsets and the loop six k-tiles long; one k-tile with the slots in registers takes four vector instructions per k-tile and is 1 % slower.
 """
 import os

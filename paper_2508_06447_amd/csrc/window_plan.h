@@ -13,9 +13,9 @@ struct WindowPlan { int slices, threads; };
 //  - few, in a launch whose workgroups all run at once: up to 16 MB of them, 8 MB with more than 32 pairs, whose sums over the slices take longer; or
 //  - no more than half of what the workgroup reads in keys, if that is 16 KB at least: then they hide under the keys' way from HBM.
 // Replayed as a graph, own launch -> inside (us), bf16 where not said:
-//   inside:  scores of 32768 tokens' keys, blocks of 64, 32 / 8 heads of 128, 4 tokens of window 14.6 -> 12.1, 8 tokens 14.5 -> 13.9; 28 / 4 heads, blocks of 128,
-//            8 tokens 7.5 -> 7.0; 131072 tokens, blocks of 32, 4 tokens 42.5 -> 38.6; one unit per block of 64, 4 tokens 20.9 -> 15.7 (one wave
-//            widened to four); from unit keys 32768 tokens, 4 tokens 6.3 -> 6.3 (16 MB), 16384 tokens 5.7 -> 5.2, blocks of 16 of one unit, 4096 tokens 9.3 -> 4.7
+//   inside:  scores of 32768 tokens' keys, blocks of 64, 32 / 8 heads of 128, 4 tokens of window 14.5 -> 12.2, 8 tokens 14.6 -> 13.9; 28 / 4 heads, blocks of 128,
+//            8 tokens 7.5 -> 7.0; 131072 tokens, blocks of 32, 4 tokens 42.4 -> 39.5; one unit per block of 64, 4 tokens 20.9 -> 15.7 (one wave
+//            widened to four); from unit keys 32768 tokens, 4 tokens 6.3 -> 6.2 (16 MB), one unit per block of 64 9.4 -> 5.3, 300 tokens in blocks of 16 8.7 -> 4.5
 //   not:     blocks of 8, 8 tokens, 32768 tokens' keys 19.2 -> 31.8, unit keys 10.4 -> 26.6; 131072 tokens' unit keys, blocks of 64, 4 tokens 15.5 -> 19.1; 8 / 1 heads
 //            of 64, 131072 tokens, blocks of 64, 8 tokens: keys 10.6 -> 12.4, unit keys 7.4 -> 11.6; 128 pairs, 16 MB 5.2 -> 5.7; 56 pairs, 14 MB 5.6 -> 6.1;
 //            keys of 2 KB per workgroup (131072 tokens, 4 / 2 heads of 64, blocks of 8) 11.2 -> 14.0
