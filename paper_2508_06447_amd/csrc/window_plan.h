@@ -19,7 +19,10 @@ struct WindowPlan { int slices, threads; };
 //   not:     blocks of 8, 8 tokens, 32768 tokens' keys 19.2 -> 31.8, unit keys 10.4 -> 26.6; 131072 tokens' unit keys, blocks of 64, 4 tokens 15.5 -> 19.1; 8 / 1 heads
 //            of 64, 131072 tokens, blocks of 64, 8 tokens: keys 10.6 -> 12.4, unit keys 7.4 -> 11.6; 128 pairs, 16 MB 5.2 -> 5.7; 56 pairs, 14 MB 5.6 -> 6.1;
 //            keys of 2 KB per workgroup (131072 tokens, 4 / 2 heads of 64, blocks of 8) 11.2 -> 14.0
-// Launched one by one the launch that is saved is another 1.5 to 2 us.
+// Launched one by one the launch that is saved is another 1.5 to 2 us, so the lines lie where the two ways of calling balance.  Unit keys in blocks of 64, 4 tokens, in a graph
+// and launched by the host: 24576 tokens (12 MB) 6.2 -> 6.1 and 7.7 -> 6.2, 32768 (16 MB, 4096 waves) 6.2 -> 6.2 and 7.7 -> 6.2, 36864 6.7 -> 7.2 and 7.7 -> 7.3, 49152 6.7 -> 7.3
+// and 7.7 -> 7.4, 65536 7.8 -> 9.4 and 7.9 -> 9.4; 28 / 4 heads, 32768 tokens (14 MB, 28 pairs) 5.5 -> 5.9 and 7.6 -> 6.0.  More waves than run at once: blocks of 128, 49152
+// tokens (6144 waves, 12 MB) 7.7 -> 8.9 and 7.9 -> 8.9.
 constexpr int kWinPairs = 64, kWinRounds = 2;
 constexpr long long kWinWaves = 4096;                    // 16 per CU: what certainly runs at once
 constexpr long long kWinRead = 16ll << 20, kWinReadMany = 8ll << 20;
