@@ -539,8 +539,9 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
 //   wlim / alim       last valid row of the tile (loads of rows beyond it are clamped to it; never stored);
 //   strides in bytes, kt = K / 64, and the three tile origins.
 // The tile starts at token m0, feature n0; M and N bound the loads and the stores.  row_scale as in gemm_tile.  KT: k-tiles to run
-// over when that is not all of K (EPI_PARTIAL).
-template <int TW, int TA, int EPI>
+// over when that is not all of K (EPI_PARTIAL).  SCALED: there may be a row_scale (without one, a factor of one per output and two for SwiGLU cost
+// products of few k-tiles 1 to 3 %, see gemm_bf16_two_size_unscaled_kernel).
+template <int TW, int TA, int EPI, bool SCALED = true>
 __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
                                            const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M,
                                            int N, int K, int m0, int n0, unsigned char* lds, const EpiExtra& re, int KT = 0) {
@@ -586,7 +587,7 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
     float inv[2 * TA];                                   // (all requested before the first is used)
 #pragma unroll
     for (int j = 0; j < 2 * TA; ++j)
-        inv[j] = re.row_scale ? re.row_scale[min(m0 + wm * TA * 32 + j * 16 + (lane_e & 15), M - 1)] : 1.f;
+        inv[j] = SCALED && re.row_scale ? re.row_scale[min(m0 + wm * TA * 32 + j * 16 + (lane_e & 15), M - 1)] : 1.f;
     // The epilogue reuses the stage buffers: every wave must be past its last fragment reads and tile loads.
     __builtin_amdgcn_s_waitcnt(0x0070);
     workgroup_barrier();
@@ -633,11 +634,10 @@ template <int EPI> struct TileShapes {
 // Two tile sizes in one launch.  Workgroups are started in id order, so the 256-token tiles run first
 // and the 128-token tiles fill the last, partly empty round of workgroups: the tail of the launch costs
 // about half a tile time instead of a whole one, and a ragged last token-tile wastes no MFMA work.
-template <int EPI>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-gemm_bf16_two_size_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
-                          const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M, int N, int K,
-                          int big_tiles_m, int small_tiles_m, int tiles_n, EpiExtra re) {
+template <int EPI, bool SCALED>
+__device__ __forceinline__ void two_size_tile(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
+                                              const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M, int N, int K,
+                                              int big_tiles_m, int small_tiles_m, int tiles_n, const EpiExtra& re) {
     using S = TileShapes<EPI>;
     extern __shared__ __align__(16) unsigned char lds[];
     const int n_big = big_tiles_m * tiles_n;
@@ -655,10 +655,28 @@ gemm_bf16_two_size_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* _
         tn -= re.tiles_n1;
     }
     if (big)
-        gemm_tile4<S::TW, S::TA_BIG, EPI>(A, lda, W0, W1, R, C, ldo, M, N, K, tm * S::BM_BIG, tn * S::BN, lds, re);
+        gemm_tile4<S::TW, S::TA_BIG, EPI, SCALED>(A, lda, W0, W1, R, C, ldo, M, N, K, tm * S::BM_BIG, tn * S::BN, lds, re);
     else
-        gemm_tile4<S::TW, S::TA_SMALL, EPI>(A, lda, W0, W1, R, C, ldo, M, N, K,
-                                            big_tiles_m * S::BM_BIG + tm * S::BM_SMALL, tn * S::BN, lds, re);
+        gemm_tile4<S::TW, S::TA_SMALL, EPI, SCALED>(A, lda, W0, W1, R, C, ldo, M, N, K,
+                                                    big_tiles_m * S::BM_BIG + tm * S::BM_SMALL, tn * S::BN, lds, re);
+}
+
+template <int EPI>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+gemm_bf16_two_size_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
+                          const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M, int N, int K,
+                          int big_tiles_m, int small_tiles_m, int tiles_n, EpiExtra re) {
+    two_size_tile<EPI, EPI != EPI_RESIDUAL>(A, lda, W0, W1, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m, tiles_n, re);
+}
+
+// Plain and SwiGLU without a row scale.  us, two LDS slots and the scale under a branch / three slots and a factor of one / so: 12345 x 4096 from 128 36.2 / 37.3 / 35.3,
+// SwiGLU of 16384 rows 76.2 / 77.7 / 72.9; 12345 x 4096 from 64 31.4 / 31.8 / 29.6, SwiGLU 49.2 / 48.5 / 44.2.
+template <int EPI>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+gemm_bf16_two_size_unscaled_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
+                                   const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M, int N, int K,
+                                   int big_tiles_m, int small_tiles_m, int tiles_n, EpiExtra re) {
+    two_size_tile<EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m, tiles_n, re);
 }
 
 // Query, Key and Value projections of the same rows in one launch: the feature tiles of the Keys (128-wide heads, rotated in the
@@ -978,11 +996,15 @@ static int launch_two_size(const bf16_t* A, int lda, const bf16_t* W0, const bf1
         hipLaunchKernelGGL(kern, grid, dim3(512), smem8, st, A, lda, W0, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m, tiles_n,
                            band);
     } else {
-        auto kern = gemm_bf16_two_size_kernel<EPI>;
+        auto kern = gemm_bf16_two_size_kernel<EPI>, unscaled = kern;
+        if constexpr (EPI == EPI_PLAIN || EPI == EPI_SWIGLU) unscaled = gemm_bf16_two_size_unscaled_kernel<EPI>;
         std::call_once(attr_once, [&] {
-            attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingBytes);
+            for (auto k : {kern, unscaled})
+                if (attr_err == hipSuccess) attr_err = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingBytes);
         });
         if (attr_err != hipSuccess) return set_hip_error(attr_err);
+        if (EPI == EPI_RESIDUAL && re.row_scale) return SLIM_UNSUPPORTED;      // (no caller has both)
+        if (!re.row_scale) kern = unscaled;
         EpiExtra walk = re;
         if (EPI == EPI_SWIGLU || EPI == EPI_PLAIN || EPI == EPI_BIAS) walk.round_m = rounds_of(big_tiles_m, tiles_n);
         hipLaunchKernelGGL(kern, grid, dim3(256), kRingBytes, st, A, lda, W0, W1, R, C, ldo, M, N, K, big_tiles_m, small_tiles_m,
