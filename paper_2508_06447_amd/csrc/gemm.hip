@@ -356,6 +356,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
     static_assert(NS >= 2 && NS <= 5, "the k-loop is written out for up to 5 stages");
     static_assert(EPI != EPI_ROPE || TW == 4, "the RoPE epilogue needs one 128-wide head per wave");
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
+    constexpr bool SPREAD = NS >= 3;
     constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM, WROWS = BN * NW;
     constexpr int STAGE = (WROWS + BM) * BK * 2;
     constexpr int LR = WV * 8;                           // tile rows that one wave-load of every wave covers
@@ -386,15 +387,17 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
     const bf16_t* w1base = NW == 2 ? W1 + (size_t)n0 * K : W0;
     const bf16_t* abase = A + (size_t)m0 * lda;
     const unsigned lds_wave = (unsigned)(uintptr_t)lds + wave * 1024;
-    auto issue_loads = [&](int k0, int stage) {
+    auto issue_part = [&](int k0, int stage, int from, int to) {   // wave-loads from .. to - 1 of a k-tile
         const unsigned ws = lds_wave + stage * STAGE, as = ws + WROWS * BK * 2;
 #pragma unroll
         for (int i = 0; i < WLD; ++i) {
+            if (i < from || i >= to) continue;
             const bool second = NW == 2 && (i * LR >= BN);       // rows of wave-load i lie in one matrix (BN % LR == 0)
             load_global_to_lds16((second ? w1base : w0base) + k0, woff[i], ws + i * WV * 1024);
         }
 #pragma unroll
-        for (int i = 0; i < ALD; ++i) load_global_to_lds16(abase + k0, aoff[i], as + i * WV * 1024);
+        for (int i = 0; i < ALD; ++i)
+            if (WLD + i >= from && WLD + i < to) load_global_to_lds16(abase + k0, aoff[i], as + i * WV * 1024);
     };
 
     f32x16 acc[NW][TW][TA];
@@ -449,27 +452,31 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
     // stage of every read is a compile-time constant.  Loads past the last k-tile re-read it (into a stage
     // that nobody reads), so the number of loads in flight at a wait is a constant.
     constexpr unsigned kStageLoads = WLD + ALD;
-    constexpr unsigned kFly = (NS - 2) * kStageLoads, kPro = (NS - 1) * kStageLoads;   // in flight behind a wait
+    constexpr unsigned kParts = SPREAD ? 4 : 1;
+    auto part = [](unsigned p) { return (int)(p * kStageLoads / kParts); };
+    constexpr unsigned kFly = (NS - 2) * kStageLoads, kPro = SPREAD ? kFly + kStageLoads / kParts : (NS - 1) * kStageLoads;   // in flight behind a wait
     auto k_tile = [&](int kt, auto stage_c) {
         constexpr int stage = decltype(stage_c)::value;
         using Next = std::integral_constant<int, (stage + 1) % NS>;
 #pragma unroll
         for (int ks = 0; ks < BK / 16 - 1; ++ks) {
             load_frags(stage_c, ks + 1, (ks + 1) & 1);
+            if (SPREAD) issue_part(min(kt + NS - 1, KT - 1) * BK, (stage + NS - 1) % NS, part(ks + 1), part(ks + 2));
             __builtin_amdgcn_sched_barrier(0);           // keep the next step's LDS reads ahead of these MFMAs
             mfmas(ks & 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_waitcnt((kFly & 15) | 0x0070 | ((kFly >> 4) << 14));   // own reads of this stage and own part of tile kt+1 done
         workgroup_barrier();
-        issue_loads(min(kt + NS, KT - 1) * BK, stage);
+        if (!SPREAD) issue_part(min(kt + NS, KT - 1) * BK, stage, 0, kStageLoads);
         load_frags(Next{}, 0, 0);
+        if (SPREAD) issue_part(min(kt + NS, KT - 1) * BK, stage, 0, part(1));
         __builtin_amdgcn_sched_barrier(0);
         mfmas((BK / 16 - 1) & 1);
         __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
-    for (int st = 0; st < NS; ++st) issue_loads(min(st, KT - 1) * BK, st);
+    for (int st = 0; st < NS; ++st) issue_part(min(st, KT - 1) * BK, st, 0, st < NS - 1 ? (int)kStageLoads : part(1));
     // only the first k-tile has to be there; the others stay in flight until the k-tiles' own waits
     __builtin_amdgcn_s_waitcnt((kPro & 15) | 0x0070 | ((kPro >> 4) << 14));
     workgroup_barrier();
