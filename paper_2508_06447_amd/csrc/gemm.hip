@@ -1047,13 +1047,15 @@ static FewShape few_shape(int M, const int* n, int count, int splits) {
     return FEW_D;
 }
 
-// Up to how many outputs the few-row tiles are taken.  The line was drawn against the two-size launch with 32 x 32 x 16 loops; against the present ones (us, few-row /
-// two-size): 4096 features from 4096, 768 rows 32 / 37, 1024 37 / 42, 1280 48 / 39, 1511 52 / 43, 2048 62 / 52; from 14336 with residual 1024 rows 122 / 134, 1280 159 /
-// 128, 1511 170 / 138, 2048 206 / 169; 3584 from 3584, 1024 rows 34 / 37, 1511 46 / 38; 1024 features, 3000 rows 32 / 38, 4096 37 / 41, 6000 51 / 42, 8192 62 / 76.
-// So from 128 tiles of 256 x 128 up to a round of them the two-size launch is now the faster one, except where it begins a second round.
-// And only where their 256 x 128 tiles are no more than a round: k_in 4096, 5120 features, 1600 rows (260 tiles) 111 against 83, 4096 features, 2300 rows (288)
-// 103 against 76.
+// Up to how many outputs the few-row tiles are taken, and only where their 256 x 128 tiles are no more than a round.  us, weights from HBM, few-row / two-size: 4096
+// features from 4096, 512 rows 31 / 53, 1024 39 / 54, 1280 to 1664 53 / 53, 2300 (288 tiles) 91 / 69; 5120 features, 1664 rows (260 tiles) 94 / 73; 1024 features, 3000 rows
+// 28 / 38, 4096 33 / 38, 6000 47 / 42, 8192 57 / 67; 512 features from 3584, 12000 rows 41 / 59.
 bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23) && (m + 127ll) / 128 * ((n + 255ll) / 256) <= cu_count(); }
+
+// Of these, the launches that the two-size tiles are faster at all the same: nearly a round of 256 x 128 tiles of a wide output.  us, few-row / two-size, with residual: 4096
+// features from 4096, 1664 rows (208 tiles) 57 / 56, 1800 (240) 58 / 52, 2048 (256) 62 / 57, from 14336 2048 rows 199 / 190; 3584 from 3584, 1800 rows (210) 50 / 49, 2048 (224) 53 /
+// 51, 2300 (252) 57 / 54; 5120 from 4096, 1511 rows (240) 57 / 54.
+static bool nearly_a_round(int m, int n) { return n >= 2048 && (m + 127ll) / 128 * ((n + 255ll) / 256) * 16 > cu_count() * 13ll; }
 
 // The most rows up to m that few_rows takes.
 int few_rows_most(int m, int n) {
@@ -1127,14 +1129,14 @@ static int residual_round_rows(const void* R, int N, int K, int ldo) {
 // 4096 features from 14336, with the finishing pass, large tiles against the unsplit few-row ones (us): 768 rows, 5 splits 92 / 132, 1024 rows, 4 113 /
 // 137, 1280 rows, 3 138 / 193, 1511 rows, 2 174 / 190, 1664 rows, 2 180 / 200; 3584 from 18944: 1024 rows, 4 128 / 174, 1500 rows, 3 191 / 244.
 // Up to 512 rows the few-row tiles: 1 / 2 / 4 / 8 splits of 14336 take 73 / 43 / 39 / 38 us for 128 rows, 101 / 75 / 67 / 73 for 300, 106 / 82 /
-// 79 / 90 for 512.  Large tiles: one round of workgroups; or 3 splits that make two full ones (2500 rows 274 / 278, 3072 rows of 18944 363 / 434).  No gain is left at 113
-// tiles and more (2 splits: 1904 rows 199 / 202, 2300 rows of 18944 286 / 276).  Those figures are the 32 x 32 x 16 loops'; with the present ones, whole layers without
-// and with 2 splits: 1904 rows 774 / 745, 2048 rows 798 / 765, 2300 rows of 18944 961 / 909 (and 1511 rows 685 / 641, 1664 rows 697 / 654, which are split).
+// 79 / 90 for 512.  Large tiles: one round of workgroups; or 3 splits that make 1.64 rounds and more, of two.  Whole layers, not split / split (us): 2 splits 1904 rows 799 / 780,
+// 2048 (128 tiles) 830 / 804, 2300 rows of 18944 1000 / 971; 3 splits 2200 rows 920 / 899, 2304 (144 tiles) 921 / 902, of 18944 2560 rows (140 tiles) 1120 / 1088, 2816 1236 / 1196,
+// 3072 1321 / 1263.  Not with 176 tiles (2600 rows 1070 / 1121) or with 2 splits of more than a round (2200 rows 950).
 static int large_splits(long long tiles_m, int n) {      // for so many 256-row tiles; 1: none
     const long long tiles = tiles_m * ((n + 255) / 256), cu = cu_count();
     long long s = 1;
-    if (tiles * 16 <= 7 * cu) s = std::min<long long>(8, cu / tiles);
-    else if (3 * tiles <= 2 * cu && 3 * tiles * 100 >= 184 * cu) s = 3;
+    if (tiles * 2 <= cu) s = std::min<long long>(8, cu / tiles);
+    else if (3 * tiles <= 2 * cu && 3 * tiles * 100 >= 164 * cu) s = 3;
     return 2 * tiles * s < cu ? 1 : (int)s;              // (narrow outputs leave the large tiles' launch half empty)
 }
 
@@ -1205,7 +1207,7 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
         if (M <= 256 && !second_round) return launch_bf16<1, 2, 2, 4, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
     } else if constexpr (EPI == EPI_ROPE) {
         if (M <= 128) return launch_bf16<4, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-    } else if (few_rows(M, N)) {
+    } else if (few_rows(M, N) && !nearly_a_round(M, N)) {
         switch (few_shape(M, &N, 1, 1)) {
             case FEW_A: return launch_bf16<2, 2, 4, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
             case FEW_B: return launch_bf16<2, 2, 2, 2, EPI, false, 4>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);

@@ -1,0 +1,53 @@
+"""Row counts at which a projection changes its kernel or its split, and what the first pass over the rows leaves behind."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import slim_oracle as so
+from paper_2508_06447_amd import inputs
+from tests.helpers import assert_residual_close, f64, oracle_shape, oracle_weights
+from tests.test_gpu_layer import run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def slim():
+    import paper_2508_06447_amd as slim
+    slim.load_library()
+    return slim
+
+
+@pytest.mark.parametrize("seq,hidden,ffn", [(2048, 4096, 8192), (2049, 4096, 8256), (2500, 3584, 8256)])   # 2 splits of 128 tiles, 3 of 144 and 140
+def test_split_down_projection(slim, seq, hidden, ffn):
+    print(f"down projection {seq} {hidden} {ffn}", flush=True)
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, hidden=hidden, n_q_heads=1, n_kv_heads=1, ffn=ffn, keep_ratio=1.0, planted=4)
+    x, w, pos = inputs.hidden_states(wl), inputs.layer_weights(wl), inputs.positions(wl)
+    z = run_gpu(slim, wl, x, w, pos, wl.n_blocks, fold=True)["x"]
+    y = run_gpu(slim, wl, x, dict(w, w_down=torch.zeros_like(w["w_down"])), pos, wl.n_blocks, fold=True)["x"]
+    rows = torch.tensor([0, 255, 256, 1023, 1792, seq - 2, seq - 1], device="cuda")
+    want = so.ffn_residual(oracle_shape(wl), oracle_weights(w, np.float64), f64(y[rows]))
+    assert_residual_close(z[rows], want, [want], f"down projection seq {seq} hidden {hidden} ffn {ffn}")
+
+
+@pytest.mark.parametrize("m,n", [(1664, 4096), (1665, 4096), (2047, 4096), (1537, 4104), (1793, 3584), (2304, 3584)])
+def test_projections_of_nearly_a_round(slim, m, n, k=192):
+    """Products of bf16 numbers are exact in float and sums of 192 of them within 192 * 2^-24 of sum |a w|: the result is the exact one rounded to bf16."""
+    print(f"projection {m} x {n} from {k}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    a, w, r = (torch.randn(*s, generator=g, device="cuda").bfloat16() for s in ((m, k), (n, k), (m, n)))
+    b = r[0].contiguous()
+    prod, mag = a.double() @ w.double().T, a.double().abs() @ w.double().abs().T
+    for want, got in ((prod, slim.slim_linear(a, w)), (prod + r.double(), slim.slim_linear(a, w, residual=r)), (prod + b.double(), slim.slim_linear_bias(a, w, b))):
+        assert bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + 200 * 2.0 ** -24 * (mag + 8)).all())
+
+
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("seq,with_pos", [(1, True), (65, False), (259, True)])
+def test_layer_that_drops_nothing_returns_blocks_and_positions(slim, seq, with_pos, fold):
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, hidden=128, n_q_heads=2, n_kv_heads=1, ffn=128, keep_ratio=1.0, planted=0)
+    x, w = inputs.hidden_states(wl), inputs.layer_weights(wl)
+    pos = torch.arange(seq, dtype=torch.int32) * 3 + 7 if with_pos else None
+    res = run_gpu(slim, wl, x, w, pos, wl.n_blocks, fold=fold)
+    assert torch.equal(res["kept"].cpu(), torch.arange(wl.n_blocks, dtype=torch.int32))
+    assert torch.equal(res["pos"].cpu(), pos if with_pos else torch.arange(seq, dtype=torch.int32))
