@@ -1,6 +1,6 @@
 // C entry points of libslim: argument checks, workspace carving and the order of kernel launches of
 // the pruned prefill layer.  No kernel lives here.
-#include "slim_common.h"
+#include "rows.h"
 #include <math.h>
 #include <algorithm>
 #include <mutex>
@@ -667,15 +667,19 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     const bool want_table = fused && (fused_score || qkv || !(p.split_k || p.split_qkv));   // the window query reads it, and the unsplit Key projection
     const void* rows_in = x_in;        // what the projections of the incoming tokens read
     const float* sc_in = nullptr;
-    if (fold_attn) {
-        // (the same pass over the rows leaves the cos / sin table of their positions for the Key projection)
-        SLIM_TRY(launch_row_rstd(x_in, N, Hd, s->rms_eps, dt, rstd_in, st, pos_in, d, s->rope_theta, want_table ? table : nullptr));
-        sc_in = rstd_in;
-    } else if (!f32) {
-        SLIM_TRY(launch_rmsnorm(x_in, w->g_attn, N, Hd, s->rms_eps, dt, h, st));
-        rows_in = h;
+    if (!f32) {
+        // The same pass over the rows leaves the cos / sin table of their positions for the Key projection and, of a layer that drops nothing,
+        // its blocks and positions.
+        RowExtras ex;
+        ex.pos = pos_in;
+        if (want_table) { ex.table = table; ex.half = d / 2; ex.fr = rope_freq(d, s->rope_theta); }
+        if (fold_attn) ex.rstd = rstd_in;
+        if (!p.prune) { ex.kept = kept_blocks_out; ex.nb = p.nb; ex.pos_out = pos_out; }
+        if (fold_attn) SLIM_TRY(launch_row_rstd(x_in, N, Hd, s->rms_eps, dt, st, ex));
+        else SLIM_TRY(launch_rmsnorm(x_in, w->g_attn, N, Hd, s->rms_eps, dt, h, st, ex));
+        if (fold_attn) sc_in = rstd_in;
+        else rows_in = h;
     }
-    if (want_table && !fold_attn) SLIM_TRY(launch_rope_table(pos_in, 0, N, d, s->rope_theta, table, st));
     const float* ktab = fused ? table : nullptr;   // cos/sin rows of the incoming tokens, for the Key projection
 
     const void* resid = x_in;          // residual stream entering the attention branch
@@ -753,7 +757,7 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
         }
         resid = x_out;
         pos = pos_out;
-    } else {
+    } else if (f32) {
         SLIM_TRY(launch_keep_all(kept_blocks_out, p.nb, pos_in, pos_out, N, st));
     }
 

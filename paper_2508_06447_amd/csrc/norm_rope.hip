@@ -1,18 +1,51 @@
 // RMSNorm and rotary position embedding: the per-token, HBM-bound parts of "QKV Generation" (Fig. 2).
-#include "slim_common.h"
-#include <math.h>
+#include "rows.h"
 
 namespace slim {
+
+RopeFreq rope_freq(int d, float theta) {
+    RopeFreq fr;
+    for (int i = 0; i < d / 2; ++i) fr.inv_freq[i] = pow((double)theta, -2.0 * (double)i / (double)d);
+    return fr;
+}
+
+// One rotation angle's cos / sin: the angle is formed in double and reduced to [-pi, pi] in double (two-term
+// 2*pi), then evaluated in float: within 3e-7 of the double result, four orders below a bf16 rounding, at a
+// fraction of the cost of a double sincos.
+__device__ __forceinline__ void rope_cos_sin(double pos, double inv_freq, float& cs, float& sn) {
+    const double a = pos * inv_freq;
+    const double k = rint(a * 0.15915494309189535);                      // a / (2 pi)
+    const double r = fma(-k, 2.4492935982947064e-16, fma(-k, 6.283185307179586, a));
+    sincosf((float)r, &sn, &cs);
+}
+
+// By one thread of the row / by `count` threads of it.
+__device__ __forceinline__ void row_extras_one(int t, float rstd, const RowExtras& ex) {
+    if (ex.rstd) ex.rstd[t] = rstd;
+    if (ex.pos_out) ex.pos_out[t] = ex.pos ? ex.pos[t] : t;
+    if (ex.kept && t < ex.nb) ex.kept[t] = t;
+}
+__device__ __forceinline__ void row_extras_table(int t, int me, int count, const RowExtras& ex) {
+    if (!ex.table) return;
+    const double ps = (double)(ex.pos ? ex.pos[t] : t);
+    for (int i = me; i < ex.half; i += count) {
+        float cs, sn;
+        rope_cos_sin(ps, ex.fr.inv_freq[i], cs, sn);
+        ex.table[(size_t)t * 2 * ex.half + i] = cs;
+        ex.table[(size_t)t * 2 * ex.half + ex.half + i] = sn;
+    }
+}
 
 // One workgroup per token row.  Pass 1 sums squares (fp32), pass 2 re-reads the row (L2-resident)
 // and writes gain * x * rsqrt(mean + eps).
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(256) rmsnorm_kernel(const T* __restrict__ x, const T* __restrict__ gain,
-                                                      int hidden, float eps, T* __restrict__ out) {
+                                                      int hidden, float eps, T* __restrict__ out, RowExtras ex) {
     constexpr int V = Elem<T>::kVec;
     __shared__ float part[4];
-    const T* row = x + (size_t)blockIdx.x * hidden;
-    T* orow = out + (size_t)blockIdx.x * hidden;
+    const int t = blockIdx.x;
+    const T* row = x + (size_t)t * hidden;
+    T* orow = out + (size_t)t * hidden;
     float ss = 0.f;
     if (VEC) {
         for (int c = threadIdx.x; c < hidden / V; c += 256) {
@@ -24,11 +57,13 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const T* __restrict__ x, c
     } else {
         for (int c = threadIdx.x; c < hidden; c += 256) { float v = Elem<T>::ld(row + c); ss += v * v; }
     }
+    row_extras_table(t, threadIdx.x, 256, ex);
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
     __syncthreads();
     const float tot = part[0] + part[1] + part[2] + part[3];
     const float inv = 1.0f / sqrtf(tot / (float)hidden + eps);
+    if (threadIdx.x == 0) row_extras_one(t, inv, ex);
     if (VEC) {
         for (int c = threadIdx.x; c < hidden / V; c += 256) {
             float f[V], g[V];
@@ -44,22 +79,24 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const T* __restrict__ x, c
     }
 }
 
-int launch_rmsnorm(const void* x, const void* gain, int n, int hidden, float eps, int dtype, void* out, hipStream_t st) {
+int launch_rmsnorm(const void* x, const void* gain, int n, int hidden, float eps, int dtype, void* out, hipStream_t st, const RowExtras& ex) {
     const size_t es = elem_size(dtype);
     const bool vec = ((size_t)hidden * es) % 16 == 0 && aligned16(x) && aligned16(out) && aligned16(gain);
 #define SLIM_RMS(T, VEC) hipLaunchKernelGGL((rmsnorm_kernel<T, VEC>), dim3(n), dim3(256), 0, st, (const T*)x, \
-                                            (const T*)gain, hidden, eps, (T*)out)
+                                            (const T*)gain, hidden, eps, (T*)out, ex)
     if (dtype == SLIM_BF16) { if (vec) SLIM_RMS(bf16_t, true); else SLIM_RMS(bf16_t, false); }
     else                    { if (vec) SLIM_RMS(float, true);  else SLIM_RMS(float, false); }
 #undef SLIM_RMS
     return check_launch();
 }
 
+int launch_rmsnorm(const void* x, const void* gain, int n, int hidden, float eps, int dtype, void* out, hipStream_t st) {
+    return launch_rmsnorm(x, gain, n, hidden, eps, dtype, out, st, RowExtras());
+}
+
 // RoPE in place on x[n, H, d].  A thread owns two adjacent rotation indices (2p, 2p+1) of one token
 // and walks over the heads, so each angle is formed once per token: angle = pos * inv_freq[i] in
 // double, sincos in double, rounded to float.  inv_freq comes from the host (theta^(-2i/d) in double).
-struct RopeFreq { double inv_freq[128]; };               // head_dim <= 256
-
 template <typename T>
 __global__ void __launch_bounds__(256) rope_kernel(T* __restrict__ x, const int* __restrict__ pos, int pos0, int n,
                                                    int H, int d, RopeFreq fr) {
@@ -98,8 +135,7 @@ __global__ void __launch_bounds__(256) rope_kernel(T* __restrict__ x, const int*
 }
 
 int launch_rope(void* x, const int* pos, int pos0, int n, int H, int d, float theta, int dtype, hipStream_t st) {
-    RopeFreq fr;
-    for (int i = 0; i < d / 2; ++i) fr.inv_freq[i] = pow((double)theta, -2.0 * (double)i / (double)d);
+    const RopeFreq fr = rope_freq(d, theta);
     const long long threads = (long long)n * (d / 4);
     dim3 grid((unsigned)((threads + 255) / 256));
     if (dtype == SLIM_BF16) hipLaunchKernelGGL(rope_kernel<bf16_t>, grid, dim3(256), 0, st, (bf16_t*)x, pos, pos0, n, H, d, fr);
@@ -127,24 +163,11 @@ int launch_fold_gain(const void* w, const void* gain, int n_out, int k_in, int d
     return check_launch();
 }
 
-// One rotation angle's cos / sin: the angle is formed in double and reduced to [-pi, pi] in double (two-term
-// 2*pi), then evaluated in float: within 3e-7 of the double result, four orders below a bf16 rounding, at a
-// fraction of the cost of a double sincos.
-__device__ __forceinline__ void rope_cos_sin(double pos, double inv_freq, float& cs, float& sn) {
-    const double a = pos * inv_freq;
-    const double k = rint(a * 0.15915494309189535);                      // a / (2 pi)
-    const double r = fma(-k, 2.4492935982947064e-16, fma(-k, 6.283185307179586, a));
-    sincosf((float)r, &sn, &cs);
-}
-
 // rstd[t] = 1 / sqrt(mean(x[t, :]^2) + eps): the row statistic of RMSNorm alone, for projections that apply it to
-// their accumulators instead of reading a normalised copy.  One wave per row, 4 rows per workgroup.  With a table
-// pointer the wave also writes the row's cos / sin table entry (see rope_table_kernel): lane i takes angle i, and
-// the arithmetic hides under the row's memory traffic.
+// their accumulators instead of reading a normalised copy.  One wave per row, 4 rows per workgroup.  The arithmetic of the cos / sin table, of
+// which lane i takes angle i, hides under the row's memory traffic.
 template <typename T, bool STREAM>
-__global__ void __launch_bounds__(256) row_rstd_kernel(const T* __restrict__ x, int n, int hidden, float eps,
-                                                       float* __restrict__ rstd, const int* __restrict__ pos, int half,
-                                                       RopeFreq fr, float* __restrict__ table) {
+__global__ void __launch_bounds__(256) row_rstd_kernel(const T* __restrict__ x, int n, int hidden, float eps, RowExtras ex) {
     constexpr int V = Elem<T>::kVec;
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (t >= n) return;
@@ -162,38 +185,26 @@ __global__ void __launch_bounds__(256) row_rstd_kernel(const T* __restrict__ x, 
     } else {
         for (int c = lane; c < hidden; c += 64) { const float v = Elem<T>::ld(row + c); ss += v * v; }
     }
-    if (table) {
-        const double ps = (double)(pos ? pos[t] : t);
-        for (int i = lane; i < half; i += 64) {
-            float cs, sn;
-            rope_cos_sin(ps, fr.inv_freq[i], cs, sn);
-            table[(size_t)t * 2 * half + i] = cs;
-            table[(size_t)t * 2 * half + half + i] = sn;
-        }
-    }
+    row_extras_table(t, lane, 64, ex);
     ss = wave_sum(ss);
-    if (lane == 0) rstd[t] = 1.0f / sqrtf(ss / (float)hidden + eps);
+    if (lane == 0) row_extras_one(t, 1.0f / sqrtf(ss / (float)hidden + eps), ex);
 }
 
-static RopeFreq rope_freq(int d, float theta) {
-    RopeFreq fr;
-    for (int i = 0; i < d / 2; ++i) fr.inv_freq[i] = pow((double)theta, -2.0 * (double)i / (double)d);
-    return fr;
-}
-
-// table != null: also the cos / sin table of the rows' positions (pos null = 0..n-1) for head_dim d.
-int launch_row_rstd(const void* x, int n, int hidden, float eps, int dtype, float* rstd, hipStream_t st,
-                    const int* pos, int d, float theta, float* table) {
-    const RopeFreq fr = table ? rope_freq(d, theta) : RopeFreq();
+int launch_row_rstd(const void* x, int n, int hidden, float eps, int dtype, hipStream_t st, const RowExtras& ex) {
     // Rows that outgrow the memory-side cache (256 MB) will not be found there by the projection that follows: past the caches.
     // 32768 rows of 4096 60 -> 53 us; smaller inputs stay in it.
     const bool stream = (size_t)n * hidden * elem_size(dtype) >= ((size_t)256 << 20);
-#define SLIM_RSTD(T, S) hipLaunchKernelGGL((row_rstd_kernel<T, S>), dim3((n + 3) / 4), dim3(256), 0, st, (const T*)x, n, hidden, eps, rstd, \
-                                           pos, d / 2, fr, table)
+#define SLIM_RSTD(T, S) hipLaunchKernelGGL((row_rstd_kernel<T, S>), dim3((n + 3) / 4), dim3(256), 0, st, (const T*)x, n, hidden, eps, ex)
     if (dtype == SLIM_BF16) { if (stream) SLIM_RSTD(bf16_t, true); else SLIM_RSTD(bf16_t, false); }
     else                    { if (stream) SLIM_RSTD(float, true);  else SLIM_RSTD(float, false); }
 #undef SLIM_RSTD
     return check_launch();
+}
+
+int launch_row_rstd(const void* x, int n, int hidden, float eps, int dtype, float* rstd, hipStream_t st) {
+    RowExtras ex;
+    ex.rstd = rstd;
+    return launch_row_rstd(x, n, hidden, eps, dtype, st, ex);
 }
 
 // cos / sin table for the RoPE epilogue of the projections: table[t][0..half) = cos(pos[t] * inv_freq[i]),

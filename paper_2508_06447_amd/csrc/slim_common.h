@@ -107,6 +107,8 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Internal launchers (each validates nothing: the C entry points do).
+struct RowExtras;                                        // (rows.h)
+int launch_rmsnorm(const void* x, const void* gain, int n, int hidden, float eps, int dtype, void* out, hipStream_t st, const RowExtras& ex);
 int launch_rmsnorm(const void* x, const void* gain, int n, int hidden, float eps, int dtype, void* out, hipStream_t st);
 int launch_rope(void* x, const int* pos, int pos0, int n, int H, int d, float theta, int dtype, hipStream_t st);
 int launch_linear(const void* a, int lda, const void* w0, const void* w1, const void* residual, const void* bias, int m,
@@ -126,8 +128,8 @@ bool qkv_together(int m, int n_q, int n_k, int n_v);
 int launch_linear_qkv(const void* a, int lda, const void* w_q, const void* bias_q, int n_q, void* out_q, const void* w_k, const void* bias_k,
                       int n_k, const float* table, void* out_k, const void* w_v, const void* bias_v, int n_v, void* out_v,
                       const float* row_scale, int m, int k_in, hipStream_t st);
-int launch_row_rstd(const void* x, int n, int hidden, float eps, int dtype, float* rstd, hipStream_t st,
-                    const int* pos = nullptr, int d = 0, float theta = 0.f, float* table = nullptr);
+int launch_row_rstd(const void* x, int n, int hidden, float eps, int dtype, hipStream_t st, const RowExtras& ex);
+int launch_row_rstd(const void* x, int n, int hidden, float eps, int dtype, float* rstd, hipStream_t st);
 int launch_fold_gain(const void* w, const void* gain, int n_out, int k_in, int dtype, void* out, hipStream_t st);
 int launch_window_query(const void* q_win, int w, int Hq, int Hkv, int d, int dtype, float* qtilde, hipStream_t st);
 // Window query from the hidden rows of the window (skinny split projection + rotation + means); `partial` holds
