@@ -27,6 +27,7 @@
 // into attn_bf16_body.inc; the C++ below computes its per-lane and per-workgroup operands.
 #include "slim_common.h"
 #include <mutex>
+#include <type_traits>
 
 namespace slim {
 
@@ -126,6 +127,176 @@ attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg, co
     );
 }
 
+// Few rows: the kernel above takes 2.5 us for a tile of 128 keys whatever the number of workgroups, and up to 2048 rows of 8 kv heads its launch is as long as its query
+// tile with the most keys.  Here a workgroup owns 32 queries of four heads of a kv group and deals the keys to two waves per head (wave = key half * 4 + head, two waves
+// per SIMD): tiles of 64 keys in four LDS stages of 32 KB, one barrier each (0.9 us a tile; its MFMAs alone 0.62 at the clock that they run at), and at the end the two
+// waves of a head swap halves of O through LDS.  Same products, layouts and kind of reference as above, but Q stays as it is and scale * log2(e) enters in float (error of
+// 1000 rows against float64 3.6e-3 -> 2.1e-3).  32 / 8 heads, us, the kernel above / this one: 128 rows 11.6 / 8.6, 512 19.1 / 14.1, 1024 27.9 / 21.6, 1511 37.4 / 30.8.
+// S(t + 1) formed under the softmax of tile t, the two key halves in opposite phases, QK and PV MFMAs in turn, the reference tested on sums: within 3 %, none faster.
+constexpr int FKV = 64;                                 // keys per tile, 32 per wave
+constexpr int FSTAGES = 4;
+constexpr int FTILE_BYTES = FKV * AD * 2, FSTAGE_BYTES = 2 * FTILE_BYTES;
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+attn_bf16_few_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg, const bf16_t* __restrict__ Vg, bf16_t* __restrict__ O, int n, int Hq, int Hkv,
+                     float c, int n_qt) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    typedef __attribute__((address_space(3))) bf16x4* LdsB64;
+    typedef __attribute__((address_space(3))) bf16x8* LdsB128;
+    typedef __attribute__((address_space(3))) f32x4* LdsF32x4;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = wave >> 2;
+    // Workgroup -> (four heads of a kv group, query tile): as above, longest first inside each XCD.
+    const int G = Hq / Hkv, chunks = (G + 3) / 4, n_units = Hkv * chunks;
+    int u, qt;
+    if (n_units % 8 == 0) {
+        const int j = blockIdx.x >> 3, upx = n_units >> 3;
+        u = (blockIdx.x & 7) * upx + j % upx;
+        qt = n_qt - 1 - j / upx;
+    } else {
+        u = blockIdx.x % n_units;
+        qt = n_qt - 1 - blockIdx.x / n_units;
+    }
+    const int g = u / chunks, hg = (u - g * chunks) * 4 + (wave & 3);
+    const int h = g * G + min(hg, G - 1);               // (a wave without a head of its own repeats the last one and stores nothing)
+    const int q0 = qt * 32, qi = q0 + l32, lim = min(qi, n - 1), q_last = min(q0 + 31, n - 1);
+    const int nkt = q_last / FKV + 1;
+    const size_t qstride = (size_t)Hq * AD;
+    const unsigned lds_base = (unsigned)(uintptr_t)lds, rowbytes = (unsigned)Hkv * AD * 2;
+
+    bf16x8 qf[8];
+    const bf16_t* qrow = Q + (size_t)lim * qstride + (size_t)h * AD + hh * 8;
+#pragma unroll
+    for (int st = 0; st < 8; ++st) qf[st] = *reinterpret_cast<const bf16x8*>(qrow + st * 16);
+
+    // Wave-load i moves rows 4 * (8 i + wave) .. + 3 of a tile, 256 B each, with the swizzles of k_off and v_off.  Rows behind the last key repeat it (masked), tiles behind
+    // the last one are it again, in a stage that nobody reads: the number of loads in flight is a constant.
+    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(Kg + (size_t)g * AD);
+    const unsigned char* vbase = reinterpret_cast<const unsigned char*>(Vg + (size_t)g * AD);
+    auto issue = [&](int t) {
+        const int k0 = min(t, nkt - 1) * FKV;
+        const unsigned dst = lds_base + (t % FSTAGES) * FSTAGE_BYTES + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 4 * (8 * i + wave) + (lane >> 4), slot = lane & 15;
+            const unsigned row = (unsigned)min(r, n - 1 - k0) * rowbytes;
+            load_global_to_lds16(kbase + (size_t)k0 * rowbytes, row + ((slot ^ (r & 15)) << 4), dst + i * 8192);
+            load_global_to_lds16(vbase + (size_t)k0 * rowbytes, row + ((slot ^ ((r & 3) << 2)) << 4), dst + FTILE_BYTES + i * 8192);
+        }
+    };
+    for (int t = 0; t < FSTAGES - 1; ++t) issue(t);
+
+    const int G4 = lane >> 4, sl = lane & 15, key_lane = 32 * half + 4 * (G4 >> 1) + (sl >> 2);
+    const unsigned koff = lds_base + k_off(32 * half + l32, hh);
+    const unsigned voff = lds_base + FTILE_BYTES + v_off(key_lane, 2 * (G4 & 1) + ((sl & 3) >> 1)) + (sl & 1) * 8;
+    f32x16 o[4];
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[dt][v] = 0.f;
+    const float step = 8.f / c;                          // how far a logit may lie above the reference: P up to 2^8
+    float m = -INFINITY, m_step = -INFINITY, nmc = 0.f, l = 0.f;     // reference, reference + step, -reference * c (0: none yet), the lane's sum of P
+    for (int t = 0; t < nkt; ++t) {
+        __builtin_amdgcn_s_waitcnt(0x0070 | 4 * (FSTAGES - 2));      // own part of tile t is there, own reads of tile t - 1 are done
+        workgroup_barrier();
+        issue(t + FSTAGES - 1);                          // into the stage of tile t - 1
+        const int k0 = t * FKV + 32 * half;
+        if (k0 > q_last) continue;
+        const unsigned so = (t % FSTAGES) * FSTAGE_BYTES;
+        bf16x8 kf[8], vf[2][4];
+#pragma unroll
+        for (int st = 0; st < 8; ++st) kf[st] = *(LdsB128)((koff + so) ^ (st << 5));
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) {
+                const unsigned a = ((voff + so) ^ (dt << 6)) + ks * 16 * AD * 2;
+                const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LdsB64)a), hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LdsB64)(a + 8 * AD * 2));
+                vf[ks][dt] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+        f32x16 s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+        for (int st = 0; st < 8; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st], qf[st], s, 0, 0, 0);
+        if (k0 + 31 > q0)                                // keys above some query (or behind the last one)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (k0 + 8 * (v >> 2) + 4 * hh + (v & 3) > lim) s[v] = -INFINITY;
+        float mx = s[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+        if (__any(mx > m_step)) {                        // rare behind the first tile: the reference moves up to the maximum of both lanes of a query
+            mx = fmaxf(mx, m);
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float f = m == mx ? 1.f : __builtin_amdgcn_exp2f((m - mx) * c);
+            m = mx;
+            m_step = m + step;
+            nmc = m == -INFINITY ? 0.f : -m * c;
+            l *= f;
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[dt][v] *= f;
+        }
+        float sum[2] = {0.f, 0.f};
+        bf16x8 pb[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            float p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                p[e] = __builtin_amdgcn_exp2f(fmaf(s[8 * ks + e], c, nmc));
+                sum[e & 1] += p[e];
+            }
+            pb[ks] = __builtin_bit_cast(bf16x8, Elem<bf16_t>::pack(p));
+        }
+        l += sum[0] + sum[1];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][dt], pb[ks], o[dt], 0, 0, 0);
+    }
+    l += __shfl_xor(l, 32, 64);
+    // The two waves of a head: each sends the half of O that the other finishes, with its reference and sum.  All loads into LDS are through.
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    workgroup_barrier();
+    const unsigned mine = lds_base + wave * 8192 + lane * 16, theirs = lds_base + (wave ^ 4) * 8192 + lane * 16;
+    const unsigned stat = lds_base + 65536 + lane * 16;
+    auto send = [&](auto first) {
+        constexpr int F = decltype(first)::value;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const f32x16& a = o[F + (i >> 2)];
+            *(LdsF32x4)(mine + i * 1024) = f32x4{a[4 * (i & 3)], a[4 * (i & 3) + 1], a[4 * (i & 3) + 2], a[4 * (i & 3) + 3]};
+        }
+    };
+    if (half) send(std::integral_constant<int, 0>{});
+    else send(std::integral_constant<int, 2>{});
+    *(LdsF32x4)(stat + wave * 1024) = f32x4{m, l, 0.f, 0.f};
+    __syncthreads();
+    const f32x4 other = *(LdsF32x4)(stat + (wave ^ 4) * 1024);
+    const float top = fmaxf(m, other[0]);
+    const float f0 = m == top ? 1.f : __builtin_amdgcn_exp2f((m - top) * c), f1 = other[0] == top ? 1.f : __builtin_amdgcn_exp2f((other[0] - top) * c);
+    const float inv = 1.f / (l * f0 + other[1] * f1), w0 = f0 * inv, w1 = f1 * inv;
+    auto finish = [&](auto first) {
+        constexpr int F = decltype(first)::value;
+        bf16_t* orow = O + (size_t)qi * qstride + (size_t)h * AD + F * 32 + 4 * hh;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const f32x16& a = o[F + (i >> 2)];
+            const f32x4 b = *(LdsF32x4)(theirs + i * 1024);
+            float r[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = a[4 * (i & 3) + e] * w0 + b[e] * w1;
+            if (qi < n && hg < G) *reinterpret_cast<uint2*>(orow + (i >> 2) * 32 + (i & 3) * 8) = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+        }
+    };
+    if (half) finish(std::integral_constant<int, 2>{});
+    else finish(std::integral_constant<int, 0>{});
+}
+
 int launch_attn(const void* q, const void* k, const void* v, int n, int Hq, int Hkv, int d, float scale,
                 int dtype, void* out, hipStream_t st) {
     if (scale == 0.f) scale = 1.0f / sqrtf((float)d);
@@ -139,9 +310,18 @@ int launch_attn(const void* q, const void* k, const void* v, int n, int Hq, int 
             attr_err = hipFuncSetAttribute((const void*)attn_bf16_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
             if (attr_err == hipSuccess)
                 attr_err = hipFuncSetAttribute((const void*)attn_bf16_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+            if (attr_err == hipSuccess)
+                attr_err = hipFuncSetAttribute((const void*)attn_bf16_few_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FSTAGES * FSTAGE_BYTES);
         });
         if (attr_err != hipSuccess) return set_hip_error(attr_err);
-        if (Hq == 4 * Hkv) {
+        // Few rows: groups whose heads fill three or four of a workgroup's four places, and up to two workgroups per CU (us, the other kernel / this one: 32 / 8 heads, 2048
+        // rows 49.2 / 46.3, 2560 63 / 74; 28 / 4 heads 48.5 / 46.3, 62 / 74).  A reference in units of unscaled logits needs a positive scale.
+        const int per_group = (Hq / Hkv + 3) / 4;
+        const long long few_wgs = (n + 31ll) / 32 * Hkv * per_group;
+        if (few_wgs <= 2 * cu_count() && Hq / Hkv % 4 != 1 && Hq / Hkv % 4 != 2 && scale > 0.f) {
+            hipLaunchKernelGGL(attn_bf16_few_kernel, dim3((unsigned)few_wgs), dim3(512), FSTAGES * FSTAGE_BYTES, st, (const bf16_t*)q, (const bf16_t*)k,
+                               (const bf16_t*)v, (bf16_t*)out, n, Hq, Hkv, scale * 1.4426950408889634f, (n + 31) / 32);
+        } else if (Hq == 4 * Hkv) {
             const int n_qt = (n + 63) / 64;
             hipLaunchKernelGGL(attn_bf16_kernel<true>, dim3(n_qt * Hkv), dim3(64 * ANW), smem, st, (const bf16_t*)q,
                                (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)out, n, Hq, Hkv, scale * 1.4426950408889634f, n_qt);

@@ -951,7 +951,7 @@ template <int EPI> constexpr double small_tile_cost(bool eight_waves) {
     return eight_waves ? 0.5 : (EPI == EPI_SWIGLU ? 0.7 : 0.6);
 }
 
-static int cu_count() {
+int cu_count() {
     static std::once_flag once;                          // immutable once read: a property of the device
     static int n = 256;
     std::call_once(once, [] {

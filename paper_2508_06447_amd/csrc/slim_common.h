@@ -102,6 +102,7 @@ inline int check_launch() {
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SLIM_OK : set_hip_error(e);
 }
+int cu_count();                                          // of the current device
 inline size_t elem_size(int dtype) { return dtype == SLIM_BF16 ? 2 : 4; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
