@@ -870,15 +870,36 @@ struct CompactSegs {
     unsigned chunk_end[4];               // first chunk of the grid behind the array's
 };
 
-__global__ void __launch_bounds__(kCopyThreads) compact_multi_kernel(CompactSegs segs, const int* __restrict__ kept,
+// Block i of the n_keep that select_few_blocks_kernel keeps of nb <= 64, found by every wave by itself: lane j ranks block j among those that are not forced.
+__device__ __forceinline__ int kept_of_wave(const float* __restrict__ scores, int nb, int n_keep, unsigned flags, int i) {
+    const int j = threadIdx.x & 63;
+    const bool f_first = flags & SLIM_FORCE_FIRST, f_last = flags & SLIM_FORCE_LAST;
+    const bool forced = (f_first && j == 0) || (f_last && j == nb - 1), open = j < nb && !forced;
+    const int take = n_keep - ((f_first ? 1 : 0) + ((f_last && !(f_first && nb == 1)) ? 1 : 0));
+    const uint32_t key = score_key(scores[min(j, nb - 1)]);
+    int rank = 0;                                        // candidates in front of block j: larger scores, and equal ones with a smaller index
+    for (int b = f_first ? 1 : 0; b < nb - (f_last ? 1 : 0); ++b) {
+        const uint32_t other = __builtin_amdgcn_readlane(key, b);
+        rank += other > key || (other == key && b < j);
+    }
+    const bool keep = (j < nb && forced) || (open && rank < take);
+    const unsigned long long mask = __ballot(keep);
+    const bool mine = keep && __popcll(mask & ((1ull << j) - 1)) == i;
+    return __ffsll(__ballot(mine)) - 1;
+}
+
+// SELECT: kept is written, from the scores, in place of being read.
+template <bool SELECT>
+__global__ void __launch_bounds__(kCopyThreads) compact_multi_kernel(CompactSegs segs, int* __restrict__ kept,
                                                                      int block, int N, int nb,
                                                                      const int* __restrict__ pos_in,
-                                                                     int* __restrict__ pos_out) {
+                                                                     int* __restrict__ pos_out, const float* __restrict__ scores, unsigned flags) {
     const int i = blockIdx.y;
     const int a = (blockIdx.x >= segs.chunk_end[0]) + (blockIdx.x >= segs.chunk_end[1]) + (blockIdx.x >= segs.chunk_end[2]);
     const unsigned first = a ? segs.chunk_end[a - 1] : 0, chunk = blockIdx.x - first;
-    const int kb = kept[i];
+    const int kb = SELECT ? kept_of_wave(scores, nb, gridDim.y, flags, i) : kept[i];
     if ((unsigned)kb >= (unsigned)nb) return;
+    if (SELECT && blockIdx.x == 0 && threadIdx.x == 0) kept[i] = kb;
     const int rows = min(block, N - kb * block);
     const size_t rb = segs.row_bytes[a];
     const size_t run = (size_t)rows * rb;
@@ -915,9 +936,10 @@ __global__ void __launch_bounds__(kCopyThreads) compact_multi_kernel(CompactSegs
     }
 }
 
-// Up to 4 arrays [N, row_bytes[a]] -> [n', row_bytes[a]]; positions ride with array 0.  row_bytes % 4 == 0.
+// Up to 4 arrays [N, row_bytes[a]] -> [n', row_bytes[a]]; positions ride with array 0.  row_bytes % 4 == 0.  With scores the launch selects the blocks itself
+// (launch_select, 64 blocks at most, n_keep < nb): every wave for its own block, which costs it a microsecond at the start where a launch in front costs two and more.
 int launch_compact_multi(int n_arrays, const void* const* src, void* const* dst, const size_t* row_bytes, const int* pos_in,
-                         int* pos_out, const int* kept, int n_keep, int block, int N, hipStream_t st) {
+                         int* pos_out, int* kept, int n_keep, int block, int N, hipStream_t st, const float* scores, unsigned flags) {
     CompactSegs segs;
     const size_t per = (size_t)kCopyThreads * kCopyVecs * 16;
     size_t chunks = 0;
@@ -930,8 +952,8 @@ int launch_compact_multi(int n_arrays, const void* const* src, void* const* dst,
         segs.chunk_end[a] = (unsigned)chunks;
     }
     const int nb = (N + block - 1) / block;
-    hipLaunchKernelGGL(compact_multi_kernel, dim3((unsigned)chunks, n_keep), dim3(kCopyThreads), 0, st, segs, kept, block, N, nb,
-                       pos_in, pos_out);
+    hipLaunchKernelGGL(scores ? compact_multi_kernel<true> : compact_multi_kernel<false>, dim3((unsigned)chunks, n_keep), dim3(kCopyThreads), 0, st, segs, kept,
+                       block, N, nb, pos_in, pos_out, scores, flags);
     return check_launch();
 }
 

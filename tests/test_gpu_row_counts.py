@@ -51,3 +51,23 @@ def test_layer_that_drops_nothing_returns_blocks_and_positions(slim, seq, with_p
     res = run_gpu(slim, wl, x, w, pos, wl.n_blocks, fold=fold)
     assert torch.equal(res["kept"].cpu(), torch.arange(wl.n_blocks, dtype=torch.int32))
     assert torch.equal(res["pos"].cpu(), pos if with_pos else torch.arange(seq, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("flags", [0, 1, 2, 3])
+@pytest.mark.parametrize("nb", [2, 3, 33, 63, 64, 65])
+def test_layer_keeps_the_blocks_that_the_selection_keeps(slim, nb, flags):
+    """Up to 64 blocks the compaction selects for itself: the same blocks and order as slim_select_topk_blocks on the layer's scores, whatever is forced, with distinct
+    scores, many equal ones (a prompt that repeats) and scores that are not a number."""
+    wl = inputs.scaled(inputs.WORKLOADS["cfg1"], seq=nb * 16, planted=0)
+    x, w = inputs.hidden_states(wl), {k: v.cuda() for k, v in inputs.layer_weights(wl).items()}
+    shape = slim.make_shape(wl.hidden, wl.n_q_heads, wl.n_kv_heads, wl.head_dim, wl.ffn, 16, wl.unit, wl.window, x.dtype, wl.rope_theta, wl.rms_eps, flags)
+    pos = torch.zeros(nb * 16, dtype=torch.int32, device="cuda")                            # no rotation: equal rows have equal keys
+    odd = x.clone()
+    odd[16:32] = float("nan")
+    for rows in (x, x[:16].repeat(nb, 1), odd):
+        for n_keep in {max(1, bin(flags).count("1")), nb // 2 + 1, nb - 1}:
+            if n_keep < min(nb, bin(flags).count("1")) or n_keep >= nb:
+                continue
+            res = slim.slim_pruned_layer(shape, w, rows.cuda(), pos, n_keep)
+            want = slim.slim_select_topk_blocks(res["scores"], n_keep, flags)
+            assert torch.equal(res["kept"], want), (nb, n_keep, flags)
