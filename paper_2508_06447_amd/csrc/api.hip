@@ -58,6 +58,16 @@ static int forced_count(unsigned flags, int nb) {
 constexpr int kSplitRows = 128;
 static int qkv_splits(int m, int k_in) { return m <= kSplitRows && k_in >= 2048 ? 4 : 1; }
 
+// The output projection of few rows, for which the finishing pass takes the place of the norm's launch (split_residual_rows_kernel; rows of up to 8192).  Whole
+// layers, not split / 2 / 4 / 8 splits (us): 4096 features from 4096, 4 rows 123.4 / 117.9 / 115.2 / 117.6, 64 147 / 140 / 137, 65 141.2 / 137.7 / 138.3, 128 156.3 / 151.0 /
+// 151.9, 200 177 / 182 / 180, 256 201 / 200 / 199, 257 229 / 217 / 219 / 227, 512 261 / 254 / 254, 513 313 / 311 / 321, 768 356 / 350 / 363, 960 415 / 418, 1024 415 / 413,
+// 1511 603 / 620; 3584 from 3584, 48 rows 153 / 146 / 143 / 148, 128 186 / 180 / 181, 300 256 / 253 / 254, 512 316 / 311 / 311, 700 378 / 378, 832 451 / 456.  (Behind 512 rows
+// neither gains; they are one class with those from 257 on, so that a row's sums do not change with a pruning between them.)
+static int out_splits(int m, int n, int k_in) {
+    if (n < 2048 || n > 8192 || n % 64 != 0 || k_in < 2048 || k_in % 64 != 0 || k_in >= (1 << 23) || (long long)m * n > 1 << 22) return 1;
+    return m <= 64 ? 4 : m <= 128 || (m > 256 && m <= 1024) ? 2 : 1;
+}
+
 // Workspace layout of slim_pruned_layer (every region 256-byte aligned).
 struct LayerPlan {
     size_t h, k_all, q_win, qt, scores, table, tscore, rstd, rstd2, kc, vc, qc, o, o_all, act, qkv_partial, total;
@@ -65,6 +75,7 @@ struct LayerPlan {
     bool prune;
     bool split_k, split_qv, split_qkv;                   // which projections go through float partial sums
     ResidualCut down;                                    // and which rows of the down projection
+    int out_splits;                                      // of the output projection, 1: not split
 };
 
 static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
@@ -117,6 +128,17 @@ static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
     p.o = take((size_t)p.n_out * qd * es);
     off = std::max(off, align_up(down_part * sizeof(float), 256));
     p.act = take((size_t)p.n_out * s->ffn * es);
+    // Partial sums of the output projection lie over act, which comes behind it; they too have room for the most that any fewer rows take.
+    p.out_splits = 1;
+    if (s->dtype == SLIM_BF16) {
+        const int Hd = s->hidden, n_most = p.prune ? n_keep * s->block : N;
+        p.out_splits = out_splits(p.n_out, Hd, (int)qd);
+        for (int rows : {64, 128, 1024, (1 << 22) / Hd}) {
+            rows = std::min(rows, n_most);
+            const int splits = out_splits(rows, Hd, (int)qd);
+            if (splits > 1) off = std::max(off, p.act + align_up((size_t)splits * rows * Hd * sizeof(float), 256));
+        }
+    }
     p.total = std::max(off, p.qkv_partial + align_up(qkv_part * sizeof(float), 256));
     return p;
 }
@@ -772,16 +794,22 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     SLIM_TRY(launch_attn(qc, kc, vc, n, Hq, Hkv, d, 0.f, dt, o, st));
     }
     // y = resid + Wo o  (into x_out);  z = y + Wdown(silu(Wgate r) * Wup r), r = RMSNorm(y)  (in place)
-    SLIM_TRY(launch_linear(o, qd, w->wo, nullptr, resid, nullptr, n, Hd, qd, Hd, dt, x_out, st));
+    if (p.out_splits > 1 && (fold_ffn || aligned16(w->g_ffn))) {
+        const SplitMats mats{{w->wo}, {Hd}, 1};
+        SLIM_TRY(launch_split_gemm(o, qd, mats, n, qd, p.out_splits, (float*)act, st));
+        SLIM_TRY(launch_split_residual_rows((const float*)act, p.out_splits, n, Hd, resid, x_out, s->rms_eps, w->g_ffn, h, rstd_kept, st));
+    } else {
+        SLIM_TRY(launch_linear(o, qd, w->wo, nullptr, resid, nullptr, n, Hd, qd, Hd, dt, x_out, st));
+        if (fold_ffn) SLIM_TRY(launch_row_rstd(x_out, n, Hd, s->rms_eps, dt, rstd_kept, st));
+        else if (!f32) SLIM_TRY(launch_rmsnorm(x_out, w->g_ffn, n, Hd, s->rms_eps, dt, h, st));
+    }
     if (fold_ffn) {
-        SLIM_TRY(launch_row_rstd(x_out, n, Hd, s->rms_eps, dt, rstd_kept, st));
         SLIM_TRY(launch_linear_scaled(x_out, Hd, w->w_gate, w->w_up, nullptr, rstd_kept, n, s->ffn, Hd, s->ffn, act, st));
     } else if (f32) {
         const F32Seg seg{(const float*)x_out, Hd, n, (const float*)w->w_gate, (const float*)w->w_up, nullptr, nullptr, (float*)act, s->ffn, s->ffn,
                          F32_SWIGLU, nullptr, 0};
         SLIM_TRY(launch_f32_linear(&seg, 1, Hd, (const float*)w->g_ffn, s->rms_eps, d, s->rope_theta, st));
     } else {
-        SLIM_TRY(launch_rmsnorm(x_out, w->g_ffn, n, Hd, s->rms_eps, dt, h, st));
         SLIM_TRY(launch_linear(h, Hd, w->w_gate, w->w_up, nullptr, nullptr, n, s->ffn, Hd, s->ffn, dt, act, st));
     }
     const int whole = p.down.splits > 1 ? p.down.whole : n, tail = n - whole;

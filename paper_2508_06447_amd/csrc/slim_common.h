@@ -173,6 +173,8 @@ ResidualCut residual_cut(int m, int n, int k_in);
 size_t residual_cut_partial_floats(int m, int n, int k_in);
 int launch_split_gemm_large(const void* a, int lda, const void* w, int m, int n, int k_in, int splits, float* partial, hipStream_t st);
 int launch_split_residual(const float* partial, int splits, int m, int n, const void* residual, void* out, hipStream_t st);
+int launch_split_residual_rows(const float* partial, int splits, int m, int n, const void* residual, void* out, float eps, const void* gain, void* normed,
+                               float* rstd, hipStream_t st);
 struct SplitHeadsArgs { void* out[3]; const void* bias[3]; int heads[3]; int rope[3]; int score; };
 int launch_split_heads(const float* partial, int splits, int m, const SplitHeadsArgs& a, const float* rstd, const int* pos, float theta,
                        const float* qt, float* token_scores, hipStream_t st);

@@ -32,6 +32,65 @@ int launch_split_residual(const float* partial, int splits, int m, int n, const 
     return check_launch();
 }
 
+// The same for rows that a norm follows, one per workgroup: also 1 / rms of the finished row, or with a gain the normalised row (from registers; n <= 8192).  2 splits
+// of 512 x 4096 read 17 MB, mostly from the caches.
+template <bool NORM>
+__global__ void __launch_bounds__(256) split_residual_rows_kernel(const float* __restrict__ partial, int splits, size_t split_stride, int n, const bf16_t* R,
+                                                                  bf16_t* out, float eps, const bf16_t* __restrict__ gain, bf16_t* __restrict__ normed,
+                                                                  float* __restrict__ rstd) {
+    __shared__ float part[4];
+    const size_t row = (size_t)blockIdx.x * n;
+    uint4 y[4];
+    float ss = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int c = (u * 256 + threadIdx.x) * 8;
+        if (c >= n) break;
+        f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int s = 0; s < splits; ++s) {
+            const float* p = partial + s * split_stride + row + c;
+            lo += *reinterpret_cast<const f32x4*>(p);
+            hi += *reinterpret_cast<const f32x4*>(p + 4);
+        }
+        float f[8];
+        Elem<bf16_t>::unpack(*reinterpret_cast<const uint4*>(R + row + c), f);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { f[i] += lo[i]; f[4 + i] += hi[i]; }
+        y[u] = Elem<bf16_t>::pack(f);
+        *reinterpret_cast<uint4*>(out + row + c) = y[u];
+        Elem<bf16_t>::unpack(y[u], f);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ss += f[i] * f[i];
+    }
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    const float inv = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)n + eps);
+    if (!NORM) {
+        if (threadIdx.x == 0) rstd[blockIdx.x] = inv;
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int c = (u * 256 + threadIdx.x) * 8;
+        if (c >= n) break;
+        float f[8], g[8];
+        Elem<bf16_t>::unpack(y[u], f);
+        Elem<bf16_t>::unpack(*reinterpret_cast<const uint4*>(gain + c), g);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) f[i] = g[i] * (f[i] * inv);
+        *reinterpret_cast<uint4*>(normed + row + c) = Elem<bf16_t>::pack(f);
+    }
+}
+
+int launch_split_residual_rows(const float* partial, int splits, int m, int n, const void* residual, void* out, float eps, const void* gain, void* normed,
+                               float* rstd, hipStream_t st) {
+    hipLaunchKernelGGL(gain ? split_residual_rows_kernel<true> : split_residual_rows_kernel<false>, dim3(m), dim3(256), 0, st, partial, splits, (size_t)m * n, n,
+                       (const bf16_t*)residual, (bf16_t*)out, eps, (const bf16_t*)gain, (bf16_t*)normed, rstd);
+    return check_launch();
+}
+
 // Query / Key / Value states of one token row per workgroup: scale (1/rms), bias, rotation of the heads of 128 and one
 // rounding; with a window query the per-(token, kv head) dots of the rounded keys with it.  A thread takes features
 // 8 u .. 8 u + 7 of a head and the eight 64 above them, so rotation partners meet in one thread and the dot of a head in

@@ -6,7 +6,7 @@ import torch
 from oracle import slim_oracle as so
 from paper_2508_06447_amd import inputs
 from tests.helpers import assert_residual_close, f64, oracle_shape, oracle_weights
-from tests.test_gpu_layer import run_gpu
+from tests.test_gpu_layer import check_layer, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,21 @@ def test_layer_keeps_the_blocks_that_the_selection_keeps(slim, nb, flags):
             res = slim.slim_pruned_layer(shape, w, rows.cuda(), pos, n_keep)
             want = slim.slim_select_topk_blocks(res["scores"], n_keep, flags)
             assert torch.equal(res["kept"], want), (nb, n_keep, flags)
+
+
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("seq,keep", [(1, 1.0), (64, 1.0), (65, 1.0), (128, 1.0), (256, 1.0), (257, 1.0), (1024, 1.0), (600, 0.5)])
+def test_split_output_projection(slim, seq, keep, fold):
+    """4, 2, none and 2 splits at the edges of their row counts and behind a pruning, against the oracle; and in a workspace of exactly the size asked for, whatever it holds."""
+    print(f"output projection seq {seq} keep {keep} fold {fold}", flush=True)
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, keep_ratio=keep, hidden=2048, n_q_heads=16, n_kv_heads=4, ffn=256, planted=max(1, seq // 50))
+    check_layer(slim, wl, np.float64, rows_count=64, label=f"output projection {seq} {keep} {fold}", fold=fold)
+    x, w = inputs.hidden_states(wl).cuda(), {k: v.cuda() for k, v in inputs.layer_weights(wl).items() if not (fold and k.startswith("g_"))}
+    shape = slim.make_shape(wl.hidden, wl.n_q_heads, wl.n_kv_heads, wl.head_dim, wl.ffn, wl.block, wl.unit, wl.window, x.dtype, wl.rope_theta, wl.rms_eps)
+    size = slim.pruned_layer_workspace_bytes(shape, seq, wl.n_keep)
+    buf, seen = torch.empty(size + 4096, dtype=torch.uint8, device="cuda"), []
+    for fill in (0, 255):
+        buf.fill_(fill)
+        seen.append(slim.slim_pruned_layer(shape, w, x, None, wl.n_keep, workspace=buf[:size])["x"].clone())
+        assert (buf[size:] == fill).all()
+    assert torch.equal(*seen)
