@@ -752,16 +752,17 @@ int slim_pruned_layer(const slim_layer_shape* s, const slim_layer_weights* w, co
     if (p.prune) {
         float* scores = scores_out ? scores_out : (float*)(ws + p.scores);
         SLIM_TRY(block_scores(q_win, w_eff, scores));
-        const bool multi = (Hd * es) % 4 == 0 && (kvd * es) % 4 == 0, select_there = multi && p.nb <= 64;
+        const size_t rb[3] = {(size_t)Hd * es, (size_t)kvd * es, sizeof(float)};
+        const int arrays = fold_attn ? 3 : 2;
+        const bool multi = (Hd * es) % 4 == 0 && (kvd * es) % 4 == 0, select_there = multi && compact_selects(arrays, rb, s->block, n_keep, p.nb);
         if (!select_there) SLIM_TRY(launch_select(scores, p.nb, n_keep, s->flags, kept_blocks_out, st));
         // Hidden rows + positions into x_out / pos_out, keys into kc, and with folded gains the rows' statistics
         // (those of the kept rows are the compacted ones): one launch.
         {
             const void* srcs[3] = {x_in, k_all, rstd_in};
             void* dsts[3] = {x_out, kc, rstd_kept};
-            const size_t rb[3] = {(size_t)Hd * es, (size_t)kvd * es, sizeof(float)};
             if (multi)
-                SLIM_TRY(launch_compact_multi(fold_attn ? 3 : 2, srcs, dsts, rb, pos_in, pos_out, kept_blocks_out, n_keep,
+                SLIM_TRY(launch_compact_multi(arrays, srcs, dsts, rb, pos_in, pos_out, kept_blocks_out, n_keep,
                                               s->block, N, st, select_there ? scores : nullptr, s->flags));
             else {
                 SLIM_TRY(launch_compact(x_in, pos_in, kept_blocks_out, n_keep, s->block, N, Hd, dt, x_out, pos_out, st));

@@ -936,19 +936,32 @@ __global__ void __launch_bounds__(kCopyThreads) compact_multi_kernel(CompactSegs
     }
 }
 
+static size_t compact_chunks(size_t block, size_t row_bytes) {
+    constexpr size_t per = (size_t)kCopyThreads * kCopyVecs * 16;
+    return (block * row_bytes + per - 1) / per;
+}
+
+// Whether the compaction selects its blocks itself (64 at most): every wave ranks them for its own, which takes 0.7 us of a wave for 47 blocks where a launch in
+// front takes two and more of the stream, so only where few waves do it.  The small float32 layer (96 workgroups, 32 blocks) 49.1 -> 48.4 us; 3840 workgroups,
+// 47 blocks 15.8 us against 7.0 and 4.9.
+bool compact_selects(int n_arrays, const size_t* row_bytes, int block, int n_keep, int nb) {
+    size_t chunks = 0;
+    for (int a = 0; a < n_arrays; ++a) chunks += compact_chunks(block, row_bytes[a]);
+    return nb <= 64 && chunks * n_keep * nb <= 64 * 256;
+}
+
 // Up to 4 arrays [N, row_bytes[a]] -> [n', row_bytes[a]]; positions ride with array 0.  row_bytes % 4 == 0.  With scores the launch selects the blocks itself
-// (launch_select, 64 blocks at most, n_keep < nb): every wave for its own block, which costs it a microsecond at the start where a launch in front costs two and more.
+// (launch_select, 64 blocks at most, n_keep < nb).
 int launch_compact_multi(int n_arrays, const void* const* src, void* const* dst, const size_t* row_bytes, const int* pos_in,
                          int* pos_out, int* kept, int n_keep, int block, int N, hipStream_t st, const float* scores, unsigned flags) {
     CompactSegs segs;
-    const size_t per = (size_t)kCopyThreads * kCopyVecs * 16;
     size_t chunks = 0;
     for (int a = 0; a < 4; ++a) {
         const bool on = a < n_arrays;
         segs.src[a] = on ? (const unsigned char*)src[a] : nullptr;
         segs.dst[a] = on ? (unsigned char*)dst[a] : nullptr;
         segs.row_bytes[a] = on ? row_bytes[a] : 0;
-        if (on) chunks += ((size_t)block * row_bytes[a] + per - 1) / per;
+        if (on) chunks += compact_chunks(block, row_bytes[a]);
         segs.chunk_end[a] = (unsigned)chunks;
     }
     const int nb = (N + block - 1) / block;

@@ -152,6 +152,7 @@ int launch_keep_all(int* kept, int nb, const int* pos_in, int* pos_out, int n, h
 int launch_select(const float* scores, int nb, int n_keep, unsigned flags, int* kept, hipStream_t st);
 int launch_compact(const void* src, const int* pos_in, const int* kept, int n_keep, int block, int N,
                    int row_elems, int dtype, void* dst, int* pos_out, hipStream_t st);
+bool compact_selects(int n_arrays, const size_t* row_bytes, int block, int n_keep, int nb);
 int launch_compact_multi(int n_arrays, const void* const* src, void* const* dst, const size_t* row_bytes, const int* pos_in,
                          int* pos_out, int* kept, int n_keep, int block, int N, hipStream_t st, const float* scores = nullptr, unsigned flags = 0);
 int launch_decode_attn(const void* q, const void* pool, size_t slot_bytes, size_t layer_offset, const int* block_of_slot,
