@@ -31,15 +31,15 @@ def test_split_down_projection(slim, seq, hidden, ffn):
 
 
 @pytest.mark.parametrize("m,n", [(1664, 4096), (1665, 4096), (2047, 4096), (1537, 4104), (1793, 3584), (2304, 3584)])
-def test_projections_of_nearly_a_round(slim, m, n, k=192):
-    """Products of bf16 numbers are exact in float and sums of 192 of them within 192 * 2^-24 of sum |a w|: the result is the exact one rounded to bf16."""
+def test_projections_of_nearly_a_round(slim, m, n, k=320):
+    """Products of bf16 numbers are exact in float and sums of 320 of them within 320 * 2^-24 of sum |a w|: the result is the exact one rounded to bf16."""
     print(f"projection {m} x {n} from {k}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(m + n)
     a, w, r = (torch.randn(*s, generator=g, device="cuda").bfloat16() for s in ((m, k), (n, k), (m, n)))
     b = r[0].contiguous()
     prod, mag = a.double() @ w.double().T, a.double().abs() @ w.double().abs().T
     for want, got in ((prod, slim.slim_linear(a, w)), (prod + r.double(), slim.slim_linear(a, w, residual=r)), (prod + b.double(), slim.slim_linear_bias(a, w, b))):
-        assert bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + 200 * 2.0 ** -24 * (mag + 8)).all())
+        assert bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + 328 * 2.0 ** -24 * (mag + 8)).all())
 
 
 @pytest.mark.parametrize("fold", [False, True])
@@ -56,7 +56,7 @@ def test_layer_that_drops_nothing_returns_blocks_and_positions(slim, seq, with_p
 @pytest.mark.parametrize("flags", [0, 1, 2, 3])
 @pytest.mark.parametrize("nb", [2, 3, 33, 63, 64, 65])
 def test_layer_keeps_the_blocks_that_the_selection_keeps(slim, nb, flags):
-    """Up to 64 blocks the compaction selects for itself: the same blocks and order as slim_select_topk_blocks on the layer's scores, whatever is forced, with distinct
+    """Of up to 64 blocks a small compaction selects for itself: the same blocks and order as slim_select_topk_blocks on the layer's scores, whatever is forced, with distinct
     scores, many equal ones (a prompt that repeats) and scores that are not a number."""
     wl = inputs.scaled(inputs.WORKLOADS["cfg1"], seq=nb * 16, planted=0)
     x, w = inputs.hidden_states(wl), {k: v.cuda() for k, v in inputs.layer_weights(wl).items()}
