@@ -767,8 +767,8 @@ int launch_positions(const int* pos_in, int* pos_out, int n, hipStream_t st) {
     return check_launch();
 }
 
-// A layer that drops nothing: kept = 0 .. nb - 1 and the positions as they came in, either may be null.  One launch instead of two:
-// 512-token layer 297.6 -> 295.6 us.
+// A float32 layer that drops nothing: kept = 0 .. nb - 1 and the positions as they came in, either may be null.  (In bf16 layers the pass over the rows
+// writes them.)
 __global__ void keep_all_kernel(int* __restrict__ kept, int nb, const int* __restrict__ pos_in, int* __restrict__ pos_out, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (kept && i < nb) kept[i] = i;
