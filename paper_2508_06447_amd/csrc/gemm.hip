@@ -20,6 +20,7 @@
 // as MFMA fragments inside that loop.  Few rows, and residuals that the loop does not take (residual_in_four_waves), use C++ tiles with the
 // same LDS layout and pipeline; a register-staged kernel with k predicates covers ragged k_in.
 #include "slim_common.h"
+#include "routes.h"
 #include "tile_plan.h"
 
 #include <algorithm>
@@ -1047,16 +1048,7 @@ static FewShape few_shape(int M, const int* n, int count, int splits) {
     return FEW_D;
 }
 
-// Up to how many outputs the few-row tiles are taken, and only where their 256 x 128 tiles are no more than a round.  us, weights from HBM, few-row / two-size: 4096
-// features from 4096, 512 rows 31 / 53, 1024 39 / 54, 1280 to 1664 53 / 53, 2300 (288 tiles) 91 / 69; 5120 features, 1664 rows (260 tiles) 94 / 73; 1024 features, 3000 rows
-// 28 / 38, 4096 33 / 38, 6000 47 / 42, 8192 57 / 67; 512 features from 3584, 12000 rows 41 / 59.
-bool few_rows(int m, int n) { return (long long)m * n <= (1ll << 23) && (m + 127ll) / 128 * ((n + 255ll) / 256) <= cu_count(); }
-
-// Of these, the launches that the two-size tiles are faster at all the same: nearly a round of 256 x 128 tiles of a wide output.  us, few-row / two-size, with residual: 4096
-// features from 4096, 1664 rows (208 tiles) 57 / 56, 1800 (240) 58 / 52, 2048 (256) 62 / 57, from 14336 2048 rows 199 / 190; 3584 from 3584, 1800 rows (210) 50 / 49, 2048 (224) 53 /
-// 51, 2300 (252) 57 / 54; 5120 from 4096, 1511 rows (240) 57 / 54.  Short rows too (2048 x 4096 from 64 8.2 / 7.6, from 256 10.4 / 9.8), but not
-// below 256 features with a residual (from 128 10.2 / 10.7).
-static bool nearly_a_round(int m, int n) { return n >= 2048 && (m + 127ll) / 128 * ((n + 255ll) / 256) * 16 > cu_count() * 13ll; }
+bool few_rows(int m, int n) { return few_rows(m, n, cu_count()); }
 
 // The most rows up to m that few_rows takes.
 int few_rows_most(int m, int n) {
@@ -1208,7 +1200,7 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
         if (M <= 256 && !second_round) return launch_bf16<1, 2, 2, 4, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
     } else if constexpr (EPI == EPI_ROPE) {
         if (M <= 128) return launch_bf16<4, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-    } else if (few_rows(M, N) && !(nearly_a_round(M, N) && (EPI != EPI_RESIDUAL || K >= 256))) {
+    } else if (in_few_row_tiles(M, N, K, ldo, EPI == EPI_RESIDUAL, cu_count())) {
         switch (few_shape(M, &N, 1, 1)) {
             case FEW_A: return launch_bf16<2, 2, 4, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
             case FEW_B: return launch_bf16<2, 2, 2, 2, EPI, false, 4>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);

@@ -1,0 +1,25 @@
+// Which of two kernels a call takes, where sizes decide (host code, no GPU).  cu: compute units of the device.
+#pragma once
+
+namespace slim {
+
+// Up to how many outputs the few-row tiles are taken, and only where their 256 x 128 tiles are no more than a round.  us, weights from HBM, few-row / two-size: 4096
+// features from 4096, 512 rows 31 / 53, 1024 39 / 54, 1280 to 1664 53 / 53, 2300 (288 tiles) 91 / 69; 5120 features, 1664 rows (260 tiles) 94 / 73; 1024 features, 3000 rows
+// 28 / 38, 4096 33 / 38, 6000 47 / 42, 8192 57 / 67; 512 features from 3584, 12000 rows 41 / 59.
+inline long long few_row_tiles(int m, int n) { return (m + 127ll) / 128 * ((n + 255ll) / 256); }
+inline bool few_rows(int m, int n, int cu) { return (long long)m * n <= (1ll << 23) && few_row_tiles(m, n) <= cu; }
+
+// Of these, the launches that the two-size tiles are faster at all the same: nearly a round of 256 x 128 tiles of a wide output.  us, few-row / two-size, with residual: 4096
+// features from 4096, 1664 rows (208 tiles) 57 / 56, 1800 (240) 58 / 52, 2048 (256) 62 / 57, from 14336 2048 rows 199 / 190; 3584 from 3584, 1800 rows (210) 50 / 49, 2048 (224) 53 /
+// 51, 2300 (252) 57 / 54; 5120 from 4096, 1511 rows (240) 57 / 54.  Short rows too (2048 x 4096 from 64 8.2 / 7.6, from 256 10.4 / 9.8), but not
+// below 256 features with a residual (from 128 10.2 / 10.7).
+inline bool nearly_a_round(int m, int n, int cu) { return n >= 2048 && few_row_tiles(m, n) * 16 > cu * 13ll; }
+
+// Whether a projection of m rows runs in the few-row tiles, which take any row stride of the output; the two-size launch takes those below 2^23.
+inline bool in_few_row_tiles(int m, int n, int k, int ldo, bool residual, int cu) {
+    if (!few_rows(m, n, cu)) return false;
+    const bool leaves = nearly_a_round(m, n, cu) && ldo < 1 << 23 && (!residual || k >= 256);
+    return !leaves;
+}
+
+}   // namespace slim

@@ -1,4 +1,6 @@
 """Row counts at which a projection changes its kernel or its split, and what the first pass over the rows leaves behind."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -89,3 +91,19 @@ def test_split_output_projection(slim, seq, keep, fold):
         seen.append(slim.slim_pruned_layer(shape, w, x, None, wl.n_keep, workspace=buf[:size])["x"].clone())
         assert (buf[size:] == fill).all()
     assert torch.equal(*seen)
+
+
+@pytest.mark.parametrize("residual", [False, True])
+def test_output_rows_that_lie_far_apart(slim, residual, m=64, n=54016, k=256, ldo=1 << 23):
+    """Nearly a round of tiles whose rows are 2^23 elements apart (1 GB between first and last), against the same product in rows of n."""
+    print(f"projection {m} x {n} from {k}, row stride {ldo}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    a, w, r = (torch.randn(*s, generator=g, device="cuda").bfloat16() for s in ((m, k), (n, k), (m, n)))
+    far = torch.empty((m - 1) * ldo + n, dtype=torch.bfloat16, device="cuda").as_strided((m, n), (ldo, 1))
+    far.copy_(r)                                          # (the residual is taken from the place that the result goes to)
+    lib, p = slim.load_library(), lambda t: ctypes.c_void_p(t.data_ptr())
+    rc = lib.slim_linear(p(a), k, p(w), p(far) if residual else None, m, n, k, ldo, 1, p(far), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, lib.slim_status_string(rc)
+    prod, mag = a.double() @ w.double().T, a.double().abs() @ w.double().abs().T
+    want = prod + r.double() if residual else prod
+    assert bool(((far.double() - want).abs() <= 2.0 ** -8 * want.abs() + (k + 8) * 2.0 ** -24 * (mag + 8)).all())

@@ -1,0 +1,36 @@
+"""Which of two kernels a call takes (csrc/routes.h), compiled for the CPU: the calls whose two sides were measured, on a chip of 256 compute units.  No GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    """Evaluates C++ expressions over csrc/routes.h: a list of them to the list of their values."""
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no host compiler")
+
+    def values(expressions):
+        d = tmp_path_factory.mktemp("routes")
+        src, exe = d / "routes.cpp", d / "routes"
+        src.write_text('#include "routes.h"\n#include <cstdio>\nusing namespace slim;\nint main() {\n'
+                       + "".join(f'    printf("%d\\n", (int)({e}));\n' for e in expressions) + "}\n")
+        subprocess.run([gxx, "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2508_06447_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+        return [int(v) for v in subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split()]
+    return values
+
+
+def check(routes, cases):
+    got = routes([e for e, _ in cases])
+    assert [(e, v) for (e, _), v in zip(cases, got)] == [(e, int(w)) for e, w in cases]
+
+
+def test_row_strides_that_only_the_few_row_tiles_take(routes):
+    """The two-size launch refuses output rows of 2^23 elements and more: such a call stays where it is served."""
+    check(routes, [(f"in_few_row_tiles({m}, {n}, 4096, {ldo}, {res}, 256)", ldo >= 1 << 23)
+                   for m, n in ((64, 54016), (2048, 4096)) for res in ("false", "true") for ldo in (54016, (1 << 23) - 8, 1 << 23, 1 << 24)])
