@@ -1200,7 +1200,7 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
         if (M <= 256 && !second_round) return launch_bf16<1, 2, 2, 4, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
     } else if constexpr (EPI == EPI_ROPE) {
         if (M <= 128) return launch_bf16<4, 1, 2, 4, EPI, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-    } else if (in_few_row_tiles(M, N, K, ldo, EPI == EPI_RESIDUAL, cu_count())) {
+    } else if (in_few_row_tiles(M, N, K, ldo, EPI == EPI_RESIDUAL, EPI == EPI_RESIDUAL && residual_in_four_waves(R, M, N, K, ldo), cu_count())) {
         switch (few_shape(M, &N, 1, 1)) {
             case FEW_A: return launch_bf16<2, 2, 4, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
             case FEW_B: return launch_bf16<2, 2, 2, 2, EPI, false, 4>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);

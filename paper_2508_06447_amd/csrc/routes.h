@@ -15,10 +15,13 @@ inline bool few_rows(int m, int n, int cu) { return (long long)m * n <= (1ll << 
 // below 256 features with a residual (from 128 10.2 / 10.7).
 inline bool nearly_a_round(int m, int n, int cu) { return n >= 2048 && few_row_tiles(m, n) * 16 > cu * 13ll; }
 
-// Whether a projection of m rows runs in the few-row tiles, which take any row stride of the output; the two-size launch takes those below 2^23.
-inline bool in_few_row_tiles(int m, int n, int k, int ldo, bool residual, int cu) {
+// Whether a projection of m rows runs in the few-row tiles, which take any row stride of the output; the two-size launch takes those below 2^23.  four_waves: the
+// residual would be added in that launch's four-wave tile.  Its eight-wave tile is the slower loop: with residual, us, few-row / eight waves: 4104 features from 4096, 1600 rows 59 / 79,
+// from 14336 197 / 272; 2880 from 4096, 2300 rows 57 / 76; 2056 from 4096, 3000 rows 56 / 76; 4000 from 4096, 2048 rows 62 / 81; 12104 from
+// 768, 640 rows 22.4 / 24.2, from 640 22.3 / 20.3; 4000 from 640, 2048 rows 23.5 / 18.8.
+inline bool in_few_row_tiles(int m, int n, int k, int ldo, bool residual, bool four_waves, int cu) {
     if (!few_rows(m, n, cu)) return false;
-    const bool leaves = nearly_a_round(m, n, cu) && ldo < 1 << 23 && (!residual || k >= 256);
+    const bool leaves = nearly_a_round(m, n, cu) && ldo < 1 << 23 && (!residual || (k >= 256 && (four_waves || k <= 640)));
     return !leaves;
 }
 

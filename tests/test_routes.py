@@ -32,5 +32,12 @@ def check(routes, cases):
 
 def test_row_strides_that_only_the_few_row_tiles_take(routes):
     """The two-size launch refuses output rows of 2^23 elements and more: such a call stays where it is served."""
-    check(routes, [(f"in_few_row_tiles({m}, {n}, 4096, {ldo}, {res}, 256)", ldo >= 1 << 23)
+    check(routes, [(f"in_few_row_tiles({m}, {n}, 4096, {ldo}, {res}, true, 256)", ldo >= 1 << 23)
                    for m, n in ((64, 54016), (2048, 4096)) for res in ("false", "true") for ldo in (54016, (1 << 23) - 8, 1 << 23, 1 << 24)])
+
+
+def test_residuals_that_the_two_size_launch_would_add_in_its_eight_wave_tile(routes):
+    """Widths that are no multiple of 256 and residuals that are not aligned: only short rows leave the few-row tiles, with the four-wave tile long ones too."""
+    shapes = ((1600, 4104), (1900, 3904), (2048, 4000), (3300, 2056), (1400, 5000), (640, 12104))
+    check(routes, [(f"in_few_row_tiles({m}, {n}, {k}, {n}, true, {four}, 256)", four == "false" and k > 640)
+                   for m, n in shapes for k in (256, 640, 1024, 4096, 14336) for four in ("false", "true")])
