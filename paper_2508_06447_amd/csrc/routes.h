@@ -11,17 +11,24 @@ inline bool few_rows(int m, int n, int cu) { return (long long)m * n <= (1ll << 
 
 // Of these, the launches that the two-size tiles are faster at all the same: nearly a round of 256 x 128 tiles of a wide output.  us, few-row / two-size, with residual: 4096
 // features from 4096, 1664 rows (208 tiles) 57 / 56, 1800 (240) 58 / 52, 2048 (256) 62 / 57, from 14336 2048 rows 199 / 190; 3584 from 3584, 1800 rows (210) 50 / 49, 2048 (224) 53 /
-// 51, 2300 (252) 57 / 54; 5120 from 4096, 1511 rows (240) 57 / 54.  Short rows too (2048 x 4096 from 64 8.2 / 7.6, from 256 10.4 / 9.8), but not
-// below 256 features with a residual (from 128 10.2 / 10.7).
+// 51, 2300 (252) 57 / 54; 5120 from 4096, 1511 rows (240) 57 / 54.  Short rows too (2048 x 4096 from 64 8.2 / 7.6, from 256 10.4 / 9.8).
 inline bool nearly_a_round(int m, int n, int cu) { return n >= 2048 && few_row_tiles(m, n) * 16 > cu * 13ll; }
 
 // Whether a projection of m rows runs in the few-row tiles, which take any row stride of the output; the two-size launch takes those below 2^23.  four_waves: the
 // residual would be added in that launch's four-wave tile.  Its eight-wave tile is the slower loop: with residual, us, few-row / eight waves: 4104 features from 4096, 1600 rows 59 / 79,
 // from 14336 197 / 272; 2880 from 4096, 2300 rows 57 / 76; 2056 from 4096, 3000 rows 56 / 76; 4000 from 4096, 2048 rows 62 / 81; 12104 from
 // 768, 640 rows 22.4 / 24.2, from 640 22.3 / 20.3; 4000 from 640, 2048 rows 23.5 / 18.8.
+// Short rows with a residual are as fast or faster in the few-row tiles where these divide evenly over the XCDs and leave a sixteenth of the chip: 4096 features, 1665 rows (224 tiles)
+// from 256 10.7 / 11.4, from 384 12.4 / 12.9, from 448 13.6 / 13.7, from 512 14.5 / 14.1; 8192, 896 rows (224) 11.2 / 11.7, 12.9 / 13.2, 13.5 / 13.4, 14.6 / 14.3; 9216, 768 rows (216)
+// from 256 10.9 / 11.0; 2880, 2300 rows (216, eight waves) from 256 11.1 / 11.6, from 384 13.0 / 13.6.  Elsewhere they depend on where the buffers lie, 2048 x 4096 from 256 (256
+// tiles) 11 to 17 / 12, from 512 14 to 20 / 15, and from 192 10 to 16 / 11 to 12; 5120, 1408 rows (220) from 256 14.0 / 12.0; 3840, 1920 rows (225) from 384 14 to 17 / 14.
 inline bool in_few_row_tiles(int m, int n, int k, int ldo, bool residual, bool four_waves, int cu) {
     if (!few_rows(m, n, cu)) return false;
-    const bool leaves = nearly_a_round(m, n, cu) && ldo < 1 << 23 && (!residual || (k >= 256 && (four_waves || k <= 640)));
+    bool leaves = nearly_a_round(m, n, cu) && ldo < 1 << 23;
+    if (residual) {
+        const bool even = few_row_tiles(m, n) % 8 == 0 && few_row_tiles(m, n) * 16 < cu * 15ll;
+        leaves = leaves && k >= (even ? 448 : 256) && (four_waves || (!even && k <= 640));
+    }
     return !leaves;
 }
 

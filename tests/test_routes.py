@@ -41,3 +41,12 @@ def test_residuals_that_the_two_size_launch_would_add_in_its_eight_wave_tile(rou
     shapes = ((1600, 4104), (1900, 3904), (2048, 4000), (3300, 2056), (1400, 5000), (640, 12104))
     check(routes, [(f"in_few_row_tiles({m}, {n}, {k}, {n}, true, {four}, 256)", four == "false" and k > 640)
                    for m, n in shapes for k in (256, 640, 1024, 4096, 14336) for four in ("false", "true")])
+
+
+def test_residuals_of_short_rows(routes):
+    """Fewer than 448 features: in the few-row tiles where these divide evenly over the XCDs in less than 15/16 of a round; fewer than 256: everywhere."""
+    even, other = ((1665, 4096), (1792, 4096), (896, 8192), (768, 9216), (2300, 2880)), ((2048, 4096), (1408, 5120), (1920, 3840), (1500, 5120), (1400, 5000))
+    check(routes, [(f"in_few_row_tiles({m}, {n}, {k}, {n}, true, {'true' if n % 256 == 0 else 'false'}, 256)",
+                    k < 256 or ((m, n) in even and (k < 448 or n % 256 != 0)))
+                   for m, n in even + other for k in (64, 192, 256, 384, 448, 512)])
+    check(routes, [(f"in_few_row_tiles({m}, {n}, {k}, {n}, false, false, 256)", False) for m, n in even + other for k in (64, 256, 4096)])
