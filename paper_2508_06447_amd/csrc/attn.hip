@@ -26,6 +26,7 @@
 // a0-a191, S tiles and everything the vector ALU touches in v0-v231) is the assembly that gen_attn_asm.py writes
 // into attn_bf16_body.inc; the C++ below computes its per-lane and per-workgroup operands.
 #include "slim_common.h"
+#include "routes.h"
 #include <mutex>
 #include <type_traits>
 
@@ -314,12 +315,9 @@ int launch_attn(const void* q, const void* k, const void* v, int n, int Hq, int 
                 attr_err = hipFuncSetAttribute((const void*)attn_bf16_few_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FSTAGES * FSTAGE_BYTES);
         });
         if (attr_err != hipSuccess) return set_hip_error(attr_err);
-        // Few rows: groups whose heads fill three or four of a workgroup's four places, and up to two workgroups per CU (us, the other kernel / this one: 32 / 8 heads, 2048
-        // rows 49.2 / 46.3, 2560 63 / 74; 28 / 4 heads 48.5 / 46.3, 62 / 74).  A reference in units of unscaled logits needs a positive scale.
-        const int per_group = (Hq / Hkv + 3) / 4;
-        const long long few_wgs = (n + 31ll) / 32 * Hkv * per_group;
-        if (few_wgs <= 2 * cu_count() && Hq / Hkv % 4 != 1 && Hq / Hkv % 4 != 2 && scale > 0.f) {
-            hipLaunchKernelGGL(attn_bf16_few_kernel, dim3((unsigned)few_wgs), dim3(512), FSTAGES * FSTAGE_BYTES, st, (const bf16_t*)q, (const bf16_t*)k,
+        if (few_row_attention(n, Hq, Hkv, scale, cu_count())) {
+            const unsigned few_wgs = (unsigned)((n + 31ll) / 32 * Hkv * ((Hq / Hkv + 3) / 4));
+            hipLaunchKernelGGL(attn_bf16_few_kernel, dim3(few_wgs), dim3(512), FSTAGES * FSTAGE_BYTES, st, (const bf16_t*)q, (const bf16_t*)k,
                                (const bf16_t*)v, (bf16_t*)out, n, Hq, Hkv, scale * 1.4426950408889634f, (n + 31) / 32);
         } else if (Hq == 4 * Hkv) {
             const int n_qt = (n + 63) / 64;

@@ -32,4 +32,18 @@ inline bool in_few_row_tiles(int m, int n, int k, int ldo, bool residual, bool f
     return !leaves;
 }
 
+// Whether bf16 attention of n rows runs in the few-row kernel: groups whose heads fill three or four of a workgroup's four places, up to two workgroups per CU.  us, the other kernel / this
+// one: 32 / 8 heads, 2048 rows 49.2 / 46.3, 2560 63 / 74; 28 / 4 heads 48.5 / 46.3, 62 / 74.  Behind one workgroup per CU only if the rows are long: with many units (four heads of a kv
+// group) the second round starts again for a few tiles of keys.  16 units of 416 and 512 workgroups 1.12 and 1.02 times as fast as the other kernel, 24 of 384 1.00 to 1.06, of 480
+// 0.92 to 0.97, 28 of 280 1.04 to 1.13, of 336 0.91 to 0.98, 48 of 288 to 384 0.90 to 1.01 (112 / 16 heads, 384 rows 16.7 / 18.7), unless the other kernel, which gives a head's 256 queries (a group of
+// four: 64) a workgroup, begins a second round: 28 units of 476 1.43, 36 of 324 to 504 1.38 to 1.64, 96 of 288 1.21 to 1.30, groups of four 30 of 510 1.05, 56 of 504 1.28 (but 20
+// to 22 of 500 0.97).  A reference in units of unscaled logits needs a positive scale.
+inline bool few_row_attention(int n, int Hq, int Hkv, float scale, int cu) {
+    const int group = Hq / Hkv, units = Hkv * ((group + 3) / 4);
+    const long long workgroups = (n + 31ll) / 32 * units, others = group == 4 ? (n + 63ll) / 64 * Hkv : (n + 255ll) / 256 * Hq;
+    if (group % 4 == 1 || group % 4 == 2 || !(scale > 0.f) || workgroups > 2ll * cu) return false;
+    const int eighths = units <= 16 ? 16 : units <= 24 ? 12 : units <= 30 ? 9 : 8;       // of a round
+    return 8 * workgroups <= (long long)eighths * cu || (others > cu && (group != 4 || units > 24));
+}
+
 }   // namespace slim

@@ -50,3 +50,14 @@ def test_residuals_of_short_rows(routes):
                     k < 256 or ((m, n) in even and (k < 448 or n % 256 != 0)))
                    for m, n in even + other for k in (64, 192, 256, 384, 448, 512)])
     check(routes, [(f"in_few_row_tiles({m}, {n}, {k}, {n}, false, false, 256)", False) for m, n in even + other for k in (64, 256, 4096)])
+
+
+def test_attention_that_would_begin_a_second_round_for_few_keys(routes):
+    """(rows, query heads, kv heads): calls on both sides of the line, as measured, and what the few-row kernel does not cover."""
+    few = ((512, 64, 8), (2048, 32, 8), (2048, 28, 4), (1024, 64, 16), (1024, 48, 16), (8192, 8, 1), (16384, 4, 1), (256, 128, 8), (256, 112, 16), (512, 96, 24), (504, 96, 8),
+           (672, 96, 8), (280, 192, 16), (320, 192, 16), (160, 96 * 4, 96), (288, 56 * 4, 56), (320, 112, 28), (288, 90, 30))
+    other = ((384, 112, 16), (320, 112, 16), (512, 112, 16), (384, 96, 32), (512, 128, 32), (384, 128, 8), (160, 256, 8), (192, 192, 16), (240, 192, 16), (640, 96, 24),
+             (800, 80, 20), (352, 112, 28), (288, 128, 32), (2049, 32, 8), (2049, 28, 4))
+    check(routes, [(f"few_row_attention({n}, {hq}, {hkv}, 0.1f, 256)", True) for n, hq, hkv in few]
+          + [(f"few_row_attention({n}, {hq}, {hkv}, 0.1f, 256)", False) for n, hq, hkv in other]
+          + [(f"few_row_attention(64, {hq}, 2, {scale}, 256)", False) for hq, scale in ((2, "0.1f"), (4, "0.1f"), (10, "0.1f"), (12, "0.f"), (8, "-0.1f"), (8, "__builtin_nanf(\"\")"))])
