@@ -1,6 +1,7 @@
 // Block-wise prompt token pruning (Section 4.2): block scores (Eq. 1-2), block selection,
 // hidden-state compaction.  All three are HBM-/latency-bound; none uses matrix cores.
 #include "slim_common.h"
+#include "routes.h"
 #include "window_plan.h"
 #include <algorithm>
 
@@ -941,13 +942,10 @@ static size_t compact_chunks(size_t block, size_t row_bytes) {
     return (block * row_bytes + per - 1) / per;
 }
 
-// Whether the compaction selects its blocks itself (64 at most): every wave ranks them for its own, which takes 0.7 us of a wave for 47 blocks where a launch in
-// front takes two and more of the stream, so only where few waves do it.  The small float32 layer (96 workgroups, 32 blocks) 49.1 -> 48.4 us; 3840 workgroups,
-// 47 blocks 15.8 us against 7.0 and 4.9.
 bool compact_selects(int n_arrays, const size_t* row_bytes, int block, int n_keep, int nb) {
     size_t chunks = 0;
     for (int a = 0; a < n_arrays; ++a) chunks += compact_chunks(block, row_bytes[a]);
-    return nb <= 64 && chunks * n_keep * nb <= 64 * 256;
+    return compact_selects((long long)chunks, n_keep, nb);
 }
 
 // Up to 4 arrays [N, row_bytes[a]] -> [n', row_bytes[a]]; positions ride with array 0.  row_bytes % 4 == 0.  With scores the launch selects the blocks itself

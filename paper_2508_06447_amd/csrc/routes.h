@@ -46,4 +46,10 @@ inline bool few_row_attention(int n, int Hq, int Hkv, float scale, int cu) {
     return 8 * workgroups <= (long long)eighths * cu || (others > cu && (group != 4 || units > 24));
 }
 
+// Whether a layer's compaction of n_keep of nb blocks, in `chunks` workgroups each, selects them itself (64 at most): every wave ranks the blocks for its own, one after another, where a launch in
+// front takes two microseconds and more of the stream, so only where few waves do it.  Layers, us, selection in front / in the compaction: small float32 (chunks 6), 16 blocks 46.5 / 45.0, 32 51.7 /
+// 50.7, 48 59.0 / 58.3, 56 60.5 / 60.5, 64 within 0.5 % either way; bf16 of 4096, blocks of 64 rows (161), 4 of 16 254.3 / 252.1, 8 of 16 (a product of 20608) 316.2 / 314.8, 16 of 32 (82432)
+// 501.7 / 500.9, 24 of 48 (185472) 682 / 687; of 2048, blocks of 32, 12 of 24 (11808) 135.0 / 133.2, 16 of 32 (20992) 151.0 / 149.1, 24 of 48 (47232) 187.3 / 187.2, 32 of 64 (83968) 222.2 / 223.4.
+inline bool compact_selects(long long chunks, int n_keep, int nb) { return nb <= 64 && chunks * n_keep * nb <= 64 * 256; }
+
 }   // namespace slim

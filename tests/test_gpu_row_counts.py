@@ -55,24 +55,27 @@ def test_layer_that_drops_nothing_returns_blocks_and_positions(slim, seq, with_p
     assert torch.equal(res["pos"].cpu(), pos if with_pos else torch.arange(seq, dtype=torch.int32))
 
 
-@pytest.mark.parametrize("flags", [0, 1, 2, 3])
-@pytest.mark.parametrize("nb", [2, 3, 33, 63, 64, 65])
+@pytest.mark.parametrize("nb,flags", [(nb, flags) for nb in (2, 3, 33, 63, 64, 65) for flags in (0, 1, 2, 3) if (nb, flags) != (2, 3)])
 def test_layer_keeps_the_blocks_that_the_selection_keeps(slim, nb, flags):
-    """Of up to 64 blocks a small compaction selects for itself: the same blocks and order as slim_select_topk_blocks on the layer's scores, whatever is forced, with distinct
-    scores, many equal ones (a prompt that repeats) and scores that are not a number."""
-    wl = inputs.scaled(inputs.WORKLOADS["cfg1"], seq=nb * 16, planted=0)
+    """Of up to 64 blocks a small compaction selects for itself (of 8 rows and 3 workgroups here, so that 63 of 64 kept are a small one): the same blocks and order as
+    slim_select_topk_blocks on the layer's scores, whatever is forced, with distinct scores, many equal ones (a prompt that repeats) and scores that are not a number.  (Both forced of 2
+    blocks leaves nothing to select.)"""
+    wl = inputs.scaled(inputs.WORKLOADS["cfg1"], seq=nb * 8, planted=0)
     x, w = inputs.hidden_states(wl), {k: v.cuda() for k, v in inputs.layer_weights(wl).items()}
-    shape = slim.make_shape(wl.hidden, wl.n_q_heads, wl.n_kv_heads, wl.head_dim, wl.ffn, 16, wl.unit, wl.window, x.dtype, wl.rope_theta, wl.rms_eps, flags)
-    pos = torch.zeros(nb * 16, dtype=torch.int32, device="cuda")                            # no rotation: equal rows have equal keys
+    shape = slim.make_shape(wl.hidden, wl.n_q_heads, wl.n_kv_heads, wl.head_dim, wl.ffn, 8, wl.unit, wl.window, x.dtype, wl.rope_theta, wl.rms_eps, flags)
+    forced = bin(flags).count("1")
+    alike = torch.zeros(nb * 8, dtype=torch.int32, device="cuda")                          # no rotation: equal rows have equal keys
+    spread = 3 * torch.arange(nb * 8, dtype=torch.int32, device="cuda") + 5
     odd = x.clone()
-    odd[16:32] = float("nan")
-    for rows in (x, x[:16].repeat(nb, 1), odd):
-        for n_keep in {max(1, bin(flags).count("1")), nb // 2 + 1, nb - 1}:
-            if n_keep < min(nb, bin(flags).count("1")) or n_keep >= nb:
-                continue
+    odd[8:16] = float("nan")
+    counts = [n for n in sorted({max(1, forced), nb // 2 + 1, nb - 1}) if forced <= n < nb]
+    assert counts
+    for rows, pos in ((x, spread), (x[:8].repeat(nb, 1), alike), (odd, spread)):
+        for n_keep in counts:
             res = slim.slim_pruned_layer(shape, w, rows.cuda(), pos, n_keep)
             want = slim.slim_select_topk_blocks(res["scores"], n_keep, flags)
             assert torch.equal(res["kept"], want), (nb, n_keep, flags)
+            assert torch.equal(res["pos"], pos.view(nb, 8)[want.long()].flatten()), (nb, n_keep, flags)
 
 
 @pytest.mark.parametrize("fold", [False, True])

@@ -61,3 +61,10 @@ def test_attention_that_would_begin_a_second_round_for_few_keys(routes):
     check(routes, [(f"few_row_attention({n}, {hq}, {hkv}, 0.1f, 256)", True) for n, hq, hkv in few]
           + [(f"few_row_attention({n}, {hq}, {hkv}, 0.1f, 256)", False) for n, hq, hkv in other]
           + [(f"few_row_attention(64, {hq}, 2, {scale}, 256)", False) for hq, scale in ((2, "0.1f"), (4, "0.1f"), (10, "0.1f"), (12, "0.f"), (8, "-0.1f"), (8, "__builtin_nanf(\"\")"))])
+
+
+def test_compactions_that_select_their_blocks(routes):
+    """(workgroups per block, kept, blocks): the small float32 layer's 6 (3 with blocks of 8 rows), and a bf16 layer of 4096 with folded gains and 64-row blocks, 161."""
+    check(routes, [(f"compact_selects({chunks}, {keep}, {nb})", want) for chunks, keep, nb, want in (
+        (6, 1, 2, True), (6, 16, 32, True), (6, 32, 64, True), (3, 63, 64, True), (6, 63, 64, False), (3, 1, 65, False), (161, 4, 16, True), (161, 8, 16, False),
+        (161, 24, 47, False))])
