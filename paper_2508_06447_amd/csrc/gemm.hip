@@ -348,7 +348,11 @@ __device__ __forceinline__ void tile_of_workgroup(int L, bool xcd_runs, int tile
 // With re.row_scale the accumulators of token row m are multiplied by row_scale[m] before the epilogue: with
 // row_scale = 1/sqrt(mean(a[m,:]^2) + eps) and a = the raw residual stream this is the projection of RMSNorm(a)
 // (unit gain; a gain vector is folded into the weights beforehand), and the normalised rows are never stored.
-template <int TW, int TA, int WGN, int WGM, int EPI, int NS = 2>
+// SPREAD: a k-tile's loads go out in four parts, each behind the LDS reads of a k-step.  In one burst behind the barrier, 4 to 8 of them keep the wave from its LDS reads while the
+// address unit works through them; with two stages the burst is still the better one, since a tile's loads have no time to spare.  us, weights from HBM, burst / dealt: 256 x 128 tiles 2360 x
+// 2176 from 960 16.4 / 14.6, 3968 x 1915 from 7744 142 / 138; 128 x 128 3993 x 640 from 3392 26.5 / 22.6, 1406 x 2012 from 2304 25.7 / 23.0; SwiGLU 200 x 14336 from 4096
+// 67.9 / 65.1; 64 x 64 tiles +-1 %.
+template <int TW, int TA, int WGN, int WGM, int EPI, int NS = 2, bool SPREAD = (NS >= 3)>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W0,
                                           const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C, int ldo, int M,
                                           int N, int K, int KT, int m0, int n0, unsigned char* lds, const EpiExtra& re) {
@@ -357,7 +361,6 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
     static_assert(NS >= 2 && NS <= 5, "the k-loop is written out for up to 5 stages");
     static_assert(EPI != EPI_ROPE || TW == 4, "the RoPE epilogue needs one 128-wide head per wave");
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
-    constexpr bool SPREAD = NS >= 3;
     constexpr int BN = 32 * TW * WGN, BM = 32 * TA * WGM, WROWS = BN * NW;
     constexpr int STAGE = (WROWS + BM) * BK * 2;
     constexpr int LR = WV * 8;                           // tile rows that one wave-load of every wave covers
@@ -447,11 +450,15 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda,
     };
     // NS LDS stages.  Fragments are read one k-step ahead of their MFMAs, also across k-tiles: the
     // workgroup barrier of a k-tile sits before its last k-step, when every wave has pulled that step's
-    // fragments into registers.  Past the barrier the stage is free, so tile kt+NS is sent into it, tile
-    // kt+1 (sent NS-1 iterations earlier, waited for just before the barrier) is visible to all waves, and
-    // its first fragments are read while the last k-step's MFMAs run.  The loop is unrolled by NS so the
-    // stage of every read is a compile-time constant.  Loads past the last k-tile re-read it (into a stage
-    // that nobody reads), so the number of loads in flight at a wait is a constant.
+    // fragments into registers.  Past the barrier the stage is free and tile kt+NS is sent into it: all of it at
+    // once, or with SPREAD a quarter there and a quarter in each of the first three k-steps of tile kt+1, whose
+    // waves still read another stage.  So at the wait before the barrier of tile kt the loads up to tile
+    // kt+NS-1 have gone out, and all but the NS-2 youngest tiles of them are waited for: tile kt+1 is visible to
+    // all waves past the barrier, and its first fragments are read while the last k-step's MFMAs run.  (The
+    // wait in front of the loop is for tile 0 alone: NS-2 tiles and with SPREAD the first quarter of another are
+    // behind it, NS-1 tiles without.)  The loop is unrolled by NS so the stage of every read is a compile-time
+    // constant.  Loads past the last k-tile re-read it (into a stage that nobody reads), so the number of loads
+    // in flight at a wait is a constant.
     constexpr unsigned kStageLoads = WLD + ALD;
     constexpr unsigned kParts = SPREAD ? 4 : 1;
     auto part = [](unsigned p) { return (int)(p * kStageLoads / kParts); };
@@ -617,7 +624,7 @@ __device__ __forceinline__ void gemm_tile4(const bf16_t* __restrict__ A, int lda
 }
 
 // Few-row kernel: every workgroup computes one tile of the same shape, from NS LDS stages.
-template <int TW, int TA, int WGN, int WGM, int EPI, int NS>
+template <int TW, int TA, int WGN, int WGM, int EPI, int NS, bool SPREAD>
 __global__ void __launch_bounds__(64 * WGN * WGM) gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda,
                                                         const bf16_t* __restrict__ W0,
                                                         const bf16_t* __restrict__ W1, const bf16_t* R, bf16_t* C,
@@ -626,7 +633,7 @@ __global__ void __launch_bounds__(64 * WGN * WGM) gemm_bf16_kernel(const bf16_t*
     extern __shared__ __align__(16) unsigned char lds[];
     int tm, tn;
     tile_of_workgroup(blockIdx.x, true, tiles_m, tiles_n, tm, tn);
-    gemm_tile<TW, TA, WGN, WGM, EPI, NS>(A, lda, W0, W1, R, C, ldo, M, N, K, K / BK, tm * 32 * TA * WGM, tn * 32 * TW * WGN, lds, re);
+    gemm_tile<TW, TA, WGN, WGM, EPI, NS, SPREAD>(A, lda, W0, W1, R, C, ldo, M, N, K, K / BK, tm * 32 * TA * WGM, tn * 32 * TW * WGN, lds, re);
 }
 
 // Shapes of the two-size launch: 256-token tiles for the first big_tiles_m token-tiles, 128-token tiles
@@ -895,7 +902,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_generic_kernel(const bf16_t* __
     store_tile<32, TW, TA, EPI>(acc, R, C, ldo, M, N, m0 + wm * TA * 32, n0 + wn * TW * 32, lane, inv);
 }
 
-template <int TW, int TA, int WGN, int WGM, int EPI, bool GENERIC, int NS = 2>
+template <int TW, int TA, int WGN, int WGM, int EPI, bool GENERIC, int NS = 2, bool SPREAD = (NS >= 3)>
 static int launch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t* W1, const bf16_t* R, bf16_t* C,
                        int ldo, int M, int N, int K, hipStream_t st, const EpiExtra& re = EpiExtra()) {
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
@@ -903,7 +910,7 @@ static int launch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t*
     constexpr size_t smem = NS * (size_t)(BN * NW + BM) * BK * 2;
     const void* kern;
     if constexpr (GENERIC) kern = (const void*)gemm_bf16_generic_kernel<TW, TA, WGN, WGM, EPI>;
-    else kern = (const void*)gemm_bf16_kernel<TW, TA, WGN, WGM, EPI, NS>;
+    else kern = (const void*)gemm_bf16_kernel<TW, TA, WGN, WGM, EPI, NS, SPREAD>;
     static std::once_flag attr_once;                     // raising the LDS limit is per function, once
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); });
@@ -913,7 +920,7 @@ static int launch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_t*
         hipLaunchKernelGGL((gemm_bf16_generic_kernel<TW, TA, WGN, WGM, EPI>), dim3(tiles_m * tiles_n), dim3(64 * WGN * WGM),
                            smem, st, A, lda, W0, W1, R, C, ldo, M, N, K, tiles_m, tiles_n);
     else
-        hipLaunchKernelGGL((gemm_bf16_kernel<TW, TA, WGN, WGM, EPI, NS>), dim3(tiles_m * tiles_n), dim3(64 * WGN * WGM), smem,
+        hipLaunchKernelGGL((gemm_bf16_kernel<TW, TA, WGN, WGM, EPI, NS, SPREAD>), dim3(tiles_m * tiles_n), dim3(64 * WGN * WGM), smem,
                            st, A, lda, W0, W1, R, C, ldo, M, N, K, tiles_m, tiles_n, re);
     return check_launch();
 }
@@ -1204,7 +1211,12 @@ static int dispatch_bf16(const bf16_t* A, int lda, const bf16_t* W0, const bf16_
         switch (few_shape(M, &N, 1, 1)) {
             case FEW_A: return launch_bf16<2, 2, 4, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
             case FEW_B: return launch_bf16<2, 2, 2, 2, EPI, false, 4>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
-            case FEW_C: return launch_bf16<2, 1, 2, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+            case FEW_C:
+                // A workgroup that has its CU for itself takes a k-tile's loads at once, two that share it deal them to the k-steps.  us, at once / dealt: 1500 x 1024 from
+                // 4096 (192 workgroups) 20.8 / 21.7, from 14336 86.3 / 87.7, 2048 x 1024 from 4096 (256) 24.3 / 25.1, 257 x 4096 from 14336 (160) 92.1 / 94.0; 2200 x 1024
+                // from 4096 (280) 35.6 / 34.5, 1100 x 2048 from 1024 (288) 14.1 / 12.9.
+                if ((M + 63ll) / 64 * ((N + 127ll) / 128) <= cu_count()) return launch_bf16<2, 1, 2, 2, EPI, false, 3, false>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
+                return launch_bf16<2, 1, 2, 2, EPI, false, 3>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
             default: return launch_bf16<1, 1, 2, 2, EPI, false, 5>(A, lda, W0, W1, R, C, ldo, M, N, K, st, re);
         }
     }

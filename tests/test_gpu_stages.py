@@ -268,6 +268,7 @@ def test_linear_all_epilogues(slim, m, n, k, dtype):
     (1153, 3584, 128), (2049, 2048, 64),          # the same, in place of more 128 x 128 tiles than CUs
     (769, 4096, 320), (641, 4040, 128),           # 128 x 128 tiles, 4 stages
     (321, 4104, 256), (319, 4096, 64),            # 128 x 64 tiles, 3 stages
+    (1089, 2056, 320), (1087, 2048, 64),          # the same, more than CUs: a k-tile's loads dealt to its k-steps
     (65, 1032, 384), (63, 4096, 64),              # 64 x 64 tiles, 5 stages
     (2048, 4096, 64), (2049, 4096, 64),           # the largest launch of the few-row tiles and the first behind it
     (32768, 104, 64), (32769, 104, 64),           # the same for narrow outputs: a round of 256 x 128 tiles and one more
