@@ -1,6 +1,7 @@
 // C entry points of libslim: argument checks, workspace carving and the order of kernel launches of
 // the pruned prefill layer.  No kernel lives here.
 #include "rows.h"
+#include "routes.h"
 #include <math.h>
 #include <algorithm>
 #include <mutex>
@@ -57,16 +58,6 @@ static int forced_count(unsigned flags, int nb) {
 // for as many rows as fill the chip and loses behind that (the partial sums are written and read once more per split).
 constexpr int kSplitRows = 128;
 static int qkv_splits(int m, int k_in) { return m <= kSplitRows && k_in >= 2048 ? 4 : 1; }
-
-// The output projection of few rows, for which the finishing pass takes the place of the norm's launch (split_residual_rows_kernel; rows of up to 8192).  Whole
-// layers, not split / 2 / 4 / 8 splits (us): 4096 features from 4096, 4 rows 123.4 / 117.9 / 115.2 / 117.6, 64 147 / 140 / 137, 65 141.2 / 137.7 / 138.3, 128 156.3 / 151.0 /
-// 151.9, 200 177 / 182 / 180, 256 201 / 200 / 199, 257 229 / 217 / 219 / 227, 512 261 / 254 / 254, 513 313 / 311 / 321, 768 356 / 350 / 363, 960 415 / 418, 1024 415 / 413,
-// 1511 603 / 620; 3584 from 3584, 48 rows 153 / 146 / 143 / 148, 128 186 / 180 / 181, 300 256 / 253 / 254, 512 316 / 311 / 311, 700 378 / 378, 832 451 / 456.  (Behind 512 rows
-// neither gains; they are one class with those from 257 on, so that a row's sums do not change with a pruning between them.)
-static int out_splits(int m, int n, int k_in) {
-    if (n < 2048 || n > 8192 || n % 64 != 0 || k_in < 2048 || k_in % 64 != 0 || k_in >= (1 << 23) || (long long)m * n > 1 << 22) return 1;
-    return m <= 64 ? 4 : m <= 128 || (m > 256 && m <= 1024) ? 2 : 1;
-}
 
 // Workspace layout of slim_pruned_layer (every region 256-byte aligned).
 struct LayerPlan {
@@ -133,7 +124,7 @@ static LayerPlan plan_layer(const slim_layer_shape* s, int N, int n_keep) {
     if (s->dtype == SLIM_BF16) {
         const int Hd = s->hidden, n_most = p.prune ? n_keep * s->block : N;
         p.out_splits = out_splits(p.n_out, Hd, (int)qd);
-        for (int rows : {64, 128, 1024, (1 << 22) / Hd}) {
+        for (int rows : {64, 128, std::min(kOutSplitRows, kOutSplitOutputs / Hd)}) {
             rows = std::min(rows, n_most);
             const int splits = out_splits(rows, Hd, (int)qd);
             if (splits > 1) off = std::max(off, p.act + align_up((size_t)splits * rows * Hd * sizeof(float), 256));

@@ -52,4 +52,15 @@ inline bool few_row_attention(int n, int Hq, int Hkv, float scale, int cu) {
 // 501.7 / 500.9, 24 of 48 (185472) 682 / 687; of 2048, blocks of 32, 12 of 24 (11808) 135.0 / 133.2, 16 of 32 (20992) 151.0 / 149.1, 24 of 48 (47232) 187.3 / 187.2, 32 of 64 (83968) 222.2 / 223.4.
 inline bool compact_selects(long long chunks, int n_keep, int nb) { return nb <= 64 && chunks * n_keep * nb <= 64 * 256; }
 
+// Splits of a layer's output projection of few rows (1: none), for which a finishing pass of rows of up to 8192 features takes the place of the norm's launch (with a gain, if that is 16-byte
+// aligned).  Whole layers, not split / 2 / 4 / 8 splits (us): 4096 features from 4096, 4 rows 123.4 / 117.9 / 115.2 / 117.6, 64 147 / 140 / 137, 65 141.2 / 137.7 / 138.3, 128 156.3 / 151.0 /
+// 151.9, 200 177 / 182 / 180, 256 201 / 200 / 199, 257 229 / 217 / 219 / 227, 512 261 / 254 / 254, 640 343 / 335, 768 375 / 369, 896 398 / 392, 1024 411 / 406, 1511 603 / 620; 3584 from 3584,
+// 48 rows 153 / 146 / 143 / 148, 128 186 / 180 / 181, 300 256 / 253 / 254, 512 316 / 311 / 311, 768 395 / 389, 819 439 / 442, 896 448 / 448, 1024 485 / 478; 2048, 512 rows 116 / 115, 819
+// 156 / 153, 1024 171 / 171; 5120, 384 rows 309 / 299, 768 481 / 471, 819 558 / 553; 8192, 64 rows 380 / 373, 512 830 / 812.
+constexpr int kOutSplitRows = 1024, kOutSplitOutputs = 1 << 22;
+inline int out_splits(int m, int n, int k_in) {
+    if (n < 2048 || n > 8192 || n % 64 != 0 || k_in < 2048 || k_in % 64 != 0 || k_in >= (1 << 23) || (long long)m * n > kOutSplitOutputs) return 1;
+    return m <= 64 ? 4 : m <= 128 || (m > 256 && m <= kOutSplitRows) ? 2 : 1;
+}
+
 }   // namespace slim

@@ -79,9 +79,9 @@ def test_layer_keeps_the_blocks_that_the_selection_keeps(slim, nb, flags):
 
 
 @pytest.mark.parametrize("fold", [False, True])
-@pytest.mark.parametrize("seq,keep", [(1, 1.0), (64, 1.0), (65, 1.0), (128, 1.0), (256, 1.0), (257, 1.0), (1024, 1.0), (600, 0.5)])
+@pytest.mark.parametrize("seq,keep", [(1, 1.0), (64, 1.0), (65, 1.0), (128, 1.0), (256, 1.0), (257, 1.0), (1024, 1.0), (1025, 1.0), (600, 0.5)])
 def test_split_output_projection(slim, seq, keep, fold):
-    """4, 2, none and 2 splits at the edges of their row counts and behind a pruning, against the oracle; and in a workspace of exactly the size asked for, whatever it holds."""
+    """4, 2, none, 2 and none again at the edges of their row counts and behind a pruning, against the oracle; and in a workspace of exactly the size asked for, whatever it holds."""
     print(f"output projection seq {seq} keep {keep} fold {fold}", flush=True)
     wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, keep_ratio=keep, hidden=2048, n_q_heads=16, n_kv_heads=4, ffn=256, planted=max(1, seq // 50))
     check_layer(slim, wl, np.float64, rows_count=64, label=f"output projection {seq} {keep} {fold}", fold=fold)
@@ -94,6 +94,17 @@ def test_split_output_projection(slim, seq, keep, fold):
         seen.append(slim.slim_pruned_layer(shape, w, x, None, wl.n_keep, workspace=buf[:size])["x"].clone())
         assert (buf[size:] == fill).all()
     assert torch.equal(*seen)
+
+
+@pytest.mark.parametrize("seq", [64, 300])
+def test_gains_that_are_not_aligned(slim, seq):
+    """The pass that finishes a split output projection reads the gain in 16 bytes: one that is not aligned takes the projection and the norm as two launches."""
+    print(f"gains not aligned, seq {seq}", flush=True)
+    wl = inputs.scaled(inputs.WORKLOADS["cfg2"], seq=seq, keep_ratio=1.0, hidden=2048, n_q_heads=16, n_kv_heads=4, ffn=256, planted=max(1, seq // 50))
+    g = torch.Generator(device="cuda").manual_seed(seq)
+    gains = [(1 + 0.1 * torch.randn(wl.hidden + 1, generator=g, device="cuda")).bfloat16()[1:] for _ in range(2)]
+    assert all(t.data_ptr() % 16 for t in gains)
+    check_layer(slim, wl, np.float64, rows_count=64, label=f"gains not aligned {seq}", gains=gains)
 
 
 @pytest.mark.parametrize("residual", [False, True])

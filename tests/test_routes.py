@@ -68,3 +68,9 @@ def test_compactions_that_select_their_blocks(routes):
     check(routes, [(f"compact_selects({chunks}, {keep}, {nb})", want) for chunks, keep, nb, want in (
         (6, 1, 2, True), (6, 16, 32, True), (6, 32, 64, True), (3, 63, 64, True), (6, 63, 64, False), (3, 1, 65, False), (161, 4, 16, True), (161, 8, 16, False),
         (161, 24, 47, False))])
+
+
+def test_splits_of_the_output_projection(routes):
+    check_values = ((1, 4096, 4), (64, 3584, 4), (65, 4096, 2), (128, 8192, 2), (129, 4096, 1), (256, 4096, 1), (257, 4096, 2), (512, 8192, 2), (513, 8192, 1), (1024, 4096, 2),
+                    (1025, 4096, 1), (1024, 2048, 2), (1025, 2048, 1), (819, 5120, 2), (820, 5120, 1), (64, 1024, 1), (64, 16384, 1))
+    assert routes([f"out_splits({m}, {n}, 4096)" for m, n, _ in check_values]) == [s for _, _, s in check_values]
