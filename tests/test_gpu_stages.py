@@ -635,12 +635,20 @@ def test_float32_attention_keeps_its_precision_over_long_sequences(slim, n, d):
     assert err <= bound
 
 
+def behind_the_few_rows(Hkv):
+    """A ragged row count of groups of four heads that the few-row kernel (32 rows of four heads per workgroup, up to two workgroups per CU) does not take."""
+    return 2 * torch.cuda.get_device_properties(0).multi_processor_count // Hkv * 32 + 37
+
+
+# bf16: up to 1280 rows of groups of four the few-row kernel; "behind" it the large tiles of groups of four, groups of one and two the large tiles of one head.
 @pytest.mark.parametrize("n,Hq,Hkv,d,dtype", [
+    ("behind", 32, 8, 128, torch.bfloat16), (1100, 6, 3, 128, torch.bfloat16),
     (1, 4, 1, 128, torch.bfloat16), (37, 4, 2, 128, torch.bfloat16), (128, 8, 8, 128, torch.bfloat16),
     (200, 4, 1, 128, torch.bfloat16), (1000, 8, 2, 128, torch.bfloat16), (1280, 32, 8, 128, torch.bfloat16),
     (256, 4, 2, 64, torch.float32), (77, 6, 3, 32, torch.float32), (130, 2, 1, 128, torch.float32),
 ])
 def test_attention_matches_oracle(slim, n, Hq, Hkv, d, dtype):
+    n = behind_the_few_rows(Hkv) if n == "behind" else n
     print(f"attn n={n} H={Hq}/{Hkv} d={d} {dtype}", flush=True)
     name = "bf16" if dtype == torch.bfloat16 else "fp32"
     q, k, v = inputs.stage_qkv(n, Hq, Hkv, d, name, seed=n)
@@ -693,13 +701,14 @@ def test_attention_peaked_logits_and_first_row(slim):
     np.testing.assert_array_equal(f64(got)[0], np.repeat(f64(v)[0], Hq // Hkv, 0))   # row 0 sees only key 0
 
 
+@pytest.mark.parametrize("n,Hq,Hkv", [(1500, 8, 2), ("behind", 32, 8), (1500, 8, 4)])      # few rows; large tiles of groups of four, and of one head
 @pytest.mark.parametrize("stair", [12.0, 160.0])
-def test_attention_reference_moves_at_every_place(slim, stair):
+def test_attention_reference_moves_at_every_place(slim, stair, n, Hq, Hkv):
     """Logits that climb a staircase along the keys (48 stairs at random keys, each about 12 binary orders high, or
     about 160: then exp2 of a logit taken against the old reference overflows): for every query the reference of the
     online softmax has to move at each stair below it, at whatever place in the key tile, unit and part of a unit the
     stair falls, in the full-tile loop and in the masked loop of the diagonal."""
-    n, Hq, Hkv, d = 1500, 8, 2, 128
+    n, d = behind_the_few_rows(Hkv) if n == "behind" else n, 128
     print(f"attn staircase n={n} H={Hq}/{Hkv} d={d} stair {stair}", flush=True)
     q, k, v = inputs.stage_qkv(n, Hq, Hkv, d, "bf16", seed=77)
     g = np.random.default_rng(5)
