@@ -1126,10 +1126,11 @@ static int residual_round_rows(const void* R, int N, int K, int ldo) {
 
 // How launch_linear's residual projection of m rows is cut when its caller has room for float partial sums: `whole` rows in full rounds,
 // the others split over `splits` workgroups per tile (1: not at all, launch_linear takes all rows; !large: split_gemm_kernel's tiles).
-// 4096 features from 14336, with the finishing pass, large tiles against the unsplit few-row ones (us): 768 rows, 5 splits 92 / 132, 1024 rows, 4 113 /
-// 137, 1280 rows, 3 138 / 193, 1511 rows, 2 174 / 190, 1664 rows, 2 180 / 200; 3584 from 18944: 1024 rows, 4 128 / 174, 1500 rows, 3 191 / 244.
-// Up to 512 rows the few-row tiles: 1 / 2 / 4 / 8 splits of 14336 take 73 / 43 / 39 / 38 us for 128 rows, 101 / 75 / 67 / 73 for 300, 106 / 82 /
-// 79 / 90 for 512.  Large tiles: one round of workgroups; or 3 splits that make 1.64 rounds and more, of two.  Whole layers, not split / split (us): 2 splits 1904 rows 799 / 780,
+// Whole layers (us).  Up to 512 rows the few-row tiles, 1 / 2 / 4 / 8 splits and 8 in large tiles: 4096 features from 14336, 64 rows 164 / 136 / 124 / 124, 137, 128 rows 182 / 157 / 153 / 149,
+// 160, 200 rows 190 / 194 / 182 / 186, 192, 300 rows 266 / 225 / 221 / 233, 224, 512 rows 297 / 268 / 259 / 273, 258; 3584 from 18944, 128 rows 224 / 188 / 183 / 177, 190, 300 rows
+// 302 / 262 / 257 / 267, 252, 512 rows 372 / 334 / 318 / 330, 311.  Behind them large tiles, not split / 4 splits of few-row tiles / split in large ones: 600 rows, 5 splits 368 / 354 / 320,
+// 768, 5 407 / 388 / 356, 1024, 4 459 / 449 / 423, 1280, 3 585 / 577 / 522, 1511, 2 653 / 662 / 627, 1664, 2 671 / 703 / 645; 3584 from 18944, 600 rows, 4 425 / 375 / 359, 1024, 4
+// 544 / 523 / 485, 1500, 3 758 / 753 / 698.  One round of workgroups; or 3 splits that make 1.64 rounds and more, of two.  Not split / split: 2 splits 1904 rows 799 / 780,
 // 2048 (128 tiles) 830 / 804, 2300 rows of 18944 1000 / 971; 3 splits 2200 rows 920 / 899, 2304 (144 tiles) 921 / 902, of 18944 2560 rows (140 tiles) 1120 / 1088, 2816 1236 / 1196,
 // 3072 1321 / 1263.  Not with 176 tiles (2600 rows 1070 / 1121) or with 2 splits of more than a round (2200 rows 950).
 static int large_splits(long long tiles_m, int n) {      // for so many 256-row tiles; 1: none
