@@ -11,7 +11,9 @@ inline bool few_rows(int m, int n, int cu) { return (long long)m * n <= (1ll << 
 
 // Of these, the launches that the two-size tiles are faster at all the same: nearly a round of 256 x 128 tiles of a wide output.  us, few-row / two-size, with residual: 4096
 // features from 4096, 1664 rows (208 tiles) 57 / 56, 1800 (240) 58 / 52, 2048 (256) 62 / 57, from 14336 2048 rows 199 / 190; 3584 from 3584, 1800 rows (210) 50 / 49, 2048 (224) 53 /
-// 51, 2300 (252) 57 / 54; 5120 from 4096, 1511 rows (240) 57 / 54.  Short rows too (2048 x 4096 from 64 8.2 / 7.6, from 256 10.4 / 9.8).
+// 51, 2300 (252) 57 / 54; 5120 from 4096, 1511 rows (240) 57 / 54.  Short rows too (2048 x 4096 from 64 8.2 / 7.6, from 256 10.4 / 9.8).  Few rows
+// of very wide outputs, without residual, gain less and within 215 tiles up to 3 % either way: 64 x 54016 (211) from 1024 24.2 / 24.9, 300 x 18000 (213) from 4096 69.3 / 70.2, 256 x 27136 (212) from 4096
+// 79.2 / 76.0, 256 x 30720 (240) 76.1 / 72.2, 200 x 28672 (224) 69.7 / 66.3.
 inline bool nearly_a_round(int m, int n, int cu) { return n >= 2048 && few_row_tiles(m, n) * 16 > cu * 13ll; }
 
 // Whether a projection of m rows runs in the few-row tiles, which take any row stride of the output; the two-size launch takes those below 2^23.  four_waves: the
